@@ -12,9 +12,9 @@
 //  * A wavefront owns a vertical strip of the image.  Lane l holds PX adjacent
 //    columns; one row of one plane is a single coalesced load of 64*PX elements
 //    (128 bits per lane for float32 at PX = 4).
-//  * Vertical taps never touch memory: the last two gray rows and the last two
-//    rows of (Ix^2, Ix*Iy, Iy^2) live in registers ("register rotation").  Row steps
-//    are unrolled, so the rotation is a renaming, not a copy.
+//  * Vertical taps never touch memory: the last two gray rows and what the window sums
+//    need of the rows of (Ix^2, Ix*Iy, Iy^2) live in registers ("register rotation").  Row
+//    steps are unrolled, so the rotation is a renaming, not a copy.
 //  * Both 3x3 stages are separated (section 4.3, "Convolution Separation"):
 //    [1 2 1]^T/[-1 0 1]^T down the column from registers first, then the horizontal
 //    taps.  Horizontal neighbours come from the lane to the right through a DPP
@@ -68,16 +68,15 @@ __device__ __forceinline__ float from_right(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 
-// The two columns to the right of a lane's PX columns: a[PX], a[PX+1].
-template <int PX>
-__device__ __forceinline__ void fetch_halo(float (&a)[PX + 2]) {
-    if constexpr (PX == 1) {
-        a[1] = from_right(a[0]);
-        a[2] = from_right(a[1]);
-    } else {
-        a[PX] = from_right(a[0]);
-        a[PX + 1] = from_right(a[1]);
-    }
+// Column I of a lane's PX columns, I < PX + 2: beyond the lane's own it is the next lane's.  Written
+// at the place of its use, with the operation that takes it, the lane shift becomes a modifier of
+// that operation; the compiler looks only some 20 instructions ahead for it, and leaves a move of
+// its own for every shift whose use lies further away.
+template <int I, int PX>
+__device__ __forceinline__ float column(const float (&a)[PX]) {
+    if constexpr (I < PX) return a[I];
+    else if constexpr (I < 2 * PX) return from_right(a[I - PX]);
+    else return from_right(from_right(a[I - 2 * PX]));
 }
 
 // ---------------------------------------------------------------- row loads and stores
@@ -283,73 +282,113 @@ __device__ __forceinline__ void gray_row(const RawRow<In, PX>& r, float wr, floa
 
 template <int PX>
 struct LineBuffers {
-    float g[3][PX];       // ring of the last three gray rows
-    float p[3][3][PX];    // ring of the last three rows of (Ix*Ix, Ix*Iy, Iy*Iy)
+    float g[2][PX];       // the last two gray rows
+    float d[2][PX];       // DIFF: and their differences along the row, [-1 0 1]
+    float x[2][PX];       // box window: Ix, Iy of the last even row
+    float p[2][3][PX];    // Ix*Ix, Ix*Iy, Iy*Iy: of the last odd row (box, in p[1]), of the last two rows (binomial)
+    float t[3][PX];       // box window: sums of the products of two neighbouring rows, an odd one and the even one below it
 };
 
-// One row step.  GS is the ring slot that receives this step's gray row.
+// One row step.  T is the row's number in its band or tile, modulo 2 at least: it fixes the slots of
+// the row's values (T % 2).
 // STAGE 0: gray only (first two rows of a band); 1: also Sobel and products (next
 // two rows); 2: also window sums and coarsity: one result row in o, for the caller to store.
-template <int STAGE, int GS, int PX, bool BINOM>
+//
+// Both Sobel kernels are separated, and either order of the two passes costs the same.  DIFF takes the
+// difference along the row first, of gray values that are close to each other: it is small and mostly
+// exact, and what is added up afterwards rounds at that size (1536x2560 float32: error of the result
+// against 64 bits 2.4e-7 of its norm, 3.0e-7 with the sums first).  It keeps two rows of differences
+// more, which 8-bit input, bound by the vector ALUs at full occupancy, pays for (8 images of
+// 1080x1920 to 8-bit codes: 19.2 against 18.4 us): that takes the sums first.
+template <int STAGE, int T, int PX, bool BINOM, bool DIFF>
 __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX]) {
-    constexpr int PS = (GS + 1) % 3;          // product slot written at this step
-#pragma unroll
-    for (int i = 0; i < PX; ++i) lb.g[GS][i] = gc[i];
-    if constexpr (STAGE >= 1) {
-        // Sobel pair, separated: down the column from the register ring, then along the row.
-        const float (&ga)[PX] = lb.g[(GS + 1) % 3];   // two rows back
-        const float (&gb)[PX] = lb.g[(GS + 2) % 3];   // one row back (the centre row)
-        float vs[PX + 2], vd[PX + 2];
-#pragma unroll
-        for (int i = 0; i < PX; ++i) {
-            vs[i] = fmaf(2.0f, gb[i], ga[i] + gc[i]);  // [1 2 1] down the column
-            vd[i] = gc[i] - ga[i];                     // [-1 0 1] down the column
-        }
-        fetch_halo<PX>(vs);
-        fetch_halo<PX>(vd);
-#pragma unroll
-        for (int i = 0; i < PX; ++i) {
-            float ix = vs[i + 2] - vs[i];                        // [-1 0 1] along the row
-            float iy = fmaf(2.0f, vd[i + 1], vd[i] + vd[i + 2]); // [1 2 1] along the row
-            // Products.
-            lb.p[PS][0][i] = ix * ix;
-            lb.p[PS][1][i] = ix * iy;
-            lb.p[PS][2][i] = iy * iy;
-        }
+    constexpr int PS = T % 2;
+    [[maybe_unused]] float dx[PX];                // DIFF: [-1 0 1] along the row
+    if constexpr (DIFF) {
+        static_for<0, PX>([&](auto ii) {
+            constexpr int i = decltype(ii)::value;
+            dx[i] = column<i + 2, PX>(gc) - gc[i];
+        });
     }
-    if constexpr (STAGE >= 2) {
-        // Window sums, separated: [1 c 1] down the column, then along the row (c = 1 for the
-        // unweighted sum, 2 for the binomial window).  Along the row neighbouring results
-        // share a pair sum, and every value that comes from the lane to the right is an
-        // operand of an addition, so that its lane shift rides on that addition.
-        float s[3][PX];
+    [[maybe_unused]] float v[3][PX];              // [1 c 1] down the column of the three products
+    if constexpr (STAGE >= 1) {
+        [[maybe_unused]] float sy[PX];            // without DIFF: [1 2 1] down the column
+        float dy[PX];                             // [-1 0 1] down the column
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            float v[PX + 2];
-#pragma unroll
-            for (int i = 0; i < PX; ++i) {
-                const float ends = lb.p[(PS + 1) % 3][q][i] + lb.p[PS][q][i];
-                const float mid = lb.p[(PS + 2) % 3][q][i];
-                v[i] = BINOM ? fmaf(2.0f, mid, ends) : ends + mid;
-            }
-            fetch_halo<PX>(v);
+        for (int i = 0; i < PX; ++i) {
+            dy[i] = gc[i] - lb.g[PS][i];
+            if constexpr (!DIFF) sy[i] = fmaf(2.0f, lb.g[1 - PS][i], lb.g[PS][i] + gc[i]);
+        }
+        static_for<0, PX>([&](auto ii) {
+            constexpr int i = decltype(ii)::value;
+            float ix;
+            if constexpr (DIFF) ix = fmaf(2.0f, lb.d[1 - PS][i], lb.d[PS][i] + dx[i]);
+            else ix = column<i + 2, PX>(sy) - sy[i];
+            const float iy = fmaf(2.0f, column<i + 1, PX>(dy), column<i + 2, PX>(dy) + dy[i]);   // [1 2 1] along the row
+            // Products and window sums down the column (the window is separated too, c = 1 for
+            // the unweighted sum, 2 for the binomial window).
+            const float fa[3] = {ix, ix, iy}, fb[3] = {ix, iy, iy};
             if constexpr (BINOM) {
-                float pair[PX + 1];                       // v[i] + v[i+1]
 #pragma unroll
-                for (int i = 0; i <= PX; ++i) pair[i] = v[i + 1] + v[i];
+                for (int q = 0; q < 3; ++q) {
+                    const float p = fa[q] * fb[q];
+                    if constexpr (STAGE >= 2) v[q][i] = fmaf(2.0f, lb.p[1 - PS][q][i], lb.p[PS][q][i] + p);
+                    lb.p[PS][q][i] = p;
+                }
+            } else if constexpr (PS == 0) {
+                // Two neighbouring sums a + b + c and b + c + d share t = b + c, with b the odd
+                // row: the even rows' products then occur only as the product of a multiply-add,
+                // and a row costs two operations a product instead of three.
+                if constexpr (STAGE >= 2) {
+                    const float ea[3] = {lb.x[0][i], lb.x[0][i], lb.x[1][i]}, eb[3] = {lb.x[0][i], lb.x[1][i], lb.x[1][i]};
 #pragma unroll
-                for (int i = 0; i < PX; ++i) s[q][i] = pair[i] + pair[i + 1];   // v[i] + 2 v[i+1] + v[i+2]
-            } else if constexpr (PX == 1) {
-                s[q][0] = (v[1] + v[0]) + v[2];
+                    for (int q = 0; q < 3; ++q) {
+                        lb.t[q][i] = fmaf(fa[q], fb[q], lb.p[1][q][i]);
+                        v[q][i] = fmaf(ea[q], eb[q], lb.t[q][i]);
+                    }
+                }
+                lb.x[0][i] = ix;
+                lb.x[1][i] = iy;
             } else {
 #pragma unroll
-                for (int j = 0; j < PX / 2; ++j) {
-                    const float pair = v[2 * j + 2] + v[2 * j + 1];
-                    s[q][2 * j] = v[2 * j] + pair;
-                    s[q][2 * j + 1] = v[2 * j + 3] + pair;
+                for (int q = 0; q < 3; ++q) {
+                    lb.p[1][q][i] = fa[q] * fb[q];
+                    if constexpr (STAGE >= 2) v[q][i] = lb.t[q][i] + lb.p[1][q][i];
                 }
             }
-        }
+        });
+    }
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+        lb.g[PS][i] = gc[i];
+        if constexpr (DIFF) lb.d[PS][i] = dx[i];
+    }
+    if constexpr (STAGE >= 2) {
+        // Along the row neighbouring results share a pair sum.
+        float s[3][PX];
+        static_for<0, 3>([&](auto qq) {
+            constexpr int q = decltype(qq)::value;
+            if constexpr (BINOM) {
+                float pair[PX];                           // v[i] + v[i+1]
+                static_for<0, PX>([&](auto ii) {
+                    constexpr int i = decltype(ii)::value;
+                    pair[i] = column<i + 1, PX>(v[q]) + v[q][i];
+                });
+                static_for<0, PX>([&](auto ii) {
+                    constexpr int i = decltype(ii)::value;
+                    s[q][i] = column<i + 1, PX>(pair) + pair[i];   // v[i] + 2 v[i+1] + v[i+2]
+                });
+            } else if constexpr (PX == 1) {
+                s[q][0] = (column<1, PX>(v[q]) + v[q][0]) + column<2, PX>(v[q]);
+            } else {
+                static_for<0, PX / 2>([&](auto jj) {
+                    constexpr int j = decltype(jj)::value;
+                    const float pair = column<2 * j + 2, PX>(v[q]) + v[q][2 * j + 1];
+                    s[q][2 * j] = v[q][2 * j] + pair;
+                    s[q][2 * j + 1] = column<2 * j + 3, PX>(v[q]) + pair;
+                });
+            }
+        });
         // Coarsity.
 #pragma unroll
         for (int i = 0; i < PX; ++i) {
@@ -372,7 +411,8 @@ __device__ __forceinline__ unsigned xcd_contiguous(unsigned b, unsigned nb) {
 
 template <typename In, int PX, int D, int LAUX, bool BINOM>
 __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::Params p) {
-    constexpr int U = lcm_c(3, D);            // row steps per loop trip: ring slots stay static
+    constexpr bool DIFF = std::is_same<In, float>::value;
+    constexpr int U = lcm_c(2, D);            // row steps per loop trip: queue slots and parities stay static
 
     const unsigned lane = threadIdx.x % kWave;
     const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -440,7 +480,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
         __builtin_amdgcn_sched_barrier(0);
         load_row<In, PX, LAUX>(queue[t % D], in_row_ptr(t + D), plane, in_row_size(t + D), load_voff);
         __builtin_amdgcn_sched_barrier(0);
-        row_step<(t < 2 ? 0 : 1), t % 3, PX, BINOM>(lb, gc, p.k, o);
+        row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, o);
     });
 
     for (int t0 = 4; t0 < steps; t0 += U) {
@@ -457,7 +497,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
             // past the band's end get an empty descriptor and store nothing.
             const int orow = max(0, min(p.n - 1, up ? y0 + rows + 3 - t : y0 + t - 4));
             const __amdgpu_buffer_rsrc_t out_rs = make_rsrc(img_out + (size_t)orow * (size_t)p.out_row_pitch, t < steps ? out_row_bytes : 0u);
-            row_step<2, (4 + u) % 3, PX, BINOM>(lb, gc, p.k, o);
+            row_step<2, 4 + u, PX, BINOM, DIFF>(lb, gc, p.k, o);
             store_row<PX>(o, out_rs, store_voff);
         });
     }
@@ -499,6 +539,7 @@ __device__ __forceinline__ void pin_values(float (&v)[PX]) {
 // aligned 32-bit words that hold them (load_row_shifted, realign_row).
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
+    constexpr bool DIFF = std::is_same<In, float>::value;
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]
     __shared__ unsigned ready[16];                              // HANDOFF: wavefront w has published its four rows
@@ -641,9 +682,9 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             if (lane == 0) __hip_atomic_store(&ready[wave], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
         if constexpr (t < 4) {
-            row_step<(t < 2 ? 0 : 1), t % 3, PX, BINOM>(lb, gc, p.k, none);
+            row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, none);
         } else {
-            row_step<2, t % 3, PX, BINOM>(lb, gc, p.k, results[t - 4]);
+            row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
             pin_values<PX>(results[t - 4]);
         }
         // Each row is worked through as soon as it has arrived: without this the compiler
@@ -668,7 +709,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             constexpr int t = decltype(tt)::value;
 #pragma unroll
             for (int i = 0; i < PX; ++i) gc[i] = below[(size_t)(t - RW) * kWave * PX + i];
-            row_step<2, t % 3, PX, BINOM>(lb, gc, p.k, results[t - 4]);
+            row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
             pin_values<PX>(results[t - 4]);
         });
     }
