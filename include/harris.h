@@ -149,9 +149,10 @@ typedef enum harris_out_dtype {
  *              with the pitches of `layout` counted in result elements; fully overwritten
  *   tuning     as in harris_coarsity_ex, but 16-bit results exist only in the tile schedule
  *              (else HARRIS_ERR_ARG)
- * Four pixels per lane need 16-bit result rows that start on 4-byte boundaries (pointer and
- * pitches) and an even W, so that no 32-bit word of a store holds the last column of a row
- * together with something behind it; other shapes run with one pixel per lane.
+ * 16-bit result rows that start on 4-byte boundaries (pointer and pitches) and have an even number of
+ * columns are stored as they are; other rows, from about 1.5 million pixels on, as the aligned
+ * 32-bit words that hold them, with the ends of each row stored element by element; smaller problems
+ * with such rows run with one pixel per lane.  Nothing outside the rows is written in any case.
  */
 int harris_coarsity_typed(const void* rgb, int dtype, int batch, int H, int W, const harris_layout* layout,
                           float k, float sobel_scale, int window, void* out, int out_dtype,
@@ -165,7 +166,8 @@ int harris_coarsity_typed(const void* rgb, int dtype, int batch, int H, int W, c
  * arrays are float32 and it defines no such code; q_scale and q_offset are the caller's.)
  *   out   device, uint8 [batch][H-4][W-4], pitches of `layout` in bytes; fully overwritten
  * Tile schedule only (else HARRIS_ERR_ARG), q_scale and q_offset finite (else HARRIS_ERR_ARG).
- * The fastest path needs 4-byte aligned result rows and W % 4 == 0.
+ * The fastest path needs 4-byte aligned result rows and W % 4 == 0; rows of
+ * codes on any other boundary are stored as described there for 16-bit results.
  */
 int harris_coarsity_quantized(const void* rgb, int dtype, int batch, int H, int W, const harris_layout* layout,
                               float k, float sobel_scale, int window, float q_scale, float q_offset,

@@ -31,8 +31,9 @@ extern "C" {
  *             takes any width and any row alignment the element type allows, as long as result
  *             rows start on 4-byte boundaries, are not 8-bit codes and, if 16-bit, have an even
  *             number of columns (vector accesses on 4-byte boundaries; 8-bit input rows on any
- *             byte are loaded as aligned words and shifted).  0 = 4 where that holds, else the
- *             widest of 2, 1 that fits.
+ *             byte are loaded as aligned words and shifted).  0 = 4 where that holds, and for
+ *             large problems with other 16-bit or 8-bit result rows if no field asks for a shape
+ *             (the rows are then stored as aligned words); else the widest of 2, 1 that fits.
  *   rows      BANDS: result rows per band (>= 1).  TILES: input rows per wavefront: 4, and
  *             with px = 4 also 5, 6, 8, 9 or 10 (4 or 8 for 8-bit input rows off 4-byte
  *             boundaries).  0 = chosen from the size.

@@ -35,12 +35,26 @@ bool px_fits(int px, int dtype, int out_dtype, int W, int rgb_align, int out_ali
 // byte: the kernel loads the aligned words that hold them and shifts.  Results: float32, or
 // 16-bit with rows that start on 4-byte boundaries and have an even number of columns: the
 // range check works on whole 32-bit words, so a word that held the last column of an odd row
-// together with two bytes behind it would either be dropped or written whole.  (8-bit codes
-// are stored as one word per lane and keep the narrower lanes.)
+// together with two bytes behind it would either be dropped or written whole.  (Other rows of 16-bit
+// results and of 8-bit codes: px4_fits_shifted.)
 bool px4_fits_word_aligned(int dtype, int out_dtype, int W, int rgb_align, int out_align) {
     if (dtype == HARRIS_F32 && rgb_align % 4 != 0) return false;
     if (out_dtype == HARRIS_OUT_U8 || out_align % 4 != 0) return false;
     return out_dtype == HARRIS_OUT_F32 || W % 2 == 0;
+}
+
+// Four pixels per lane for rows of 16-bit results and 8-bit codes on any boundary of their element type:
+// the tile kernel stores the aligned words that hold them and the ends of each row element by
+// element.  Default shapes only (a caller that asks for a shape gets the lanes it names or the
+// narrower ones).  Worth it from about 1.5 million pixels on: below, a launch is bound by its latency,
+// which the longer store code adds to, and the narrower lanes' many wavefronts do no harm (wide
+// against narrow: 700x401 float32 to binary16 4.9 / 3.5 us, 768x1366 uint8 to codes 5.5 / 4.2); above,
+// the narrow lanes are bound by their instructions (1079x1919 float32 to binary16 7.6 / 9.0 us, 8
+// such images from uint8 25.2 / 49.1).
+constexpr long long kShiftedPixels = 3LL << 19;
+bool px4_fits_shifted(int dtype, int out_dtype, long long pixels, int rgb_align, const harris_tuning& t) {
+    if (out_dtype == HARRIS_OUT_F32 || (dtype == HARRIS_F32 && rgb_align % 4 != 0)) return false;
+    return t.rows == 0 && t.waves_per_block == 0 && t.flags == 0u && t.lds_kb == 0 && pixels >= kShiftedPixels;
 }
 
 int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_tuning* tuning,
@@ -66,9 +80,11 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     const int n = H - 4, m = W - 4;
     const bool tiles_allowed = (t.schedule == 0 || t.schedule == HARRIS_SCHEDULE_TILES) && t.prefetch == 0;
     const bool word_aligned_px4 = tiles_allowed && px4_fits_word_aligned(dtype, out_dtype, W, rgb_align, out_align);
+    bool out_shifted = false;
     if (t.px == 0) {
         t.px = 1;
         if (px_fits(4, dtype, out_dtype, W, rgb_align, out_align) || word_aligned_px4) t.px = 4;
+        else if (tiles_allowed && px4_fits_shifted(dtype, out_dtype, (long long)batch * H * W, rgb_align, t)) { t.px = 4; out_shifted = true; }
         else if (px_fits(2, dtype, out_dtype, W, rgb_align, out_align)) t.px = 2;
     } else if (!((t.px == 1 || t.px == 2 || t.px == 4) &&
                  (px_fits(t.px, dtype, out_dtype, W, rgb_align, out_align) || (t.px == 4 && word_aligned_px4)))) {
@@ -101,7 +117,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     const long long border_reach = (t.flags & HARRIS_TUNE_ALIGNED_STORES) ? 64 / out_elem_size(out_dtype) - 4 : 0;
     // 8-bit rows loaded as aligned words and shifted: the last lane only supplies bytes to its left neighbour.
     const bool in_shifted = dtype == HARRIS_U8 && tile4 && !can_align;
-    const long long max_pitch = (long long)harris_launch::valid_lanes(t.px) * t.px - border_reach - (in_shifted ? 4 : 0);
+    // Shifted result rows: the strip's last word may take columns of the lane beyond the strip.
+    const long long max_pitch = (long long)harris_launch::valid_lanes(t.px) * t.px - border_reach - (in_shifted ? 4 : 0) - (out_shifted ? 4 : 0);
     const long long n_strips = m > 0 ? (m + max_pitch - 1) / max_pitch : 0;
     const long long pitch = n_strips > 0 ? ((m + n_strips - 1) / n_strips + t.px - 1) / t.px * t.px : max_pitch;
 
@@ -269,7 +286,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->blocks_per_image = (unsigned)blocks_per_image;
         params->n_blocks = (unsigned)blocks;
         params->waves_per_block = (unsigned)t.waves_per_block;
-        params->flags = t.flags;
+        params->flags = t.flags | (out_shifted ? harris_launch::kOutShifted : 0u);
         params->out_kind = (unsigned)out_dtype;
         params->in_shifted = in_shifted ? 1 : 0;
         params->lds_bytes = (unsigned)t.lds_kb * 1024u;

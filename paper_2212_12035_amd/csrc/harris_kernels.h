@@ -513,6 +513,64 @@ __device__ __forceinline__ void pin_values(float (&v)[PX]) {
     for (int i = 0; i < PX; ++i) asm volatile("" : "+v"(v[i]));
 }
 
+// Rows of 16-bit results or 8-bit codes that may start on any byte their element type allows, four
+// pixels per lane (kOutShifted).  Stores are checked against the end of a row by whole 32-bit words, so
+// lanes store the aligned words of the row: with `shift` bytes in front of the strip's first aligned
+// word, a lane's word is the upper bytes of its own packed results and the lower ones of the lane
+// to its right (one lane shift and one byte-align).  The border between two strips lies on such a
+// boundary, so that only a row's first and last word are shared with what lies around the row: their
+// elements, up to three codes or one 16-bit result at either end, are stored one by one by a few lanes
+// of the strip that holds the end (store_row_ends).
+// Against the narrower lanes such rows had before: 2831x4255 float32 to binary16 33.1 us (one pixel per
+// lane: 39.3), 8 images of 1079x1919 uint8 to binary16 25.2 us (49.1), 16 images of 768x1366 uint8 to
+// codes 23.9 us (two pixels per lane: 26.2).
+template <int KIND>
+struct PackedRow {
+    static constexpr int NW = KIND == HARRIS_OUT_U8 ? 1 : 2;        // 32-bit words of four results
+    uint32_t own[NW], word[NW];                                     // packed as computed; the aligned words
+};
+
+template <int KIND>
+__device__ __forceinline__ PackedRow<KIND> pack_row_shifted(const float (&o)[4], float q_scale, float q_offset, uint32_t shift) {
+    PackedRow<KIND> r;
+    if constexpr (KIND == HARRIS_OUT_U8) {
+        r.own[0] = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.own[0] = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(o[i], q_scale, q_offset), (uint32_t)i, r.own[0]);
+    } else {
+        r.own[0] = to_16bit_pair<KIND == HARRIS_OUT_BF16>(o[0], o[1]);
+        r.own[1] = to_16bit_pair<KIND == HARRIS_OUT_BF16>(o[2], o[3]);
+    }
+    const uint32_t right = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r.own[0], 0x130, 0xf, 0xf, true);
+    if constexpr (KIND == HARRIS_OUT_U8) {
+        r.word[0] = __builtin_amdgcn_alignbyte(right, r.own[0], shift);
+    } else {
+        r.word[0] = __builtin_amdgcn_alignbyte(r.own[1], r.own[0], shift);
+        r.word[1] = __builtin_amdgcn_alignbyte(right, r.own[1], shift);
+    }
+    return r;
+}
+
+// Bytes [0, lead) and [tail_at, tail_at + tail) of a row of row_bytes bytes, lead and tail below 4: the
+// first come from lane 0's own word, the second from the aligned word number tail_word of the strip.
+template <int KIND, int AUX>
+__device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr_t row, uint32_t row_bytes, uint32_t lead, uint32_t tail,
+                                               uint32_t tail_at, uint32_t tail_word, unsigned lane) {
+    constexpr uint32_t SIZE = KIND == HARRIS_OUT_U8 ? 1u : 2u;
+    const uint32_t first = __builtin_amdgcn_readfirstlane(r.own[0]);
+    uint32_t last = __builtin_amdgcn_readlane(r.word[0], tail_word / PackedRow<KIND>::NW);
+    if constexpr (PackedRow<KIND>::NW == 2) last = (tail_word & 1u) ? __builtin_amdgcn_readlane(r.word[1], tail_word / 2u) : last;
+    // Lanes 0 to 2: the first elements; lanes 4 to 6: the last ones.
+    const bool at_end = lane >= 4u;
+    const uint32_t byte = (lane & 3u) * SIZE;
+    const bool store = at_end ? lane < 8u && byte < tail : byte < lead;
+    const uint32_t at = store ? (at_end ? tail_at : 0u) + byte : 0x80000000u;
+    const uint32_t value = (at_end ? last : first) >> (8u * (byte & 3u));
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const void*>(row), row_bytes);
+    if constexpr (SIZE == 1u) __builtin_amdgcn_raw_buffer_store_b8((unsigned char)value, rs, at, 0, AUX);
+    else __builtin_amdgcn_raw_buffer_store_b16((unsigned short)value, rs, at, 0, AUX);
+}
+
 // ---------------------------------------------------------------- the tile kernel
 //
 // The default schedule: a
@@ -585,11 +643,15 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // on the first 64-byte boundary of that row's address at or after the nominal border: up to
     // 12 (float32), 28 (16-bit) or 60 (8-bit) columns further right.  border_mask is the number
     // of columns per 64 bytes, minus one (15, 31 or 63), or 0.
-    const unsigned border_mask = (p.flags & HARRIS_TUNE_ALIGNED_STORES) ? (64u >> esh) - 1u : 0u;
+    // Shifted result rows (16-bit results and 8-bit codes on rows off 4-byte boundaries, see
+    // pack_row_shifted): the border moves to the next 4-byte boundary, up to 1 or 3 columns.
+    const bool out_shifted = PX == 4 && (p.flags & harris_launch::kOutShifted);
+    const unsigned border_mask = (p.flags & HARRIS_TUNE_ALIGNED_STORES) ? (64u >> esh) - 1u : out_shifted ? (4u >> esh) - 1u : 0u;
     const unsigned x0 = (unsigned)strip * p.strip_pitch;        // first result column of this strip
     // Lanes beyond the strip's columns, the border's reach and the 4-column halo request nothing
     // (out-of-range offset).
-    const uint32_t load_voff = lane * PX < p.strip_pitch + 4 + (border_mask & ~3u) ? lcol * (uint32_t)sizeof(In) : 0x80000000u;
+    const unsigned reach = out_shifted ? 4u : border_mask & ~3u;
+    const uint32_t load_voff = lane * PX < p.strip_pitch + 4 + reach ? lcol * (uint32_t)sizeof(In) : 0x80000000u;
     const uint32_t in_row_bytes = (uint32_t)p.W * (uint32_t)sizeof(In);
 
     const size_t plane = (size_t)p.in_plane_pitch;
@@ -602,7 +664,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // Shifted rows: every lane within reach loads the word at its own column (one lane further
     // right than otherwise, which supplies the last lane's missing bytes); the descriptor's
     // size stops the lanes right of the row.
-    [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_pitch + 8 ? col : 0x80000000u;
+    [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_pitch + 8 + reach ? col : 0x80000000u;
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         const int r = y_wave + t;
@@ -640,14 +702,15 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     int sy = y_wave;
     asm volatile("" : "+s"(sx0), "+s"(sy) : : "memory");
     const unsigned sx1 = sx0 + p.strip_pitch;
+    const uint32_t whole_words = out_shifted ? ~3u : ~0u;       // shifted rows: a row's last word is not stored whole
     const uintptr_t out_first = img_out + (((size_t)sy * (size_t)p.out_row_pitch) << esh);
     static_for<0, RW>([&](auto jj) {
         constexpr int j = decltype(jj)::value;
         const uintptr_t row_addr = out_first + (size_t)j * ((size_t)p.out_row_pitch << esh);
         const unsigned a = (unsigned)(row_addr >> esh);         // address in result elements
-        const unsigned b0 = sx0 == 0 ? 0u : sx0 + ((0u - (a + sx0)) & border_mask);
+        const unsigned b0 = sx0 == 0 && !out_shifted ? 0u : sx0 + ((0u - (a + sx0)) & border_mask);
         const unsigned b1 = min((unsigned)p.m, sx1 + ((0u - (a + sx1)) & border_mask));
-        const uint32_t bytes = (j < out_rows && b1 > b0) ? (b1 - b0) << esh : 0u;
+        const uint32_t bytes = (j < out_rows && b1 > b0) ? ((b1 - b0) << esh) & whole_words : 0u;
         out_rs[j] = make_rsrc(reinterpret_cast<const void*>(row_addr + ((size_t)b0 << esh)), bytes);
         out_lead[j] = (sx0 - b0) << esh;
         asm volatile("" : "+s"(out_lead[j]));                   // finished here, not next to the store
@@ -723,6 +786,31 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             constexpr int j = decltype(jj)::value;
             if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
         });
+    } else if (PX == 4 && out_shifted) {
+        if constexpr (PX == 4) {
+            auto store_all = [&](auto kind) {
+                constexpr int KIND = decltype(kind)::value;
+                // The row's ends lie in this strip or not: decided per row, looked at only where one can.
+                const bool ends = sx0 == 0u || sx1 + 4u > (unsigned)p.m;
+                static_for<0, RW>([&](auto jj) {
+                    constexpr int j = decltype(jj)::value;
+                    const uint32_t shift = 0u - out_lead[j];                    // 0 to 3 bytes
+                    const PackedRow<KIND> r = pack_row_shifted<KIND>(results[j], p.q_scale, p.q_offset, shift);
+                    if constexpr (KIND == HARRIS_OUT_U8) __builtin_amdgcn_raw_buffer_store_b32(r.word[0], out_rs[j], lane_bytes, 0, SAUX);
+                    else __builtin_amdgcn_raw_buffer_store_b64(u32x2{r.word[0], r.word[1]}, out_rs[j], lane_bytes, 0, SAUX);
+                    if (ends && j < out_rows) {
+                        const uint32_t row_bytes = (uint32_t)p.m << esh, b0 = (sx0 << esh) + shift, b1 = min(row_bytes, (sx1 << esh) + shift);
+                        const uint32_t bytes = b1 > b0 ? b1 - b0 : 0u;
+                        const uint32_t lead = sx0 == 0u ? min(shift, row_bytes) : 0u, tail = b1 == row_bytes ? bytes & 3u : 0u;
+                        if (lead + tail != 0u)
+                            store_row_ends<KIND, SAUX>(r, out_first + (size_t)j * ((size_t)p.out_row_pitch << esh), row_bytes, lead, tail, b0 + (bytes & ~3u), bytes / 4u, lane);
+                    }
+                });
+            };
+            if (p.out_kind == HARRIS_OUT_U8) store_all(std::integral_constant<int, HARRIS_OUT_U8>{});
+            else if (p.out_kind == HARRIS_OUT_F16) store_all(std::integral_constant<int, HARRIS_OUT_F16>{});
+            else store_all(std::integral_constant<int, HARRIS_OUT_BF16>{});
+        }
     } else if (p.out_kind == HARRIS_OUT_F16) {
         static_for<0, RW>([&](auto jj) {
             constexpr int j = decltype(jj)::value;

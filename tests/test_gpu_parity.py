@@ -738,6 +738,47 @@ def test_8_bit_codes(gpu, oracle):
         gpu.harris_coarsity_quantized(src, codes, 1.0, 0.0, tuning=dict(schedule=1))
 
 
+@pytest.mark.parametrize("fmt", ["f16", "bf16", "codes"])
+@pytest.mark.parametrize("W", [4 + 248 + 1, 4 + 2 * 248 - 1, 4 + 248 + 2, 517, 730, 1003, 7])
+def test_narrow_results_on_rows_of_any_alignment(gpu, oracle, fmt, W):
+    # 16-bit results and 8-bit codes whose rows start on any byte of their type, from the size on that
+    # takes four pixels per lane: the aligned words of a row are stored whole, its ends one by one.
+    # Widths at the strip border (248 columns) and one, two or three columns beside it, every phase of
+    # the row address, dense and padded rows, both input types.  Every result equals, bit for bit, the
+    # rounded float32 result of the same tile shape, and nothing beside the rows is written.
+    import torch
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "codes": torch.uint8}[fmt]
+    m = W - 4
+    H = (3 << 19) // (2 * W) + 1
+    B, n = 2, H - 4
+    mark = 77 if fmt == "codes" else float("nan")
+    for u8 in (False, True):
+        rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(310 + W, B, H, W)
+        src = torch.from_numpy(rgb).cuda()
+        f32 = torch.empty((B, n, m), device="cuda")
+        want = oracle.harris(rgb, K)
+        for pitch, off in ((m, 0), (m + 1, 1), (m + 3, 2), (m + 2, 3)):
+            say("case %s results on any boundary, %s %s, pitch %d offset %d" % (fmt, rgb.dtype, rgb.shape, pitch, off))
+            flat = torch.full((8 + B * n * pitch + 8,), mark, dtype=tdt, device="cuda")
+            view = flat[8 + off:8 + off + B * n * pitch].view(B, n, pitch)[:, :, :m]
+            if fmt == "codes":
+                gpu.harris_coarsity_quantized(src, view, 1.5, 90.0, K)
+            else:
+                gpu.harris_coarsity_typed(src, view, K)
+            kind = {"f16": gpu.HARRIS_OUT_F16, "bf16": gpu.HARRIS_OUT_BF16, "codes": gpu.HARRIS_OUT_U8}[fmt]
+            shape = gpu.harris_plan_typed(int(u8), kind, B, H, W, rgb_align=1 if u8 else 4, out_align=1 if fmt == "codes" else 2)[0]
+            assert shape["px"] == 4
+            gpu.harris_coarsity_typed(src, f32, K, tuning=dict(rows=shape["rows"], waves_per_block=shape["waves_per_block"]))
+            torch.cuda.synchronize()
+            check(f32.cpu().numpy(), want)
+            if fmt == "codes":
+                assert np.array_equal(view.cpu().numpy(), oracle.quantize_u8(f32.cpu().numpy(), 1.5, 90.0))
+            else:
+                assert np.array_equal(view.contiguous().view(torch.int16).cpu().numpy().view(np.uint16), oracle.round_to_16bit(f32.cpu().numpy(), fmt))
+            flat[8 + off:8 + off + B * n * pitch].view(B, n, pitch)[:, :, :m] = mark
+            assert bool((flat == 77).all() if fmt == "codes" else torch.isnan(flat).all())
+
+
 # ---------------------------------------------------------------- seeded random shapes, layouts and launch shapes
 
 def test_random_shapes_layouts_and_launch_shapes(gpu, oracle):
