@@ -90,9 +90,15 @@ __device__ __forceinline__ float column(const float (&a)[PX]) {
 // same workgroup.
 // The policies are compile-time constants of the instructions; the macros exist so that a build
 // with other values can be timed against this one.  Measured (us, interleaved runs on one GPU):
-//   stores nt + sc1 (written through at device scope) instead of nt, many small tiles:
-//     8192x8192 uint8 83.1 against 84.8, 2832x4256 32.6 / 32.9, 64x1080x1920 351.9 / 353.9;
-//     one tile per CU, 1536x2560: 12.7 against 12.0 -- so only the many-tile kernels take it;
+//   stores nt + sc1 (written through at device scope) instead of nt, many small tiles whose strip
+//     borders lie on 64-byte boundaries of float32 rows: 8192x8192 uint8 84.8 against 86.6, 64x1080x1920
+//     354.1 / 355.6, 4096x4096 44.7 / 45.0;
+//     borders and row ends inside 64-byte blocks, which then reach the memory in parts: 16x1079x1919
+//     100.3 / 91.8, 8191x8191 uint8 94.1 / 89.5, to 16-bit and 8-bit results 16x1079x1919 float32 to
+//     binary16 87.9 / 81.0, 8192x8192 uint8 to binary16 77.3 / 72.3 and to codes 73.0 / 69.5 -- so only
+//     float32 results with moved borders take it, and those only where a row has more strips than
+//     ends (2048 images of 64x64, one strip: 44.5 / 37.1; 300 of 128x128: 18.8 / 15.7);
+//     one tile per CU, 1536x2560: 12.7 against 12.0 -- nor does that kernel;
 //   default-policy stores: 13.4 (1536x2560), 97.6 (8192x8192 uint8), 39.8 (2832x4256);
 //   loads nt + sc1: 12.8 on 1536x2560, no change on the large workloads; sc1 without nt, or
 //     sc1 on the rows two tiles share: 4 to 22 % slower.
@@ -109,8 +115,8 @@ constexpr int kAuxDefault = 0;
 constexpr int kAuxNonTemporal = HARRIS_LOAD_AUX;
 // Tile kernel only, not a hardware value: non-temporal, except that the first and the last
 // four input rows of a tile, which the tile above or below reads as well, are loaded with the
-// default policy.  The launches that use it are those of many small tiles; their stores are
-// written through (kAuxManyStore).
+// default policy.  The launches that use it are those of many small tiles; their float32 stores are
+// written through (kAuxManyStore) if strips end on 64-byte boundaries.
 constexpr int kAuxKeepShared = -1;
 constexpr int kAuxStore = HARRIS_STORE_AUX, kAuxManyStore = HARRIS_MANY_STORE_AUX;
 
@@ -780,12 +786,19 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // The last wavefront skips the four rows it has no data for.
     if constexpr (HANDOFF) __syncthreads();                     // stores only after all of the workgroup's loads
     __builtin_amdgcn_sched_barrier(0);
-    constexpr int SAUX = LAUX == kAuxKeepShared ? kAuxManyStore : kAuxStore;
+    constexpr int SAUX = kAuxStore;
     if (__builtin_expect(p.out_kind == HARRIS_OUT_F32, 1)) {
-        static_for<0, RW>([&](auto jj) {
-            constexpr int j = decltype(jj)::value;
-            if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
-        });
+        if (LAUX == kAuxKeepShared && (p.flags & HARRIS_TUNE_ALIGNED_STORES) && p.n_strips > 2u) {
+            static_for<0, RW>([&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, kAuxManyStore>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+            });
+        } else {
+            static_for<0, RW>([&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+            });
+        }
     } else if (PX == 4 && out_shifted) {
         if constexpr (PX == 4) {
             auto store_all = [&](auto kind) {
