@@ -57,7 +57,60 @@ bool px4_fits_shifted(int dtype, int out_dtype, long long pixels, int rgb_align,
     return t.rows == 0 && t.waves_per_block == 0 && t.flags == 0u && t.lds_kb == 0 && pixels >= kShiftedPixels;
 }
 
-int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_tuning* tuning,
+// Batches of narrow images, float32 results, default shapes only: as many images side by side in a
+// wavefront as its 64 lanes of four columns hold (harris_patches.hip), from two on (W <= 128).
+//   - A workgroup holds up to kPatchWaves wavefronts of four rows, the last of which only hands its
+//     rows on; taller images are cut into bands of equal height.  (Eight: 16 start and end more
+//     together, 256 images of 64x64 5.4 against 7.1 us; 4 and 6 read more rows twice, 1500 of 100x80 39.6
+//     with 6 against 38.8.)
+//   - float32 rows whose length is no multiple of 4 must be contiguous: the lane at the end of a row
+//     reads what follows it.  With two images only, where little is gained, such rows keep a
+//     wavefront each: their ends cost two more stores a row (600 of 110x121 24.7 us, 25.9 packed).
+//   - Offsets from the first to the last image of a wavefront are 32-bit.
+//   - From 2^18 pixels on: smaller launches are bound by latency and better spread over more
+//     wavefronts (64 images of 64x64 3.8 against 4.1 us, but 30 of them 3.7 / 3.1, 4 of 480x100 4.0 / 3.4).
+constexpr int kPatchWaves = 8;
+constexpr long long kPatchPixels = 1LL << 18;
+bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, const harris_layout& lay, const harris_tuning& t,
+                  harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
+    if (t.schedule != 0 || t.px != 0 || t.rows != 0 || t.prefetch != 0 || t.waves_per_block != 0 || t.flags != 0u || t.lds_kb != 0) return false;
+    const int n = H - 4, m = W - 4, lanes = (W + 3) / 4, images = 64 / lanes;
+    if (out_dtype != HARRIS_OUT_F32 || n < 1 || m < 1 || batch < 2 || images < 2 || (images == 2 && dtype == HARRIS_F32 && W % 4 != 0)) return false;
+    if ((long long)batch * H * W < kPatchPixels) return false;
+    if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && lay.rgb_row_pitch != W))) return false;
+    const long long reach = 1LL << 30;
+    if (lay.rgb_image_pitch > reach / (images * elem_size(dtype)) || lay.out_image_pitch > reach / (images * 4)) return false;
+    const int max_rows = 4 * (kPatchWaves - 1), bands = (n + max_rows - 1) / max_rows, rows = (n + bands - 1) / bands;
+    const int waves = (rows + 3) / 4 + 1;
+    const long long blocks = ((long long)batch + images - 1) / images * bands;
+    if (blocks > 0x7fffffffLL) return false;
+    harris_tuning c = {HARRIS_SCHEDULE_TILES, 4, 4, 0, waves, HARRIS_TUNE_STREAM_LOADS | HARRIS_TUNE_PLAIN_STORES, 4 * waves};
+    if (chosen) *chosen = c;
+    if (n_blocks) *n_blocks = blocks;
+    if (params) {
+        *params = harris_launch::Params{};
+        params->H = H; params->W = W; params->n = n; params->m = m;
+        params->rows_per_band = rows;
+        params->tiles_per_image = (unsigned)bands;
+        params->by_tiles_per_image = harris_launch::make_fastdiv((unsigned)bands);
+        params->n_blocks = (unsigned)blocks;
+        params->waves_per_block = (unsigned)waves;
+        params->flags = c.flags | harris_launch::kPatches;
+        params->lds_bytes = (unsigned)waves * 4096u;
+        params->image_lanes = (unsigned)lanes;
+        params->image_lanes_inverse = (unsigned)((65535 + lanes) / lanes);
+        params->images = (unsigned)images;
+        params->batch = (unsigned)batch;
+    }
+    return true;
+}
+
+harris_layout dense_layout(int H, int W) {
+    const long long n = H - 4, m = W - 4;
+    return {W, (long long)H * W, 3LL * H * W, m, n * m};
+}
+
+int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_layout& lay, const harris_tuning* tuning,
          harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
     if (dtype != HARRIS_F32 && dtype != HARRIS_U8) return HARRIS_ERR_ARG;
     if (!known_out_dtype(out_dtype)) return HARRIS_ERR_ARG;
@@ -76,6 +129,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     if ((t.flags & HARRIS_TUNE_FLAG_HANDOFF) && (t.flags & (HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_KEEP_SHARED_ROWS))) return HARRIS_ERR_ARG;
     if ((t.flags & HARRIS_TUNE_ALIGNED_STORES) && (t.flags & HARRIS_TUNE_PLAIN_STORES)) return HARRIS_ERR_ARG;
     if (t.schedule != 0 && t.schedule != HARRIS_SCHEDULE_BANDS && t.schedule != HARRIS_SCHEDULE_TILES) return HARRIS_ERR_ARG;
+
+    if (plan_patches(dtype, out_dtype, batch, H, W, rgb_align, lay, t, chosen, n_blocks, params)) return HARRIS_OK;
 
     const int n = H - 4, m = W - 4;
     const bool tiles_allowed = (t.schedule == 0 || t.schedule == HARRIS_SCHEDULE_TILES) && t.prefetch == 0;
@@ -307,12 +362,12 @@ extern "C" {
 
 int harris_plan(int dtype, int batch, int H, int W, int rgb_align, int out_align,
                 const harris_tuning* tuning, harris_tuning* chosen, long long* n_blocks) {
-    return plan(dtype, HARRIS_OUT_F32, batch, H, W, rgb_align, out_align, tuning, chosen, n_blocks, nullptr);
+    return plan(dtype, HARRIS_OUT_F32, batch, H, W, rgb_align, out_align, dense_layout(H, W), tuning, chosen, n_blocks, nullptr);
 }
 
 int harris_plan_typed(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align,
                       const harris_tuning* tuning, harris_tuning* chosen, long long* n_blocks) {
-    return plan(dtype, out_dtype, batch, H, W, rgb_align, out_align, tuning, chosen, n_blocks, nullptr);
+    return plan(dtype, out_dtype, batch, H, W, rgb_align, out_align, dense_layout(H, W), tuning, chosen, n_blocks, nullptr);
 }
 
 }  // extern "C"
@@ -330,13 +385,7 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
     if (!isfinite(k) || !isfinite(sobel_scale)) return HARRIS_ERR_ARG;
     if (window != HARRIS_WINDOW_BOX && window != HARRIS_WINDOW_BINOMIAL) return HARRIS_ERR_ARG;
     const long long n = H - 4, m = W - 4;
-    harris_layout lay;
-    if (layout) {
-        lay = *layout;
-    } else {
-        lay.rgb_row_pitch = W; lay.rgb_plane_pitch = (long long)H * W; lay.rgb_image_pitch = 3LL * H * W;
-        lay.out_row_pitch = m; lay.out_image_pitch = n * m;
-    }
+    const harris_layout lay = layout ? *layout : dense_layout(H, W);
     const long long in_rows_span = (long long)(H - 1) * lay.rgb_row_pitch + W;
     if (lay.rgb_row_pitch < W || lay.rgb_plane_pitch < in_rows_span || lay.rgb_image_pitch < 2 * lay.rgb_plane_pitch + in_rows_span)
         return HARRIS_ERR_SHAPE;
@@ -368,7 +417,7 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
     harris_launch::Params p;
     harris_tuning shape;
     long long n_blocks = 0;
-    int rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, tuning, &shape, &n_blocks, &p);
+    int rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, tuning, &shape, &n_blocks, &p);
     if (rc != HARRIS_OK) return rc;
     if (empty) return HARRIS_OK;
 

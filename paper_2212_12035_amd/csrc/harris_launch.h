@@ -46,6 +46,8 @@ HARRIS_HOST_DEVICE inline unsigned fastdiv(unsigned x, const FastDiv& f) {
 // Bit of Params::flags, beside the HARRIS_TUNE_* bits: 16- or 8-bit result rows are stored as the
 // aligned words that hold them (tile kernel, four pixels per lane).
 constexpr unsigned kOutShifted = 0x80000000u;
+// Another such bit: several narrow images side by side in a wavefront (harris_patches.hip).
+constexpr unsigned kPatches = 0x40000000u;
 
 // Kernel arguments (passed by value).  What the tile kernel reads before its first load sits
 // together, so that a few wide scalar loads fetch it at once.
@@ -65,7 +67,7 @@ struct Params {
     unsigned waves_per_block;  // wavefronts per workgroup (the block size / 64)
     float wr, wg, wb;       // gray weights, times the Sobel scale (and 1/255 for 8-bit input)
     float k;                // coarsity constant
-    unsigned flags;         // HARRIS_TUNE_* bits and kOutShifted
+    unsigned flags;         // HARRIS_TUNE_* bits, kOutShifted, kPatches
     unsigned out_kind;      // a harris_out_dtype (other than float32: tile kernel only)
     float q_scale, q_offset;   // 8-bit results: code = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)
     int binomial;           // 1: window [1 2 1; 2 4 2; 1 2 1], 0: unweighted 3x3 sum
@@ -74,6 +76,9 @@ struct Params {
     unsigned n_bands;       // bands (BANDS) or tiles down the image (TILES)
     unsigned blocks_x;      // BANDS: workgroups across a row of bands
     unsigned blocks_per_image;  // BANDS: workgroups per image
+    // kPatches: lanes of an image, 65536 / that rounded up, images of a wavefront, images of the call.
+    // tiles_per_image is then the number of bands down the images, rows_per_band their height.
+    unsigned image_lanes, image_lanes_inverse, images, batch;
 };
 
 // Enqueue the fused kernel.  `shape` must come from harris_plan (all fields set).
@@ -85,6 +90,7 @@ int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int 
 // (hipErrorInvalidValue for a shape it has no kernel for).
 int launch_tiles_f32(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
 int launch_tiles_u8(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
+int launch_patches(const Params& p, int dtype, unsigned grid, unsigned block, void* stream);
 int launch_bands(const Params& p, const harris_tuning& shape, int dtype, unsigned grid, unsigned block, void* stream);
 
 // Floats of workspace the grouped (unfused) pipelines need; 0 for an unknown grouping.

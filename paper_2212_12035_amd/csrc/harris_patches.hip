@@ -1,0 +1,144 @@
+// The tile schedule for batches of narrow images (patches): several images side by side in a wavefront.
+//
+// harris_tile_kernel gives every strip of an image a wavefront of its own, 64 lanes of four
+// columns; an image of 64 columns keeps 16 of them busy.  Here a wavefront's lanes are cut into
+// groups of W / 4 (rounded up), one image each, as many as fit.  All groups work on the same rows of
+// their images, so rows stay uniform per wavefront and only the lanes' offsets differ.  The lane
+// shift between neighbouring columns crosses from one group into the next, but only into a
+// group's last lane, whose columns are halo: every result column c takes input columns up to c + 4
+// < W, all of its own group.
+//
+// A workgroup holds whole images, or bands of equal height where they are taller than 16 wavefronts of
+// four rows: the four rows that two tiles would both read are read once.  Everything else is
+// the tile kernel's barrier form (harris_kernels.h): all rows requested at once, four gray rows handed
+// to the wavefront above through LDS, results stored in one burst.
+//
+// Input is loaded with the default policy: rows of a narrow image share their cache lines with the rows
+// above and below, which other wavefronts of the workgroup load (2048 images of 64x64 uint8:
+// 11.6 us, non-temporal 15.4; 1000 of 65x65 float32 13.3 / 16.1).  Results are stored non-temporal, not
+// written through, for the same reason (28.2 / 33.0 us for 2048 of 64x64 float32 at 16 wavefronts).
+// Measured against one image per wavefront (harris_tile_kernel): 2048 images of 64x64 float32 26.4 us
+// (5.0 TB/s; 38.2), 8192 of 32x32 26.7 (82.2), 1000 of 65x65 13.3 (24.0), 300 of 128x128 13.7 (15.8), 2048 of
+// 64x64 uint8 11.6 (28.2), 1343 of 80x27 uint8 9.2 (30.2).
+#include "harris_kernels.h"
+
+namespace {
+
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+// One row of the three planes of a lane's image.  rows[c] is the row's first element in the group's
+// first image, `bytes` what lies from there to the row's end in the group's last image; voff the
+// lane's offset.  Loads beyond the end give zeros.  A float32 lane that straddles the end of its row
+// reads what follows it (rows are then contiguous, see the planner); nobody uses that.
+// 8-bit rows start on any byte: a lane loads its four bytes where they are, the last lane of a row the
+// row's last four, shifted down by `drop` bits.
+__device__ __forceinline__ void load_patch_row(RawRow<float, 4>& r, const float* row, size_t plane, uint32_t bytes, uint32_t voff, uint32_t) {
+    load_row<float, 4, kAuxDefault>(r, row, plane, bytes, voff);
+}
+__device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint8_t* row, size_t plane, uint32_t, uint32_t voff, uint32_t drop) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) r.w[c][0] = *reinterpret_cast<const u32_any*>(row + c * plane + voff) >> drop;
+}
+
+template <typename In, bool BINOM>
+__global__ __launch_bounds__(1024) void harris_patch_kernel(const harris_launch::Params p) {
+    constexpr int PX = 4, RW = 4;
+    constexpr bool F32 = std::is_same<In, float>::value;
+    extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]
+
+    const unsigned lane = threadIdx.x % kWave;
+    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const unsigned tile = xcd_contiguous(blockIdx.x, p.n_blocks);
+    const unsigned group = harris_launch::fastdiv(tile, p.by_tiles_per_image);      // of p.images images
+    const int band = (int)(tile - group * p.tiles_per_image);
+
+    const int tile_rows = p.rows_per_band;
+    const int y_wave = band * tile_rows + (int)wave * RW;
+    const int y_end = min(p.n, (band + 1) * tile_rows);
+    const int out_rows = max(0, min(RW, y_end - y_wave));
+
+    const unsigned per_image = p.image_lanes;                   // lanes of an image
+    const unsigned sub = (lane * p.image_lanes_inverse) >> 16;  // lane / per_image
+    const unsigned images = min(p.images, p.batch - group * p.images);   // of this group
+    const unsigned col = (lane - sub * per_image) * PX;
+    const bool live = sub < images;
+
+    const size_t first = (size_t)group * p.images;
+    const In* in = static_cast<const In*>(p.rgb) + first * (size_t)p.in_image_pitch;
+    float* out = static_cast<float*>(p.out) + first * (size_t)p.out_image_pitch;
+    const uint32_t in_image = (uint32_t)(p.in_image_pitch * sizeof(In)), out_image = (uint32_t)(p.out_image_pitch * sizeof(float));
+    const uint32_t in_bytes = (images - 1) * in_image + (uint32_t)p.W * (uint32_t)sizeof(In);
+    const uint32_t out_bytes = (images - 1) * out_image + (uint32_t)p.m * 4u;
+    const unsigned last_col = (unsigned)p.W - 4u;
+    // 8-bit lanes without an image load the first image's bytes: every load lies inside a row.
+    const uint32_t in_voff = F32 ? (live ? sub * in_image + col * 4u : 0x80000000u) : (live ? sub * in_image + min(col, last_col) : 0u);
+    const uint32_t drop = col > last_col ? 8u * ((col - last_col) & 3u) : 0u;
+
+    RawRow<In, PX> raw[RW];
+    const size_t plane = (size_t)p.in_plane_pitch;
+    static_for<0, RW>([&](auto tt) {
+        constexpr int t = decltype(tt)::value;
+        const int r = y_wave + t;
+        load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? in_bytes : 0u, in_voff, drop);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+
+    constexpr bool DIFF = F32;
+    LineBuffers<PX> lb;
+    float gc[PX], none[PX], results[RW][PX];
+    float* my_halo = halo_lds + ((size_t)wave * 4 * kWave + lane) * PX;
+    static_for<0, RW>([&](auto tt) {
+        constexpr int t = decltype(tt)::value;
+        gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
+#pragma unroll
+        for (int i = 0; i < PX; ++i) my_halo[(size_t)t * kWave * PX + i] = gc[i];
+        row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, none);
+        __builtin_amdgcn_sched_barrier(0);
+    });
+    __syncthreads();
+    if (out_rows <= 0) return;                                  // the last wavefront only supplies rows; no barrier follows
+    const float* below = my_halo + (size_t)4 * kWave * PX;      // out_rows > 0: there is a wavefront below (planner)
+    static_for<RW, RW + 4>([&](auto tt) {
+        constexpr int t = decltype(tt)::value;
+#pragma unroll
+        for (int i = 0; i < PX; ++i) gc[i] = below[(size_t)(t - RW) * kWave * PX + i];
+        row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
+        pin_values<PX>(results[t - 4]);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+
+    const unsigned m = (unsigned)p.m, rest = m & 3u;
+    const uint32_t at = sub * out_image + col * 4u;
+    const uint32_t whole_voff = live && col + 4u <= m ? at : 0x80000000u;
+    const bool straddles = live && col < m && col + 4u > m;     // the row's last `rest` columns
+    const uint32_t pair_voff = straddles && rest >= 2u ? at : 0x80000000u;
+    const uint32_t single_voff = straddles && (rest & 1u) ? at + (rest & 2u) * 4u : 0x80000000u;
+    static_for<0, RW>([&](auto jj) {
+        constexpr int j = decltype(jj)::value;
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(out + (size_t)(y_wave + j) * (size_t)p.out_row_pitch, j < out_rows ? out_bytes : 0u);
+        store_row<PX, kAuxStore>(results[j], rs, whole_voff);
+        if (rest != 0u) {
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(results[j][0]), __float_as_uint(results[j][1])}, rs, pair_voff, 0, kAuxStore);
+            const uint32_t r0 = __float_as_uint(results[j][0]), r2 = __float_as_uint(results[j][2]);
+            __builtin_amdgcn_raw_buffer_store_b32((rest & 2u) ? r2 : r0, rs, single_voff, 0, kAuxStore);
+        }
+    });
+}
+
+}  // namespace
+
+namespace harris_launch {
+
+int launch_patches(const Params& p, int dtype, unsigned grid, unsigned block, void* stream_) {
+    hipStream_t stream = static_cast<hipStream_t>(stream_);
+    if (dtype == HARRIS_U8) {
+        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<uint8_t, true>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
+        else hipLaunchKernelGGL((harris_patch_kernel<uint8_t, false>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
+    } else {
+        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<float, true>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
+        else hipLaunchKernelGGL((harris_patch_kernel<float, false>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
+    }
+    return (int)hipGetLastError();
+}
+
+}  // namespace harris_launch

@@ -418,6 +418,31 @@ def test_sweep_candidates_are_launch_shapes_the_library_knows(pkg):
     assert any((s["rows"], s["waves_per_block"], s["flags"] & pkg.HARRIS_TUNE_FLAG_HANDOFF) == (chosen["rows"], chosen["waves_per_block"], chosen["flags"] & pkg.HARRIS_TUNE_FLAG_HANDOFF) for s in shapes)
 
 
+def test_plan_for_batches_of_narrow_images(pkg):
+    # Images side by side in a wavefront: the launch must hold every image and every result row, whatever
+    # the width, and the lanes' division by the lanes of an image (a multiplication) must be exact.
+    for W in range(5, 140):
+        lanes = (W + 3) // 4
+        images = 64 // lanes
+        inverse = (65535 + lanes) // lanes
+        assert all((lane * inverse) >> 16 == lane // lanes for lane in range(64))
+        for dtype in (pkg.HARRIS_F32, pkg.HARRIS_U8):
+            for H in (5, 31, 32, 33, 60, 61, 64, 200):
+                B = (1 << 18) // (H * W) + 2
+                shape, blocks = pkg.harris_plan(dtype, B, H, W)
+                packed = images >= 2 and not (images == 2 and dtype == pkg.HARRIS_F32 and W % 4)
+                assert (shape["flags"] & pkg.HARRIS_TUNE_STREAM_LOADS) and shape["schedule"] == pkg.HARRIS_SCHEDULE_TILES
+                if not packed:
+                    continue
+                n, groups = H - 4, -(-B // images)
+                assert shape["px"] == 4 and shape["rows"] == 4 and 2 <= shape["waves_per_block"] <= 8 and blocks % groups == 0
+                bands = blocks // groups
+                assert bands * 4 * (shape["waves_per_block"] - 1) >= n > (bands - 1) * -(-n // bands)
+                # a caller's own shape, other result types and single images are not affected
+                assert pkg.harris_plan(dtype, B, H, W, tuning=dict(rows=4, waves_per_block=4))[1] == B * -(-n // 12) * -(-(W - 4) // 252)
+        assert pkg.harris_plan(pkg.HARRIS_F32, 1, 1 << 14, W)[1] != 0
+
+
 def test_benchmark_refuses_more_than_one_gpu():
     # The benchmark measures one GPU; asked for more it says so and exits before touching a device.
     import subprocess

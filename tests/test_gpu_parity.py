@@ -779,6 +779,44 @@ def test_narrow_results_on_rows_of_any_alignment(gpu, oracle, fmt, W):
             assert bool((flat == 77).all() if fmt == "codes" else torch.isnan(flat).all())
 
 
+@pytest.mark.parametrize("H,W", [(5, 5), (32, 8), (33, 29), (61, 31), (40, 33), (64, 64), (24, 65), (60, 84), (37, 85), (90, 121), (32, 128), (29, 126)])
+def test_batches_of_narrow_images(gpu, oracle, H, W):
+    # Several narrow images side by side in a wavefront: widths that fill the lanes' groups exactly and
+    # with remainders of one to three columns, two to 32 images per wavefront, heights of one band
+    # exactly, one row more and several bands, a last group that is not full, dense images and padded
+    # rows and planes, both input types, both windows.  Against the oracle, and nothing beside the results is written.
+    import torch
+    images = 64 // ((W + 3) // 4)
+    B = (1 << 18) // (H * W) + 1
+    B += 1 if B % images == 0 else 0
+    n, m = H - 4, W - 4
+    for u8 in (False, True):
+        rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(500 + W, B, H, W)
+        src = torch.from_numpy(rgb).cuda()
+        for window in (gpu.HARRIS_WINDOW_BOX, gpu.HARRIS_WINDOW_BINOMIAL):
+            say("case %d images of %dx%d, %s, window %d" % (B, H, W, rgb.dtype, window))
+            want = oracle.harris(rgb, K, 1.0, window)
+            flat = torch.full((64 + B * n * m + 64,), float("nan"), device="cuda")
+            out = flat[64:64 + B * n * m].view(B, n, m)
+            gpu.harris_coarsity_ex(src, K, 1.0, window, out=out)
+            torch.cuda.synchronize()
+            check(out.cpu().numpy(), want)
+            assert bool(torch.isnan(flat[:64]).all()) and bool(torch.isnan(flat[64 + B * n * m:]).all())
+        # Rows, planes and images apart (an odd number of elements each for 8-bit input), results likewise.
+        pad = 3 if u8 else 4
+        big = torch.zeros((B, 3, H + 2, W + pad), dtype=src.dtype, device="cuda")
+        big[:] = 199 if u8 else float("nan")
+        view = big[:, :, 1:H + 1, 2 if u8 else 4:(2 if u8 else 4) + W] if u8 or W % 4 == 0 else big[:, :, 1:H + 1, 1:1 + W]
+        view.copy_(src)
+        flat = torch.full((B, n + 1, m + 5), float("nan"), device="cuda")
+        out = flat[:, :n, 2:2 + m]
+        gpu.harris_coarsity_pitched(view, out, K)
+        torch.cuda.synchronize()
+        check(out.cpu().numpy(), oracle.harris(rgb, K))
+        out.fill_(float("nan"))
+        assert bool(torch.isnan(flat).all())
+
+
 # ---------------------------------------------------------------- seeded random shapes, layouts and launch shapes
 
 def test_random_shapes_layouts_and_launch_shapes(gpu, oracle):
