@@ -123,23 +123,23 @@ def _tuning_arg(tuning):
 
 def _prepare(rgb, out, want_dtype):
     import torch
-    if not isinstance(rgb, torch.Tensor) or rgb.device.type != "cuda":
+    if not isinstance(rgb, torch.Tensor) or not rgb.is_cuda:
         raise TypeError("rgb must be a torch tensor on a ROCm device")
     if rgb.dtype != want_dtype:
         raise TypeError("rgb must have dtype %s" % want_dtype)
-    if rgb.dim() != 4 or rgb.shape[1] != 3:
+    shape = rgb.shape
+    if len(shape) != 4 or shape[1] != 3:
         raise ValueError("rgb must have shape [batch][3][H][W]")
     if not rgb.is_contiguous():
         raise ValueError("rgb must be contiguous (dense planar layout)")
-    B, _, H, W = rgb.shape
+    B, _, H, W = shape
     if H < 4 or W < 4:
         raise HarrisError(-2, harris_strerror(-2))
     if out is None:
         out = torch.empty((B, H - 4, W - 4), dtype=torch.float32, device=rgb.device)
-    else:
-        if (not isinstance(out, torch.Tensor) or out.device != rgb.device or out.dtype != torch.float32
-                or tuple(out.shape) != (B, H - 4, W - 4) or not out.is_contiguous()):
-            raise ValueError("out must be a contiguous float32 tensor [batch][H-4][W-4] on rgb's device")
+    elif (not isinstance(out, torch.Tensor) or out.device != rgb.device or out.dtype != torch.float32
+            or out.shape != (B, H - 4, W - 4) or not out.is_contiguous()):
+        raise ValueError("out must be a contiguous float32 tensor [batch][H-4][W-4] on rgb's device")
     return B, H, W, out
 
 
@@ -150,12 +150,28 @@ def _stream_ptr(stream, device):
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
+def _enqueue(function, device, stream, *args):
+    """Calls a library function, its last argument the stream, with `device` current.  The call costs less
+    than the two objects it would otherwise make, a Stream and a device guard (3.5 of 9.4 us for a small
+    image): the current stream's handle is asked for by itself, and the guard is entered only
+    where another device is current."""
+    import torch
+    index = device.index
+    handle = torch._C._cuda_getCurrentRawStream(index) if stream is None else _stream_ptr(stream, device)
+    if index == torch.cuda.current_device():
+        status = function(*args, handle)
+    else:
+        with torch.cuda.device(device):
+            status = function(*args, handle)
+    if status != 0:
+        _check(status)
+
+
 def harris_coarsity(rgb, k: float = 0.04, out=None, stream=None):
     """float32 rgb[batch][3][H][W] -> float32 out[batch][H-4][W-4]; integer Sobel, 3x3 sum."""
     import torch
     B, H, W, out = _prepare(rgb, out, torch.float32)
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity(rgb.data_ptr(), B, H, W, k, out.data_ptr(), _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity, rgb.device, stream, rgb.data_ptr(), B, H, W, k, out.data_ptr())
     return out
 
 
@@ -163,8 +179,7 @@ def harris_coarsity_u8(rgb, k: float = 0.04, out=None, stream=None):
     """uint8 rgb[batch][3][H][W] (taken as u/255) -> float32 out[batch][H-4][W-4]."""
     import torch
     B, H, W, out = _prepare(rgb, out, torch.uint8)
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_u8(rgb.data_ptr(), B, H, W, k, out.data_ptr(), _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_u8, rgb.device, stream, rgb.data_ptr(), B, H, W, k, out.data_ptr())
     return out
 
 
@@ -176,9 +191,8 @@ def harris_coarsity_ex(rgb, k: float = 0.04, sobel_scale: float = 1.0, window: i
         raise TypeError("rgb must be a float32 or uint8 torch tensor")
     B, H, W, out = _prepare(rgb, out, rgb.dtype)
     dtype = HARRIS_U8 if rgb.dtype == torch.uint8 else HARRIS_F32
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_ex(rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window,
-                                                 out.data_ptr(), _tuning_arg(tuning), _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_ex, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window,
+             out.data_ptr(), _tuning_arg(tuning))
     return out
 
 
@@ -187,19 +201,21 @@ def _strided(rgb, out, out_dtypes, what):
     rgb [batch][3][H][W] and out [batch][H-4][W-4] may be views (padded rows, a region of
     interest, a slice of planes) as long as the last stride is 1; the pitches are the strides."""
     import torch
-    if (not isinstance(rgb, torch.Tensor) or rgb.device.type != "cuda" or rgb.dtype not in (torch.float32, torch.uint8)
+    if (not isinstance(rgb, torch.Tensor) or not rgb.is_cuda or rgb.dtype not in (torch.float32, torch.uint8)
             or rgb.dim() != 4 or rgb.shape[1] != 3):
         raise TypeError("rgb must be a float32 or uint8 ROCm tensor of shape [batch][3][H][W]")
     B, _, H, W = rgb.shape
     if H < 4 or W < 4:
         raise HarrisError(-2, harris_strerror(-2))
     if (not isinstance(out, torch.Tensor) or out.device != rgb.device or out.dtype not in out_dtypes
-            or tuple(out.shape) != (B, H - 4, W - 4)):
+            or out.shape != (B, H - 4, W - 4)):
         raise ValueError("out must be a %s tensor [batch][H-4][W-4] on rgb's device" % what)
-    if (W > 1 and rgb.stride(3) != 1) or (W - 4 > 1 and out.stride(2) != 1):
+    image, plane, row, column = rgb.stride()
+    out_image, out_row, out_column = out.stride()
+    if (W > 1 and column != 1) or (W - 4 > 1 and out_column != 1):
         raise ValueError("the last dimension of rgb and out must have stride 1")
-    lay = HarrisLayout(rgb.stride(2) if H > 1 else W, rgb.stride(1), rgb.stride(0) if B > 1 else 3 * rgb.stride(1),
-                       out.stride(1) if H - 4 > 1 else max(W - 4, 1), out.stride(0) if B > 1 else max(1, (H - 4) * out.stride(1)))
+    lay = HarrisLayout(row if H > 1 else W, plane, image if B > 1 else 3 * plane,
+                       out_row if H - 4 > 1 else max(W - 4, 1), out_image if B > 1 else max(1, (H - 4) * out_row))
     return B, H, W, lay, HARRIS_U8 if rgb.dtype == torch.uint8 else HARRIS_F32
 
 
@@ -208,9 +224,8 @@ def harris_coarsity_pitched(rgb, out, k: float = 0.04, sobel_scale: float = 1.0,
     """General form for strided tensors (views); float32 result."""
     import torch
     B, H, W, lay, dtype = _strided(rgb, out, (torch.float32,), "float32")
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_pitched(rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k, sobel_scale, window,
-                                                      out.data_ptr(), _tuning_arg(tuning), _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_pitched, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k,
+             sobel_scale, window, out.data_ptr(), _tuning_arg(tuning))
     return out
 
 
@@ -220,10 +235,8 @@ def harris_coarsity_typed(rgb, out, k: float = 0.04, sobel_scale: float = 1.0, w
     import torch
     kinds = {torch.float32: HARRIS_OUT_F32, torch.float16: HARRIS_OUT_F16, torch.bfloat16: HARRIS_OUT_BF16}
     B, H, W, lay, dtype = _strided(rgb, out, kinds, "float32, float16 or bfloat16")
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_typed(rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k, sobel_scale, window,
-                                                    out.data_ptr(), kinds[out.dtype], _tuning_arg(tuning),
-                                                    _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_typed, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k,
+             sobel_scale, window, out.data_ptr(), kinds[out.dtype], _tuning_arg(tuning))
     return out
 
 
@@ -232,10 +245,8 @@ def harris_coarsity_quantized(rgb, out, q_scale: float, q_offset: float, k: floa
     """8-bit result: out (uint8 [batch][H-4][W-4], may be a view) = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)."""
     import torch
     B, H, W, lay, dtype = _strided(rgb, out, (torch.uint8,), "uint8")
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_quantized(rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k, sobel_scale, window,
-                                                        q_scale, q_offset, out.data_ptr(), _tuning_arg(tuning),
-                                                        _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_quantized, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k,
+             sobel_scale, window, q_scale, q_offset, out.data_ptr(), _tuning_arg(tuning))
     return out
 
 
@@ -281,10 +292,8 @@ def harris_coarsity_grouped(rgb, k: float = 0.04, sobel_scale: float = 1.0, wind
     if workspace is None:
         workspace = torch.empty(max(1, need // 4), dtype=torch.float32, device=rgb.device)
     dtype = HARRIS_U8 if rgb.dtype == torch.uint8 else HARRIS_F32
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_grouped(rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window, grouping,
-                                                      workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                                                      out.data_ptr(), _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_grouped, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window,
+             grouping, workspace.data_ptr(), workspace.numel() * workspace.element_size(), out.data_ptr())
     return out
 
 
@@ -302,9 +311,8 @@ def harris_coarsity_grouped_static(rgb, out, k: float = 0.04, sobel_scale: float
         raise ValueError("out must be given: this entry point allocates nothing")
     B, H, W, out = _prepare(rgb, out, rgb.dtype)
     dtype = HARRIS_U8 if rgb.dtype == torch.uint8 else HARRIS_F32
-    with torch.cuda.device(rgb.device):
-        _check(load_library().harris_coarsity_grouped_static(rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window, grouping,
-                                                             out.data_ptr(), _stream_ptr(stream, rgb.device)))
+    _enqueue(load_library().harris_coarsity_grouped_static, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window,
+             grouping, out.data_ptr())
     return out
 
 
