@@ -11,8 +11,13 @@
 // (The thesis's table starts from a grayscale image; the grayscale stage is a kernel
 // of its own here.)  They exist to measure what fusion buys on this GPU with the same
 // harness, and as a second GPU implementation that shares no code with the fused
-// kernels: one thread per result pixel, every tap a global load, no LDS, no lane
-// exchange, no separation of the 3x3 kernels.  They are baselines, not tuned.
+// kernels: no LDS, no lane exchange, no separation of the 3x3 kernels.  What bounds them is what
+// they are compared for, the intermediate images' way through memory and one launch per kernel, so
+// a thread takes four neighbouring pixels (16-byte accesses; rows of width W-2 and W-4 start on 4-byte
+// boundaries, which is all that global accesses of several words need) and, where it reads a 3x3
+// neighbourhood, two rows of them, so that a tap is loaded 1.5 x 2 times instead of 9.
+// One 1080x1920 float32 image, groupings 1, 2 and 3 together: 97.5 us (one pixel per thread 119), 8 such
+// images 600 us (810).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -29,69 +34,154 @@ static __device__ __align__(256) float scratch[HARRIS_GROUPED_SCRATCH_BYTES / si
 
 namespace {
 
-constexpr int kTileX = 64, kTileY = 4;      // 256 threads: 64 consecutive columns of 4 rows
+// Kernels are templates over a thread's neighbouring pixels PX (4 or 1), and rows ROWS in the 3x3 stages
+// (2 or 1): PX = 4, ROWS = 2 from kWidePixels on.  Smaller images keep one pixel per thread: a launch
+// is then bound by its latency, and eight times the wavefronts hide more of it (the three groupings on
+// 600x800: 48.7 us, wide 52.4; on 720x1000 60.4 and 55.0).
+constexpr int kTileX = 64, kTileY = 4;      // 256 threads: 64 PX columns of 4 ROWS rows
 
+typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef uint32_t word_any __attribute__((aligned(1)));
+
+// N values from p on, of which the first `left` (>= 1) exist; the others are 0.
+template <int N>
+__device__ __forceinline__ void load_values(const float* p, int left, float (&v)[N]) {
+    if (N >= 4 && left >= N) {
+        const f4 a = *reinterpret_cast<const f4*>(p);
+        v[0] = a.x; v[1 % N] = a.y; v[2 % N] = a.z; v[3 % N] = a.w;
+        if constexpr (N == 6) {
+            const f2 b = *reinterpret_cast<const f2*>(p + 4);
+            v[4] = b.x; v[5] = b.y;
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = i < left ? p[i] : 0.0f;
+    }
+}
+template <int N>
+__device__ __forceinline__ void load_values(const uint8_t* p, int left, float (&v)[N]) {
+    if (N == 4 && left >= N) {
+        const uint32_t w = *reinterpret_cast<const word_any*>(p);
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = (float)((w >> (8 * i)) & 0xffu);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = i < left ? (float)p[i] : 0.0f;
+    }
+}
+template <int N>
+__device__ __forceinline__ void store_values(float* p, int left, const float (&v)[N]) {
+    if (N == 4 && left >= N) {
+        *reinterpret_cast<f4*>(p) = f4{v[0], v[1 % N], v[2 % N], v[3 % N]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) if (i < left) p[i] = v[i];
+    }
+}
+
+// First value of this thread in a flat array of `count`, or false.  The last thread of an array or a
+// row takes its last four values, some of which its neighbour computes and stores as well (the same
+// ones): a path of its own for what is left would cost its wavefront a second memory latency
+// (1431x970, the three groupings: 73.8 against 74.5 us).
+template <int PX>
+__device__ __forceinline__ bool flat(size_t count, size_t& at, int& left) {
+    at = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * PX;
+    if (at >= count) return false;
+    at = min(at, max(count, (size_t)PX) - PX);
+    left = (int)min(count - at, (size_t)PX);
+    return true;
+}
+
+// First pixel of this thread in a w x h image, or false.
+template <int PX, int ROWS>
 __device__ __forceinline__ bool pixel(int w, int h, int& x, int& y) {
-    x = blockIdx.x * kTileX + threadIdx.x;
-    y = blockIdx.y * kTileY + threadIdx.y;
-    return x < w && y < h;
+    x = (blockIdx.x * kTileX + threadIdx.x) * PX;
+    y = (blockIdx.y * kTileY + threadIdx.y) * ROWS;
+    if (x >= w || y >= h) return false;
+    x = min(x, max(w - PX, 0));
+    return true;
+}
+
+// The input rows of ROWS result rows from (y, x) on, of an h x w result; in is (h+2) x (w+2).  Rows below
+// the image repeat its last one (their results are not stored).
+template <int PX, int ROWS>
+struct Taps {
+    float v[ROWS + 2][PX + 2];
+    __device__ __forceinline__ void load(const float* in, int w, int h, int y, int x) {
+#pragma unroll
+        for (int r = 0; r < ROWS + 2; ++r) load_values<PX + 2>(in + (size_t)min(y + r, h + 1) * (w + 2) + x, w + 2 - x, v[r]);
+    }
+};
+template <int PX, int ROWS>
+__device__ __forceinline__ void store_rows(float* out, int w, int h, int y, int x, const float (&v)[ROWS][PX]) {
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        if (y + r < h) store_values(out + (size_t)(y + r) * w + x, w - x, v[r]);
 }
 
 // Conversion and grayscale.  rgb[b][3][H][W] -> gray[b][H][W]; in_scale is 1 (float32) or 1/255 (uint8).
-template <typename In>
-__global__ void gray_kernel(const In* rgb, float* gray, int H, int W, float in_scale) {
-    int x, y;
-    if (!pixel(W, H, x, y)) return;
-    const size_t plane = (size_t)H * W, img = (size_t)blockIdx.z * 3 * plane, at = (size_t)y * W + x;
-    const float r = (float)rgb[img + at] * in_scale, g = (float)rgb[img + plane + at] * in_scale, b = (float)rgb[img + 2 * plane + at] * in_scale;
-    gray[(size_t)blockIdx.z * plane + at] = 0.299f * r + 0.587f * g + 0.114f * b;
+template <int PX, typename In>
+__global__ void gray_kernel(const In* rgb, float* gray, size_t plane, float in_scale) {
+    size_t at;
+    int left;
+    if (!flat<PX>(plane, at, left)) return;
+    const In* p = rgb + (size_t)blockIdx.z * 3 * plane + at;
+    float r[PX], g[PX], b[PX], o[PX];
+    load_values(p, left, r);
+    load_values(p + plane, left, g);
+    load_values(p + 2 * plane, left, b);
+#pragma unroll
+    for (int i = 0; i < PX; ++i) o[i] = 0.299f * (r[i] * in_scale) + 0.587f * (g[i] * in_scale) + 0.114f * (b[i] * in_scale);
+    store_values(gray + (size_t)blockIdx.z * plane + at, left, o);
 }
 
-// The two Sobel responses at result pixel (y, x) of an h x w result; in is (h+2) x (w+2).
-__device__ __forceinline__ void sobel_at(const float* in, int w, int y, int x, float s, float& ix, float& iy) {
-    const float* r0 = in + (size_t)y * (w + 2) + x;
-    const float* r1 = r0 + (w + 2);
-    const float* r2 = r1 + (w + 2);
+// The two Sobel responses at row r, column i of a thread's pixels.
+template <int PX, int ROWS>
+__device__ __forceinline__ void sobel_at(const Taps<PX, ROWS>& t, int r, int i, float s, float& ix, float& iy) {
+    const float *r0 = t.v[r] + i, *r1 = t.v[r + 1] + i, *r2 = t.v[r + 2] + i;
     ix = s * ((r0[2] - r0[0]) + 2.0f * (r1[2] - r1[0]) + (r2[2] - r2[0]));
     iy = s * ((r2[0] - r0[0]) + 2.0f * (r2[1] - r0[1]) + (r2[2] - r0[2]));
 }
 
-// Sobel stage, one response per launch: which = 0 for Sx, 1 for Sy.  in[b][h+2][w+2] -> out[b][h][w].
-__global__ void sobel_kernel(const float* in, float* out, int h, int w, float s, int which) {
+// Sobel stage: one response per launch (Sx or Sy), both, or their three products.  in[b][h+2][w+2] ->
+// out_i[b][h][w].
+enum Stage { kSx, kSy, kSobelPair, kSobelProducts };
+template <int PX, int ROWS, int STAGE>
+__global__ void sobel_kernel(const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
     int x, y;
-    if (!pixel(w, h, x, y)) return;
-    float ix, iy;
-    sobel_at(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, y, x, s, ix, iy);
-    out[(size_t)blockIdx.z * h * w + (size_t)y * w + x] = which == 0 ? ix : iy;
-}
-
-// Sobel stage, both responses.
-__global__ void sobel_pair_kernel(const float* in, float* ix_out, float* iy_out, int h, int w, float s) {
-    int x, y;
-    if (!pixel(w, h, x, y)) return;
-    float ix, iy;
-    sobel_at(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, y, x, s, ix, iy);
-    const size_t at = (size_t)blockIdx.z * h * w + (size_t)y * w + x;
-    ix_out[at] = ix;
-    iy_out[at] = iy;
-}
-
-// Sobel pair and products.
-__global__ void sobel_products_kernel(const float* in, float* ixx, float* ixy, float* iyy, int h, int w, float s) {
-    int x, y;
-    if (!pixel(w, h, x, y)) return;
-    float ix, iy;
-    sobel_at(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, y, x, s, ix, iy);
-    const size_t at = (size_t)blockIdx.z * h * w + (size_t)y * w + x;
-    ixx[at] = ix * ix;
-    ixy[at] = ix * iy;
-    iyy[at] = iy * iy;
+    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    Taps<PX, ROWS> t;
+    t.load(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, h, y, x);
+    float a[ROWS][PX], b[ROWS][PX], c[ROWS][PX];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int i = 0; i < PX; ++i) {
+            float ix, iy;
+            sobel_at(t, r, i, s, ix, iy);
+            a[r][i] = STAGE == kSobelProducts ? ix * ix : STAGE == kSy ? iy : ix;
+            b[r][i] = STAGE == kSobelProducts ? ix * iy : iy;
+            c[r][i] = iy * iy;
+        }
+    const size_t image = (size_t)blockIdx.z * h * w;
+    store_rows(out0 + image, w, h, y, x, a);
+    if constexpr (STAGE >= kSobelPair) store_rows(out1 + image, w, h, y, x, b);
+    if constexpr (STAGE == kSobelProducts) store_rows(out2 + image, w, h, y, x, c);
 }
 
 // Products, one per launch.
+template <int PX>
 __global__ void mul_kernel(const float* a, const float* b, float* out, size_t count) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) out[i] = a[i] * b[i];
+    size_t at;
+    int left;
+    if (!flat<PX>(count, at, left)) return;
+    float u[PX], v[PX], o[PX];
+    load_values(a + at, left, u);
+    load_values(b + at, left, v);
+#pragma unroll
+    for (int i = 0; i < PX; ++i) o[i] = u[i] * v[i];
+    store_values(out + at, left, o);
 }
 
 // 3x3 window weights: all ones, or [1 2 1; 2 4 2; 1 2 1].
@@ -99,15 +189,30 @@ __device__ __forceinline__ float window_weight(int i, int j, int binomial) {
     return binomial ? (float)((2 - (i > 1 ? i - 1 : 1 - i)) * (2 - (j > 1 ? j - 1 : 1 - j))) : 1.0f;
 }
 
+// Window sum at row r, column i of a thread's pixels.
+template <int PX, int ROWS>
+__device__ __forceinline__ float window_at(const Taps<PX, ROWS>& t, int r, int i, int binomial) {
+    float acc = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) acc += window_weight(a, b, binomial) * t.v[r + a][i + b];
+    return acc;
+}
+
 // Window sums, one per launch.  in[b][h+2][w+2] -> out[b][h][w].
+template <int PX, int ROWS>
 __global__ void window_kernel(const float* in, float* out, int h, int w, int binomial) {
     int x, y;
-    if (!pixel(w, h, x, y)) return;
-    const float* p = in + (size_t)blockIdx.z * (h + 2) * (w + 2) + (size_t)y * (w + 2) + x;
-    float acc = 0.0f;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) acc += window_weight(i, j, binomial) * p[(size_t)i * (w + 2) + j];
-    out[(size_t)blockIdx.z * h * w + (size_t)y * w + x] = acc;
+    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    Taps<PX, ROWS> t;
+    t.load(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, h, y, x);
+    float o[ROWS][PX];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int i = 0; i < PX; ++i) o[r][i] = window_at(t, r, i, binomial);
+    store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
 __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, float k) {
@@ -116,48 +221,102 @@ __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, fl
 }
 
 // Coarsity.
+template <int PX>
 __global__ void coarsity_kernel(const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) out[i] = coarsity_of(sxx[i], sxy[i], syy[i], k);
+    size_t at;
+    int left;
+    if (!flat<PX>(count, at, left)) return;
+    float a[PX], b[PX], c[PX], o[PX];
+    load_values(sxx + at, left, a);
+    load_values(sxy + at, left, b);
+    load_values(syy + at, left, c);
+#pragma unroll
+    for (int i = 0; i < PX; ++i) o[i] = coarsity_of(a[i], b[i], c[i], k);
+    store_values(out + at, left, o);
 }
 
 // Window sums and coarsity from the three product images.
+template <int PX, int ROWS>
 __global__ void window_coarsity_kernel(const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
     int x, y;
-    if (!pixel(w, h, x, y)) return;
-    const size_t at = (size_t)blockIdx.z * (h + 2) * (w + 2) + (size_t)y * (w + 2) + x;
-    float sxx = 0.0f, sxy = 0.0f, syy = 0.0f;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            const float wt = window_weight(i, j, binomial);
-            const size_t q = at + (size_t)i * (w + 2) + j;
-            sxx += wt * ixx[q];
-            sxy += wt * ixy[q];
-            syy += wt * iyy[q];
-        }
-    out[(size_t)blockIdx.z * h * w + (size_t)y * w + x] = coarsity_of(sxx, sxy, syy, k);
+    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    const size_t image = (size_t)blockIdx.z * (h + 2) * (w + 2);
+    Taps<PX, ROWS> a, b, c;
+    a.load(ixx + image, w, h, y, x);
+    b.load(ixy + image, w, h, y, x);
+    c.load(iyy + image, w, h, y, x);
+    float o[ROWS][PX];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int i = 0; i < PX; ++i) o[r][i] = coarsity_of(window_at(a, r, i, binomial), window_at(b, r, i, binomial), window_at(c, r, i, binomial), k);
+    store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
 // Products, window sums and coarsity from the two Sobel images.
+template <int PX, int ROWS>
 __global__ void products_window_coarsity_kernel(const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
     int x, y;
-    if (!pixel(w, h, x, y)) return;
-    const size_t at = (size_t)blockIdx.z * (h + 2) * (w + 2) + (size_t)y * (w + 2) + x;
-    float sxx = 0.0f, sxy = 0.0f, syy = 0.0f;
-    for (int i = 0; i < 3; ++i)
-        for (int j = 0; j < 3; ++j) {
-            const float wt = window_weight(i, j, binomial);
-            const size_t q = at + (size_t)i * (w + 2) + j;
-            const float gx = ix[q], gy = iy[q];
-            sxx += wt * gx * gx;
-            sxy += wt * gx * gy;
-            syy += wt * gy * gy;
+    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    const size_t image = (size_t)blockIdx.z * (h + 2) * (w + 2);
+    Taps<PX, ROWS> gx, gy;
+    gx.load(ix + image, w, h, y, x);
+    gy.load(iy + image, w, h, y, x);
+    float o[ROWS][PX];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int i = 0; i < PX; ++i) {
+            float sxx = 0.0f, sxy = 0.0f, syy = 0.0f;
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const float wt = window_weight(p, q, binomial), u = gx.v[r + p][i + q], v = gy.v[r + p][i + q];
+                    sxx += wt * u * u;
+                    sxy += wt * u * v;
+                    syy += wt * v * v;
+                }
+            o[r][i] = coarsity_of(sxx, sxy, syy, k);
         }
-    out[(size_t)blockIdx.z * h * w + (size_t)y * w + x] = coarsity_of(sxx, sxy, syy, k);
+    store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
-dim3 grid2d(int w, int h, int batch) { return dim3((w + kTileX - 1) / kTileX, (h + kTileY - 1) / kTileY, batch); }
-dim3 grid1d(size_t count) { return dim3((unsigned)((count + 255) / 256)); }
+constexpr long long kWidePixels = 5LL << 17;
+
+// Every launch of grouping 1, 2 or 3.
+template <int PX, int ROWS>
+void enqueue(const void* rgb, int dtype, int batch, int H, int W, float k, float s, int binomial, int grouping, float* ws, float* out, hipStream_t st) {
+    const int h2 = H - 2, w2 = W - 2, h4 = H - 4, w4 = W - 4;
+    const size_t n0 = (size_t)batch * H * W, n2 = (size_t)batch * h2 * w2, n4 = (size_t)batch * h4 * w4, plane = (size_t)H * W;
+    const dim3 blk2(kTileX, kTileY), blk1(256);
+    auto grid = [&](int w, int h) { return dim3((w + kTileX * PX - 1) / (kTileX * PX), (h + kTileY * ROWS - 1) / (kTileY * ROWS), batch); };
+    auto grid1 = [](size_t count, int images) { return dim3((unsigned)((count + 256 * PX - 1) / (256 * PX)), 1, images); };
+    const dim3 grid2 = grid(w2, h2), grid4 = grid(w4, h4);
+    float* gray = ws;
+    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<PX, uint8_t>), grid1(plane, batch), blk1, 0, st, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
+    else hipLaunchKernelGGL((gray_kernel<PX, float>), grid1(plane, batch), blk1, 0, st, static_cast<const float*>(rgb), gray, plane, 1.0f);
+    if (grouping == 1) {
+        float *ix = gray + n0, *iy = ix + n2, *ixx = iy + n2, *ixy = ixx + n2, *iyy = ixy + n2, *sxx = iyy + n2, *sxy = sxx + n4, *syy = sxy + n4;
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSx>), grid2, blk2, 0, st, gray, ix, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSy>), grid2, blk2, 0, st, gray, iy, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL(mul_kernel<PX>, grid1(n2, 1), blk1, 0, st, ix, ix, ixx, n2);
+        hipLaunchKernelGGL(mul_kernel<PX>, grid1(n2, 1), blk1, 0, st, ix, iy, ixy, n2);
+        hipLaunchKernelGGL(mul_kernel<PX>, grid1(n2, 1), blk1, 0, st, iy, iy, iyy, n2);
+        hipLaunchKernelGGL((window_kernel<PX, ROWS>), grid4, blk2, 0, st, ixx, sxx, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<PX, ROWS>), grid4, blk2, 0, st, ixy, sxy, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<PX, ROWS>), grid4, blk2, 0, st, iyy, syy, h4, w4, binomial);
+        hipLaunchKernelGGL(coarsity_kernel<PX>, grid1(n4, 1), blk1, 0, st, sxx, sxy, syy, out, n4, k);
+    } else if (grouping == 2) {
+        float *ixx = gray + n0, *ixy = ixx + n2, *iyy = ixy + n2;
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelProducts>), grid2, blk2, 0, st, gray, ixx, ixy, iyy, h2, w2, s);
+        hipLaunchKernelGGL((window_coarsity_kernel<PX, ROWS>), grid4, blk2, 0, st, ixx, ixy, iyy, out, h4, w4, k, binomial);
+    } else {
+        float *ix = gray + n0, *iy = ix + n2;
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelPair>), grid2, blk2, 0, st, gray, ix, iy, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((products_window_coarsity_kernel<PX, ROWS>), grid4, blk2, 0, st, ix, iy, out, h4, w4, k, binomial);
+    }
+}
 
 }  // namespace
 
@@ -177,32 +336,8 @@ int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k,
                    int grouping, float* ws, float* out, void* stream_) {
     hipStream_t st = static_cast<hipStream_t>(stream_);
     if (batch > 65535) return HARRIS_ERR_SHAPE;        // images ride on gridDim.z
-    const int h2 = H - 2, w2 = W - 2, h4 = H - 4, w4 = W - 4;
-    const size_t n0 = (size_t)batch * H * W, n2 = (size_t)batch * h2 * w2, n4 = (size_t)batch * h4 * w4;
-    const dim3 blk2(kTileX, kTileY), blk1(256);
-    float* gray = ws;
-    if (dtype == HARRIS_U8) hipLaunchKernelGGL(gray_kernel<uint8_t>, grid2d(W, H, batch), blk2, 0, st, static_cast<const uint8_t*>(rgb), gray, H, W, 1.0f / 255.0f);
-    else hipLaunchKernelGGL(gray_kernel<float>, grid2d(W, H, batch), blk2, 0, st, static_cast<const float*>(rgb), gray, H, W, 1.0f);
-    if (grouping == 1) {
-        float *ix = gray + n0, *iy = ix + n2, *ixx = iy + n2, *ixy = ixx + n2, *iyy = ixy + n2, *sxx = iyy + n2, *sxy = sxx + n4, *syy = sxy + n4;
-        hipLaunchKernelGGL(sobel_kernel, grid2d(w2, h2, batch), blk2, 0, st, gray, ix, h2, w2, sobel_scale, 0);
-        hipLaunchKernelGGL(sobel_kernel, grid2d(w2, h2, batch), blk2, 0, st, gray, iy, h2, w2, sobel_scale, 1);
-        hipLaunchKernelGGL(mul_kernel, grid1d(n2), blk1, 0, st, ix, ix, ixx, n2);
-        hipLaunchKernelGGL(mul_kernel, grid1d(n2), blk1, 0, st, ix, iy, ixy, n2);
-        hipLaunchKernelGGL(mul_kernel, grid1d(n2), blk1, 0, st, iy, iy, iyy, n2);
-        hipLaunchKernelGGL(window_kernel, grid2d(w4, h4, batch), blk2, 0, st, ixx, sxx, h4, w4, binomial);
-        hipLaunchKernelGGL(window_kernel, grid2d(w4, h4, batch), blk2, 0, st, ixy, sxy, h4, w4, binomial);
-        hipLaunchKernelGGL(window_kernel, grid2d(w4, h4, batch), blk2, 0, st, iyy, syy, h4, w4, binomial);
-        hipLaunchKernelGGL(coarsity_kernel, grid1d(n4), blk1, 0, st, sxx, sxy, syy, out, n4, k);
-    } else if (grouping == 2) {
-        float *ixx = gray + n0, *ixy = ixx + n2, *iyy = ixy + n2;
-        hipLaunchKernelGGL(sobel_products_kernel, grid2d(w2, h2, batch), blk2, 0, st, gray, ixx, ixy, iyy, h2, w2, sobel_scale);
-        hipLaunchKernelGGL(window_coarsity_kernel, grid2d(w4, h4, batch), blk2, 0, st, ixx, ixy, iyy, out, h4, w4, k, binomial);
-    } else {
-        float *ix = gray + n0, *iy = ix + n2;
-        hipLaunchKernelGGL(sobel_pair_kernel, grid2d(w2, h2, batch), blk2, 0, st, gray, ix, iy, h2, w2, sobel_scale);
-        hipLaunchKernelGGL(products_window_coarsity_kernel, grid2d(w4, h4, batch), blk2, 0, st, ix, iy, out, h4, w4, k, binomial);
-    }
+    if ((long long)batch * H * W >= kWidePixels) enqueue<4, 2>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
+    else enqueue<1, 1>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
     return hipGetLastError() == hipSuccess ? HARRIS_OK : HARRIS_ERR_LAUNCH;
 }
 

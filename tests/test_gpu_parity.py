@@ -817,6 +817,26 @@ def test_batches_of_narrow_images(gpu, oracle, H, W):
         assert bool(torch.isnan(flat).all())
 
 
+@pytest.mark.parametrize("B,H,W", [(1, 132000, 5), (2, 42000, 8), (1, 809, 811), (3, 497, 442), (1, 1001, 655)])
+def test_groupings_of_large_images(gpu, oracle, B, H, W):
+    # From about 0.65 million pixels on a thread of the groupings takes four neighbouring pixels of two
+    # rows: results of one to four columns, widths with every remainder, odd heights, several images.
+    import torch
+    for u8 in (False, True):
+        rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(700 + W, B, H, W)
+        src = torch.from_numpy(rgb).cuda()
+        for window in (gpu.HARRIS_WINDOW_BOX, gpu.HARRIS_WINDOW_BINOMIAL):
+            want = oracle.harris(rgb, K, 1.0, window)
+            for grouping in (1, 2, 3):
+                say("case grouping %d of %d images of %dx%d, %s, window %d" % (grouping, B, H, W, rgb.dtype, window))
+                flat = torch.full((64 + want.size + 64,), float("nan"), device="cuda")
+                out = flat[64:64 + want.size].view(want.shape)
+                gpu.harris_coarsity_grouped(src, K, 1.0, window, grouping, out=out)
+                torch.cuda.synchronize()
+                check(out.cpu().numpy(), want)
+                assert bool(torch.isnan(flat[:64]).all()) and bool(torch.isnan(flat[64 + want.size:]).all())
+
+
 # ---------------------------------------------------------------- seeded random shapes, layouts and launch shapes
 
 def test_random_shapes_layouts_and_launch_shapes(gpu, oracle):
