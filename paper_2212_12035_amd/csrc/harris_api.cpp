@@ -227,6 +227,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
             if (best < 0 || cost < best) { best = cost; tile_rw = rw; tile_nw = (int)nw; one_per_cu = true; }
         }
     }
+    if (!one_per_cu && tile4 && dtype == HARRIS_U8 && out_dtype == HARRIS_OUT_U8 && !in_shifted && footprint > (128LL << 20)) tile_rw = 10;
     if (!one_per_cu && tile4 && dtype == HARRIS_F32) {
         // Many tiles of float32 input.  Such launches are fastest with 10 to 16 wavefronts in
         // flight per CU, not with the 28 to 32 the registers allow (every wavefront requests all
@@ -235,20 +236,25 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         // 36 KB -> 4 tiles per CU, 48 KB -> 3, 64 KB -> 2.  Measured (shape x reservation swept
         // together; 4 x 4 rows without reservation in brackets):
         //   float32 results, up to 400 MB: 4 wavefronts x 5 rows, 3 per CU (2832x4256 32.7 [34.8]
-        //     us, 2x2160x3840 44.5 [49.1], 8192x8192 at 1 GB 174.6 [191.6]);
+        //     us, 2x2160x3840 44.5 [49.1]);
         //   beyond, 8 images or more: 5 x 5, 2 per CU (16x1080x1920 87.1 [103.7] us, 64x1080x1920
         //     351 [378], 128x720x1280 318 [350]); fewer, larger images: 5 x 6, 2 per CU
-        //     (4320x7680 92.2 [105.7] us, 8192x8192 176.6);
-        //   16-bit results and 8-bit codes above 128 MB: 4 x 6, 3 per CU (2832x4256 to binary16
-        //     29.1 [31.2] us, 16x1080x1920 75.7 [89.7], 64x1080x1920 331 [355], 4320x7680 80.8
-        //     [94.2]); one image beyond 800 MB: 5 x 6, 2 per CU (8192x8192 161 [184] us, 175
-        //     with 4 x 6);
+        //     (4320x7680 92.2 [105.7] us, 7236x6617 138.3; 8192x8192 180.8 [191.6], where 4 x 5 would take 172.4);
+        //   16-bit results and 8-bit codes up to 256 MB: 4 x 4, 4 per CU (2832x4256 to binary16 27.8 us, 29.4
+        //     with 4 x 6 and 3 per CU; 3000x3000 22.1 / 23.2, 8x1080x1920 39.0 / 40.1, 2832x4256 to codes
+        //     27.3 / 29.1); above: 4 x 6, 3 per CU (16x1080x1920 75.7 [89.7] us, 64x1080x1920 331
+        //     [355], 4320x7680 80.8 [94.2]); one image beyond 800 MB: 5 x 6, 2 per CU (8192x8192 161
+        //     [184] us, 175 with 4 x 6);
         //   up to 128 MB (several images, too many tiles for one per CU): 4 x 4, 4 per CU
         //     (32x512x512 24.9 [25.6] us).
         // 8-bit input is the opposite: every reservation costs time (8192x8192 uint8: 93 us with
-        // none, 102 us with 4 tiles per CU), so it keeps 4 x 4 and all the wavefronts that fit.
+        // none, 102 us with 4 tiles per CU), so it keeps 4 x 4 and all the wavefronts that fit.  Only to
+        // 8-bit codes, which leave the vector ALUs as the one limit, taller tiles gain by computing fewer rows
+        // twice: above 128 MB 4 wavefronts x 10 rows (8192x8192 66.1 us, 69.4 with 4 x 4; 19x1424x1964
+        // 53.0 / 55.9; but 8x1080x1920, 66 MB, 19.9 / 19.2).
         if (footprint <= (128LL << 20)) { tile_rw = 4; tile_nw = 4; tile_lds_kb = 36; }
         else if (out_dtype != HARRIS_OUT_F32 && batch == 1 && footprint > (800LL << 20)) { tile_rw = 6; tile_nw = 5; tile_lds_kb = 64; }
+        else if (out_dtype != HARRIS_OUT_F32 && footprint <= (256LL << 20)) { tile_rw = 4; tile_nw = 4; tile_lds_kb = 36; }
         else if (out_dtype != HARRIS_OUT_F32) { tile_rw = 6; tile_nw = 4; tile_lds_kb = 48; }
         else if (footprint <= (400LL << 20)) { tile_rw = 5; tile_nw = 4; tile_lds_kb = 48; }
         else if (batch >= 8) { tile_rw = 5; tile_nw = 5; tile_lds_kb = 64; }
