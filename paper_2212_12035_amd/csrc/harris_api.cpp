@@ -106,8 +106,9 @@ bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_ali
 }
 
 harris_layout dense_layout(int H, int W) {
-    const long long n = H - 4, m = W - 4;
-    return {W, (long long)H * W, 3LL * H * W, m, n * m};
+    // (Shapes that the planner has yet to refuse come here as well: no signed overflow.)
+    const long long n = H - 4LL, m = W - 4LL, plane = (long long)H * W;
+    return {W, plane, (long long)(3ull * (unsigned long long)plane), m, n * m};
 }
 
 int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_layout& lay, const harris_tuning* tuning,
