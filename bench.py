@@ -35,9 +35,9 @@ SETTLE_MS = 20.0               # untimed launches before the timed region, in GP
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (summaries under profiles/), valid only
 # for the kernel sources they were taken with: (sha256 of the csrc files without comments, {workload: bytes}).
-TRAFFIC_SOURCES_SHA256 = "afb62ddae48fa5f0140fe70a49733a13eb522ec8c8da10fe2dfd692c10a8c2e7"
-TRAFFIC_BYTES = {"noise_f32_1536x2560": 65109553, "rects_f32_64x1080x1920": 2138767251,
-                 "blobs_f32_2832x4256": 196600535, "noise_u8_8192x8192": 474898329}
+TRAFFIC_SOURCES_SHA256 = "49c8c54d5f04836ef448f427345c130a08ca6284c3ca50738f1277d844092aaa"
+TRAFFIC_BYTES = {"noise_f32_1536x2560": 65112236, "rects_f32_64x1080x1920": 2134586643,
+                 "blobs_f32_2832x4256": 196461339, "noise_u8_8192x8192": 474344734}
 
 
 def kernel_sources_sha256():
