@@ -182,7 +182,7 @@ int harris_coarsity_quantized(const void* rgb, int dtype, int batch, int H, int 
  *   grouping 2  [Sx, Sy, x] [+, coarsity]
  *   grouping 3  [Sx, Sy] [x, +, coarsity]
  *   grouping 4  one fused kernel: identical to harris_coarsity_ex without tuning
- * These are untuned baselines for measuring what fusion buys, and a second
+ * These are baselines for measuring what fusion buys, and a second
  * implementation to cross-check the fused kernels; arguments as harris_coarsity_ex, plus
  *   workspace        device memory for the intermediates, 4-byte aligned, owned by the
  *                    caller, contents undefined afterwards; may be NULL for grouping 4
