@@ -63,8 +63,9 @@ bool px4_fits_shifted(int dtype, int out_dtype, long long pixels, int rgb_align,
 //     rows on; taller images are cut into bands of equal height.  (Eight: 16 start and end more
 //     together, 256 images of 64x64 5.4 against 7.1 us; 4 and 6 read more rows twice, 1500 of 100x80 39.6
 //     with 6 against 38.8.)
-//   - float32 rows whose length is no multiple of 4 must be contiguous: the lane at the end of a row
-//     reads what follows it.  With two images only, where little is gained, such rows keep a
+//   - float32 rows whose length is no multiple of 4 must follow each other without a gap, those of
+//     neighbouring planes and images too: the lane at the end of a row reads up to three floats of what
+//     follows it, which must be a row of the call and nothing else.  With two images only, where little is gained, such rows keep a
 //     wavefront each: their ends cost two more stores a row (600 of 110x121 24.7 us, 25.9 packed).
 //   - Offsets from the first to the last image of a wavefront are 32-bit.
 //   - From 2^18 pixels on: smaller launches are bound by latency and better spread over more
@@ -77,7 +78,8 @@ bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_ali
     const int n = H - 4, m = W - 4, lanes = (W + 3) / 4, images = 64 / lanes;
     if (out_dtype != HARRIS_OUT_F32 || n < 1 || m < 1 || batch < 2 || images < 2 || (images == 2 && dtype == HARRIS_F32 && W % 4 != 0)) return false;
     if ((long long)batch * H * W < kPatchPixels) return false;
-    if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && lay.rgb_row_pitch != W))) return false;
+    const bool dense = lay.rgb_row_pitch == W && lay.rgb_plane_pitch == (long long)H * W && lay.rgb_image_pitch == 3 * lay.rgb_plane_pitch;
+    if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && !dense))) return false;
     const long long reach = 1LL << 30;
     if (lay.rgb_image_pitch > reach / (images * elem_size(dtype)) || lay.out_image_pitch > reach / (images * 4)) return false;
     const int max_rows = 4 * (kPatchWaves - 1), bands = (n + max_rows - 1) / max_rows, rows = (n + bands - 1) / bands;

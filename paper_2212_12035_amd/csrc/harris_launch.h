@@ -81,6 +81,34 @@ struct Params {
     unsigned image_lanes, image_lanes_inverse, images, batch;
 };
 
+// kPatches: what one lane of a wavefront loads of a row.  Offsets and sizes are in
+// bytes from the row's first element in the first of the group's `images` images; elem is the input
+// element's size.
+struct PatchLane {
+    unsigned image;         // which image of the group this lane works on
+    unsigned col;           // its first column
+    bool live;              // whether there is such an image
+    unsigned in_bytes;      // from the row's start in the first image to its end in the last: loads of
+                            // float32 rows end there
+    unsigned in_voff;       // the lane's load, of four elements
+    unsigned drop;          // 8-bit input: bits by which the loaded word is shifted down
+};
+HARRIS_HOST_DEVICE inline PatchLane patch_lane(const Params& p, unsigned images, unsigned lane, unsigned elem) {
+    PatchLane l;
+    const unsigned in_image = (unsigned)(p.in_image_pitch * elem), last_col = (unsigned)p.W - 4u;
+    l.image = (lane * p.image_lanes_inverse) >> 16;             // lane / image_lanes
+    l.col = (lane - l.image * p.image_lanes) * 4u;
+    l.live = l.image < images;
+    l.in_bytes = (images - 1u) * in_image + (unsigned)p.W * elem;
+    // 8-bit lanes load the row's last four bytes where they straddle its end, and the first image's where
+    // they have no image: every load lies inside a row.  float32 lanes that straddle the end of a row
+    // load what follows it up to in_bytes; the planner lets them where that is another row of the call.
+    if (elem == 1u) l.in_voff = l.live ? l.image * in_image + (l.col < last_col ? l.col : last_col) : 0u;
+    else l.in_voff = l.live ? l.image * in_image + l.col * elem : 0x80000000u;
+    l.drop = l.col > last_col ? 8u * ((l.col - last_col) & 3u) : 0u;
+    return l;
+}
+
 // Enqueue the fused kernel.  `shape` must come from harris_plan (all fields set).
 // Returns a harris_status.
 int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int dtype, void* stream);

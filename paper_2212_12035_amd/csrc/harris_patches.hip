@@ -28,8 +28,9 @@ typedef uint32_t u32_any __attribute__((aligned(1)));
 
 // One row of the three planes of a lane's image.  rows[c] is the row's first element in the group's
 // first image, `bytes` what lies from there to the row's end in the group's last image; voff the
-// lane's offset.  Loads beyond the end give zeros.  A float32 lane that straddles the end of its row
-// reads what follows it (rows are then contiguous, see the planner); nobody uses that.
+// lane's offset (patch_lane).  Loads beyond the end give zeros.  A float32 lane that straddles the end of its
+// row reads the start of the row that follows it in memory, of whichever plane or image: the planner lets it
+// where the images are dense, so that all of this belongs to the call.  Nobody uses it.
 // 8-bit rows start on any byte: a lane loads its four bytes where they are, the last lane of a row the
 // row's last four, shifted down by `drop` bits.
 __device__ __forceinline__ void load_patch_row(RawRow<float, 4>& r, const float* row, size_t plane, uint32_t bytes, uint32_t voff, uint32_t) {
@@ -57,29 +58,23 @@ __global__ __launch_bounds__(1024) void harris_patch_kernel(const harris_launch:
     const int y_end = min(p.n, (band + 1) * tile_rows);
     const int out_rows = max(0, min(RW, y_end - y_wave));
 
-    const unsigned per_image = p.image_lanes;                   // lanes of an image
-    const unsigned sub = (lane * p.image_lanes_inverse) >> 16;  // lane / per_image
     const unsigned images = min(p.images, p.batch - group * p.images);   // of this group
-    const unsigned col = (lane - sub * per_image) * PX;
-    const bool live = sub < images;
+    const harris_launch::PatchLane l = harris_launch::patch_lane(p, images, lane, sizeof(In));
+    const unsigned col = l.col;
+    const bool live = l.live;
 
     const size_t first = (size_t)group * p.images;
     const In* in = static_cast<const In*>(p.rgb) + first * (size_t)p.in_image_pitch;
     float* out = static_cast<float*>(p.out) + first * (size_t)p.out_image_pitch;
-    const uint32_t in_image = (uint32_t)(p.in_image_pitch * sizeof(In)), out_image = (uint32_t)(p.out_image_pitch * sizeof(float));
-    const uint32_t in_bytes = (images - 1) * in_image + (uint32_t)p.W * (uint32_t)sizeof(In);
+    const uint32_t out_image = (uint32_t)(p.out_image_pitch * sizeof(float));
     const uint32_t out_bytes = (images - 1) * out_image + (uint32_t)p.m * 4u;
-    const unsigned last_col = (unsigned)p.W - 4u;
-    // 8-bit lanes without an image load the first image's bytes: every load lies inside a row.
-    const uint32_t in_voff = F32 ? (live ? sub * in_image + col * 4u : 0x80000000u) : (live ? sub * in_image + min(col, last_col) : 0u);
-    const uint32_t drop = col > last_col ? 8u * ((col - last_col) & 3u) : 0u;
 
     RawRow<In, PX> raw[RW];
     const size_t plane = (size_t)p.in_plane_pitch;
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         const int r = y_wave + t;
-        load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? in_bytes : 0u, in_voff, drop);
+        load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? l.in_bytes : 0u, l.in_voff, l.drop);
     });
     __builtin_amdgcn_sched_barrier(0);
 
@@ -108,7 +103,7 @@ __global__ __launch_bounds__(1024) void harris_patch_kernel(const harris_launch:
     __builtin_amdgcn_sched_barrier(0);
 
     const unsigned m = (unsigned)p.m, rest = m & 3u;
-    const uint32_t at = sub * out_image + col * 4u;
+    const uint32_t at = l.image * out_image + col * 4u;
     const uint32_t whole_voff = live && col + 4u <= m ? at : 0x80000000u;
     const bool straddles = live && col < m && col + 4u > m;     // the row's last `rest` columns
     const uint32_t pair_voff = straddles && rest >= 2u ? at : 0x80000000u;

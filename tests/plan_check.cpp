@@ -1,0 +1,103 @@
+// Host check of planned launches: the library's C interface (harris_api.cpp) is compiled with a
+// launcher that keeps what the planner hands over instead of enqueueing it, and what the kernel's lanes
+// would load is worked out from that, with the same header functions that the kernel uses.
+// Built and run by tests/test_abi_host.py; prints "ok <launches checked>" or the first fault.
+#include <cstdint>
+#include <cstdio>
+#include <vector>
+
+#include "harris_launch.h"
+
+namespace harris_launch {
+
+static Params last;
+static harris_tuning last_shape;
+static int launches = 0;
+
+int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int, void*) {
+    if (n_blocks != (long long)p.n_blocks) return HARRIS_ERR_LAUNCH;
+    last = p; last_shape = shape; ++launches;
+    return HARRIS_OK;
+}
+size_t grouped_workspace_floats(int, int, int, int) { return 0; }
+int launch_grouped(const void*, int, int, int, int, float, float, int, int, float*, float*, void*) { return HARRIS_ERR_LAUNCH; }
+float* scratch_of_current_device() { return nullptr; }
+int launch_copy_probe(const void*, int, int, int, int, float*, void*) { return HARRIS_ERR_LAUNCH; }
+int launch_stream_probe(int, const void*, void*, long long, void*) { return HARRIS_ERR_LAUNCH; }
+
+}  // namespace harris_launch
+
+using harris_launch::Params;
+
+// Is byte `at` (from element 0 of the call) part of a row of the call?
+static bool inside_a_row(long long at, const harris_layout& lay, int batch, int H, int W, int elem) {
+    const long long e = at / elem;
+    if (e < 0) return false;
+    for (long long b = e / lay.rgb_image_pitch, b0 = b; b <= b0; ++b) {
+        if (b >= batch) return false;
+        const long long in_image = e - b * lay.rgb_image_pitch;
+        for (int c = 0; c < 3; ++c) {
+            const long long in_plane = in_image - c * lay.rgb_plane_pitch;
+            if (in_plane < 0) continue;
+            const long long row = in_plane / lay.rgb_row_pitch;
+            if (row < H && in_plane - row * lay.rgb_row_pitch < W) return true;
+        }
+    }
+    return false;
+}
+
+// Every byte that a launch of the narrow-image kernel loads: rows first and last of the planes (the others
+// lie between them), every lane, full and partial groups.
+static bool patch_loads_inside_rows(const Params& p, const harris_layout& lay, int batch, int elem) {
+    const unsigned groups = (p.batch + p.images - 1) / p.images;
+    for (unsigned group = 0; group < groups; group += groups > 2 ? groups - 1 : 1) {
+        const unsigned left = p.batch - group * p.images, images = left < p.images ? left : p.images;
+        for (int row : {0, 1, p.H - 2, p.H - 1})
+            for (int c = 0; c < 3; ++c)
+                for (unsigned lane = 0; lane < 64; ++lane) {
+                    const harris_launch::PatchLane l = harris_launch::patch_lane(p, images, lane, (unsigned)elem);
+                    if (l.image != lane / p.image_lanes) { std::printf("lane %u / %u gives %u\n", lane, p.image_lanes, l.image); return false; }
+                    const long long start = ((long long)group * p.images * lay.rgb_image_pitch + c * lay.rgb_plane_pitch + row * lay.rgb_row_pitch) * elem;
+                    for (unsigned i = 0; i < 4u * (unsigned)elem; ++i) {
+                        if (elem == 4 && (unsigned long long)l.in_voff + i >= l.in_bytes) continue;     // range check of the descriptor
+                        if (!inside_a_row(start + l.in_voff + i, lay, batch, p.H, p.W, elem)) {
+                            std::printf("%d images of %dx%d, elements of %d bytes, pitches %lld %lld %lld: lane %u reads byte %u of image %u, plane %d, row %d, which is in no row\n",
+                                        batch, p.H, p.W, elem, lay.rgb_row_pitch, lay.rgb_plane_pitch, lay.rgb_image_pitch, lane, l.in_voff + i - l.image * (unsigned)(lay.rgb_image_pitch * elem), l.image, c, row);
+                            return false;
+                        }
+                    }
+                }
+    }
+    return true;
+}
+
+int main() {
+    int packed = 0, gaps_packed = 0;
+    for (int W = 5; W <= 128; ++W)
+        for (int H : {5, 31, 64})
+            for (int dtype : {HARRIS_F32, HARRIS_U8}) {
+                const int n = H - 4, m = W - 4, batch = (1 << 20) / (H * W) + 3;
+                // Rows, planes and images without gaps, and every combination of gaps between them.
+                for (int gaps = 0; gaps < 8; ++gaps) {
+                    harris_layout lay;
+                    lay.rgb_row_pitch = W + (gaps & 1 ? 3 : 0);
+                    lay.rgb_plane_pitch = H * lay.rgb_row_pitch + (gaps & 2 ? 2 : 0);
+                    lay.rgb_image_pitch = 3 * lay.rgb_plane_pitch + (gaps & 4 ? 1 : 0);
+                    lay.out_row_pitch = m; lay.out_image_pitch = (long long)n * m;
+                    const int before = harris_launch::launches;
+                    if (harris_coarsity_pitched((const void*)0x100000, dtype, batch, H, W, &lay, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (float*)0x200000, nullptr, nullptr) != HARRIS_OK ||
+                        harris_launch::launches != before + 1) {
+                        std::printf("refused: %d images of %dx%d\n", batch, H, W);
+                        return 1;
+                    }
+                    const Params& p = harris_launch::last;
+                    if (!(p.flags & harris_launch::kPatches)) continue;
+                    ++packed;
+                    if (gaps) ++gaps_packed;
+                    if (!patch_loads_inside_rows(p, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;
+                }
+            }
+    if (packed == 0 || gaps_packed == 0) { std::printf("the narrow-image kernel was never planned\n"); return 1; }
+    std::printf("ok %d\n", harris_launch::launches);
+    return 0;
+}

@@ -293,6 +293,19 @@ def test_index_division_by_multiplication_is_exact(tmp_path):
     assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout
 
 
+def test_planned_launches_load_rows_of_the_call_only(tmp_path):
+    # Batches of narrow images in every combination of gaps between rows, planes and images: whatever
+    # kernel the planner takes, no lane loads a byte that belongs to no row of the call (harris.h excepts
+    # only 8-bit rows off 4-byte boundaries, by whole words, in the other kernels).
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2212_12035_amd", "csrc")
+    exe = str(tmp_path / "plan_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+                    os.path.join(ROOT, "tests", "plan_check.cpp"), os.path.join(csrc, "harris_api.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout
+
+
 def test_entry_points_validate_before_touching_the_device(pkg):
     # None of these reaches a kernel launch, so they are safe without a GPU.
     lib = pkg.load_library()

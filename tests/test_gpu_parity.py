@@ -817,6 +817,26 @@ def test_batches_of_narrow_images(gpu, oracle, H, W):
         assert bool(torch.isnan(flat).all())
 
 
+@pytest.mark.parametrize("H,W,plane_gap,image_gap", [(33, 29, 5, 0), (40, 33, 0, 3), (61, 31, 2, 9), (24, 65, 1, 0), (37, 36, 7, 4), (64, 64, 0, 12)])
+def test_batches_of_narrow_images_with_gaps_between_planes_and_images(gpu, oracle, H, W, plane_gap, image_gap):
+    # Contiguous rows, planes and images apart, NaN (199 for 8-bit input) in the gaps, from the size on that
+    # takes the narrow-image kernel: widths that four does not divide and widths that it does.
+    import torch
+    B = (1 << 18) // (H * W) + 2
+    plane = H * W + plane_gap
+    image = 3 * plane + image_gap
+    for u8 in (False, True):
+        rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(540 + W, B, H, W)
+        say("case %d images of %dx%d, %s, planes %d and images %d elements apart" % (B, H, W, rgb.dtype, plane, image))
+        store = torch.full((B * image,), 199 if u8 else float("nan"), dtype=torch.uint8 if u8 else torch.float32, device="cuda")
+        src = store.as_strided((B, 3, H, W), (image, plane, W, 1))
+        src.copy_(torch.from_numpy(rgb).cuda())
+        out = torch.full((B, H - 4, W - 4), float("nan"), device="cuda")
+        gpu.harris_coarsity_pitched(src, out, K)
+        torch.cuda.synchronize()
+        check(out.cpu().numpy(), oracle.harris(rgb, K))
+
+
 @pytest.mark.parametrize("B,H,W", [(1, 132000, 5), (2, 42000, 8), (1, 809, 811), (3, 497, 442), (1, 1001, 655)])
 def test_groupings_of_large_images(gpu, oracle, B, H, W):
     # From about 0.65 million pixels on a thread of the groupings takes four neighbouring pixels of two
