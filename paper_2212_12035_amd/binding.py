@@ -150,6 +150,16 @@ def _stream_ptr(stream, device):
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
 
+def _allocation_stream(stream, device):
+    """The torch stream to allocate on what only kernels on `stream` (a torch stream, an object with its handle, or
+    the handle) will use; torch hands such a block out again in that stream's order, also while they still run."""
+    import torch
+    if stream is None or isinstance(stream, torch.cuda.Stream):
+        return stream
+    handle = int(_stream_ptr(stream, device).value or 0)
+    return torch.cuda.ExternalStream(handle, device=device) if handle else torch.cuda.default_stream(device)
+
+
 def _enqueue(function, device, stream, *args):
     """Calls a library function, its last argument the stream, with `device` current.  The call costs less
     than the two objects it would otherwise make, a Stream and a device guard (3.5 of 9.4 us for a small
@@ -281,7 +291,8 @@ def harris_grouped_workspace_bytes(grouping: int, batch: int, H: int, W: int) ->
 
 def harris_coarsity_grouped(rgb, k: float = 0.04, sobel_scale: float = 1.0, window: int = HARRIS_WINDOW_BOX,
                             grouping: int = 1, workspace=None, out=None, stream=None):
-    """The unfused / partly fused kernel groupings; `workspace` is a float32 device tensor (made here if None)."""
+    """The unfused / partly fused kernel groupings; `workspace` is a float32 device tensor (made here if None, in the
+    order of the stream that the kernels run on)."""
     import torch
     if not isinstance(rgb, torch.Tensor) or rgb.dtype not in (torch.float32, torch.uint8):
         raise TypeError("rgb must be a float32 or uint8 torch tensor")
@@ -290,7 +301,9 @@ def harris_coarsity_grouped(rgb, k: float = 0.04, sobel_scale: float = 1.0, wind
     if need < 0:
         raise HarrisError(-3, harris_strerror(-3))
     if workspace is None:
-        workspace = torch.empty(max(1, need // 4), dtype=torch.float32, device=rgb.device)
+        # The block goes back to torch when this function returns, before the kernels have run.
+        with torch.cuda.stream(_allocation_stream(stream, rgb.device)):
+            workspace = torch.empty(max(1, need // 4), dtype=torch.float32, device=rgb.device)
     dtype = HARRIS_U8 if rgb.dtype == torch.uint8 else HARRIS_F32
     _enqueue(load_library().harris_coarsity_grouped, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, k, sobel_scale, window,
              grouping, workspace.data_ptr(), workspace.numel() * workspace.element_size(), out.data_ptr())

@@ -408,6 +408,51 @@ def test_binding_refuses_host_tensors(pkg):
         pkg.harris_coarsity(torch.zeros(1, 3, 8, 8))
 
 
+@pytest.mark.parametrize("kind", ["none", "torch", "handle", "object", "null"])
+def test_internal_workspace_is_allocated_in_the_order_of_the_launch_stream(pkg, monkeypatch, kind):
+    # harris_coarsity_grouped gives its own workspace back to torch on return, with its kernels still
+    # queued: only a block of the stream they run on is safe from being handed out before they end.
+    # (Without a GPU: torch's streams are stand-ins, and the library call is caught.)
+    import contextlib
+    import types
+    import torch
+
+    class Stream:
+        def __init__(self, handle, device=None):
+            self.cuda_stream = handle
+
+    current = [Stream(11)]
+    used = []
+
+    @contextlib.contextmanager
+    def on(stream):
+        before = current[0]
+        if stream is not None:
+            current[0] = stream
+        yield
+        current[0] = before
+
+    def empty(*args, **kw):
+        used.append(current[0].cuda_stream)
+        return torch.zeros(args[0])
+
+    monkeypatch.setattr(torch.cuda, "Stream", Stream)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", Stream)
+    monkeypatch.setattr(torch.cuda, "default_stream", lambda device=None: Stream(0))
+    monkeypatch.setattr(torch.cuda, "stream", on)
+    monkeypatch.setattr(torch, "empty", empty)
+    launched = []
+    monkeypatch.setattr(pkg.binding, "_prepare", lambda rgb, out, dtype: (1, rgb.shape[2], rgb.shape[3], out))
+    monkeypatch.setattr(pkg.binding, "_enqueue", lambda function, device, stream, *args: launched.append(stream))
+    stream, handle = {"none": (None, 11), "torch": (Stream(22), 22), "handle": (33, 33),
+                      "object": (types.SimpleNamespace(cuda_stream=44), 44), "null": (0, 0)}[kind]
+    rgb = torch.zeros(1, 3, 8, 8)
+    pkg.harris_coarsity_grouped(rgb, grouping=2, out=torch.zeros(1, 4, 4), stream=stream)
+    assert used == [handle] and launched == [stream] and current[0].cuda_stream == 11
+    pkg.harris_coarsity_grouped(rgb, grouping=2, workspace=torch.zeros(4096), out=torch.zeros(1, 4, 4), stream=stream)
+    assert used == [handle] and launched == [stream, stream]     # the caller's workspace is the caller's
+
+
 def test_sweep_candidates_are_launch_shapes_the_library_knows(pkg):
     # The launch-shape sweep times the planner's choice against candidates; every candidate must be a
     # shape harris_plan accepts or cleanly refuses (never one that would only fail at launch), the

@@ -1118,6 +1118,28 @@ def test_runs_on_a_side_stream(gpu, oracle):
     check(out.cpu().numpy(), oracle.harris(rgb, K))
 
 
+def test_internal_workspace_of_the_groupings_on_another_stream(gpu, oracle):
+    # The kernels wait behind a long wait on a side stream when the call returns; a tensor of the
+    # workspace's size that the current stream makes and fills meanwhile must not share its memory.
+    import torch
+    rgb = hi.white_noise_f32(78, 1, 300, 500)
+    src = torch.from_numpy(rgb).cuda()
+    want = oracle.harris(rgb, K)
+    side = torch.cuda.Stream()
+    for stream in (side, side.cuda_stream):
+        for grouping in (1, 2, 3):
+            say("case grouping %d, workspace made by the call, stream given as %s" % (grouping, type(stream).__name__))
+            out = torch.empty((1, 296, 496), device="cuda")
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                torch.cuda._sleep(20000000)
+            gpu.harris_coarsity_grouped(src, K, grouping=grouping, out=out, stream=stream)
+            other = torch.full((gpu.harris_grouped_workspace_bytes(grouping, 1, 300, 500) // 4,), 7.0, device="cuda")
+            torch.cuda.synchronize()
+            check(out.cpu().numpy(), want)
+            assert bool((other == 7.0).all())
+
+
 def test_concurrent_calls_from_host_threads_on_their_own_streams(gpu, oracle):
     # The library keeps no state between calls: four host threads, each with a stream, inputs and
     # results of its own (default stream priority), launch different problems at the same time,
