@@ -68,8 +68,16 @@ bool px4_fits_shifted(int dtype, int out_dtype, long long pixels, int rgb_align,
 //     follows it, which must be a row of the call and nothing else.  With two images only, where little is gained, such rows keep a
 //     wavefront each: their ends cost two more stores a row (600 of 110x121 24.7 us, 25.9 packed).
 //   - Offsets from the first to the last image of a wavefront are 32-bit.
-//   - From 2^18 pixels on: smaller launches are bound by latency and better spread over more
-//     wavefronts (64 images of 64x64 3.8 against 4.1 us, but 30 of them 3.7 / 3.1, 4 of 480x100 4.0 / 3.4).
+//   - From 2^18 pixels on, and only where one image per wavefront would take more than one tile of 4 x 4
+//     rows per CU: smaller launches are bound by latency and better spread over more wavefronts (packed
+//     against one by one, float32: 64 images of 32x128, 192 tiles, 4.0 / 3.2 us; 20 of 120x128, 200 tiles,
+//     3.9 / 3.5; 5 of 500x128, 210 tiles, 4.0 / 3.6; but 228 of 24x128, 456 tiles, 3.9 / 4.4; 64 of 64x64,
+//     320 tiles, 3.8 / 4.1).
+//   - Two wide float32 images, which keep more than 24 of the 64 lanes busy by themselves, gain least.  They
+//     stay apart where that fills the third tile of every CU and packed they would leave half of the CUs
+//     without a workgroup (packed against one by one: 244 of 32x128, 732 tiles, 122 workgroups, 5.4 / 5.0
+//     us, 252 of 32x124 5.4 / 5.0; but 293 of 32x128, 147 workgroups, 6.0 / 6.4, 260 of 32x120 5.4 / 6.1, and
+//     with 24 lanes 228 of 32x96, 684 tiles, 114 workgroups, 4.3 / 4.7).
 constexpr int kPatchWaves = 8;
 constexpr long long kPatchPixels = 1LL << 18;
 bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, const harris_layout& lay, const harris_tuning& t,
@@ -77,7 +85,8 @@ bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_ali
     if (t.schedule != 0 || t.px != 0 || t.rows != 0 || t.prefetch != 0 || t.waves_per_block != 0 || t.flags != 0u || t.lds_kb != 0) return false;
     const int n = H - 4, m = W - 4, lanes = (W + 3) / 4, images = 64 / lanes;
     if (out_dtype != HARRIS_OUT_F32 || n < 1 || m < 1 || batch < 2 || images < 2 || (images == 2 && dtype == HARRIS_F32 && W % 4 != 0)) return false;
-    if ((long long)batch * H * W < kPatchPixels) return false;
+    const long long tiles = (long long)batch * ((n + 11) / 12);         // of one image per wavefront
+    if ((long long)batch * H * W < kPatchPixels || tiles <= 256) return false;
     const bool dense = lay.rgb_row_pitch == W && lay.rgb_plane_pitch == (long long)H * W && lay.rgb_image_pitch == 3 * lay.rgb_plane_pitch;
     if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && !dense))) return false;
     const long long reach = 1LL << 30;
@@ -86,6 +95,7 @@ bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_ali
     const int waves = (rows + 3) / 4 + 1;
     const long long blocks = ((long long)batch + images - 1) / images * bands;
     if (blocks > 0x7fffffffLL) return false;
+    if (images == 2 && lanes > 24 && dtype == HARRIS_F32 && tiles > 640 && tiles <= 768 && blocks <= 128) return false;
     harris_tuning c = {HARRIS_SCHEDULE_TILES, 4, 4, 0, waves, HARRIS_TUNE_STREAM_LOADS | HARRIS_TUNE_PLAIN_STORES, 4 * waves};
     if (chosen) *chosen = c;
     if (n_blocks) *n_blocks = blocks;

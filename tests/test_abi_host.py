@@ -486,7 +486,7 @@ def test_plan_for_batches_of_narrow_images(pkg):
         assert all((lane * inverse) >> 16 == lane // lanes for lane in range(64))
         for dtype in (pkg.HARRIS_F32, pkg.HARRIS_U8):
             for H in (5, 31, 32, 33, 60, 61, 64, 200):
-                B = (1 << 18) // (H * W) + 2
+                B = max((1 << 18) // (H * W), 768 // -(-(H - 4) // 12)) + 2
                 shape, blocks = pkg.harris_plan(dtype, B, H, W)
                 packed = images >= 2 and not (images == 2 and dtype == pkg.HARRIS_F32 and W % 4)
                 assert (shape["flags"] & pkg.HARRIS_TUNE_STREAM_LOADS) and shape["schedule"] == pkg.HARRIS_SCHEDULE_TILES
@@ -499,6 +499,22 @@ def test_plan_for_batches_of_narrow_images(pkg):
                 # a caller's own shape, other result types and single images are not affected
                 assert pkg.harris_plan(dtype, B, H, W, tuning=dict(rows=4, waves_per_block=4))[1] == B * -(-n // 12) * -(-(W - 4) // 252)
         assert pkg.harris_plan(pkg.HARRIS_F32, 1, 1 << 14, W)[1] != 0
+
+
+def test_small_batches_of_narrow_images_keep_a_wavefront_each(pkg):
+    # As long as one image per wavefront takes at most one tile of 12 result rows per CU (256), and for
+    # two wide float32 images also where it takes three and the packed launch would have at most 128
+    # workgroups: measured faster so (see the planner).
+    def packed(dtype, B, H, W):
+        images, bands = 64 // ((W + 3) // 4), -(-(H - 4) // 28)
+        return pkg.harris_plan(dtype, B, H, W)[1] == -(-B // images) * bands
+    F32, U8 = pkg.HARRIS_F32, pkg.HARRIS_U8
+    for dtype in (F32, U8):
+        for B, H, W in ((20, 120, 128), (64, 32, 128), (5, 500, 128), (32, 100, 88), (85, 32, 96), (25, 120, 84)):
+            assert not packed(dtype, B, H, W), (dtype, B, H, W)
+        for B, H, W in ((26, 120, 88), (86, 32, 100), (64, 64, 64), (2048, 64, 64), (341, 24, 128), (8192, 32, 32)):
+            assert packed(dtype, B, H, W), (dtype, B, H, W)
+    assert not packed(F32, 256, 32, 128) and packed(U8, 256, 32, 128) and packed(F32, 258, 32, 128) and packed(F32, 228, 32, 96)
 
 
 def test_benchmark_refuses_more_than_one_gpu():

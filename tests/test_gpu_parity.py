@@ -787,7 +787,7 @@ def test_batches_of_narrow_images(gpu, oracle, H, W):
     # rows and planes, both input types, both windows.  Against the oracle, and nothing beside the results is written.
     import torch
     images = 64 // ((W + 3) // 4)
-    B = (1 << 18) // (H * W) + 1
+    B = max((1 << 18) // (H * W), 768 // -(-(H - 4) // 12)) + 1
     B += 1 if B % images == 0 else 0
     n, m = H - 4, W - 4
     for u8 in (False, True):
@@ -822,7 +822,7 @@ def test_batches_of_narrow_images_with_gaps_between_planes_and_images(gpu, oracl
     # Contiguous rows, planes and images apart, NaN (199 for 8-bit input) in the gaps, from the size on that
     # takes the narrow-image kernel: widths that four does not divide and widths that it does.
     import torch
-    B = (1 << 18) // (H * W) + 2
+    B = max((1 << 18) // (H * W), 768 // -(-(H - 4) // 12)) + 2
     plane = H * W + plane_gap
     image = 3 * plane + image_gap
     for u8 in (False, True):
