@@ -35,9 +35,7 @@ static __device__ __align__(256) float scratch[HARRIS_GROUPED_SCRATCH_BYTES / si
 namespace {
 
 // Kernels are templates over a thread's neighbouring pixels PX (4 or 1), and rows ROWS in the 3x3 stages
-// (2 or 1): PX = 4, ROWS = 2 from kWidePixels on.  Smaller images keep one pixel per thread: a launch
-// is then bound by its latency, and eight times the wavefronts hide more of it (the three groupings on
-// 600x800: 48.7 us, wide 52.4; on 720x1000 60.4 and 55.0).
+// (2 or 1); grouped_wide says which.
 constexpr int kTileX = 64, kTileY = 4;      // 256 threads: 64 PX columns of 4 ROWS rows
 
 typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -282,8 +280,6 @@ __global__ void products_window_coarsity_kernel(const float* ix, const float* iy
     store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
-constexpr long long kWidePixels = 5LL << 17;
-
 // Every launch of grouping 1, 2 or 3.
 template <int PX, int ROWS>
 void enqueue(const void* rgb, int dtype, int batch, int H, int W, float k, float s, int binomial, int grouping, float* ws, float* out, hipStream_t st) {
@@ -336,7 +332,7 @@ int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k,
                    int grouping, float* ws, float* out, void* stream_) {
     hipStream_t st = static_cast<hipStream_t>(stream_);
     if (batch > 65535) return HARRIS_ERR_SHAPE;        // images ride on gridDim.z
-    if ((long long)batch * H * W >= kWidePixels) enqueue<4, 2>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
+    if (grouped_wide(batch, H, W)) enqueue<4, 2>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
     else enqueue<1, 1>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
     return hipGetLastError() == hipSuccess ? HARRIS_OK : HARRIS_ERR_LAUNCH;
 }

@@ -124,6 +124,14 @@ int launch_bands(const Params& p, const harris_tuning& shape, int dtype, unsigne
 // Floats of workspace the grouped (unfused) pipelines need; 0 for an unknown grouping.
 size_t grouped_workspace_floats(int grouping, int batch, int H, int W);
 
+// Whether the kernels of a grouping take four neighbouring pixels of two rows per thread, or one pixel.
+// Smaller images keep one: a launch is then bound by its latency, and eight times the wavefronts hide
+// more of it (the three groupings on 600x800: 48.7 us, wide 52.4; on 720x1000 60.4 and 55.0).  So do narrower
+// ones: a row of 64 threads takes 256 columns when wide, and most threads of the 3x3 stages would have
+// none (wide against one pixel, 1 million pixels: 16 columns 153 / 132 us, 40 columns 91 / 78, 64 columns
+// 75 / 67, 96 columns 69 / 75, 128 columns 62 / 69; 8 million: 64 columns 363 / 331, 96 columns 304 / 402).
+inline bool grouped_wide(int batch, int H, int W) { return (long long)batch * H * W >= 5LL << 17 && W >= 96; }
+
 // Enqueue grouping 1, 2 or 3 (see harris_coarsity_grouped).  Returns a harris_status.
 int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k, float sobel_scale, int binomial,
                    int grouping, float* workspace, float* out, void* stream);

@@ -97,6 +97,11 @@ int main() {
                     if (!patch_loads_inside_rows(p, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;
                 }
             }
+    // Groupings: four pixels of two rows per thread only for images that give a row of threads work.
+    for (const auto& c : {std::vector<int>{500, 40, 40}, {20000, 8, 8}, {3, 300000, 8}, {16, 7812, 64}, {1, 600, 800}})
+        if (harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("wide groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }
+    for (const auto& c : {std::vector<int>{1, 1080, 1920}, {64, 128, 128}, {16, 651, 96}, {1, 720, 1000}})
+        if (!harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("narrow groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }
     if (packed == 0 || gaps_packed == 0) { std::printf("the narrow-image kernel was never planned\n"); return 1; }
     std::printf("ok %d\n", harris_launch::launches);
     return 0;

@@ -837,10 +837,11 @@ def test_batches_of_narrow_images_with_gaps_between_planes_and_images(gpu, oracl
         check(out.cpu().numpy(), oracle.harris(rgb, K))
 
 
-@pytest.mark.parametrize("B,H,W", [(1, 132000, 5), (2, 42000, 8), (1, 809, 811), (3, 497, 442), (1, 1001, 655)])
+@pytest.mark.parametrize("B,H,W", [(1, 132000, 5), (2, 42000, 8), (1, 7001, 95), (1, 6900, 96), (2, 3401, 97), (1, 6701, 98), (1, 809, 811), (3, 497, 442), (1, 1001, 655)])
 def test_groupings_of_large_images(gpu, oracle, B, H, W):
-    # From about 0.65 million pixels on a thread of the groupings takes four neighbouring pixels of two
-    # rows: results of one to four columns, widths with every remainder, odd heights, several images.
+    # From about 0.65 million pixels and 96 columns on a thread of the groupings takes four neighbouring
+    # pixels of two rows: widths with every remainder, odd heights, several images, and narrower images of
+    # that size, which keep one pixel per thread.
     import torch
     for u8 in (False, True):
         rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(700 + W, B, H, W)
