@@ -240,7 +240,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
             if (best < 0 || cost < best) { best = cost; tile_rw = rw; tile_nw = (int)nw; one_per_cu = true; }
         }
     }
-    if (!one_per_cu && tile4 && dtype == HARRIS_U8 && out_dtype == HARRIS_OUT_U8 && !in_shifted && footprint > (128LL << 20)) tile_rw = 10;
+    if (!one_per_cu && tile4 && dtype == HARRIS_U8 && out_dtype == HARRIS_OUT_U8 && !in_shifted && footprint > (128LL << 20) &&
+        25LL * ((n + 35) / 36) <= 9LL * ((n + 11) / 12)) tile_rw = 10;
     if (!one_per_cu && tile4 && dtype == HARRIS_F32) {
         // Many tiles of float32 input.  Such launches are fastest with 10 to 16 wavefronts in
         // flight per CU, not with the 28 to 32 the registers allow (every wavefront requests all
@@ -264,7 +265,11 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         // none, 102 us with 4 tiles per CU), so it keeps 4 x 4 and all the wavefronts that fit.  Only to
         // 8-bit codes, which leave the vector ALUs as the one limit, taller tiles gain by computing fewer rows
         // twice: above 128 MB 4 wavefronts x 10 rows (8192x8192 66.1 us, 69.4 with 4 x 4; 19x1424x1964
-        // 53.0 / 55.9; but 8x1080x1920, 66 MB, 19.9 / 19.2).
+        // 53.0 / 55.9; but 8x1080x1920, 66 MB, 19.9 / 19.2), if the image's tiles of 36 result rows come to at
+        // most 0.9 of the input rows that tiles of 12 compute: the last tile of an image is computed whole.  240
+        // MB of 256-column images, 4 x 10 against 4 x 4: 40 rows high 50.9 / 53.2 us (0.83 of the rows), 240 rows
+        // 57.5 / 58.0 (0.88), 96 rows 61.0 / 58.8 (0.94), 60 rows 63.3 / 59.3 (1.0), 44 rows 79.1 / 61.9 (1.25),
+        // 16 rows 104 / 47 (2.5).
         if (footprint <= (128LL << 20)) { tile_rw = 4; tile_nw = 4; tile_lds_kb = 36; }
         else if (out_dtype != HARRIS_OUT_F32 && batch == 1 && footprint > (800LL << 20)) { tile_rw = 6; tile_nw = 5; tile_lds_kb = 64; }
         else if (out_dtype != HARRIS_OUT_F32 && footprint <= (256LL << 20)) { tile_rw = 4; tile_nw = 4; tile_lds_kb = 36; }

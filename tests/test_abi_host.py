@@ -253,6 +253,17 @@ def test_plan_for_16_bit_results(pkg):
     assert lib.harris_coarsity_typed(None, 0, 0, 64, 64, None, 0.04, 1.0, 0, None, 2, None, None) == 0
 
 
+def test_plan_of_codes_from_8_bit_images_weighs_the_last_tile(pkg):
+    # Codes of 8-bit images above 128 MB: tiles of 36 result rows where they compute at most 0.9 of the
+    # rows that tiles of 12 do, as images of a few rows more than a multiple of 36 do not.
+    for H, rows in ((16, 4), (24, 4), (40, 10), (44, 4), (60, 4), (80, 4), (96, 4), (112, 10), (240, 10), (720, 10)):
+        B = 250000000 // (4 * H * 512)
+        shape = pkg.harris_plan_typed(pkg.HARRIS_U8, pkg.HARRIS_OUT_U8, B, H, 512)[0]
+        assert (shape["px"], shape["rows"], shape["waves_per_block"]) == (4, rows, 4), H
+    assert pkg.harris_plan_typed(pkg.HARRIS_U8, pkg.HARRIS_OUT_U8, 1, 8192, 8192)[0]["rows"] == 10
+    assert pkg.harris_plan_typed(pkg.HARRIS_U8, pkg.HARRIS_OUT_U8, 8, 1080, 1920)[0]["rows"] == 4
+
+
 def test_copy_probe_validates_its_arguments(pkg):
     lib = pkg.load_library()
     one = ctypes.c_void_p(4096)
