@@ -15,8 +15,8 @@ CSRC = os.path.join(_PKG, "csrc")
 LIB = os.path.join(_PKG, "libharris.so")
 BUILD_DIR = os.path.join(_PKG, "_build")
 
-SOURCES = ("harris_tiles_f32.hip", "harris_tiles_u8.hip", "harris_patches.hip", "harris_bands.hip", "harris_grouped.hip", "harris_copy.hip",
-           "harris_launch.cpp", "harris_api.cpp")
+SOURCES = ("harris_tiles_f32.hip", "harris_tiles_u8.hip", "harris_tiles_f32_words.hip", "harris_tiles_u8_words.hip",
+           "harris_patches.hip", "harris_bands.hip", "harris_grouped.hip", "harris_copy.hip", "harris_launch.cpp", "harris_api.cpp")
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # the compiler must not form packed-FP32 instructions on its own

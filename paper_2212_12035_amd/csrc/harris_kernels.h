@@ -601,10 +601,20 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 //
 // SHIFTED (8-bit input, four pixels per lane): rows start on any byte and are loaded as the
 // aligned 32-bit words that hold them (load_row_shifted, realign_row).
-template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false>
+//
+// WORDS (16-bit results or 8-bit codes, four pixels per lane): result rows start on any byte of their
+// type and are stored as the aligned words that hold them (pack_row_shifted).  Instances of their
+// own: as a branch of every four-pixel kernel this code cost the others registers (float32, 10 rows: up
+// to 28 vector registers in scratch memory; 2160x3840 23.0 us, 22.2 without; 2159x3839 to binary16
+// itself 21.9 and 20.8).
+template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool WORDS = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
-    constexpr bool DIFF = std::is_same<In, float>::value;
+    // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
+    // two rows of differences would push into scratch memory (none that float32 results take by default)
+    // take the sums first.
+    constexpr bool DIFF = std::is_same<In, float>::value && !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF)));
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
+    static_assert(!WORDS || PX == 4, "result rows as aligned words: four pixels per lane");
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]
     __shared__ unsigned ready[16];                              // HANDOFF: wavefront w has published its four rows
 
@@ -649,14 +659,12 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // on the first 64-byte boundary of that row's address at or after the nominal border: up to
     // 12 (float32), 28 (16-bit) or 60 (8-bit) columns further right.  border_mask is the number
     // of columns per 64 bytes, minus one (15, 31 or 63), or 0.
-    // Shifted result rows (16-bit results and 8-bit codes on rows off 4-byte boundaries, see
-    // pack_row_shifted): the border moves to the next 4-byte boundary, up to 1 or 3 columns.
-    const bool out_shifted = PX == 4 && (p.flags & harris_launch::kOutShifted);
-    const unsigned border_mask = (p.flags & HARRIS_TUNE_ALIGNED_STORES) ? (64u >> esh) - 1u : out_shifted ? (4u >> esh) - 1u : 0u;
+    // WORDS: the border moves to the next 4-byte boundary, up to 1 or 3 columns.
+    const unsigned border_mask = WORDS ? (4u >> esh) - 1u : (p.flags & HARRIS_TUNE_ALIGNED_STORES) ? (64u >> esh) - 1u : 0u;
     const unsigned x0 = (unsigned)strip * p.strip_pitch;        // first result column of this strip
     // Lanes beyond the strip's columns, the border's reach and the 4-column halo request nothing
     // (out-of-range offset).
-    const unsigned reach = out_shifted ? 4u : border_mask & ~3u;
+    const unsigned reach = WORDS ? 4u : border_mask & ~3u;
     const uint32_t load_voff = lane * PX < p.strip_pitch + 4 + reach ? lcol * (uint32_t)sizeof(In) : 0x80000000u;
     const uint32_t in_row_bytes = (uint32_t)p.W * (uint32_t)sizeof(In);
 
@@ -708,18 +716,18 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     int sy = y_wave;
     asm volatile("" : "+s"(sx0), "+s"(sy) : : "memory");
     const unsigned sx1 = sx0 + p.strip_pitch;
-    const uint32_t whole_words = out_shifted ? ~3u : ~0u;       // shifted rows: a row's last word is not stored whole
+    constexpr uint32_t whole_words = WORDS ? ~3u : ~0u;         // WORDS: a row's last word is not stored whole
     const uintptr_t out_first = img_out + (((size_t)sy * (size_t)p.out_row_pitch) << esh);
     static_for<0, RW>([&](auto jj) {
         constexpr int j = decltype(jj)::value;
         const uintptr_t row_addr = out_first + (size_t)j * ((size_t)p.out_row_pitch << esh);
         const unsigned a = (unsigned)(row_addr >> esh);         // address in result elements
-        const unsigned b0 = sx0 == 0 && !out_shifted ? 0u : sx0 + ((0u - (a + sx0)) & border_mask);
+        const unsigned b0 = sx0 == 0 && !WORDS ? 0u : sx0 + ((0u - (a + sx0)) & border_mask);
         const unsigned b1 = min((unsigned)p.m, sx1 + ((0u - (a + sx1)) & border_mask));
         const uint32_t bytes = (j < out_rows && b1 > b0) ? ((b1 - b0) << esh) & whole_words : 0u;
         out_rs[j] = make_rsrc(reinterpret_cast<const void*>(row_addr + ((size_t)b0 << esh)), bytes);
         out_lead[j] = (sx0 - b0) << esh;
-        asm volatile("" : "+s"(out_lead[j]));                   // finished here, not next to the store
+        if constexpr (!WORDS) asm volatile("" : "+s"(out_lead[j]));   // finished here, not next to the store
     });
     uint32_t lane_bytes = (lane * PX) << esh;
     asm volatile("" : "+v"(lane_bytes));
@@ -787,7 +795,31 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     if constexpr (HANDOFF) __syncthreads();                     // stores only after all of the workgroup's loads
     __builtin_amdgcn_sched_barrier(0);
     constexpr int SAUX = kAuxStore;
-    if (__builtin_expect(p.out_kind == HARRIS_OUT_F32, 1)) {
+    if constexpr (WORDS) {
+        auto store_all = [&](auto kind) {
+            constexpr int KIND = decltype(kind)::value;
+            // The row's ends lie in this strip or not: decided per row, looked at only where one can.
+            const bool ends = sx0 == 0u || sx1 + 4u > (unsigned)p.m;
+            static_for<0, RW>([&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                // -out_lead[j], 0 to 3 bytes: worked out again here, it is cheaper than the scalar registers.
+                const uint32_t shift = (0u - (uint32_t)(out_first + (size_t)j * ((size_t)p.out_row_pitch << esh)) - (sx0 << esh)) & 3u;
+                const PackedRow<KIND> r = pack_row_shifted<KIND>(results[j], p.q_scale, p.q_offset, shift);
+                if constexpr (KIND == HARRIS_OUT_U8) __builtin_amdgcn_raw_buffer_store_b32(r.word[0], out_rs[j], lane_bytes, 0, SAUX);
+                else __builtin_amdgcn_raw_buffer_store_b64(u32x2{r.word[0], r.word[1]}, out_rs[j], lane_bytes, 0, SAUX);
+                if (ends && j < out_rows) {
+                    const uint32_t row_bytes = (uint32_t)p.m << esh, b0 = (sx0 << esh) + shift, b1 = min(row_bytes, (sx1 << esh) + shift);
+                    const uint32_t bytes = b1 > b0 ? b1 - b0 : 0u;
+                    const uint32_t lead = sx0 == 0u ? min(shift, row_bytes) : 0u, tail = b1 == row_bytes ? bytes & 3u : 0u;
+                    if (lead + tail != 0u)
+                        store_row_ends<KIND, SAUX>(r, out_first + (size_t)j * ((size_t)p.out_row_pitch << esh), row_bytes, lead, tail, b0 + (bytes & ~3u), bytes / 4u, lane);
+                }
+            });
+        };
+        if (p.out_kind == HARRIS_OUT_U8) store_all(std::integral_constant<int, HARRIS_OUT_U8>{});
+        else if (p.out_kind == HARRIS_OUT_F16) store_all(std::integral_constant<int, HARRIS_OUT_F16>{});
+        else store_all(std::integral_constant<int, HARRIS_OUT_BF16>{});
+    } else if (__builtin_expect(p.out_kind == HARRIS_OUT_F32, 1)) {
         if (LAUX == kAuxKeepShared && (p.flags & HARRIS_TUNE_ALIGNED_STORES) && p.n_strips > 2u) {
             static_for<0, RW>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
@@ -798,31 +830,6 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
                 constexpr int j = decltype(jj)::value;
                 if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
             });
-        }
-    } else if (PX == 4 && out_shifted) {
-        if constexpr (PX == 4) {
-            auto store_all = [&](auto kind) {
-                constexpr int KIND = decltype(kind)::value;
-                // The row's ends lie in this strip or not: decided per row, looked at only where one can.
-                const bool ends = sx0 == 0u || sx1 + 4u > (unsigned)p.m;
-                static_for<0, RW>([&](auto jj) {
-                    constexpr int j = decltype(jj)::value;
-                    const uint32_t shift = 0u - out_lead[j];                    // 0 to 3 bytes
-                    const PackedRow<KIND> r = pack_row_shifted<KIND>(results[j], p.q_scale, p.q_offset, shift);
-                    if constexpr (KIND == HARRIS_OUT_U8) __builtin_amdgcn_raw_buffer_store_b32(r.word[0], out_rs[j], lane_bytes, 0, SAUX);
-                    else __builtin_amdgcn_raw_buffer_store_b64(u32x2{r.word[0], r.word[1]}, out_rs[j], lane_bytes, 0, SAUX);
-                    if (ends && j < out_rows) {
-                        const uint32_t row_bytes = (uint32_t)p.m << esh, b0 = (sx0 << esh) + shift, b1 = min(row_bytes, (sx1 << esh) + shift);
-                        const uint32_t bytes = b1 > b0 ? b1 - b0 : 0u;
-                        const uint32_t lead = sx0 == 0u ? min(shift, row_bytes) : 0u, tail = b1 == row_bytes ? bytes & 3u : 0u;
-                        if (lead + tail != 0u)
-                            store_row_ends<KIND, SAUX>(r, out_first + (size_t)j * ((size_t)p.out_row_pitch << esh), row_bytes, lead, tail, b0 + (bytes & ~3u), bytes / 4u, lane);
-                    }
-                });
-            };
-            if (p.out_kind == HARRIS_OUT_U8) store_all(std::integral_constant<int, HARRIS_OUT_U8>{});
-            else if (p.out_kind == HARRIS_OUT_F16) store_all(std::integral_constant<int, HARRIS_OUT_F16>{});
-            else store_all(std::integral_constant<int, HARRIS_OUT_BF16>{});
         }
     } else if (p.out_kind == HARRIS_OUT_F16) {
         static_for<0, RW>([&](auto jj) {

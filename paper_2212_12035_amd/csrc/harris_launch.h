@@ -118,6 +118,8 @@ int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int 
 // (hipErrorInvalidValue for a shape it has no kernel for).
 int launch_tiles_f32(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
 int launch_tiles_u8(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
+int launch_tiles_f32_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);   // kOutShifted
+int launch_tiles_u8_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
 int launch_patches(const Params& p, int dtype, unsigned grid, unsigned block, void* stream);
 int launch_bands(const Params& p, const harris_tuning& shape, int dtype, unsigned grid, unsigned block, void* stream);
 

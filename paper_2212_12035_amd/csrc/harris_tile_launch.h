@@ -1,6 +1,6 @@
-// Host-side selection of a tile-kernel instance from a planned launch; included by the two
-// translation units that instantiate harris_tile_kernel (one per input type, so that they
-// compile in parallel).
+// Host-side selection of a tile-kernel instance from a planned launch; included by the
+// translation units that instantiate harris_tile_kernel (two per input type, one of them for result
+// rows stored as aligned words, so that they compile in parallel).
 #ifndef HARRIS_TILE_LAUNCH_H
 #define HARRIS_TILE_LAUNCH_H
 
@@ -8,79 +8,67 @@
 
 namespace {
 
-template <typename In, int PX, int RW>
+// Enqueues the instance that the other arguments and the call's flags name.
+template <typename In, int PX, int RW, int LAUX, bool HANDOFF, bool SHIFTED, bool WORDS>
+hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, WORDS>), grid, block, lds, stream, p);
+    else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, WORDS>), grid, block, lds, stream, p);
+    return hipGetLastError();
+}
+
+// WORDS: result rows stored as the aligned words that hold them, four pixels per lane.  Rows of 8-bit input
+// are then always loaded that way too (the planner takes them so wherever a row is not naturally aligned).
+template <typename In, int PX, int RW, bool WORDS>
 hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, hipStream_t stream) {
+    constexpr bool U8 = std::is_same<In, uint8_t>::value;
     // The four gray rows each wavefront publishes; the planner may reserve more to bound the
     // number of workgroups resident on a CU.
     const size_t lds_needed = (size_t)(block.x / kWave) * 4 * kWave * PX * sizeof(float);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
-    const bool cached = p.flags & HARRIS_TUNE_CACHED_LOADS;
-    if (p.in_shifted) {
+    const bool cached = p.flags & HARRIS_TUNE_CACHED_LOADS, keep = p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS, handoff = p.flags & HARRIS_TUNE_FLAG_HANDOFF;
+    if constexpr (U8 && PX == 4 && (RW == 4 || RW == 8)) {
         // 8-bit rows on any byte: kernels for 4 and 8 rows per wavefront, barrier hand-over.
-        if constexpr (std::is_same<In, uint8_t>::value && PX == 4 && (RW == 4 || RW == 8)) {
-            if (p.flags & HARRIS_TUNE_FLAG_HANDOFF) return hipErrorInvalidValue;
-            const bool keep = p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS;
-            if (p.binomial) {
-                if (keep) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxKeepShared, true, false, true>), grid, block, lds, stream, p);
-                else if (cached) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxDefault, true, false, true>), grid, block, lds, stream, p);
-                else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxNonTemporal, true, false, true>), grid, block, lds, stream, p);
-            } else {
-                if (keep) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxKeepShared, false, false, true>), grid, block, lds, stream, p);
-                else if (cached) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxDefault, false, false, true>), grid, block, lds, stream, p);
-                else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxNonTemporal, false, false, true>), grid, block, lds, stream, p);
-            }
-            return hipGetLastError();
-        } else {
-            return hipErrorInvalidValue;
+        if (p.in_shifted) {
+            if (handoff) return hipErrorInvalidValue;
+            if (keep) return launch_tile_kernel<In, PX, RW, kAuxKeepShared, false, true, WORDS>(p, grid, block, lds, stream);
+            if (cached) return launch_tile_kernel<In, PX, RW, kAuxDefault, false, true, WORDS>(p, grid, block, lds, stream);
+            return launch_tile_kernel<In, PX, RW, kAuxNonTemporal, false, true, WORDS>(p, grid, block, lds, stream);
         }
     }
-    if constexpr (PX == 4) {
-        // Kernels that exist for 16-byte lanes only (the planner asks for them nowhere else);
-        // ready flags for float32 input only.
-        if (p.flags & HARRIS_TUNE_FLAG_HANDOFF) {
-            if constexpr (std::is_same<In, float>::value) {
-                if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxNonTemporal, true, true>), grid, block, lds, stream, p);
-                else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxNonTemporal, false, true>), grid, block, lds, stream, p);
-                return hipGetLastError();
-            } else {
-                return hipErrorInvalidValue;
+    if (p.in_shifted) return hipErrorInvalidValue;
+    if constexpr (!(U8 && WORDS)) {
+        // The hand-over by ready flags (float32 input only) and the mixed load policy exist for 16-byte
+        // lanes only (the planner asks for them nowhere else).
+        if constexpr (PX == 4) {
+            if (handoff) {
+                if constexpr (!U8) return launch_tile_kernel<In, PX, RW, kAuxNonTemporal, true, false, WORDS>(p, grid, block, lds, stream);
+                else return hipErrorInvalidValue;
             }
+            if (keep) return launch_tile_kernel<In, PX, RW, kAuxKeepShared, false, false, WORDS>(p, grid, block, lds, stream);
         }
-        if (p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) {
-            if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxKeepShared, true, false>), grid, block, lds, stream, p);
-            else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxKeepShared, false, false>), grid, block, lds, stream, p);
-            return hipGetLastError();
-        }
-    }
-    if (p.binomial) {
-        if (cached) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxDefault, true, false>), grid, block, lds, stream, p);
-        else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxNonTemporal, true, false>), grid, block, lds, stream, p);
+        if (cached) return launch_tile_kernel<In, PX, RW, kAuxDefault, false, false, WORDS>(p, grid, block, lds, stream);
+        return launch_tile_kernel<In, PX, RW, kAuxNonTemporal, false, false, WORDS>(p, grid, block, lds, stream);
     } else {
-        if (cached) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxDefault, false, false>), grid, block, lds, stream, p);
-        else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, kAuxNonTemporal, false, false>), grid, block, lds, stream, p);
+        return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 // Tile kernels exist for 4 rows per wavefront at every lane width, and for 5, 6, 8, 9 and 10
 // rows with four pixels per lane.
-template <typename In>
+template <typename In, bool WORDS>
 hipError_t launch_tiles_any(const harris_launch::Params& p, const harris_tuning& t, dim3 grid, dim3 block, hipStream_t stream) {
-    if (t.rows == 4) {
-        switch (t.px) {
-            case 1: return launch_tiles<In, 1, 4>(p, grid, block, stream);
-            case 2: return launch_tiles<In, 2, 4>(p, grid, block, stream);
-            case 4: return launch_tiles<In, 4, 4>(p, grid, block, stream);
-            default: return hipErrorInvalidValue;
-        }
+    if constexpr (!WORDS) {
+        if (t.rows == 4 && t.px == 1) return launch_tiles<In, 1, 4, false>(p, grid, block, stream);
+        if (t.rows == 4 && t.px == 2) return launch_tiles<In, 2, 4, false>(p, grid, block, stream);
     }
     if (t.px != 4) return hipErrorInvalidValue;
     switch (t.rows) {
-        case 5: return launch_tiles<In, 4, 5>(p, grid, block, stream);
-        case 6: return launch_tiles<In, 4, 6>(p, grid, block, stream);
-        case 8: return launch_tiles<In, 4, 8>(p, grid, block, stream);
-        case 9: return launch_tiles<In, 4, 9>(p, grid, block, stream);
-        case 10: return launch_tiles<In, 4, 10>(p, grid, block, stream);
+        case 4: return launch_tiles<In, 4, 4, WORDS>(p, grid, block, stream);
+        case 5: return launch_tiles<In, 4, 5, WORDS>(p, grid, block, stream);
+        case 6: return launch_tiles<In, 4, 6, WORDS>(p, grid, block, stream);
+        case 8: return launch_tiles<In, 4, 8, WORDS>(p, grid, block, stream);
+        case 9: return launch_tiles<In, 4, 9, WORDS>(p, grid, block, stream);
+        case 10: return launch_tiles<In, 4, 10, WORDS>(p, grid, block, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -44,6 +44,29 @@ def test_version_and_strerror(pkg):
     assert pkg.harris_strerror(-99) == "unknown harris_status"
 
 
+def test_kernels_use_no_scratch_memory(pkg):
+    # The library allocates nothing, and a kernel with a private segment makes the runtime back it with device
+    # memory.  The code objects inside the library say what every kernel uses.  Scalar registers may go to
+    # vector lanes (no memory) in the kernels that store result rows as aligned words (the last template argument) alone.
+    data = open(pkg.library_path(), "rb").read()
+    kernels = {}
+    for m in re.finditer(rb"\.name(?:\xd9(.)|\xda(..)|([\xa0-\xbf]))(_ZN?[A-Za-z0-9_]+?(?:6ParamsE|[a-z]))(?=[\x80-\xff])", data, re.S):
+        end = data.find(b".wavefront_size", m.end())
+        used = {}
+        for key in (b".private_segment_fixed_size", b".sgpr_spill_count", b".vgpr_spill_count"):
+            at = data.find(key, m.end(), end)
+            if at >= 0:
+                used[key] = data[at + len(key)]              # one byte: a count below 128
+        if len(used) == 3:
+            kernels[m.group(4)] = used
+    assert len(kernels) > 150
+    tiles = [name for name in kernels if b"harris_tile_kernel" in name]
+    assert len(tiles) > 100 and any(b"harris_patch_kernel" in name for name in kernels)
+    for name, used in kernels.items():
+        assert used[b".private_segment_fixed_size"] == 0 and used[b".vgpr_spill_count"] == 0, (name, used)
+        assert used[b".sgpr_spill_count"] == 0 or (b"harris_tile_kernel" in name and b"ELb1EEEv" in name), (name, used)
+
+
 def test_plan_picks_widest_vector_path(pkg):
     shape, blocks = pkg.harris_plan(pkg.HARRIS_F32, 1, 1536, 2560)
     assert shape["px"] == 4 and blocks > 128 and shape["rows"] >= 4
