@@ -31,9 +31,10 @@ extern "C" {
  *             takes any width and any row alignment the element type allows, as long as result
  *             rows start on 4-byte boundaries, are not 8-bit codes and, if 16-bit, have an even
  *             number of columns (vector accesses on 4-byte boundaries; 8-bit input rows on any
- *             byte are loaded as aligned words and shifted).  0 = 4 where that holds, and for
- *             large problems with other 16-bit or 8-bit result rows if no field asks for a shape
- *             (the rows are then stored as aligned words); else the widest of 2, 1 that fits.
+ *             byte are loaded as aligned words and shifted), and with HARRIS_TUNE_WORD_STORES other
+ *             16-bit and 8-bit result rows too.  0 = 4 where that holds, and for large problems
+ *             with such other result rows if no field asks for a shape (plans then report
+ *             the bit); else the widest of 2, 1 that fits.
  *   rows      BANDS: result rows per band (>= 1).  TILES: input rows per wavefront: 4, and
  *             with px = 4 also 5, 6, 8, 9 or 10 (4 or 8 for 8-bit input rows off 4-byte
  *             boundaries).  0 = chosen from the size.
@@ -86,12 +87,27 @@ struct harris_tuning {
                                         columns wide instead of 252                                 */
 #define HARRIS_TUNE_PLAIN_STORES 32u /* strips end at the same column in every row.  With neither bit
                                         the library decides                                         */
+#define HARRIS_TUNE_WORD_STORES 256u /* TILES with px = 4, 16-bit results or 8-bit codes: rows of any width on any
+                                        boundary of their type are stored as the aligned 32-bit words
+                                        that hold them, the ends of each row element by element.  Rows that px = 4
+                                        can store directly are, and plans then leave the bit out; not
+                                        with HARRIS_TUNE_ALIGNED_STORES                              */
+#define HARRIS_TUNE_PACKED_IMAGES 512u /* TILES with px = 4 and rows = 4, float32 results, at least two images of at
+                                        most 128 columns: as many images side by side in a wavefront as
+                                        its 64 lanes hold; waves_per_block 2 to 8, result rows in bands of
+                                        at most 4 * (waves_per_block - 1) rows; loads with the default
+                                        policy and fixed strip borders only.  Image distances that do not fit
+                                        32-bit offsets, and float32 rows whose length is no multiple of 4 with gaps
+                                        between rows, planes or images, run with one image per wavefront
+                                        and the other fields as given                                */
 
 /*
  * The launch shape harris_coarsity_ex would use for this problem (after applying
  * `tuning`, which may be NULL), written to *chosen; also the number of workgroups
  * in *n_blocks if n_blocks is not NULL.  rgb_align / out_align are the byte
- * alignments of the base pointers (pass 16 for ordinary allocations).  Host only;
+ * alignments of the base pointers (pass 16 for ordinary allocations).  Images without gaps
+ * between rows, planes and images are assumed, which matters for HARRIS_TUNE_PACKED_IMAGES alone.
+ * The chosen shape, passed back as `tuning` for the same problem, gives the same launch.  Host only;
  * touches no device.  Returns a harris_status.
  */
 int harris_plan(int dtype, int batch, int H, int W, int rgb_align, int out_align,

@@ -45,15 +45,17 @@ bool px4_fits_word_aligned(int dtype, int out_dtype, int W, int rgb_align, int o
 
 // Four pixels per lane for rows of 16-bit results and 8-bit codes on any boundary of their element type:
 // the tile kernel stores the aligned words that hold them and the ends of each row element by
-// element.  Default shapes only (a caller that asks for a shape gets the lanes it names or the
-// narrower ones).  Worth it from about 1.5 million pixels on: below, a launch is bound by its latency,
+// element.  By default for default shapes only (a caller that asks for a shape gets the lanes it names or the
+// narrower ones, and these with HARRIS_TUNE_WORD_STORES).  Worth it from about 1.5 million pixels on: below, a launch is bound by its latency,
 // which the longer store code adds to, and the narrower lanes' many wavefronts do no harm (wide
 // against narrow: 700x401 float32 to binary16 4.9 / 3.5 us, 768x1366 uint8 to codes 5.5 / 4.2); above,
 // the narrow lanes are bound by their instructions (1079x1919 float32 to binary16 7.6 / 9.0 us, 8
 // such images from uint8 25.2 / 49.1).
+bool px4_fits_shifted(int dtype, int out_dtype, int rgb_align) {
+    return out_dtype != HARRIS_OUT_F32 && !(dtype == HARRIS_F32 && rgb_align % 4 != 0);
+}
 constexpr long long kShiftedPixels = 3LL << 19;
-bool px4_fits_shifted(int dtype, int out_dtype, long long pixels, int rgb_align, const harris_tuning& t) {
-    if (out_dtype == HARRIS_OUT_F32 || (dtype == HARRIS_F32 && rgb_align % 4 != 0)) return false;
+bool px4_shifted_by_default(long long pixels, const harris_tuning& t) {
     return t.rows == 0 && t.waves_per_block == 0 && t.flags == 0u && t.lds_kb == 0 && pixels >= kShiftedPixels;
 }
 
@@ -78,25 +80,41 @@ bool px4_fits_shifted(int dtype, int out_dtype, long long pixels, int rgb_align,
 //     without a workgroup (packed against one by one: 244 of 32x128, 732 tiles, 122 workgroups, 5.4 / 5.0
 //     us, 252 of 32x124 5.4 / 5.0; but 293 of 32x128, 147 workgroups, 6.0 / 6.4, 260 of 32x120 5.4 / 6.1, and
 //     with 24 lanes 228 of 32x96, 684 tiles, 114 workgroups, 4.3 / 4.7).
+//   A caller may ask for it with HARRIS_TUNE_PACKED_IMAGES wherever the kernel can take the problem.
 constexpr int kPatchWaves = 8;
 constexpr long long kPatchPixels = 1LL << 18;
-bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, const harris_layout& lay, const harris_tuning& t,
-                  harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
-    if (t.schedule != 0 || t.px != 0 || t.rows != 0 || t.prefetch != 0 || t.waves_per_block != 0 || t.flags != 0u || t.lds_kb != 0) return false;
+
+// HARRIS_OK: planned.  HARRIS_ERR_ARG: asked for where it cannot be.  kNotPacked: one image per wavefront.
+constexpr int kNotPacked = 1;
+int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, const harris_layout& lay, const harris_tuning& t,
+                 harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
+    const bool asked = t.flags & HARRIS_TUNE_PACKED_IMAGES;
+    if (!asked && (t.schedule != 0 || t.px != 0 || t.rows != 0 || t.prefetch != 0 || t.waves_per_block != 0 || t.flags != 0u || t.lds_kb != 0)) return kNotPacked;
     const int n = H - 4, m = W - 4, lanes = (W + 3) / 4, images = 64 / lanes;
-    if (out_dtype != HARRIS_OUT_F32 || n < 1 || m < 1 || batch < 2 || images < 2 || (images == 2 && dtype == HARRIS_F32 && W % 4 != 0)) return false;
-    const long long tiles = (long long)batch * ((n + 11) / 12);         // of one image per wavefront
-    if ((long long)batch * H * W < kPatchPixels || tiles <= 256) return false;
+    if (asked) {
+        if (t.flags & ~(HARRIS_TUNE_PACKED_IMAGES | HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_PLAIN_STORES)) return HARRIS_ERR_ARG;
+        if (t.schedule == HARRIS_SCHEDULE_BANDS || t.prefetch != 0 || !(t.px == 0 || t.px == 4) || !(t.rows == 0 || t.rows == 4)) return HARRIS_ERR_ARG;
+        if (!(t.waves_per_block == 0 || (t.waves_per_block >= 2 && t.waves_per_block <= kPatchWaves)) || t.lds_kb < 0 || t.lds_kb > 64) return HARRIS_ERR_ARG;
+        if (out_dtype != HARRIS_OUT_F32 || (dtype == HARRIS_F32 && rgb_align % 4 != 0)) return HARRIS_ERR_ARG;
+    }
+    if (n < 1 || m < 1 || batch < 1) return kNotPacked;
+    if (asked && (batch < 2 || images < 2)) return HARRIS_ERR_ARG;
     const bool dense = lay.rgb_row_pitch == W && lay.rgb_plane_pitch == (long long)H * W && lay.rgb_image_pitch == 3 * lay.rgb_plane_pitch;
-    if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && !dense))) return false;
+    if (out_dtype != HARRIS_OUT_F32 || batch < 2 || images < 2) return kNotPacked;
+    if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && !dense))) return kNotPacked;
     const long long reach = 1LL << 30;
-    if (lay.rgb_image_pitch > reach / (images * elem_size(dtype)) || lay.out_image_pitch > reach / (images * 4)) return false;
-    const int max_rows = 4 * (kPatchWaves - 1), bands = (n + max_rows - 1) / max_rows, rows = (n + bands - 1) / bands;
-    const int waves = (rows + 3) / 4 + 1;
+    if (lay.rgb_image_pitch > reach / (images * elem_size(dtype)) || lay.out_image_pitch > reach / (images * 4)) return kNotPacked;
+    const int max_rows = 4 * ((t.waves_per_block ? t.waves_per_block : kPatchWaves) - 1), bands = (n + max_rows - 1) / max_rows, rows = (n + bands - 1) / bands;
+    const int waves = t.waves_per_block ? t.waves_per_block : (rows + 3) / 4 + 1;
     const long long blocks = ((long long)batch + images - 1) / images * bands;
-    if (blocks > 0x7fffffffLL) return false;
-    if (images == 2 && lanes > 24 && dtype == HARRIS_F32 && tiles > 640 && tiles <= 768 && blocks <= 128) return false;
-    harris_tuning c = {HARRIS_SCHEDULE_TILES, 4, 4, 0, waves, HARRIS_TUNE_STREAM_LOADS | HARRIS_TUNE_PLAIN_STORES, 4 * waves};
+    if (blocks > 0x7fffffffLL) return kNotPacked;
+    if (!asked) {
+        const long long tiles = (long long)batch * ((n + 11) / 12);         // of one image per wavefront
+        if ((long long)batch * H * W < kPatchPixels || tiles <= 256) return kNotPacked;
+        if (images == 2 && dtype == HARRIS_F32 && (W % 4 != 0 || (lanes > 24 && tiles > 640 && tiles <= 768 && blocks <= 128))) return kNotPacked;
+    }
+    const harris_tuning c = {HARRIS_SCHEDULE_TILES, 4, 4, 0, waves, HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_PLAIN_STORES | HARRIS_TUNE_PACKED_IMAGES,
+                             t.lds_kb > 4 * waves ? t.lds_kb : 4 * waves};
     if (chosen) *chosen = c;
     if (n_blocks) *n_blocks = blocks;
     if (params) {
@@ -107,14 +125,14 @@ bool plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_ali
         params->by_tiles_per_image = harris_launch::make_fastdiv((unsigned)bands);
         params->n_blocks = (unsigned)blocks;
         params->waves_per_block = (unsigned)waves;
-        params->flags = c.flags | harris_launch::kPatches;
-        params->lds_bytes = (unsigned)waves * 4096u;
+        params->flags = c.flags;
+        params->lds_bytes = (unsigned)c.lds_kb * 1024u;
         params->image_lanes = (unsigned)lanes;
         params->image_lanes_inverse = (unsigned)((65535 + lanes) / lanes);
         params->images = (unsigned)images;
         params->batch = (unsigned)batch;
     }
-    return true;
+    return HARRIS_OK;
 }
 
 harris_layout dense_layout(int H, int W) {
@@ -136,28 +154,36 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     harris_tuning t = {0, 0, 0, 0, 0, 0u, 0};
     if (tuning) t = *tuning;
     if (t.flags & ~(HARRIS_TUNE_NO_ALTERNATE | HARRIS_TUNE_NO_XCD_REMAP | HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_STREAM_LOADS |
-                    HARRIS_TUNE_ALIGNED_STORES | HARRIS_TUNE_PLAIN_STORES | HARRIS_TUNE_KEEP_SHARED_ROWS | HARRIS_TUNE_FLAG_HANDOFF)) return HARRIS_ERR_ARG;
+                    HARRIS_TUNE_ALIGNED_STORES | HARRIS_TUNE_PLAIN_STORES | HARRIS_TUNE_KEEP_SHARED_ROWS | HARRIS_TUNE_FLAG_HANDOFF |
+                    HARRIS_TUNE_WORD_STORES | HARRIS_TUNE_PACKED_IMAGES)) return HARRIS_ERR_ARG;
     if ((t.flags & HARRIS_TUNE_CACHED_LOADS) && (t.flags & HARRIS_TUNE_STREAM_LOADS)) return HARRIS_ERR_ARG;
     if ((t.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) && !(t.flags & HARRIS_TUNE_STREAM_LOADS)) return HARRIS_ERR_ARG;
     if ((t.flags & HARRIS_TUNE_FLAG_HANDOFF) && (t.flags & (HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_KEEP_SHARED_ROWS))) return HARRIS_ERR_ARG;
     if ((t.flags & HARRIS_TUNE_ALIGNED_STORES) && (t.flags & HARRIS_TUNE_PLAIN_STORES)) return HARRIS_ERR_ARG;
     if (t.schedule != 0 && t.schedule != HARRIS_SCHEDULE_BANDS && t.schedule != HARRIS_SCHEDULE_TILES) return HARRIS_ERR_ARG;
 
-    if (plan_patches(dtype, out_dtype, batch, H, W, rgb_align, lay, t, chosen, n_blocks, params)) return HARRIS_OK;
+    const int packed = plan_patches(dtype, out_dtype, batch, H, W, rgb_align, lay, t, chosen, n_blocks, params);
+    if (packed != kNotPacked) return packed;
+    t.flags &= ~HARRIS_TUNE_PACKED_IMAGES;
 
     const int n = H - 4, m = W - 4;
     const bool tiles_allowed = (t.schedule == 0 || t.schedule == HARRIS_SCHEDULE_TILES) && t.prefetch == 0;
     const bool word_aligned_px4 = tiles_allowed && px4_fits_word_aligned(dtype, out_dtype, W, rgb_align, out_align);
-    bool out_shifted = false;
-    if (t.px == 0) {
+    const bool direct_px4 = px_fits(4, dtype, out_dtype, W, rgb_align, out_align) || word_aligned_px4;
+    if (t.flags & HARRIS_TUNE_WORD_STORES) {
+        if (!tiles_allowed || !px4_fits_shifted(dtype, out_dtype, rgb_align) || (t.flags & HARRIS_TUNE_ALIGNED_STORES) || !(t.px == 0 || t.px == 4)) return HARRIS_ERR_ARG;
+        t.px = 4;
+        if (direct_px4) t.flags &= ~HARRIS_TUNE_WORD_STORES;
+    } else if (t.px == 0) {
         t.px = 1;
-        if (px_fits(4, dtype, out_dtype, W, rgb_align, out_align) || word_aligned_px4) t.px = 4;
-        else if (tiles_allowed && px4_fits_shifted(dtype, out_dtype, (long long)batch * H * W, rgb_align, t)) { t.px = 4; out_shifted = true; }
+        if (direct_px4) t.px = 4;
+        else if (tiles_allowed && px4_fits_shifted(dtype, out_dtype, rgb_align) && px4_shifted_by_default((long long)batch * H * W, t)) { t.px = 4; t.flags |= HARRIS_TUNE_WORD_STORES; }
         else if (px_fits(2, dtype, out_dtype, W, rgb_align, out_align)) t.px = 2;
     } else if (!((t.px == 1 || t.px == 2 || t.px == 4) &&
                  (px_fits(t.px, dtype, out_dtype, W, rgb_align, out_align) || (t.px == 4 && word_aligned_px4)))) {
         return HARRIS_ERR_ARG;
     }
+    const bool out_shifted = t.flags & HARRIS_TUNE_WORD_STORES;
     if (t.rows < 0 || t.prefetch < 0 || t.waves_per_block < 0 || t.lds_kb < 0 || t.lds_kb > 64) return HARRIS_ERR_ARG;
     // A prefetch depth exists only in the band schedule.
     if (t.schedule == 0) t.schedule = t.prefetch == 0 ? HARRIS_SCHEDULE_TILES : HARRIS_SCHEDULE_BANDS;
@@ -365,7 +391,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->blocks_per_image = (unsigned)blocks_per_image;
         params->n_blocks = (unsigned)blocks;
         params->waves_per_block = (unsigned)t.waves_per_block;
-        params->flags = t.flags | (out_shifted ? harris_launch::kOutShifted : 0u);
+        params->flags = t.flags;
         params->out_kind = (unsigned)out_dtype;
         params->in_shifted = in_shifted ? 1 : 0;
         params->lds_bytes = (unsigned)t.lds_kb * 1024u;

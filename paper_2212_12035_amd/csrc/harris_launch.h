@@ -43,12 +43,6 @@ HARRIS_HOST_DEVICE inline unsigned fastdiv(unsigned x, const FastDiv& f) {
     return (t + ((x - t) >> f.sh1)) >> f.sh2;
 }
 
-// Bit of Params::flags, beside the HARRIS_TUNE_* bits: 16- or 8-bit result rows are stored as the
-// aligned words that hold them (tile kernel, four pixels per lane).
-constexpr unsigned kOutShifted = 0x80000000u;
-// Another such bit: several narrow images side by side in a wavefront (harris_patches.hip).
-constexpr unsigned kPatches = 0x40000000u;
-
 // Kernel arguments (passed by value).  What the tile kernel reads before its first load sits
 // together, so that a few wide scalar loads fetch it at once.
 struct Params {
@@ -67,7 +61,7 @@ struct Params {
     unsigned waves_per_block;  // wavefronts per workgroup (the block size / 64)
     float wr, wg, wb;       // gray weights, times the Sobel scale (and 1/255 for 8-bit input)
     float k;                // coarsity constant
-    unsigned flags;         // HARRIS_TUNE_* bits, kOutShifted, kPatches
+    unsigned flags;         // HARRIS_TUNE_* bits
     unsigned out_kind;      // a harris_out_dtype (other than float32: tile kernel only)
     float q_scale, q_offset;   // 8-bit results: code = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)
     int binomial;           // 1: window [1 2 1; 2 4 2; 1 2 1], 0: unweighted 3x3 sum
@@ -76,12 +70,12 @@ struct Params {
     unsigned n_bands;       // bands (BANDS) or tiles down the image (TILES)
     unsigned blocks_x;      // BANDS: workgroups across a row of bands
     unsigned blocks_per_image;  // BANDS: workgroups per image
-    // kPatches: lanes of an image, 65536 / that rounded up, images of a wavefront, images of the call.
+    // HARRIS_TUNE_PACKED_IMAGES: lanes of an image, 65536 / that rounded up, images of a wavefront, images of the call.
     // tiles_per_image is then the number of bands down the images, rows_per_band their height.
     unsigned image_lanes, image_lanes_inverse, images, batch;
 };
 
-// kPatches: what one lane of a wavefront loads of a row.  Offsets and sizes are in
+// HARRIS_TUNE_PACKED_IMAGES: what one lane of a wavefront loads of a row.  Offsets and sizes are in
 // bytes from the row's first element in the first of the group's `images` images; elem is the input
 // element's size.
 struct PatchLane {
@@ -118,7 +112,7 @@ int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int 
 // (hipErrorInvalidValue for a shape it has no kernel for).
 int launch_tiles_f32(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
 int launch_tiles_u8(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
-int launch_tiles_f32_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);   // kOutShifted
+int launch_tiles_f32_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);   // HARRIS_TUNE_WORD_STORES
 int launch_tiles_u8_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
 int launch_patches(const Params& p, int dtype, unsigned grid, unsigned block, void* stream);
 int launch_bands(const Params& p, const harris_tuning& shape, int dtype, unsigned grid, unsigned block, void* stream);

@@ -4,6 +4,7 @@
 // Built and run by tests/test_abi_host.py; prints "ok <launches checked>" or the first fault.
 #include <cstdint>
 #include <cstdio>
+#include <cstring>
 #include <vector>
 
 #include "harris_launch.h"
@@ -49,6 +50,7 @@ static bool inside_a_row(long long at, const harris_layout& lay, int batch, int 
 // Every byte that a launch of the narrow-image kernel loads: rows first and last of the planes (the others
 // lie between them), every lane, full and partial groups.
 static bool patch_loads_inside_rows(const Params& p, const harris_layout& lay, int batch, int elem) {
+    if (!(p.flags & HARRIS_TUNE_PACKED_IMAGES)) return true;
     const unsigned groups = (p.batch + p.images - 1) / p.images;
     for (unsigned group = 0; group < groups; group += groups > 2 ? groups - 1 : 1) {
         const unsigned left = p.batch - group * p.images, images = left < p.images ? left : p.images;
@@ -90,8 +92,21 @@ int main() {
                         std::printf("refused: %d images of %dx%d\n", batch, H, W);
                         return 1;
                     }
-                    const Params& p = harris_launch::last;
-                    if (!(p.flags & harris_launch::kPatches)) continue;
+                    // The shape of that launch, given back, gives it again; the shape planned for images without
+                    // gaps is accepted too.
+                    const Params first = harris_launch::last;
+                    const harris_tuning given = harris_launch::last_shape;
+                    harris_tuning planned;
+                    if (harris_coarsity_pitched((const void*)0x100000, dtype, batch, H, W, &lay, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (float*)0x200000, &given, nullptr) != HARRIS_OK ||
+                        std::memcmp(&given, &harris_launch::last_shape, sizeof given) != 0 || first.n_blocks != harris_launch::last.n_blocks ||
+                        harris_plan(dtype, batch, H, W, dtype == HARRIS_U8 ? 1 : 4, 16, nullptr, &planned, nullptr) != HARRIS_OK ||
+                        harris_coarsity_pitched((const void*)0x100000, dtype, batch, H, W, &lay, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (float*)0x200000, &planned, nullptr) != HARRIS_OK) {
+                        std::printf("planned shape not accepted, or another launch: %d images of %dx%d, dtype %d, gaps %d\n", batch, H, W, dtype, gaps);
+                        return 1;
+                    }
+                    if (!patch_loads_inside_rows(harris_launch::last, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;
+                    const Params& p = first;
+                    if (!(p.flags & HARRIS_TUNE_PACKED_IMAGES)) continue;
                     ++packed;
                     if (gaps) ++gaps_packed;
                     if (!patch_loads_inside_rows(p, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;

@@ -203,6 +203,49 @@ def test_plan_defaults_follow_the_problem_size(pkg):
     assert (bands["rows"], bands["prefetch"], bands["waves_per_block"]) == (32, 3, 4) and blocks == 64 * 17 * 4
 
 
+def test_a_planned_shape_gives_the_same_launch(pkg):
+    # What a plan reports can be passed back: same shape, same workgroups.  Over the calls of the
+    # performance cases, and over sizes, types and row boundaries drawn at random.
+    import random
+    F32, U8 = pkg.HARRIS_F32, pkg.HARRIS_U8
+    O32, O16, OB16, O8 = pkg.HARRIS_OUT_F32, pkg.HARRIS_OUT_F16, pkg.HARRIS_OUT_BF16, pkg.HARRIS_OUT_U8
+    calls = [(F32, O32, 1, 64, 96, 16, 16), (U8, O32, 1, 480, 640, 16, 16), (F32, O32, 1, 1536, 2560, 16, 16), (F32, O32, 1, 2832, 4256, 16, 16),
+             (F32, O32, 64, 1080, 1920, 16, 16), (U8, O32, 1, 8192, 8192, 16, 16), (U8, O32, 8, 1079, 1919, 1, 4), (F32, O32, 1, 1501, 2203, 4, 4),
+             (F32, O16, 1, 2831, 4255, 4, 2), (U8, O8, 16, 768, 1366, 2, 2), (U8, O8, 16, 768, 1366, 1, 1), (F32, O32, 2048, 64, 64, 16, 16),
+             (F32, O32, 1000, 65, 65, 4, 4), (U8, O32, 3000, 61, 31, 1, 4), (F32, O32, 1, 2160, 3840, 16, 16), (U8, O8, 1, 8192, 8192, 16, 16)]
+    rng = random.Random(7)
+    for _ in range(3000):
+        dtype, out = rng.choice((F32, U8)), rng.choice((O32, O16, OB16, O8))
+        px, W = 10 ** rng.uniform(3, 8), int(10 ** rng.uniform(0.8, 3.9))
+        H = max(5, int(10 ** rng.uniform(0.8, 3.9)))
+        calls.append((dtype, out, max(1, int(px / (H * W))), H, W, rng.choice((1, 2, 4, 16) if dtype == U8 else (4, 8, 16)),
+                      rng.choice({O32: (4, 8, 16), O8: (1, 2, 4, 16)}.get(out, (2, 4, 16)))))
+    words = packed = 0
+    for dtype, out, B, H, W, rgb_align, out_align in calls:
+        shape, blocks = pkg.harris_plan_typed(dtype, out, B, H, W, rgb_align, out_align)
+        assert pkg.harris_plan_typed(dtype, out, B, H, W, rgb_align, out_align, tuning=shape) == (shape, blocks), (dtype, out, B, H, W, rgb_align, out_align)
+        words += bool(shape["flags"] & pkg.HARRIS_TUNE_WORD_STORES)
+        packed += bool(shape["flags"] & pkg.HARRIS_TUNE_PACKED_IMAGES)
+    assert words > 20 and packed > 20
+    # the two bits by themselves: where the kernels can take the problem, and nowhere else
+    W_, P_ = pkg.HARRIS_TUNE_WORD_STORES, pkg.HARRIS_TUNE_PACKED_IMAGES
+    assert pkg.harris_plan_typed(F32, O16, 1, 64, 97, 4, 2, tuning=dict(flags=W_))[0]["px"] == 4
+    assert pkg.harris_plan_typed(U8, O8, 1, 64, 7, 1, 1, tuning=dict(flags=W_, rows=8, waves_per_block=2))[0]["flags"] & W_
+    assert not pkg.harris_plan_typed(F32, O16, 1, 64, 96, 16, 16, tuning=dict(flags=W_))[0]["flags"] & W_       # stored directly
+    assert pkg.harris_plan(F32, 2, 5, 5, 4, 4, tuning=dict(flags=P_)) == (dict(schedule=2, px=4, rows=4, prefetch=0, waves_per_block=2, flags=P_ | 36, lds_kb=8), 1)
+    assert pkg.harris_plan(F32, 7, 64, 101, 4, 4, tuning=dict(flags=P_, waves_per_block=3))[1] == 4 * 8
+    for out, shape, bad in ((O32, (2, 64, 96), dict(flags=W_)), (O16, (2, 64, 97), dict(flags=W_, px=2)), (O16, (2, 64, 97), dict(flags=W_, schedule=1)),
+                            (O16, (2, 64, 97), dict(flags=W_ | 16)), (O16, (2, 64, 96), dict(flags=P_)), (O32, (1, 64, 96), dict(flags=P_)),
+                            (O32, (2, 64, 129), dict(flags=P_)), (O32, (2, 64, 96), dict(flags=P_ | 8)), (O32, (2, 64, 96), dict(flags=P_ | 16)),
+                            (O32, (2, 64, 96), dict(flags=P_, rows=5)), (O32, (2, 64, 96), dict(flags=P_, waves_per_block=9)),
+                            (O32, (2, 64, 96), dict(flags=P_, px=2)), (O32, (2, 64, 96), dict(flags=P_, schedule=1)), (O32, (2, 64, 96), dict(flags=P_ | W_))):
+        with pytest.raises(pkg.HarrisError) as e:
+            pkg.harris_plan_typed(F32, out, *shape, 4, 4 if out == O32 else 2, tuning=bad)
+        assert e.value.status == -3, bad
+    # empty results are planned, not refused
+    assert pkg.harris_plan(F32, 0, 64, 64, tuning=dict(flags=P_))[1] == 0 and pkg.harris_plan(F32, 2, 4, 64, tuning=dict(flags=P_))[1] == 0
+
+
 def test_plan_rejects_bad_arguments(pkg):
     E = pkg.HarrisError
     for args, status in [
@@ -524,9 +567,11 @@ def test_plan_for_batches_of_narrow_images(pkg):
                 B = max((1 << 18) // (H * W), 768 // -(-(H - 4) // 12)) + 2
                 shape, blocks = pkg.harris_plan(dtype, B, H, W)
                 packed = images >= 2 and not (images == 2 and dtype == pkg.HARRIS_F32 and W % 4)
-                assert (shape["flags"] & pkg.HARRIS_TUNE_STREAM_LOADS) and shape["schedule"] == pkg.HARRIS_SCHEDULE_TILES
+                assert shape["schedule"] == pkg.HARRIS_SCHEDULE_TILES and bool(shape["flags"] & pkg.HARRIS_TUNE_PACKED_IMAGES) == packed
                 if not packed:
+                    assert shape["flags"] & pkg.HARRIS_TUNE_STREAM_LOADS
                     continue
+                assert shape["flags"] == pkg.HARRIS_TUNE_PACKED_IMAGES | pkg.HARRIS_TUNE_CACHED_LOADS | pkg.HARRIS_TUNE_PLAIN_STORES
                 n, groups = H - 4, -(-B // images)
                 assert shape["px"] == 4 and shape["rows"] == 4 and 2 <= shape["waves_per_block"] <= 8 and blocks % groups == 0
                 bands = blocks // groups
@@ -541,8 +586,7 @@ def test_small_batches_of_narrow_images_keep_a_wavefront_each(pkg):
     # two wide float32 images also where it takes three and the packed launch would have at most 128
     # workgroups: measured faster so (see the planner).
     def packed(dtype, B, H, W):
-        images, bands = 64 // ((W + 3) // 4), -(-(H - 4) // 28)
-        return pkg.harris_plan(dtype, B, H, W)[1] == -(-B // images) * bands
+        return bool(pkg.harris_plan(dtype, B, H, W)[0]["flags"] & pkg.HARRIS_TUNE_PACKED_IMAGES)
     F32, U8 = pkg.HARRIS_F32, pkg.HARRIS_U8
     for dtype in (F32, U8):
         for B, H, W in ((20, 120, 128), (64, 32, 128), (5, 500, 128), (32, 100, 88), (85, 32, 96), (25, 120, 84)):

@@ -779,6 +779,84 @@ def test_narrow_results_on_rows_of_any_alignment(gpu, oracle, fmt, W):
             assert bool((flat == 77).all() if fmt == "codes" else torch.isnan(flat).all())
 
 
+@pytest.mark.parametrize("B,H,W", [(2, 5, 5), (3, 33, 29), (9, 61, 31), (2, 36, 101), (5, 40, 128), (33, 9, 8), (4, 70, 64)])
+def test_packed_images_asked_for(gpu, oracle, B, H, W):
+    # Below the size from which the planner packs images by itself, with every number of wavefronts:
+    # single rows, bands of every height, groups of images that are not full.  Where gaps between the planes
+    # keep float32 rows of such a width apart the same call runs with one image per wavefront.
+    import torch
+    for u8 in (False, True):
+        rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(560 + W, B, H, W)
+        want = oracle.harris(rgb, K)
+        store = torch.full((B * 3 * (H * W + 3),), 199 if u8 else float("nan"), dtype=torch.uint8 if u8 else torch.float32, device="cuda")
+        apart = store.as_strided((B, 3, H, W), (3 * (H * W + 3), H * W + 3, W, 1))
+        src = torch.from_numpy(rgb).cuda()
+        apart.copy_(src)
+        for waves in range(2, 9):
+            say("case %d images of %dx%d, %s, packed, %d wavefronts" % (B, H, W, rgb.dtype, waves))
+            for view in (src, apart):
+                flat = torch.full((64 + want.size + 64,), float("nan"), device="cuda")
+                out = flat[64:64 + want.size].view(want.shape)
+                gpu.harris_coarsity_pitched(view, out, K, tuning=dict(flags=gpu.HARRIS_TUNE_PACKED_IMAGES, waves_per_block=waves))
+                torch.cuda.synchronize()
+                check(out.cpu().numpy(), want)
+                out.fill_(float("nan"))
+                assert bool(torch.isnan(flat).all())
+
+
+@pytest.mark.parametrize("fmt", ["f16", "bf16", "codes"])
+@pytest.mark.parametrize("rows", [4, 5, 6, 8, 9, 10])
+def test_word_stores_every_kernel_instance(gpu, oracle, fmt, rows):
+    # Result rows stored as aligned words, asked for below the size that takes them by default: every number of rows
+    # per wavefront, load policy and hand-over, both windows, rows of fewer columns than a word holds,
+    # one strip and two.  The values are those of the float32 result of the same tile shape, rounded; with
+    # ten rows, whose instances differ in the order of their sums, those of the float32 oracle within a
+    # unit of the last place of the 16-bit value (a code) on top of the bar.
+    import torch
+    tdt = {"f16": torch.float16, "bf16": torch.bfloat16, "codes": torch.uint8}[fmt]
+    policies = [0, gpu.HARRIS_TUNE_CACHED_LOADS, gpu.HARRIS_TUNE_STREAM_LOADS | gpu.HARRIS_TUNE_KEEP_SHARED_ROWS, gpu.HARRIS_TUNE_FLAG_HANDOFF]
+    for u8 in (False, True):
+        if u8 and rows not in (4, 8):
+            continue
+        for W, waves in ((5, 2), (7, 3), (130, 5), (4 + 248 + 2, 3), (501, 2)):
+            H = 2 * (rows * waves - 4) + 7
+            rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(330 + W, 2, H, W)
+            src = torch.from_numpy(rgb).cuda()
+            n, m = H - 4, W - 4
+            for flags in policies:
+                if u8 and flags == gpu.HARRIS_TUNE_FLAG_HANDOFF:
+                    continue
+                for window in (0, 1):
+                    say("case %s as words, %s %s, %d rows x %d, flags %d, window %d" % (fmt, rgb.dtype, rgb.shape, rows, waves, flags, window))
+                    tune = dict(px=4, rows=rows, waves_per_block=waves, flags=flags)
+                    flat = torch.full((8 + 2 * n * (m + 1) + 8,), 77 if fmt == "codes" else float("nan"), dtype=tdt, device="cuda")
+                    inner = flat[9:9 + 2 * n * (m + 1)].view(2, n, m + 1)[:, :, :m]
+                    words = dict(tune, flags=flags | gpu.HARRIS_TUNE_WORD_STORES)
+                    if fmt == "codes":
+                        gpu.harris_coarsity_quantized(src, inner, 1.5, 90.0, K, 1.0, window, tuning=words)
+                    else:
+                        gpu.harris_coarsity_typed(src, inner, K, 1.0, window, tuning=words)
+                    f32 = torch.empty((2, n, m), device="cuda")
+                    gpu.harris_coarsity_typed(src, f32, K, 1.0, window, tuning=tune)
+                    torch.cuda.synchronize()
+                    want = oracle.harris(rgb, K, 1.0, window)
+                    check(f32.cpu().numpy(), want)
+                    bar = 1e-4 * float(np.abs(want).max()) + 1e-6
+                    if fmt == "codes":
+                        got = inner.cpu().numpy()
+                        if rows != 10:
+                            assert np.array_equal(got, oracle.quantize_u8(f32.cpu().numpy(), 1.5, 90.0))
+                        assert np.all(np.abs(got.astype(np.float64) - oracle.quantize_u8(want, 1.5, 90.0)) <= 1.0 + 1.5 * bar)
+                    else:
+                        got = inner.contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+                        if rows != 10:
+                            assert np.array_equal(got, oracle.round_to_16bit(f32.cpu().numpy(), fmt))
+                        want16 = _as_f32(oracle.round_to_16bit(want, fmt), fmt)
+                        assert np.all(np.abs(_as_f32(got, fmt).astype(np.float64) - want16) <= bar + _ulp16(want, fmt))
+                    inner[:] = 77 if fmt == "codes" else float("nan")
+                    assert bool((flat == 77).all() if fmt == "codes" else torch.isnan(flat).all())
+
+
 @pytest.mark.parametrize("H,W", [(5, 5), (32, 8), (33, 29), (61, 31), (40, 33), (64, 64), (24, 65), (60, 84), (37, 85), (90, 121), (32, 128), (29, 126)])
 def test_batches_of_narrow_images(gpu, oracle, H, W):
     # Several narrow images side by side in a wavefront: widths that fill the lanes' groups exactly and
@@ -795,6 +873,9 @@ def test_batches_of_narrow_images(gpu, oracle, H, W):
         src = torch.from_numpy(rgb).cuda()
         for window in (gpu.HARRIS_WINDOW_BOX, gpu.HARRIS_WINDOW_BINOMIAL):
             say("case %d images of %dx%d, %s, window %d" % (B, H, W, rgb.dtype, window))
+            shape, blocks = gpu.harris_plan(int(u8), B, H, W, rgb_align=1 if u8 else 4, out_align=4)
+            if u8 or W % 4 == 0 or images > 2:
+                assert shape["flags"] & gpu.HARRIS_TUNE_PACKED_IMAGES and blocks == -(-B // images) * -(-n // 28)
             want = oracle.harris(rgb, K, 1.0, window)
             flat = torch.full((64 + B * n * m + 64,), float("nan"), device="cuda")
             out = flat[64:64 + B * n * m].view(B, n, m)
