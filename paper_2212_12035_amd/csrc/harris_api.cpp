@@ -45,18 +45,35 @@ bool px4_fits_word_aligned(int dtype, int out_dtype, int W, int rgb_align, int o
 
 // Four pixels per lane for rows of 16-bit results and 8-bit codes on any boundary of their element type:
 // the tile kernel stores the aligned words that hold them and the ends of each row element by
-// element.  By default for default shapes only (a caller that asks for a shape gets the lanes it names or the
-// narrower ones, and these with HARRIS_TUNE_WORD_STORES).  Worth it from about 1.5 million pixels on: below, a launch is bound by its latency,
-// which the longer store code adds to, and the narrower lanes' many wavefronts do no harm (wide
-// against narrow: 700x401 float32 to binary16 4.9 / 3.5 us, 768x1366 uint8 to codes 5.5 / 4.2); above,
-// the narrow lanes are bound by their instructions (1079x1919 float32 to binary16 7.6 / 9.0 us, 8
-// such images from uint8 25.2 / 49.1).
+// element (HARRIS_TUNE_WORD_STORES).
 bool px4_fits_shifted(int dtype, int out_dtype, int rgb_align) {
     return out_dtype != HARRIS_OUT_F32 && !(dtype == HARRIS_F32 && rgb_align % 4 != 0);
 }
-constexpr long long kShiftedPixels = 3LL << 19;
-bool px4_shifted_by_default(long long pixels, const harris_tuning& t) {
-    return t.rows == 0 && t.waves_per_block == 0 && t.flags == 0u && t.lds_kb == 0 && pixels >= kShiftedPixels;
+
+// Whether to take them by default, for default shapes (a caller that asks for a shape gets the lanes that it
+// names or the narrower ones), instead of lanes of `narrower` pixels, 1 or 2.
+//   - A strip of them takes the time of several narrower strips, whatever its width (float32 input 1.8 of one
+//     pixel and 1.2 to 1.6 of two, 8-bit input 1.6 of either): it must replace more than that.  13889 images
+//     of 64x9 float32 to binary16, one strip for one, 263 us wide and 146 narrow; 2049 of 64x61 45.9 / 24.5; 776
+//     of 64x161, one for three, 23.2 / 28.6, from 8-bit input 17.5 / 26.3.
+//   - From 14 tiles of the narrower lanes per CU on, or, where a wide strip replaces three of one pixel, from
+//     about 1.5 million pixels on: below, a launch is bound by its latency, which the longer store code
+//     adds to, and the narrower lanes' many wavefronts do no harm (700x401 float32 to binary16 4.9 / 3.5 us;
+//     33 of 200x301, two strips for five, 11 tiles, 9.1 / 8.5; but 1079x1919, 8 strips for 32, 11 tiles,
+//     7.6 / 9.1, and 776 of 64x161 as above).  Not from 1.5 million on if the planner's one tile per CU
+//     would leave a third of the CUs without (130 of 64x241, 130 tiles, 9.4 / 8.4; 50 of 64x501, 150, 8.3 / 7.4).
+//   Over 1174 shapes of 1.6 to 32 million pixels, 62 to 2831 columns wide, the choice takes on average 0.4 %
+//   longer than the faster of the two; always wide would take 6.8 %, always narrow 12.5 %.
+bool px4_shifted_by_default(int dtype, int batch, int H, int W, int narrower, const harris_tuning& t) {
+    if (t.rows != 0 || t.waves_per_block != 0 || t.flags != 0u || t.lds_kb != 0) return false;
+    const long long n = H - 4, m = W - 4;
+    if (n < 1 || m < 1 || (long long)batch * H * W < 3LL << 19) return false;
+    const long long wide_pitch = harris_launch::valid_lanes(4) * 4 - (dtype == HARRIS_U8 ? 8 : 4), narrow_pitch = harris_launch::valid_lanes(narrower) * narrower;
+    const long long wide = (m + wide_pitch - 1) / wide_pitch, narrow = (m + narrow_pitch - 1) / narrow_pitch;
+    const int worth = dtype == HARRIS_U8 ? (narrower == 1 ? 180 : 170) : (narrower == 1 ? 215 : 150);     // hundredths of a narrower strip
+    if (100 * narrow < worth * wide) return false;
+    if (batch * narrow * ((n + 11) / 12) >= 14 * 256) return true;
+    return narrower == 1 && narrow >= 3 * wide && !(batch * wide > 128 && batch * wide <= 170);
 }
 
 // Batches of narrow images, float32 results, default shapes only: as many images side by side in a
@@ -177,7 +194,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     } else if (t.px == 0) {
         t.px = 1;
         if (direct_px4) t.px = 4;
-        else if (tiles_allowed && px4_fits_shifted(dtype, out_dtype, rgb_align) && px4_shifted_by_default((long long)batch * H * W, t)) { t.px = 4; t.flags |= HARRIS_TUNE_WORD_STORES; }
+        else if (tiles_allowed && px4_fits_shifted(dtype, out_dtype, rgb_align) &&
+                 px4_shifted_by_default(dtype, batch, H, W, px_fits(2, dtype, out_dtype, W, rgb_align, out_align) ? 2 : 1, t)) { t.px = 4; t.flags |= HARRIS_TUNE_WORD_STORES; }
         else if (px_fits(2, dtype, out_dtype, W, rgb_align, out_align)) t.px = 2;
     } else if (!((t.px == 1 || t.px == 2 || t.px == 4) &&
                  (px_fits(t.px, dtype, out_dtype, W, rgb_align, out_align) || (t.px == 4 && word_aligned_px4)))) {

@@ -330,6 +330,22 @@ def test_plan_of_codes_from_8_bit_images_weighs_the_last_tile(pkg):
     assert pkg.harris_plan_typed(pkg.HARRIS_U8, pkg.HARRIS_OUT_U8, 8, 1080, 1920)[0]["rows"] == 4
 
 
+def test_plan_takes_wide_lanes_for_odd_rows_where_they_replace_enough_strips(pkg):
+    # 16-bit results and codes on rows off 4-byte boundaries: four pixels per lane only where a strip of
+    # them replaces more strips of the narrower lanes than it costs, and from a size on (see the planner).
+    F32, U8, O16, O8 = pkg.HARRIS_F32, pkg.HARRIS_U8, pkg.HARRIS_OUT_F16, pkg.HARRIS_OUT_U8
+    for dtype, out, B, H, W, px in (
+            (F32, O16, 13889, 64, 9, 1), (U8, O8, 2049, 64, 61, 1), (F32, O16, 1289, 64, 97, 1), (U8, O16, 1289, 64, 97, 4), (U8, O8, 248, 64, 101, 1),
+            (F32, O16, 776, 64, 161, 4), (F32, O16, 33, 200, 301, 1), (F32, O16, 415, 64, 301, 4), (F32, O16, 130, 64, 241, 1), (F32, O16, 1, 1079, 1919, 4),
+            (F32, O16, 1, 2831, 4255, 4), (U8, O16, 8, 1079, 1919, 4), (F32, O16, 1, 401, 700 + 1, 1),
+            # an even number of codes: the narrower lanes hold two pixels
+            (U8, O8, 248, 64, 102, 2), (F32, O8, 8000, 64, 122, 2), (U8, O8, 1000, 64, 242, 4), (F32, O8, 1000, 64, 254, 4), (U8, O8, 1000, 64, 254, 2),
+            (U8, O8, 16, 768, 1366, 4), (U8, O8, 1, 768, 1366, 2)):
+        two = out == O8 and W % 2 == 0
+        shape = pkg.harris_plan_typed(dtype, out, B, H, W, rgb_align=4 if dtype == F32 else 2 if two else 1, out_align=2 if two or out == O16 else 1)[0]
+        assert shape["px"] == px and bool(shape["flags"] & pkg.HARRIS_TUNE_WORD_STORES) == (px == 4), (dtype, out, B, H, W, shape)
+
+
 def test_copy_probe_validates_its_arguments(pkg):
     lib = pkg.load_library()
     one = ctypes.c_void_p(4096)

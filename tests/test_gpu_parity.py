@@ -741,8 +741,9 @@ def test_8_bit_codes(gpu, oracle):
 @pytest.mark.parametrize("fmt", ["f16", "bf16", "codes"])
 @pytest.mark.parametrize("W", [4 + 248 + 1, 4 + 2 * 248 - 1, 4 + 248 + 2, 517, 730, 1003, 7])
 def test_narrow_results_on_rows_of_any_alignment(gpu, oracle, fmt, W):
-    # 16-bit results and 8-bit codes whose rows start on any byte of their type, from the size on that
-    # takes four pixels per lane: the aligned words of a row are stored whole, its ends one by one.
+    # 16-bit results and 8-bit codes whose rows start on any byte of their type, four pixels per lane in the
+    # shapes of problems large enough to take them by default (narrow images do not): the aligned
+    # words of a row are stored whole, its ends one by one.
     # Widths at the strip border (248 columns) and one, two or three columns beside it, every phase of
     # the row address, dense and padded rows, both input types.  Every result equals, bit for bit, the
     # rounded float32 result of the same tile shape, and nothing beside the rows is written.
@@ -761,12 +762,13 @@ def test_narrow_results_on_rows_of_any_alignment(gpu, oracle, fmt, W):
             say("case %s results on any boundary, %s %s, pitch %d offset %d" % (fmt, rgb.dtype, rgb.shape, pitch, off))
             flat = torch.full((8 + B * n * pitch + 8,), mark, dtype=tdt, device="cuda")
             view = flat[8 + off:8 + off + B * n * pitch].view(B, n, pitch)[:, :, :m]
+            words = dict(flags=gpu.HARRIS_TUNE_WORD_STORES)
             if fmt == "codes":
-                gpu.harris_coarsity_quantized(src, view, 1.5, 90.0, K)
+                gpu.harris_coarsity_quantized(src, view, 1.5, 90.0, K, tuning=words)
             else:
-                gpu.harris_coarsity_typed(src, view, K)
+                gpu.harris_coarsity_typed(src, view, K, tuning=words)
             kind = {"f16": gpu.HARRIS_OUT_F16, "bf16": gpu.HARRIS_OUT_BF16, "codes": gpu.HARRIS_OUT_U8}[fmt]
-            shape = gpu.harris_plan_typed(int(u8), kind, B, H, W, rgb_align=1 if u8 else 4, out_align=1 if fmt == "codes" else 2)[0]
+            shape = gpu.harris_plan_typed(int(u8), kind, B, H, W, rgb_align=1 if u8 else 4, out_align=1 if fmt == "codes" else 2, tuning=words)[0]
             assert shape["px"] == 4
             gpu.harris_coarsity_typed(src, f32, K, tuning=dict(rows=shape["rows"], waves_per_block=shape["waves_per_block"]))
             torch.cuda.synchronize()
