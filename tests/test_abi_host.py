@@ -342,7 +342,7 @@ def test_plan_takes_wide_lanes_for_odd_rows_where_they_replace_enough_strips(pkg
             (U8, O8, 248, 64, 102, 2), (F32, O8, 8000, 64, 122, 2), (U8, O8, 1000, 64, 242, 4), (F32, O8, 1000, 64, 254, 4), (U8, O8, 1000, 64, 254, 2),
             (U8, O8, 16, 768, 1366, 4), (U8, O8, 1, 768, 1366, 2)):
         two = out == O8 and W % 2 == 0
-        shape = pkg.harris_plan_typed(dtype, out, B, H, W, rgb_align=4 if dtype == F32 else 2 if two else 1, out_align=2 if two or out == O16 else 1)[0]
+        shape = pkg.harris_plan_typed(dtype, out, B, H, W, rgb_align=(8 if two else 4) if dtype == F32 else 2 if two else 1, out_align=2 if two or out == O16 else 1)[0]
         assert shape["px"] == px and bool(shape["flags"] & pkg.HARRIS_TUNE_WORD_STORES) == (px == 4), (dtype, out, B, H, W, shape)
 
 
