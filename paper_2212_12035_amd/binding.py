@@ -164,11 +164,17 @@ def _allocation_stream(stream, device):
 def _enqueue(function, device, stream, *args):
     """Calls a library function, its last argument the stream, with `device` current.  The call costs less
     than the two objects it would otherwise make, a Stream and a device guard (3.5 of 9.4 us for a small
-    image): the current stream's handle is asked for by itself, and the guard is entered only
-    where another device is current."""
+    image): the current stream's handle is asked for by itself, of an internal function of torch where it
+    has that, and the guard is entered only where another device is current."""
     import torch
     index = device.index
-    handle = torch._C._cuda_getCurrentRawStream(index) if stream is None else _stream_ptr(stream, device)
+    if stream is None:
+        try:
+            handle = torch._C._cuda_getCurrentRawStream(index)
+        except AttributeError:
+            handle = _stream_ptr(None, device)
+    else:
+        handle = _stream_ptr(stream, device)
     if index == torch.cuda.current_device():
         status = function(*args, handle)
     else:

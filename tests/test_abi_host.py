@@ -502,6 +502,30 @@ def test_binding_refuses_host_tensors(pkg):
         pkg.harris_coarsity(torch.zeros(1, 3, 8, 8))
 
 
+@pytest.mark.parametrize("raw", [True, False])
+def test_current_stream_with_and_without_torchs_internal_function(pkg, monkeypatch, raw):
+    # Without a GPU: torch's answers are stand-ins, the library function is caught.
+    import types
+    import torch
+    if raw:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 100 + index, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device: types.SimpleNamespace(cuda_stream=100 + device.index))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    calls = []
+
+    def function(*args):
+        calls.append([getattr(a, "value", a) for a in args])
+        return 0
+
+    device = torch.device("cuda", 3)
+    pkg.binding._enqueue(function, device, None, 1, 2)
+    pkg.binding._enqueue(function, device, 55, 1, 2)
+    pkg.binding._enqueue(function, device, types.SimpleNamespace(cuda_stream=66), 1, 2)
+    assert calls == [[1, 2, 103], [1, 2, 55], [1, 2, 66]]
+
+
 @pytest.mark.parametrize("kind", ["none", "torch", "handle", "object", "null"])
 def test_internal_workspace_is_allocated_in_the_order_of_the_launch_stream(pkg, monkeypatch, kind):
     # harris_coarsity_grouped gives its own workspace back to torch on return, with its kernels still
