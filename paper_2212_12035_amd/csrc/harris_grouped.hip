@@ -34,6 +34,8 @@ static __device__ __align__(256) float scratch[HARRIS_GROUPED_SCRATCH_BYTES / si
 
 namespace {
 
+using harris_launch::groups_covering;
+
 // Kernels are templates over a thread's neighbouring pixels PX (4 or 1), and rows ROWS in the 3x3 stages
 // (2 or 1); grouped_wide says which.
 constexpr int kTileX = 64, kTileY = 4;      // 256 threads: 64 PX columns of 4 ROWS rows
@@ -94,10 +96,10 @@ __device__ __forceinline__ bool flat(size_t count, size_t& at, int& left) {
 // First pixel of this thread in a w x h image, or false.
 template <int PX, int ROWS>
 __device__ __forceinline__ bool pixel(int w, int h, int& x, int& y) {
-    x = (blockIdx.x * kTileX + threadIdx.x) * PX;
-    y = (blockIdx.y * kTileY + threadIdx.y) * ROWS;
-    if (x >= w || y >= h) return false;
-    x = min(x, max(w - PX, 0));
+    const unsigned ux = (blockIdx.x * kTileX + threadIdx.x) * PX, uy = (blockIdx.y * kTileY + threadIdx.y) * ROWS;
+    if (ux >= (unsigned)w || uy >= (unsigned)h) return false;
+    x = min((int)ux, max(w - PX, 0));
+    y = (int)uy;
     return true;
 }
 
@@ -286,7 +288,7 @@ void enqueue(const void* rgb, int dtype, int batch, int H, int W, float k, float
     const int h2 = H - 2, w2 = W - 2, h4 = H - 4, w4 = W - 4;
     const size_t n0 = (size_t)batch * H * W, n2 = (size_t)batch * h2 * w2, n4 = (size_t)batch * h4 * w4, plane = (size_t)H * W;
     const dim3 blk2(kTileX, kTileY), blk1(256);
-    auto grid = [&](int w, int h) { return dim3((w + kTileX * PX - 1) / (kTileX * PX), (h + kTileY * ROWS - 1) / (kTileY * ROWS), batch); };
+    auto grid = [&](int w, int h) { return dim3(groups_covering(w, kTileX * PX), groups_covering(h, kTileY * ROWS), batch); };
     auto grid1 = [](size_t count, int images) { return dim3((unsigned)((count + 256 * PX - 1) / (256 * PX)), 1, images); };
     const dim3 grid2 = grid(w2, h2), grid4 = grid(w4, h4);
     float* gray = ws;

@@ -128,6 +128,9 @@ size_t grouped_workspace_floats(int grouping, int batch, int H, int W);
 // 75 / 67, 96 columns 69 / 75, 128 columns 62 / 69; 8 million: 64 columns 363 / 331, 96 columns 304 / 402).
 inline bool grouped_wide(int batch, int H, int W) { return (long long)batch * H * W >= 5LL << 17 && W >= 96; }
 
+// Workgroups of `each` pixels (or rows) that cover `size` of them; size + each may lie beyond int.
+inline unsigned groups_covering(int size, int each) { return ((unsigned)size + (unsigned)each - 1u) / (unsigned)each; }
+
 // Enqueue grouping 1, 2 or 3 (see harris_coarsity_grouped).  Returns a harris_status.
 int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k, float sobel_scale, int binomial,
                    int grouping, float* workspace, float* out, void* stream);

@@ -117,6 +117,10 @@ int main() {
         if (harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("wide groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }
     for (const auto& c : {std::vector<int>{1, 1080, 1920}, {64, 128, 128}, {16, 651, 96}, {1, 720, 1000}})
         if (!harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("narrow groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }
+    // The widest images: the number of workgroups across them.
+    for (int each : {4, 8, 64, 256})
+        for (int size : {1, each, each + 1, 0x7fffffff - 256, 0x7fffffff - 64, 0x7fffffff - 4, 0x7fffffff})
+            if (harris_launch::groups_covering(size, each) != (unsigned)(((long long)size + each - 1) / each)) { std::printf("workgroups for %d by %d\n", size, each); return 1; }
     if (packed == 0 || gaps_packed == 0) { std::printf("the narrow-image kernel was never planned\n"); return 1; }
     std::printf("ok %d\n", harris_launch::launches);
     return 0;
