@@ -98,7 +98,7 @@ bool px4_shifted_by_default(int dtype, int batch, int H, int W, int narrower, co
 //     us, 252 of 32x124 5.4 / 5.0; but 293 of 32x128, 147 workgroups, 6.0 / 6.4, 260 of 32x120 5.4 / 6.1, and
 //     with 24 lanes 228 of 32x96, 684 tiles, 114 workgroups, 4.3 / 4.7).
 //   A caller may ask for it with HARRIS_TUNE_PACKED_IMAGES wherever the kernel can take the problem.
-constexpr int kPatchWaves = 8;
+using harris_launch::kPatchWaves;
 constexpr long long kPatchPixels = 1LL << 18;
 
 // HARRIS_OK: planned.  HARRIS_ERR_ARG: asked for where it cannot be.  kNotPacked: one image per wavefront.

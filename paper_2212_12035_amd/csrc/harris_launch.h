@@ -75,6 +75,10 @@ struct Params {
     unsigned image_lanes, image_lanes_inverse, images, batch;
 };
 
+// HARRIS_TUNE_PACKED_IMAGES: most wavefronts of a workgroup, each with four rows; the last one only hands its
+// rows on, so that images of more than 28 result rows are cut into bands.
+constexpr int kPatchWaves = 8;
+
 // HARRIS_TUNE_PACKED_IMAGES: what one lane of a wavefront loads of a row.  Offsets and sizes are in
 // bytes from the row's first element in the first of the group's `images` images; elem is the input
 // element's size.

@@ -8,18 +8,21 @@
 // group's last lane, whose columns are halo: every result column c takes input columns up to c + 4
 // < W, all of its own group.
 //
-// A workgroup holds whole images, or bands of equal height where they are taller than 16 wavefronts of
-// four rows: the four rows that two tiles would both read are read once.  Everything else is
+// A workgroup of at most kPatchWaves wavefronts holds whole images of up to 28 result rows, or bands of equal
+// height of taller ones: the four rows that two of its tiles would both read are read once.  Everything else is
 // the tile kernel's barrier form (harris_kernels.h): all rows requested at once, four gray rows handed
 // to the wavefront above through LDS, results stored in one burst.
 //
-// Input is loaded with the default policy: rows of a narrow image share their cache lines with the rows
-// above and below, which other wavefronts of the workgroup load (2048 images of 64x64 uint8:
-// 11.6 us, non-temporal 15.4; 1000 of 65x65 float32 13.3 / 16.1).  Results are stored non-temporal, not
-// written through, for the same reason (28.2 / 33.0 us for 2048 of 64x64 float32 at 16 wavefronts).
-// Measured against one image per wavefront (harris_tile_kernel): 2048 images of 64x64 float32 26.4 us
-// (5.0 TB/s; 38.2), 8192 of 32x32 26.7 (82.2), 1000 of 65x65 13.3 (24.0), 300 of 128x128 13.7 (15.8), 2048 of
-// 64x64 uint8 11.6 (28.2), 1343 of 80x27 uint8 9.2 (30.2).
+// Bound by memory, at 4.5 to 5.6 TB/s for float32.  Input is loaded with the default policy: rows of a
+// narrow image share their cache lines with the rows above and below, which other wavefronts of the
+// workgroup load.  Results are stored non-temporal, not written through, for the same reason.  Default loads
+// / non-temporal ones / results written through (us): 2048 images of 64x64 float32 26.9 / 28.5 / 30.9, uint8
+// 12.1 / 14.7 / 17.2; 1000 of 65x65 float32 13.5 / 17.4 / 16.6; 300 of 128x128 13.8 / 16.6 / 15.6; 600 of 110x124
+// uint8 11.5 / 14.6 / 15.0 (non-temporal loads gain with 1343 of 80x27 uint8, 9.1 / 7.9, and 5000 of 24x100
+// float32, 37.8 / 36.9).
+// Measured against one image per wavefront (harris_tile_kernel): 2048 images of 64x64 float32 26.9 us
+// (4.8 TB/s; 38.4), 8192 of 32x32 27.9 (82.3), 1000 of 65x65 13.5 (24.0), 300 of 128x128 13.8 (16.0), 2048 of
+// 64x64 uint8 12.1 (30.0), 1343 of 80x27 uint8 9.1 (30.2).
 #include "harris_kernels.h"
 
 namespace {
@@ -42,7 +45,7 @@ __device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint
 }
 
 template <typename In, bool BINOM>
-__global__ __launch_bounds__(1024) void harris_patch_kernel(const harris_launch::Params p) {
+__global__ __launch_bounds__(kWave * harris_launch::kPatchWaves) void harris_patch_kernel(const harris_launch::Params p) {
     constexpr int PX = 4, RW = 4;
     constexpr bool F32 = std::is_same<In, float>::value;
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]
