@@ -69,7 +69,9 @@ typedef enum harris_window {
  * Launch-shape override for benchmarks and tests; NULL in ordinary use (the library then
  * chooses the shape from the problem).  The structure, its flag bits and the planning
  * calls are declared in harris_tuning.h, which is not needed to use the operator.
- * Results never depend on the launch shape beyond rounding.
+ * Results never depend on the launch shape beyond rounding.  They do depend on it to that extent, and
+ * on a row's place in the image: the same image alone, in a batch or as a region of a larger one, or two
+ * equal rows of an image, may differ in the last bits.  One call repeated gives the same bits.
  */
 typedef struct harris_tuning harris_tuning;
 

@@ -16,8 +16,9 @@
 //    need of the rows of (Ix^2, Ix*Iy, Iy^2) live in registers ("register rotation").  Row
 //    steps are unrolled, so the rotation is a renaming, not a copy.
 //  * Both 3x3 stages are separated (section 4.3, "Convolution Separation"):
-//    [1 2 1]^T/[-1 0 1]^T down the column from registers first, then the horizontal
-//    taps.  Horizontal neighbours come from the lane to the right through a DPP
+//    taps down the column from registers, taps along the row from the lanes beside (the window
+//    sums and 8-bit input down the column first; float32 input takes [-1 0 1] along the row
+//    first, row_step says why).  Horizontal neighbours come from the lane to the right through a DPP
 //    wave shift; each stage consumes two columns from the right, so a lane's
 //    output columns start at the lane's own first input column and the result row
 //    is stored with aligned vector stores.
@@ -97,7 +98,9 @@ __device__ __forceinline__ float column(const float (&a)[PX]) {
 //     100.3 / 91.8, 8191x8191 uint8 94.1 / 89.5, to 16-bit and 8-bit results 16x1079x1919 float32 to
 //     binary16 87.9 / 81.0, 8192x8192 uint8 to binary16 77.3 / 72.3 and to codes 73.0 / 69.5 -- so only
 //     float32 results with moved borders take it, and those only where a row has more strips than
-//     ends (2048 images of 64x64, one strip: 44.5 / 37.1; 300 of 128x128: 18.8 / 15.7);
+//     ends (one strip: 781 images of 240x160 105.0 / 86.5, 521 of 240x240 91.4 / 80.9; two: 391 of 240x320 100.3 /
+//     86.9, 312 of 240x400 90.7 / 82.2, but 258 of 240x484, 480 result columns, 78.6 / 78.5; three and four,
+//     still written through: 174 of 240x720 81.1 / 78.2, 156 of 240x800 87.0 / 82.2; many: see above);
 //     one tile per CU, 1536x2560: 12.7 against 12.0 -- nor does that kernel;
 //   default-policy stores: 13.4 (1536x2560), 97.6 (8192x8192 uint8), 39.8 (2832x4256);
 //   loads nt + sc1: 12.8 on 1536x2560, no change on the large workloads; sc1 without nt, or
@@ -295,7 +298,9 @@ struct LineBuffers {
     float t[3][PX];       // box window: sums of the products of two neighbouring rows, an odd one and the even one below it
 };
 
-// One row step.  T is the row's number in its band or tile, modulo 2 at least: it fixes the slots of
+// One row step.  The sums that a row's results are made of are added up in an order that depends on whether the
+// row's number in its band or tile is even: equal input rows may differ in their results' last bits.
+// T is the row's number in its band or tile, modulo 2 at least: it fixes the slots of
 // the row's values (T % 2).
 // STAGE 0: gray only (first two rows of a band); 1: also Sobel and products (next
 // two rows); 2: also window sums and coarsity: one result row in o, for the caller to store.
