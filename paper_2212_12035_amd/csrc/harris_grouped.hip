@@ -44,12 +44,17 @@ typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
 typedef uint32_t word_any __attribute__((aligned(1)));
 
-// N values from p on, of which the first `left` (>= 1) exist; the others are 0.
+// N values from p on, of which the first `left` (>= 1) exist; the others are 0.  One value, and the three of a
+// row that one pixel takes, always exist: a check of each would put every tap behind a branch (the three
+// groupings on 729x776: 60.1 us with it).
 template <int N>
 __device__ __forceinline__ void load_values(const float* p, int left, float (&v)[N]) {
-    if (N >= 4 && left >= N) {
+    if constexpr (N < 4) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = p[i];
+    } else if (left >= N) {
         const f4 a = *reinterpret_cast<const f4*>(p);
-        v[0] = a.x; v[1 % N] = a.y; v[2 % N] = a.z; v[3 % N] = a.w;
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
         if constexpr (N == 6) {
             const f2 b = *reinterpret_cast<const f2*>(p + 4);
             v[4] = b.x; v[5] = b.y;
@@ -61,7 +66,9 @@ __device__ __forceinline__ void load_values(const float* p, int left, float (&v)
 }
 template <int N>
 __device__ __forceinline__ void load_values(const uint8_t* p, int left, float (&v)[N]) {
-    if (N == 4 && left >= N) {
+    if constexpr (N == 1) {
+        v[0] = (float)p[0];
+    } else if (N == 4 && left >= N) {
         const uint32_t w = *reinterpret_cast<const word_any*>(p);
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = (float)((w >> (8 * i)) & 0xffu);
@@ -72,7 +79,9 @@ __device__ __forceinline__ void load_values(const uint8_t* p, int left, float (&
 }
 template <int N>
 __device__ __forceinline__ void store_values(float* p, int left, const float (&v)[N]) {
-    if (N == 4 && left >= N) {
+    if constexpr (N == 1) {
+        p[0] = v[0];
+    } else if (N == 4 && left >= N) {
         *reinterpret_cast<f4*>(p) = f4{v[0], v[1 % N], v[2 % N], v[3 % N]};
     } else {
 #pragma unroll
@@ -87,9 +96,12 @@ __device__ __forceinline__ void store_values(float* p, int left, const float (&v
 template <int PX>
 __device__ __forceinline__ bool flat(size_t count, size_t& at, int& left) {
     at = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * PX;
+    left = 1;
     if (at >= count) return false;
-    at = min(at, max(count, (size_t)PX) - PX);
-    left = (int)min(count - at, (size_t)PX);
+    if constexpr (PX > 1) {
+        at = min(at, max(count, (size_t)PX) - PX);
+        left = (int)min(count - at, (size_t)PX);
+    }
     return true;
 }
 
@@ -110,14 +122,14 @@ struct Taps {
     float v[ROWS + 2][PX + 2];
     __device__ __forceinline__ void load(const float* in, int w, int h, int y, int x) {
 #pragma unroll
-        for (int r = 0; r < ROWS + 2; ++r) load_values<PX + 2>(in + (size_t)min(y + r, h + 1) * (w + 2) + x, w + 2 - x, v[r]);
+        for (int r = 0; r < ROWS + 2; ++r) load_values<PX + 2>(in + (size_t)(ROWS == 1 ? y + r : min(y + r, h + 1)) * (w + 2) + x, w + 2 - x, v[r]);
     }
 };
 template <int PX, int ROWS>
 __device__ __forceinline__ void store_rows(float* out, int w, int h, int y, int x, const float (&v)[ROWS][PX]) {
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
-        if (y + r < h) store_values(out + (size_t)(y + r) * w + x, w - x, v[r]);
+        if (ROWS == 1 || y + r < h) store_values(out + (size_t)(y + r) * w + x, w - x, v[r]);
 }
 
 // Conversion and grayscale.  rgb[b][3][H][W] -> gray[b][H][W]; in_scale is 1 (float32) or 1/255 (uint8).
