@@ -101,7 +101,11 @@ __device__ __forceinline__ float column(const float (&a)[PX]) {
 //     ends (one strip: 781 images of 240x160 105.0 / 86.5, 521 of 240x240 91.4 / 80.9; two: 391 of 240x320 100.3 /
 //     86.9, 312 of 240x400 90.7 / 82.2, but 258 of 240x484, 480 result columns, 78.6 / 78.5; three and four,
 //     still written through: 174 of 240x720 81.1 / 78.2, 156 of 240x800 87.0 / 82.2; many: see above);
-//     one tile per CU, 1536x2560: 12.7 against 12.0 -- nor does that kernel;
+//     small launches gain whatever their borders: up to 16 MB from uint8 to float32 and 16 bits (17 images of
+//     237x320 4.99 / 5.37, 1101x1630 5.64 / 6.21, 7 of 480x642 at 15 MB 6.36 / 6.71, but 19 of 300x401 at 16.4 MB the
+//     same either way; 727x2200 to binary16 4.79 / 5.12), up to 13 MB from float32 to float32 (6 of 260x332
+//     4.16 / 4.54, 9 of them 4.70 / 4.90, but 3 of 480x642 at 15 MB 5.23 / 5.13; to 16 bits and codes never);
+//     one tile per CU, 1536x2560: 12.7 against 12.0 -- nor does that kernel (kWriteThrough is the rule);
 //   default-policy stores: 13.4 (1536x2560), 97.6 (8192x8192 uint8), 39.8 (2832x4256);
 //   loads nt + sc1: 12.8 on 1536x2560, no change on the large workloads; sc1 without nt, or
 //     sc1 on the rows two tiles share: 4 to 22 % slower.
@@ -800,8 +804,20 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     if constexpr (HANDOFF) __syncthreads();                     // stores only after all of the workgroup's loads
     __builtin_amdgcn_sched_barrier(0);
     constexpr int SAUX = kAuxStore;
+    // The rows of this wavefront in one burst, written through or not (many-tile kernels only).
+    [[maybe_unused]] auto store_all = [&](auto&& store_one) {
+        if (LAUX == kAuxKeepShared && (p.flags & harris_launch::kWriteThrough)) {
+            static_for<0, RW>([&](auto jj) {
+                if (decltype(jj)::value < RW - 4 || wave + 1 < n_waves) store_one(std::integral_constant<int, kAuxManyStore>{}, jj);
+            });
+        } else {
+            static_for<0, RW>([&](auto jj) {
+                if (decltype(jj)::value < RW - 4 || wave + 1 < n_waves) store_one(std::integral_constant<int, SAUX>{}, jj);
+            });
+        }
+    };
     if constexpr (WORDS) {
-        auto store_all = [&](auto kind) {
+        auto store_words = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
             // The row's ends lie in this strip or not: decided per row, looked at only where one can.
             const bool ends = sx0 == 0u || sx1 + 4u > (unsigned)p.m;
@@ -821,30 +837,23 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
                 }
             });
         };
-        if (p.out_kind == HARRIS_OUT_U8) store_all(std::integral_constant<int, HARRIS_OUT_U8>{});
-        else if (p.out_kind == HARRIS_OUT_F16) store_all(std::integral_constant<int, HARRIS_OUT_F16>{});
-        else store_all(std::integral_constant<int, HARRIS_OUT_BF16>{});
+        if (p.out_kind == HARRIS_OUT_U8) store_words(std::integral_constant<int, HARRIS_OUT_U8>{});
+        else if (p.out_kind == HARRIS_OUT_F16) store_words(std::integral_constant<int, HARRIS_OUT_F16>{});
+        else store_words(std::integral_constant<int, HARRIS_OUT_BF16>{});
     } else if (__builtin_expect(p.out_kind == HARRIS_OUT_F32, 1)) {
-        if (LAUX == kAuxKeepShared && (p.flags & HARRIS_TUNE_ALIGNED_STORES) && p.n_strips > 2u) {
-            static_for<0, RW>([&](auto jj) {
-                constexpr int j = decltype(jj)::value;
-                if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, kAuxManyStore>(results[j], out_rs[j], lane_bytes + out_lead[j]);
-            });
-        } else {
-            static_for<0, RW>([&](auto jj) {
-                constexpr int j = decltype(jj)::value;
-                if (j < RW - 4 || wave + 1 < n_waves) store_row<PX, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
-            });
-        }
-    } else if (p.out_kind == HARRIS_OUT_F16) {
-        static_for<0, RW>([&](auto jj) {
+        store_all([&](auto aux, auto jj) {
             constexpr int j = decltype(jj)::value;
-            if (j < RW - 4 || wave + 1 < n_waves) store_row_16<PX, false, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+            store_row<PX, decltype(aux)::value>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+        });
+    } else if (p.out_kind == HARRIS_OUT_F16) {
+        store_all([&](auto aux, auto jj) {
+            constexpr int j = decltype(jj)::value;
+            store_row_16<PX, false, decltype(aux)::value>(results[j], out_rs[j], lane_bytes + out_lead[j]);
         });
     } else if (p.out_kind == HARRIS_OUT_BF16) {
-        static_for<0, RW>([&](auto jj) {
+        store_all([&](auto aux, auto jj) {
             constexpr int j = decltype(jj)::value;
-            if (j < RW - 4 || wave + 1 < n_waves) store_row_16<PX, true, SAUX>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+            store_row_16<PX, true, decltype(aux)::value>(results[j], out_rs[j], lane_bytes + out_lead[j]);
         });
     } else {
         static_for<0, RW>([&](auto jj) {

@@ -43,6 +43,10 @@ HARRIS_HOST_DEVICE inline unsigned fastdiv(unsigned x, const FastDiv& f) {
     return (t + ((x - t) >> f.sh1)) >> f.sh2;
 }
 
+// Bit of Params::flags beside the HARRIS_TUNE_* bits: the tile kernel stores float32 and 16-bit results
+// written through (kAuxManyStore in harris_kernels.h, which says where that is faster).
+constexpr unsigned kWriteThrough = 0x80000000u;
+
 // Kernel arguments (passed by value).  What the tile kernel reads before its first load sits
 // together, so that a few wide scalar loads fetch it at once.
 struct Params {
@@ -61,7 +65,7 @@ struct Params {
     unsigned waves_per_block;  // wavefronts per workgroup (the block size / 64)
     float wr, wg, wb;       // gray weights, times the Sobel scale (and 1/255 for 8-bit input)
     float k;                // coarsity constant
-    unsigned flags;         // HARRIS_TUNE_* bits
+    unsigned flags;         // HARRIS_TUNE_* bits, kWriteThrough
     unsigned out_kind;      // a harris_out_dtype (other than float32: tile kernel only)
     float q_scale, q_offset;   // 8-bit results: code = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)
     int binomial;           // 1: window [1 2 1; 2 4 2; 1 2 1], 0: unweighted 3x3 sum

@@ -112,6 +112,18 @@ int main() {
                     if (!patch_loads_inside_rows(p, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;
                 }
             }
+    // Store policy: {input type, result type, images, height, width, written through}.
+    static const int store[][6] = {{HARRIS_U8, HARRIS_OUT_F32, 17, 237, 320, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 1101, 1630, 1}, {HARRIS_U8, HARRIS_OUT_F16, 2, 700, 1200, 1},
+                                   {HARRIS_U8, HARRIS_OUT_F32, 66, 237, 320, 0}, {HARRIS_U8, HARRIS_OUT_F16, 66, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 6, 260, 332, 1},
+                                   {HARRIS_F32, HARRIS_OUT_F32, 21, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F16, 8, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 781, 240, 160, 0},
+                                   {HARRIS_F32, HARRIS_OUT_F32, 64, 1080, 1920, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 8192, 8192, 1}, {HARRIS_U8, HARRIS_OUT_F32, 8, 1079, 1919, 0}};
+    for (const auto& c : store) {
+        if (harris_coarsity_typed((const void*)0x100000, c[0], c[2], c[3], c[4], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, c[1], nullptr, nullptr) != HARRIS_OK ||
+            ((harris_launch::last.flags & harris_launch::kWriteThrough) != 0) != (c[5] != 0)) {
+            std::printf("store policy of %d images of %dx%d, types %d and %d\n", c[2], c[3], c[4], c[0], c[1]);
+            return 1;
+        }
+    }
     // Groupings: four pixels of two rows per thread only for images that give a row of threads work.
     for (const auto& c : {std::vector<int>{500, 40, 40}, {20000, 8, 8}, {3, 300000, 8}, {16, 7812, 64}, {1, 600, 800}})
         if (harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("wide groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }

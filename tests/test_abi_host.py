@@ -390,7 +390,7 @@ def test_planned_launches(tmp_path):
     # Batches of narrow images in every combination of gaps between rows, planes and images: whatever
     # kernel the planner takes, no lane loads a byte that belongs to no row of the call (harris.h excepts
     # only 8-bit rows off 4-byte boundaries, by whole words, in the other kernels).  And the groupings take
-    # four pixels of two rows per thread only where that is measured faster.
+    # four pixels of two rows per thread, and stores are written through, only where that is measured faster.
     import subprocess
     csrc = os.path.join(ROOT, "paper_2212_12035_amd", "csrc")
     exe = str(tmp_path / "plan_check")
