@@ -105,8 +105,10 @@ HARRIS_HOST_DEVICE inline PatchLane patch_lane(const Params& p, unsigned images,
     // 8-bit lanes load the row's last four bytes where they straddle its end, and the first image's where
     // they have no image: every load lies inside a row.  float32 lanes that straddle the end of a row
     // load what follows it up to in_bytes; the planner lets them where that is another row of the call.
-    if (elem == 1u) l.in_voff = l.live ? l.image * in_image + (l.col < last_col ? l.col : last_col) : 0u;
-    else l.in_voff = l.live ? l.image * in_image + l.col * elem : 0x80000000u;
+    const unsigned col = elem == 1u && l.col > last_col ? last_col : l.col;
+    const unsigned at = l.image * in_image + col * elem;        // below 2^31 for every lane (planner)
+    if (elem == 1u) l.in_voff = l.live ? at : 0u;
+    else l.in_voff = at | (l.live ? 0u : 0x80000000u);          // beyond in_bytes without an image; no branch
     l.drop = l.col > last_col ? 8u * ((l.col - last_col) & 3u) : 0u;
     return l;
 }
