@@ -104,7 +104,8 @@ __device__ __forceinline__ float column(const float (&a)[PX]) {
 //     small launches gain whatever their borders: up to 16 MB from uint8 to float32 and 16 bits (17 images of
 //     237x320 4.99 / 5.37, 1101x1630 5.64 / 6.21, 7 of 480x642 at 15 MB 6.36 / 6.71, but 19 of 300x401 at 16.4 MB the
 //     same either way; 727x2200 to binary16 4.79 / 5.12), up to 13 MB from float32 to float32 (6 of 260x332
-//     4.16 / 4.54, 9 of them 4.70 / 4.90, but 3 of 480x642 at 15 MB 5.23 / 5.13; to 16 bits and codes never);
+//     4.16 / 4.54, 9 of them 4.70 / 4.90, but 3 of 480x642 at 15 MB 5.23 / 5.13; to 16 bits and codes never;
+//     nor where the strip is the row: 268 of 34x25 uint8 6.41 / 6.11, 21 of 240x240 float32 5.57 / 5.17);
 //     one tile per CU, 1536x2560: 12.7 against 12.0 -- nor does that kernel (kWriteThrough is the rule);
 //   default-policy stores: 13.4 (1536x2560), 97.6 (8192x8192 uint8), 39.8 (2832x4256);
 //   loads nt + sc1: 12.8 on 1536x2560, no change on the large workloads; sc1 without nt, or

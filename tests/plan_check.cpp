@@ -114,7 +114,7 @@ int main() {
             }
     // Store policy: {input type, result type, images, height, width, written through}.
     static const int store[][6] = {{HARRIS_U8, HARRIS_OUT_F32, 17, 237, 320, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 1101, 1630, 1}, {HARRIS_U8, HARRIS_OUT_F16, 2, 700, 1200, 1},
-                                   {HARRIS_U8, HARRIS_OUT_F32, 66, 237, 320, 0}, {HARRIS_U8, HARRIS_OUT_F16, 66, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 6, 260, 332, 1},
+                                   {HARRIS_U8, HARRIS_OUT_F32, 66, 237, 320, 0}, {HARRIS_U8, HARRIS_OUT_F16, 66, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 6, 260, 332, 1}, {HARRIS_U8, HARRIS_OUT_F32, 14, 240, 240, 0},
                                    {HARRIS_F32, HARRIS_OUT_F32, 21, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F16, 8, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 781, 240, 160, 0},
                                    {HARRIS_F32, HARRIS_OUT_F32, 64, 1080, 1920, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 8192, 8192, 1}, {HARRIS_U8, HARRIS_OUT_F32, 8, 1079, 1919, 0}};
     for (const auto& c : store) {
