@@ -35,9 +35,9 @@ SETTLE_MS = 20.0               # untimed launches before the timed region, in GP
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (summaries under profiles/), valid only
 # for the kernel sources they were taken with: (sha256 of the csrc files without comments, {workload: bytes}).
-TRAFFIC_SOURCES_SHA256 = "49c8c54d5f04836ef448f427345c130a08ca6284c3ca50738f1277d844092aaa"
-TRAFFIC_BYTES = {"noise_f32_1536x2560": 65112236, "rects_f32_64x1080x1920": 2134586643,
-                 "blobs_f32_2832x4256": 196461339, "noise_u8_8192x8192": 474344734}
+TRAFFIC_SOURCES_SHA256 = "704a55dc42e5205846449623b3941fecacb41eb1ec8e02280d7e99b66eec2c0d"
+TRAFFIC_BYTES = {"noise_f32_1536x2560": 65188008, "rects_f32_64x1080x1920": 2136627414,
+                 "blobs_f32_2832x4256": 196555357, "noise_u8_8192x8192": 475115569}
 
 
 def kernel_sources_sha256():

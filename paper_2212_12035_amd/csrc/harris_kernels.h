@@ -315,7 +315,9 @@ struct LineBuffers {
 // exact, and what is added up afterwards rounds at that size (1536x2560 float32: error of the result
 // against 64 bits 2.4e-7 of its norm, 3.0e-7 with the sums first).  It keeps two rows of differences
 // more, which 8-bit input, bound by the vector ALUs at full occupancy, pays for (8 images of
-// 1080x1920 to 8-bit codes: 19.2 against 18.4 us): that takes the sums first.
+// 1080x1920 to 8-bit codes: 19.2 against 18.4 us): that takes the sums first.  float32 input pays 3 to 7
+// registers a lane and, in launches of 8 to 15 MB in tiles of 4 x 4, up to 4 % (6 images of 260x332 4.16 us, 3.95
+// with the sums first; 4 of 480x642 5.39 / 5.31; larger ones nothing).
 template <int STAGE, int T, int PX, bool BINOM, bool DIFF>
 __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX]) {
     constexpr int PS = T % 2;
