@@ -44,7 +44,8 @@ extern "C" {
  *             4: the same for two adjacent strips).  TILES: 2 to 16.  0 = default.
  *   flags     HARRIS_TUNE_* bits.
  *   lds_kb    TILES only: kilobytes of LDS to reserve per workgroup, 0 to 64.  A tile needs 4 KB
- *             per wavefront (px = 4); reserving more bounds the workgroups resident on a CU
+ *             per wavefront (px = 4; from 8-bit input up to 6 KB, taken where the reservation
+ *             reported is smaller); reserving more bounds the workgroups resident on a CU
  *             (160 KB of LDS per CU: 64 -> 2, 48 -> 3, 36 -> 4, 28 -> 5).  Many-tile float32
  *             launches are faster with 10 to 16 wavefronts per CU in flight than with the 28 to
  *             32 that the registers would allow.  0 = chosen from the size (plans report the

@@ -318,11 +318,16 @@ struct LineBuffers {
 // 1080x1920 to 8-bit codes: 19.2 against 18.4 us): that takes the sums first.  float32 input pays 3 to 7
 // registers a lane and, in launches of 8 to 15 MB in tiles of 4 x 4, up to 4 % (6 images of 260x332 4.16 us, 3.95
 // with the sums first; 4 of 480x642 5.39 / 5.31; larger ones nothing).
-template <int STAGE, int T, int PX, bool BINOM, bool DIFF>
-__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX]) {
+//
+// A row's Sobel responses can go out to the wavefront above (kSobelOut, in `sobel`) or come from the one below
+// (kSobelIn; gc is not looked at then).
+enum SobelRow { kSobelOwn, kSobelOut, kSobelIn };
+template <int STAGE, int T, int PX, bool BINOM, bool DIFF, int SOBEL>
+__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX], float (&sobel)[2][PX]) {
     constexpr int PS = T % 2;
+    constexpr bool GIVEN = SOBEL == kSobelIn;
     [[maybe_unused]] float dx[PX];                // DIFF: [-1 0 1] along the row
-    if constexpr (DIFF) {
+    if constexpr (DIFF && !GIVEN) {
         static_for<0, PX>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
             dx[i] = column<i + 2, PX>(gc) - gc[i];
@@ -331,18 +336,21 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
     [[maybe_unused]] float v[3][PX];              // [1 c 1] down the column of the three products
     if constexpr (STAGE >= 1) {
         [[maybe_unused]] float sy[PX];            // without DIFF: [1 2 1] down the column
-        float dy[PX];                             // [-1 0 1] down the column
+        [[maybe_unused]] float dy[PX];            // [-1 0 1] down the column
 #pragma unroll
-        for (int i = 0; i < PX; ++i) {
+        for (int i = 0; i < PX && !GIVEN; ++i) {
             dy[i] = gc[i] - lb.g[PS][i];
             if constexpr (!DIFF) sy[i] = fmaf(2.0f, lb.g[1 - PS][i], lb.g[PS][i] + gc[i]);
         }
         static_for<0, PX>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
-            float ix;
-            if constexpr (DIFF) ix = fmaf(2.0f, lb.d[1 - PS][i], lb.d[PS][i] + dx[i]);
+            float ix, iy;
+            if constexpr (GIVEN) ix = sobel[0][i];
+            else if constexpr (DIFF) ix = fmaf(2.0f, lb.d[1 - PS][i], lb.d[PS][i] + dx[i]);
             else ix = column<i + 2, PX>(sy) - sy[i];
-            const float iy = fmaf(2.0f, column<i + 1, PX>(dy), column<i + 2, PX>(dy) + dy[i]);   // [1 2 1] along the row
+            if constexpr (GIVEN) iy = sobel[1][i];
+            else iy = fmaf(2.0f, column<i + 1, PX>(dy), column<i + 2, PX>(dy) + dy[i]);   // [1 2 1] along the row
+            if constexpr (SOBEL == kSobelOut) { sobel[0][i] = ix; sobel[1][i] = iy; }
             // Products and window sums down the column (the window is separated too, c = 1 for
             // the unweighted sum, 2 for the binomial window).
             const float fa[3] = {ix, ix, iy}, fb[3] = {ix, iy, iy};
@@ -377,7 +385,7 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
         });
     }
 #pragma unroll
-    for (int i = 0; i < PX; ++i) {
+    for (int i = 0; i < PX && !GIVEN; ++i) {
         lb.g[PS][i] = gc[i];
         if constexpr (DIFF) lb.d[PS][i] = dx[i];
     }
@@ -415,6 +423,12 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
             o[i] = fmaf(-(k * tr), tr, det);
         }
     }
+}
+
+template <int STAGE, int T, int PX, bool BINOM, bool DIFF>
+__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX]) {
+    [[maybe_unused]] float none[2][PX];
+    row_step<STAGE, T, PX, BINOM, DIFF, kSobelOwn>(lb, gc, k, o, none);
 }
 
 // ---------------------------------------------------------------- the kernel
@@ -596,8 +610,8 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // wavefront requests its RW rows (3*RW loads) at once, so no wavefront goes through a
 // chain of dependent memory round trips.  Wavefront w turns its rows into gray,
 // publishes its first four gray rows in LDS and, after one barrier, takes the four
-// gray rows below its own from wavefront w+1 there: nothing is read twice inside a
-// tile.  Each wavefront then runs the same register pipeline as the band kernel over
+// gray rows below its own from wavefront w+1 there (8-bit input: two gray rows and two
+// of Sobel responses, below): nothing is read twice inside a tile.  Each wavefront then runs the same register pipeline as the band kernel over
 // its RW+4 gray rows and stores RW result rows (the last wavefront has no neighbour
 // below and stores RW-4).  A tile yields NW*RW-4 result rows; the tile below re-reads
 // four rows.
@@ -619,6 +633,17 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // own: as a branch of every four-pixel kernel this code cost the others registers (float32, 10 rows: up
 // to 28 vector registers in scratch memory; 2160x3840 23.0 us, 22.2 without; 2159x3839 to binary16
 // itself 21.9 and 20.8).
+//
+// 8-bit input with four pixels per lane hands over, instead of four gray rows, the first two and the Sobel responses
+// that the wavefront has computed from all four (six rows of LDS): the wavefront above needs exactly these, and does
+// not compute them again (4 instead of 6 rows of responses for 4 result rows; 50 of some 430 vector operations per
+// wavefront at 4 x 4).  8-bit launches that are not held up by memory gain: 16 images of 768x1366 to codes 22.4 us (23.0
+// before), 9 of 2442x1862 to codes 51.8 (54.1), 10 of 480x640 to float32 6.80 (6.92), 600x800 3.71 (3.82); 8192x8192 to
+// float32 is bound by the memory's view of its tiles (83 us, 84 without any arithmetic) and takes the same time.  At 4 x 4
+// the 19 KB leave eight workgroups on a CU.  float32 input is bound by memory and keeps the gray rows.
+template <typename In, int PX>
+__host__ __device__ constexpr bool hands_sobel() { return std::is_same<In, uint8_t>::value && PX == 4; }
+
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool WORDS = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
@@ -627,7 +652,8 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     constexpr bool DIFF = std::is_same<In, float>::value && !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF)));
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
     static_assert(!WORDS || PX == 4, "result rows as aligned words: four pixels per lane");
-    extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]
+    constexpr bool HAND_SOBEL = hands_sobel<In, PX>();
+    extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]; HAND_SOBEL: [1 + (NW - 1) * 6][64][PX]
     __shared__ unsigned ready[16];                              // HANDOFF: wavefront w has published its four rows
 
     const unsigned lane = threadIdx.x % kWave;
@@ -751,13 +777,24 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // are stored together at the end: bursts of reads and bursts of writes use the memory
     // better than a fine mixture (measured on 1536x2560: 13.0 us against 14.4 us).
     float results[RW][PX];
-    float* my_halo = halo_lds + ((size_t)wave * 4 * kWave + lane) * PX;
+    // HAND_SOBEL: the first wavefront, which has nobody to publish for, writes its six rows over each other into
+    // a row of its own.
+    const unsigned my_row = !HAND_SOBEL ? wave * 4u : wave == 0 ? 0u : wave * 6u - 5u;
+    const unsigned my_pitch = HAND_SOBEL && wave == 0 ? 0u : kWave * PX;
+    float* my_halo = halo_lds + ((size_t)my_row * kWave + lane) * PX;
+    auto publish = [&](unsigned row, const float (&v)[PX]) {
+        float* at = my_halo + row * my_pitch;
+#pragma unroll
+        for (int i = 0; i < PX; ++i) at[i] = v[i];
+    };
 
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         if constexpr (SHIFTED) realign_row(raw[t], shift[t]);
         gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
-        if constexpr (t < 4) {
+        if constexpr (HAND_SOBEL) {
+            if constexpr (t < 2) publish(t, gc);
+        } else if constexpr (t < 4) {
 #pragma unroll
             for (int i = 0; i < PX; ++i) my_halo[(size_t)t * kWave * PX + i] = gc[i];
         }
@@ -770,7 +807,12 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (lane == 0) __hip_atomic_store(&ready[wave], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if constexpr (t < 4) {
+        if constexpr (HAND_SOBEL && (t == 2 || t == 3)) {
+            float sobel[2][PX];
+            row_step<1, t, PX, BINOM, DIFF, kSobelOut>(lb, gc, p.k, none, sobel);
+            publish(2 * t - 2, sobel[0]);
+            publish(2 * t - 1, sobel[1]);
+        } else if constexpr (t < 4) {
             row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, none);
         } else {
             row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
@@ -793,12 +835,39 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             while (__hip_atomic_load(&ready[wave + 1], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u)
                 __builtin_amdgcn_s_sleep(4);
         }
-        const float* below = halo_lds + ((size_t)(wave + 1) * 4 * kWave + lane) * PX;
-        static_for<RW, RW + 4>([&](auto tt) {
-            constexpr int t = decltype(tt)::value;
+        const float* below = halo_lds + ((size_t)(HAND_SOBEL ? wave * 6u + 1u : (wave + 1) * 4u) * kWave + lane) * PX;
+        auto fetch = [&](unsigned row, float (&v)[PX]) {
 #pragma unroll
-            for (int i = 0; i < PX; ++i) gc[i] = below[(size_t)(t - RW) * kWave * PX + i];
-            row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
+            for (int i = 0; i < PX; ++i) v[i] = below[(size_t)row * kWave * PX + i];
+        };
+        // HAND_SOBEL: two rows are read ahead of their use.  Not with WORDS: those launches are bound by the vector
+        // ALUs, other wavefronts hide the reads, and the registers that hold the rows cost more (9 images of 2442x1862
+        // to codes 54.3 us, 51.8 without; 13 of 277x448 to float32 4.82 with, 5.00 without).
+        constexpr bool AHEAD = HAND_SOBEL && !WORDS;
+        [[maybe_unused]] float sobel[2][2][PX];
+        [[maybe_unused]] float second[PX];
+        if constexpr (AHEAD) {
+            fetch(0, gc);
+            fetch(1, second);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        static_for<RW, RW + 4>([&](auto tt) {
+            constexpr int t = decltype(tt)::value, row = t - RW;
+            if constexpr (HAND_SOBEL && (AHEAD ? row % 2 == 0 : row >= 2)) {
+                // The responses that the step after next takes (two steps ahead), or this step's own.
+                constexpr int from = AHEAD ? row / 2 : row - 2;
+                fetch(2 * from + 2, sobel[from][0]);
+                fetch(2 * from + 3, sobel[from][1]);
+                if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (HAND_SOBEL && row >= 2) {
+                row_step<2, t, PX, BINOM, DIFF, kSobelIn>(lb, gc, p.k, results[t - 4], sobel[row - 2]);
+            } else if constexpr (AHEAD && row == 1) {
+                row_step<2, t, PX, BINOM, DIFF>(lb, second, p.k, results[t - 4]);
+            } else {
+                if constexpr (!AHEAD) fetch(row, gc);
+                row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
+            }
             pin_values<PX>(results[t - 4]);
         });
     }

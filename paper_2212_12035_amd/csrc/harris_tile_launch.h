@@ -23,7 +23,8 @@ hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, h
     constexpr bool U8 = std::is_same<In, uint8_t>::value;
     // The four gray rows each wavefront publishes; the planner may reserve more to bound the
     // number of workgroups resident on a CU.
-    const size_t lds_needed = (size_t)(block.x / kWave) * 4 * kWave * PX * sizeof(float);
+    const size_t n_waves = block.x / kWave;
+    const size_t lds_needed = (hands_sobel<In, PX>() ? 1 + (n_waves - 1) * 6 : n_waves * 4) * kWave * PX * sizeof(float);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
     const bool cached = p.flags & HARRIS_TUNE_CACHED_LOADS, keep = p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS, handoff = p.flags & HARRIS_TUNE_FLAG_HANDOFF;
     if constexpr (U8 && PX == 4 && (RW == 4 || RW == 8)) {

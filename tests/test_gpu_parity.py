@@ -268,6 +268,20 @@ def test_lds_reservation_changes_nothing_but_the_residency(gpu, oracle):
         assert e.value.status == -3
 
 
+@pytest.mark.parametrize("rows", [4, 5, 8, 10])
+@pytest.mark.parametrize("waves", [2, 3, 12, 16])        # 6 KB of LDS each: from 12 on more than 64 KB
+def test_u8_sobel_responses_handed_over(gpu, oracle, rows, waves):
+    # One tile more than whole ones, the last of 1, rows and rows + 1 result rows; rows of whole words and on any byte.
+    for H, W, window in ((2 * (rows * waves - 4) + 5, 252, 0), (rows * waves + rows, 511, 1), (rows * waves + rows + 1, 260, 1)):
+        rgb = hi.white_noise_u8(700 + H + W, 2, H, W)
+        if W % 4 != 0 and rows not in (4, 8):            # the rows that kernels for unaligned bytes exist for
+            W = W + 1
+            rgb = hi.white_noise_u8(700 + H + W, 2, H, W)
+        say("case u8 hand-over 2x3x%dx%d window %d, tiles %dx%d" % (H, W, window, waves, rows))
+        got = run_gpu(gpu, rgb, k=K, window=window, tuning=dict(schedule=2, px=4, rows=rows, waves_per_block=waves))
+        check(got, oracle.harris(rgb, K, 1.0, window), referee=(oracle, rgb, K, 1.0, window))
+
+
 @pytest.mark.parametrize("px", [1, 2, 4])
 @pytest.mark.parametrize("prefetch", [3])
 def test_u8_every_kernel_instance(gpu, oracle, px, prefetch):
