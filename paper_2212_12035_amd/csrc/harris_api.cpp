@@ -152,6 +152,26 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
     return HARRIS_OK;
 }
 
+// Number of turns in which a launch of many tiles is dealt to the XCDs (dealt_tile in harris_launch.h says why).  One, eight
+// stretches as before, if about all tiles are resident at once: their order is then no matter.  Otherwise as many
+// as give each XCD runs of some bands of tiles, a band being a row of tiles across an image:
+//   - 8 bands, but at most some 136 tiles, where float32 input up to 400 MB (16-bit results and codes: 256 MB) keeps 3 or 4
+//     tiles on a CU.  Shorter runs have more bands at their ends, whose shared rows another L2 has: 2832x4256 (18 tiles
+//     a band) one turn 33.0 us, 7 bands 32.1, 4 bands 32.6, 2 bands 33.4; 2 images of 2160x3840 44.5 / 8 bands 42.5 / 2
+//     bands 44.9; 2400x8000 (34 a band) 52.5 / 4 bands 50.1 / 8 bands 53.3.
+//   - At least 2 bands and 16 tiles for larger launches, with 2 tiles on a CU, and for 8-bit input: 64 images of 1080x1920
+//     float32 (8 a band) one turn 353 us, 2 bands 334, 6 bands 338, 16 bands 351; 6000x8000 127.2, 2 bands 124.9, 1 band 128; 64 images
+//     of 1080x1920 uint8 176.4, 2 bands 159.5, 16 bands 166; 2832x4256 uint8 19.5, 2 bands 18.9, 10 bands 19.4.
+// Over 45 shapes no launch got slower by more than its spread but 5000x3500 float32 (45.8 and 46.2).
+unsigned chunk_turns(int dtype, int out_dtype, long long footprint, long long n_strips, long long n_tiles) {
+    if (n_tiles <= 2048) return 1;
+    const bool few = dtype == HARRIS_F32 && footprint <= ((out_dtype == HARRIS_OUT_F32 ? 400LL : 256LL) << 20);
+    const long long bands = few ? (136 >= 8 * n_strips ? 8 : 136 / n_strips) : (16 + n_strips - 1) / n_strips;
+    const long long chunk = (bands < 2 ? 2 : bands) * n_strips;
+    const long long turns = (n_tiles + 4 * chunk) / (8 * chunk);
+    return (unsigned)(turns < 1 ? 1 : turns > 65535 ? 65535 : turns);
+}
+
 harris_layout dense_layout(int H, int W) {
     // (Shapes that the planner has yet to refuse come here as well: no signed overflow.)
     const long long n = H - 4LL, m = W - 4LL, plane = (long long)H * W;
@@ -411,6 +431,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->blocks_per_image = (unsigned)blocks_per_image;
         params->n_blocks = (unsigned)blocks;
         params->waves_per_block = (unsigned)t.waves_per_block;
+        params->turns = chunk_turns(dtype, out_dtype, footprint, n_strips, n_tiles);
+        params->chunk = (unsigned)((n_tiles + 8LL * params->turns - 1) / (8LL * params->turns));
         // Store policy of many-tile launches (the figures stand with kAuxManyStore): written through are
         // float32 results where a row has more strips than ends and their borders lie on 64-byte
         // boundaries, and small launches with two strips or more, up to 16 MB from 8-bit input and 13 from

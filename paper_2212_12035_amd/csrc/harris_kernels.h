@@ -33,8 +33,8 @@
 //  * Bands (harris_fused_kernel): one long-lived wavefront walks a band of R result
 //    rows with a register queue of D input rows in flight; no LDS, no barrier.  Odd
 //    bands walk upwards, so two neighbouring bands begin on the rows they share.
-// In both, tiles are dealt to workgroups so that each XCD (own L2) gets one
-// contiguous run of tiles.
+// In both, tiles are dealt to workgroups so that each XCD (own L2) gets contiguous runs of
+// tiles: one, or in launches of many tiles several by turns.
 #ifndef HARRIS_KERNELS_H
 #define HARRIS_KERNELS_H
 
@@ -670,10 +670,16 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // The grid size is read with all other arguments, not in a branch of its own: one wait
     // for the arguments instead of two before the first load can be issued.
     unsigned n_blocks = p.n_blocks;
-    asm volatile("" : "+s"(n_blocks));
-    tile = (p.flags & HARRIS_TUNE_NO_XCD_REMAP) ? tile : xcd_contiguous(tile, n_blocks);
-    // The grid has p.n_blocks == n_tiles workgroups: every workgroup has a tile and every
-    // wavefront reaches the barrier.
+    if constexpr (LAUX == kAuxKeepShared) {
+        unsigned chunk = p.chunk;
+        asm volatile("" : "+s"(n_blocks), "+s"(chunk));
+        if (!(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) tile = harris_launch::dealt_tile(tile, blockIdx.y, chunk);
+        if (tile >= n_blocks) return;                           // at the end of the last turn; a whole workgroup, before any barrier
+    } else {
+        asm volatile("" : "+s"(n_blocks));
+        tile = (p.flags & HARRIS_TUNE_NO_XCD_REMAP) ? tile : xcd_contiguous(tile, n_blocks);
+    }
+    // Every workgroup that gets here has a tile, and every wavefront of it reaches the barrier.
 
     const unsigned img = harris_launch::fastdiv(tile, p.by_tiles_per_image);
     const unsigned rem = tile - img * p.tiles_per_image;

@@ -26,6 +26,8 @@ hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, h
     const size_t n_waves = block.x / kWave;
     const size_t lds_needed = (hands_sobel<In, PX>() ? 1 + (n_waves - 1) * 6 : n_waves * 4) * kWave * PX * sizeof(float);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
+    // Many tiles with shared rows kept: dealt to the XCDs by turns (dealt_tile).
+    if ((p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) && !(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) grid = dim3(8 * p.chunk, p.turns);
     const bool cached = p.flags & HARRIS_TUNE_CACHED_LOADS, keep = p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS, handoff = p.flags & HARRIS_TUNE_FLAG_HANDOFF;
     if constexpr (U8 && PX == 4 && (RW == 4 || RW == 8)) {
         // 8-bit rows on any byte: kernels for 4 and 8 rows per wavefront, barrier hand-over.

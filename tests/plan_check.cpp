@@ -124,6 +124,27 @@ int main() {
             return 1;
         }
     }
+    // Launches of many tiles: every tile is dealt out once, to a grid that the hardware takes; by turns from some size on.
+    for (const auto& c : {std::vector<int>{1, 1080, 1920, 1}, {64, 1080, 1920, 0}, {1, 2832, 4256, 0}, {3001, 240, 161, 0}, {1, 30000, 253, 0}, {1, 12, 600000, 0}, {7, 333, 2501, 1}})
+        for (int dtype : {HARRIS_F32, HARRIS_U8})
+            for (int out : {HARRIS_OUT_F32, HARRIS_OUT_F16}) {
+                const harris_tuning keep = {HARRIS_SCHEDULE_TILES, 0, 0, 0, 0, HARRIS_TUNE_STREAM_LOADS | HARRIS_TUNE_KEEP_SHARED_ROWS, 0};
+                if (harris_coarsity_typed((const void*)0x100000, dtype, c[0], c[1], c[2], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, out, c[3] ? &keep : nullptr, nullptr) == HARRIS_ERR_ARG) continue;
+                const Params& p = harris_launch::last;
+                const unsigned long long grid = 8ull * p.chunk * p.turns;
+                std::vector<unsigned char> dealt(p.n_blocks, 0);
+                bool good = p.turns >= 1 && p.turns <= 65535 && p.chunk >= 1 && grid < 0x7fffffffull && grid - p.n_blocks < 8ull * p.turns;
+                for (unsigned y = 0; good && y < p.turns; ++y)
+                    for (unsigned x = 0; x < 8 * p.chunk; ++x) {
+                        const unsigned tile = harris_launch::dealt_tile(x, y, p.chunk);
+                        if (tile < p.n_blocks && dealt[tile]++ != 0) good = false;
+                    }
+                for (unsigned char d : dealt) good = good && d == 1;
+                if (!good || (p.turns > 1 && p.n_blocks <= 2048)) {
+                    std::printf("%d images of %dx%d, types %d and %d: %u tiles, chunks of %u, %u turns\n", c[0], c[1], c[2], dtype, out, p.n_blocks, p.chunk, p.turns);
+                    return 1;
+                }
+            }
     // Groupings: four pixels of two rows per thread only for images that give a row of threads work.
     for (const auto& c : {std::vector<int>{500, 40, 40}, {20000, 8, 8}, {3, 300000, 8}, {16, 7812, 64}, {1, 600, 800}})
         if (harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("wide groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }
