@@ -644,7 +644,8 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 template <typename In, int PX>
 __host__ __device__ constexpr bool hands_sobel() { return std::is_same<In, uint8_t>::value && PX == 4; }
 
-template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool WORDS = false>
+// SMALL (8-bit input, shared rows kept): a launch whose tiles are all resident at once.
+template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool WORDS = false, bool SMALL = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
     // two rows of differences would push into scratch memory (none that float32 results take by default)
@@ -846,10 +847,11 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
 #pragma unroll
             for (int i = 0; i < PX; ++i) v[i] = below[(size_t)row * kWave * PX + i];
         };
-        // HAND_SOBEL: two rows are read ahead of their use.  Not with WORDS: those launches are bound by the vector
-        // ALUs, other wavefronts hide the reads, and the registers that hold the rows cost more (9 images of 2442x1862
-        // to codes 54.3 us, 51.8 without; 13 of 277x448 to float32 4.82 with, 5.00 without).
-        constexpr bool AHEAD = HAND_SOBEL && !WORDS;
+        // HAND_SOBEL: two rows are read ahead of their use where a launch's tiles are all resident at once and a CU has
+        // few wavefronts to hide the reads (AHEAD).  Others hide them, and are slower with the rows in registers
+        // (13 images of 277x448 to float32 4.81 us ahead, 5.00 not; 600x800 3.65 / 3.73; but 8 of 1080x1920 to binary16
+        // 21.3 / 19.7, 4000x3000 to codes 15.0 / 14.3, 9 of 2442x1862 to codes on any byte 54.3 / 51.8).
+        constexpr bool AHEAD = HAND_SOBEL && !WORDS && (LAUX == kAuxNonTemporal || SMALL);
         [[maybe_unused]] float sobel[2][2][PX];
         [[maybe_unused]] float second[PX];
         if constexpr (AHEAD) {
