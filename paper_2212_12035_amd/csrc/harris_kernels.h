@@ -645,7 +645,7 @@ template <typename In, int PX>
 __host__ __device__ constexpr bool hands_sobel() { return std::is_same<In, uint8_t>::value && PX == 4; }
 
 // SMALL (8-bit input, shared rows kept): a launch whose tiles are all resident at once.
-template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool WORDS = false, bool SMALL = false>
+template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool SMALL = false, bool WORDS = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
     // two rows of differences would push into scratch memory (none that float32 results take by default)

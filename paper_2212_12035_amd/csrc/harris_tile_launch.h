@@ -13,13 +13,13 @@ template <typename In, int PX, int RW, int LAUX, bool HANDOFF, bool SHIFTED, boo
 hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
     if constexpr (std::is_same<In, uint8_t>::value && PX == 4 && RW == 4 && LAUX == kAuxKeepShared && !WORDS) {
         if (p.turns == 1) {
-            if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, WORDS, true>), grid, block, lds, stream, p);
-            else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, WORDS, true>), grid, block, lds, stream, p);
+            if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, p);
+            else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, p);
             return hipGetLastError();
         }
     }
-    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, WORDS>), grid, block, lds, stream, p);
-    else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, WORDS>), grid, block, lds, stream, p);
+    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, false, WORDS>), grid, block, lds, stream, p);
+    else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, false, WORDS>), grid, block, lds, stream, p);
     return hipGetLastError();
 }
 
