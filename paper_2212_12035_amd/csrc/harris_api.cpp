@@ -434,10 +434,10 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->turns = chunk_turns(dtype, out_dtype, footprint, n_strips, n_tiles);
         params->chunk = (unsigned)((n_tiles + 8LL * params->turns - 1) / (8LL * params->turns));
         // Store policy of many-tile launches (the figures stand with kAuxManyStore): written through are
-        // float32 results where a row has more strips than ends and their borders lie on 64-byte
-        // boundaries, and small launches with two strips or more, up to 16 MB from 8-bit input and 13 from
+        // float32 results where a row has more strips than ends, from float32 input beyond 400 MB more than six, and
+        // their borders lie on 64-byte boundaries, and small launches with two strips or more, up to 16 MB from 8-bit input and 13 from
         // float32 to float32.
-        const bool aligned_strips = (t.flags & HARRIS_TUNE_ALIGNED_STORES) && n_strips > 2;
+        const bool aligned_strips = (t.flags & HARRIS_TUNE_ALIGNED_STORES) && n_strips > (dtype == HARRIS_F32 && footprint > (400LL << 20) ? 6 : 2);
         const bool small_launch = n_strips < 2 ? false : dtype == HARRIS_U8 ? footprint <= (16LL << 20) : out_dtype == HARRIS_OUT_F32 && footprint <= (13LL << 20);
         const bool through = small_launch || (out_dtype == HARRIS_OUT_F32 && aligned_strips);
         params->flags = t.flags | (through ? harris_launch::kWriteThrough : 0u);

@@ -99,8 +99,10 @@ __device__ __forceinline__ float column(const float (&a)[PX]) {
 //     binary16 87.9 / 81.0, 8192x8192 uint8 to binary16 77.3 / 72.3 and to codes 73.0 / 69.5 -- so only
 //     float32 results with moved borders take it, and those only where a row has more strips than
 //     ends (one strip: 781 images of 240x160 105.0 / 86.5, 521 of 240x240 91.4 / 80.9; two: 391 of 240x320 100.3 /
-//     86.9, 312 of 240x400 90.7 / 82.2, but 258 of 240x484, 480 result columns, 78.6 / 78.5; three and four,
-//     still written through: 174 of 240x720 81.1 / 78.2, 156 of 240x800 87.0 / 82.2; many: see above);
+//     86.9, 312 of 240x400 90.7 / 82.2, but 258 of 240x484, 480 result columns, 78.6 / 78.5), from float32 input beyond
+//     400 MB more than six (480 MB of images of 720 rows: three strips 81.1 / 78.1, four 77.8 / 76.9, six 79.6 / 78.1 and 75.1 /
+//     74.7, eight 76.2 / 76.2; 128 of 720x1280, six, 316 / 308; but 64 of 1080x1920, eight, 333 / 337; up to 400 MB, and
+//     from uint8 input, three to eight strips are 0.98 to 1.03 of the time either way, on the whole better written through);
 //     small launches gain whatever their borders: up to 16 MB from uint8 to float32 and 16 bits (17 images of
 //     237x320 4.99 / 5.37, 1101x1630 5.64 / 6.21, 7 of 480x642 at 15 MB 6.36 / 6.71, but 19 of 300x401 at 16.4 MB the
 //     same either way; 727x2200 to binary16 4.79 / 5.12), up to 13 MB from float32 to float32 (6 of 260x332

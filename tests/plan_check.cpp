@@ -116,7 +116,8 @@ int main() {
     static const int store[][6] = {{HARRIS_U8, HARRIS_OUT_F32, 17, 237, 320, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 1101, 1630, 1}, {HARRIS_U8, HARRIS_OUT_F16, 2, 700, 1200, 1},
                                    {HARRIS_U8, HARRIS_OUT_F32, 66, 237, 320, 0}, {HARRIS_U8, HARRIS_OUT_F16, 66, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 6, 260, 332, 1}, {HARRIS_U8, HARRIS_OUT_F32, 14, 240, 240, 0},
                                    {HARRIS_F32, HARRIS_OUT_F32, 21, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F16, 8, 237, 320, 0}, {HARRIS_F32, HARRIS_OUT_F32, 781, 240, 160, 0},
-                                   {HARRIS_F32, HARRIS_OUT_F32, 64, 1080, 1920, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 8192, 8192, 1}, {HARRIS_U8, HARRIS_OUT_F32, 8, 1079, 1919, 0}};
+                                   {HARRIS_F32, HARRIS_OUT_F32, 64, 1080, 1920, 1}, {HARRIS_U8, HARRIS_OUT_F32, 1, 8192, 8192, 1}, {HARRIS_U8, HARRIS_OUT_F32, 8, 1079, 1919, 0},
+                                   {HARRIS_F32, HARRIS_OUT_F32, 128, 720, 1280, 0}, {HARRIS_F32, HARRIS_OUT_F32, 32, 720, 1280, 0}, {HARRIS_F32, HARRIS_OUT_F32, 13, 720, 1280, 1}};
     for (const auto& c : store) {
         if (harris_coarsity_typed((const void*)0x100000, c[0], c[2], c[3], c[4], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, c[1], nullptr, nullptr) != HARRIS_OK ||
             ((harris_launch::last.flags & harris_launch::kWriteThrough) != 0) != (c[5] != 0)) {
