@@ -16,8 +16,8 @@
 // a thread takes four neighbouring pixels (16-byte accesses; rows of width W-2 and W-4 start on 4-byte
 // boundaries, which is all that global accesses of several words need) and, where it reads a 3x3
 // neighbourhood, two rows of them, so that a tap is loaded 1.5 x 2 times instead of 9.
-// One 1080x1920 float32 image, groupings 1, 2 and 3 together: 97.5 us (one pixel per thread 119), 8 such
-// images 600 us (810).
+// One 1080x1920 float32 image, groupings 1, 2 and 3 together: 90.4 us (one pixel per thread and one row: 119 us with
+// workgroups dealt out one by one).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -38,7 +38,19 @@ using harris_launch::groups_covering;
 
 // Kernels are templates over a thread's neighbouring pixels PX (4 or 1), and rows ROWS in the 3x3 stages
 // (2 or 1); grouped_wide says which.
-constexpr int kTileX = 64, kTileY = 4;      // 256 threads: 64 PX columns of 4 ROWS rows
+constexpr int kTileX = 64, kTileY = 4, kThreads = kTileX * kTileY;      // 64 PX columns of 4 ROWS rows
+
+// Where a workgroup works.  Grids are one-dimensional, 8 x chunk workgroups an image: the hardware deals them out to the
+// eight XCDs one by one, and each XCD takes one run of neighbours.  The rows that two of its workgroups both read, and
+// most of what the kernel before has just written, are then behind the same L2; with two-dimensional grids dealt out one
+// by one the three groupings of 1600x2400 took 151 us, now 136, 1080x1920 97.7 / 93.4, 480x640 41.6 / 37.7, 4
+// images of 1080x1920 289 / 272.  Workgroups beyond the last have nothing to do.
+struct Blocks {
+    unsigned chunk;                         // workgroups of an XCD
+    unsigned across;                        // workgroups across an image (3x3 stages)
+    harris_launch::FastDiv by_across;
+};
+__device__ __forceinline__ unsigned block_of(const Blocks& b) { return blockIdx.x % 8u * b.chunk + blockIdx.x / 8u; }
 
 typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -77,12 +89,16 @@ __device__ __forceinline__ void load_values(const uint8_t* p, int left, float (&
         for (int i = 0; i < N; ++i) v[i] = i < left ? (float)p[i] : 0.0f;
     }
 }
-template <int N>
+// LAST: results, which no kernel reads again: four at a time they are stored non-temporal (the three groupings of 1080x1920
+// 90.4 us, 93.4 without; uint8 1079x1919 81.2 / 86.6; 1600x2400 137.2 / 136.0).
+template <bool LAST, int N>
 __device__ __forceinline__ void store_values(float* p, int left, const float (&v)[N]) {
     if constexpr (N == 1) {
         p[0] = v[0];
     } else if (N == 4 && left >= N) {
-        *reinterpret_cast<f4*>(p) = f4{v[0], v[1 % N], v[2 % N], v[3 % N]};
+        const f4 all = f4{v[0], v[1 % N], v[2 % N], v[3 % N]};
+        if constexpr (LAST) __builtin_nontemporal_store(all, reinterpret_cast<f4*>(p));
+        else *reinterpret_cast<f4*>(p) = all;
     } else {
 #pragma unroll
         for (int i = 0; i < N; ++i) if (i < left) p[i] = v[i];
@@ -94,8 +110,8 @@ __device__ __forceinline__ void store_values(float* p, int left, const float (&v
 // ones): a path of its own for what is left would cost its wavefront a second memory latency
 // (1431x970, the three groupings: 73.8 against 74.5 us).
 template <int PX>
-__device__ __forceinline__ bool flat(size_t count, size_t& at, int& left) {
-    at = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * PX;
+__device__ __forceinline__ bool flat(const Blocks& blocks, size_t count, size_t& at, int& left) {
+    at = ((size_t)block_of(blocks) * kThreads + threadIdx.x) * PX;
     left = 1;
     if (at >= count) return false;
     if constexpr (PX > 1) {
@@ -107,8 +123,9 @@ __device__ __forceinline__ bool flat(size_t count, size_t& at, int& left) {
 
 // First pixel of this thread in a w x h image, or false.
 template <int PX, int ROWS>
-__device__ __forceinline__ bool pixel(int w, int h, int& x, int& y) {
-    const unsigned ux = (blockIdx.x * kTileX + threadIdx.x) * PX, uy = (blockIdx.y * kTileY + threadIdx.y) * ROWS;
+__device__ __forceinline__ bool pixel(const Blocks& blocks, int w, int h, int& x, int& y) {
+    const unsigned b = block_of(blocks), by = harris_launch::fastdiv(b, blocks.by_across), bx = b - by * blocks.across;
+    const unsigned ux = (bx * kTileX + threadIdx.x % kTileX) * PX, uy = (by * kTileY + threadIdx.x / kTileX) * ROWS;
     if (ux >= (unsigned)w || uy >= (unsigned)h) return false;
     x = min((int)ux, max(w - PX, 0));
     y = (int)uy;
@@ -125,19 +142,19 @@ struct Taps {
         for (int r = 0; r < ROWS + 2; ++r) load_values<PX + 2>(in + (size_t)(ROWS == 1 ? y + r : min(y + r, h + 1)) * (w + 2) + x, w + 2 - x, v[r]);
     }
 };
-template <int PX, int ROWS>
+template <bool LAST, int PX, int ROWS>
 __device__ __forceinline__ void store_rows(float* out, int w, int h, int y, int x, const float (&v)[ROWS][PX]) {
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
-        if (ROWS == 1 || y + r < h) store_values(out + (size_t)(y + r) * w + x, w - x, v[r]);
+        if (ROWS == 1 || y + r < h) store_values<LAST>(out + (size_t)(y + r) * w + x, w - x, v[r]);
 }
 
 // Conversion and grayscale.  rgb[b][3][H][W] -> gray[b][H][W]; in_scale is 1 (float32) or 1/255 (uint8).
 template <int PX, typename In>
-__global__ void gray_kernel(const In* rgb, float* gray, size_t plane, float in_scale) {
+__global__ void gray_kernel(const Blocks blocks, const In* rgb, float* gray, size_t plane, float in_scale) {
     size_t at;
     int left;
-    if (!flat<PX>(plane, at, left)) return;
+    if (!flat<PX>(blocks, plane, at, left)) return;
     const In* p = rgb + (size_t)blockIdx.z * 3 * plane + at;
     float r[PX], g[PX], b[PX], o[PX];
     load_values(p, left, r);
@@ -145,7 +162,7 @@ __global__ void gray_kernel(const In* rgb, float* gray, size_t plane, float in_s
     load_values(p + 2 * plane, left, b);
 #pragma unroll
     for (int i = 0; i < PX; ++i) o[i] = 0.299f * (r[i] * in_scale) + 0.587f * (g[i] * in_scale) + 0.114f * (b[i] * in_scale);
-    store_values(gray + (size_t)blockIdx.z * plane + at, left, o);
+    store_values<false>(gray + (size_t)blockIdx.z * plane + at, left, o);
 }
 
 // The two Sobel responses at row r, column i of a thread's pixels.
@@ -160,9 +177,9 @@ __device__ __forceinline__ void sobel_at(const Taps<PX, ROWS>& t, int r, int i, 
 // out_i[b][h][w].
 enum Stage { kSx, kSy, kSobelPair, kSobelProducts };
 template <int PX, int ROWS, int STAGE>
-__global__ void sobel_kernel(const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
+__global__ void sobel_kernel(const Blocks blocks, const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
     int x, y;
-    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
     Taps<PX, ROWS> t;
     t.load(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, h, y, x);
     float a[ROWS][PX], b[ROWS][PX], c[ROWS][PX];
@@ -177,23 +194,23 @@ __global__ void sobel_kernel(const float* in, float* out0, float* out1, float* o
             c[r][i] = iy * iy;
         }
     const size_t image = (size_t)blockIdx.z * h * w;
-    store_rows(out0 + image, w, h, y, x, a);
-    if constexpr (STAGE >= kSobelPair) store_rows(out1 + image, w, h, y, x, b);
-    if constexpr (STAGE == kSobelProducts) store_rows(out2 + image, w, h, y, x, c);
+    store_rows<false>(out0 + image, w, h, y, x, a);
+    if constexpr (STAGE >= kSobelPair) store_rows<false>(out1 + image, w, h, y, x, b);
+    if constexpr (STAGE == kSobelProducts) store_rows<false>(out2 + image, w, h, y, x, c);
 }
 
 // Products, one per launch.
 template <int PX>
-__global__ void mul_kernel(const float* a, const float* b, float* out, size_t count) {
+__global__ void mul_kernel(const Blocks blocks, const float* a, const float* b, float* out, size_t count) {
     size_t at;
     int left;
-    if (!flat<PX>(count, at, left)) return;
+    if (!flat<PX>(blocks, count, at, left)) return;
     float u[PX], v[PX], o[PX];
     load_values(a + at, left, u);
     load_values(b + at, left, v);
 #pragma unroll
     for (int i = 0; i < PX; ++i) o[i] = u[i] * v[i];
-    store_values(out + at, left, o);
+    store_values<false>(out + at, left, o);
 }
 
 // 3x3 window weights: all ones, or [1 2 1; 2 4 2; 1 2 1].
@@ -214,9 +231,9 @@ __device__ __forceinline__ float window_at(const Taps<PX, ROWS>& t, int r, int i
 
 // Window sums, one per launch.  in[b][h+2][w+2] -> out[b][h][w].
 template <int PX, int ROWS>
-__global__ void window_kernel(const float* in, float* out, int h, int w, int binomial) {
+__global__ void window_kernel(const Blocks blocks, const float* in, float* out, int h, int w, int binomial) {
     int x, y;
-    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
     Taps<PX, ROWS> t;
     t.load(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, h, y, x);
     float o[ROWS][PX];
@@ -224,7 +241,7 @@ __global__ void window_kernel(const float* in, float* out, int h, int w, int bin
     for (int r = 0; r < ROWS; ++r)
 #pragma unroll
         for (int i = 0; i < PX; ++i) o[r][i] = window_at(t, r, i, binomial);
-    store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
+    store_rows<false>(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
 __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, float k) {
@@ -234,24 +251,24 @@ __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, fl
 
 // Coarsity.
 template <int PX>
-__global__ void coarsity_kernel(const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
+__global__ void coarsity_kernel(const Blocks blocks, const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
     size_t at;
     int left;
-    if (!flat<PX>(count, at, left)) return;
+    if (!flat<PX>(blocks, count, at, left)) return;
     float a[PX], b[PX], c[PX], o[PX];
     load_values(sxx + at, left, a);
     load_values(sxy + at, left, b);
     load_values(syy + at, left, c);
 #pragma unroll
     for (int i = 0; i < PX; ++i) o[i] = coarsity_of(a[i], b[i], c[i], k);
-    store_values(out + at, left, o);
+    store_values<true>(out + at, left, o);
 }
 
 // Window sums and coarsity from the three product images.
 template <int PX, int ROWS>
-__global__ void window_coarsity_kernel(const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
+__global__ void window_coarsity_kernel(const Blocks blocks, const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
     int x, y;
-    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
     const size_t image = (size_t)blockIdx.z * (h + 2) * (w + 2);
     Taps<PX, ROWS> a, b, c;
     a.load(ixx + image, w, h, y, x);
@@ -262,14 +279,14 @@ __global__ void window_coarsity_kernel(const float* ixx, const float* ixy, const
     for (int r = 0; r < ROWS; ++r)
 #pragma unroll
         for (int i = 0; i < PX; ++i) o[r][i] = coarsity_of(window_at(a, r, i, binomial), window_at(b, r, i, binomial), window_at(c, r, i, binomial), k);
-    store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
+    store_rows<true>(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
 // Products, window sums and coarsity from the two Sobel images.
 template <int PX, int ROWS>
-__global__ void products_window_coarsity_kernel(const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
+__global__ void products_window_coarsity_kernel(const Blocks blocks, const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
     int x, y;
-    if (!pixel<PX, ROWS>(w, h, x, y)) return;
+    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
     const size_t image = (size_t)blockIdx.z * (h + 2) * (w + 2);
     Taps<PX, ROWS> gx, gy;
     gx.load(ix + image, w, h, y, x);
@@ -291,7 +308,7 @@ __global__ void products_window_coarsity_kernel(const float* ix, const float* iy
                 }
             o[r][i] = coarsity_of(sxx, sxy, syy, k);
         }
-    store_rows(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
+    store_rows<true>(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
 }
 
 // Every launch of grouping 1, 2 or 3.
@@ -299,32 +316,37 @@ template <int PX, int ROWS>
 void enqueue(const void* rgb, int dtype, int batch, int H, int W, float k, float s, int binomial, int grouping, float* ws, float* out, hipStream_t st) {
     const int h2 = H - 2, w2 = W - 2, h4 = H - 4, w4 = W - 4;
     const size_t n0 = (size_t)batch * H * W, n2 = (size_t)batch * h2 * w2, n4 = (size_t)batch * h4 * w4, plane = (size_t)H * W;
-    const dim3 blk2(kTileX, kTileY), blk1(256);
-    auto grid = [&](int w, int h) { return dim3(groups_covering(w, kTileX * PX), groups_covering(h, kTileY * ROWS), batch); };
-    auto grid1 = [](size_t count, int images) { return dim3((unsigned)((count + 256 * PX - 1) / (256 * PX)), 1, images); };
-    const dim3 grid2 = grid(w2, h2), grid4 = grid(w4, h4);
+    const dim3 threads(kThreads);
+    struct Launch { Blocks blocks; dim3 grid; };
+    auto launch = [](unsigned long long count, unsigned across, int images) {
+        const unsigned chunk = (unsigned)((count + 7) / 8);
+        return Launch{{chunk, across, harris_launch::make_fastdiv(across)}, dim3(8 * chunk, 1, images)};
+    };
+    auto area = [&](int w, int h) { const unsigned across = groups_covering(w, kTileX * PX); return launch((unsigned long long)across * groups_covering(h, kTileY * ROWS), across, batch); };
+    auto line = [&](size_t count, int images) { return launch((count + kThreads * PX - 1) / (kThreads * PX), 1, images); };
+    const Launch gray_l = line(plane, batch), l2 = area(w2, h2), l4 = area(w4, h4), f2 = line(n2, 1), f4 = line(n4, 1);
     float* gray = ws;
-    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<PX, uint8_t>), grid1(plane, batch), blk1, 0, st, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
-    else hipLaunchKernelGGL((gray_kernel<PX, float>), grid1(plane, batch), blk1, 0, st, static_cast<const float*>(rgb), gray, plane, 1.0f);
+    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<PX, uint8_t>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
+    else hipLaunchKernelGGL((gray_kernel<PX, float>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const float*>(rgb), gray, plane, 1.0f);
     if (grouping == 1) {
         float *ix = gray + n0, *iy = ix + n2, *ixx = iy + n2, *ixy = ixx + n2, *iyy = ixy + n2, *sxx = iyy + n2, *sxy = sxx + n4, *syy = sxy + n4;
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSx>), grid2, blk2, 0, st, gray, ix, nullptr, nullptr, h2, w2, s);
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSy>), grid2, blk2, 0, st, gray, iy, nullptr, nullptr, h2, w2, s);
-        hipLaunchKernelGGL(mul_kernel<PX>, grid1(n2, 1), blk1, 0, st, ix, ix, ixx, n2);
-        hipLaunchKernelGGL(mul_kernel<PX>, grid1(n2, 1), blk1, 0, st, ix, iy, ixy, n2);
-        hipLaunchKernelGGL(mul_kernel<PX>, grid1(n2, 1), blk1, 0, st, iy, iy, iyy, n2);
-        hipLaunchKernelGGL((window_kernel<PX, ROWS>), grid4, blk2, 0, st, ixx, sxx, h4, w4, binomial);
-        hipLaunchKernelGGL((window_kernel<PX, ROWS>), grid4, blk2, 0, st, ixy, sxy, h4, w4, binomial);
-        hipLaunchKernelGGL((window_kernel<PX, ROWS>), grid4, blk2, 0, st, iyy, syy, h4, w4, binomial);
-        hipLaunchKernelGGL(coarsity_kernel<PX>, grid1(n4, 1), blk1, 0, st, sxx, sxy, syy, out, n4, k);
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSx>), l2.grid, threads, 0, st, l2.blocks, gray, ix, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSy>), l2.grid, threads, 0, st, l2.blocks, gray, iy, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, ix, ix, ixx, n2);
+        hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, ix, iy, ixy, n2);
+        hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, iy, iy, iyy, n2);
+        hipLaunchKernelGGL((window_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, sxx, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixy, sxy, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, iyy, syy, h4, w4, binomial);
+        hipLaunchKernelGGL(coarsity_kernel<PX>, f4.grid, threads, 0, st, f4.blocks, sxx, sxy, syy, out, n4, k);
     } else if (grouping == 2) {
         float *ixx = gray + n0, *ixy = ixx + n2, *iyy = ixy + n2;
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelProducts>), grid2, blk2, 0, st, gray, ixx, ixy, iyy, h2, w2, s);
-        hipLaunchKernelGGL((window_coarsity_kernel<PX, ROWS>), grid4, blk2, 0, st, ixx, ixy, iyy, out, h4, w4, k, binomial);
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelProducts>), l2.grid, threads, 0, st, l2.blocks, gray, ixx, ixy, iyy, h2, w2, s);
+        hipLaunchKernelGGL((window_coarsity_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, ixy, iyy, out, h4, w4, k, binomial);
     } else {
         float *ix = gray + n0, *iy = ix + n2;
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelPair>), grid2, blk2, 0, st, gray, ix, iy, nullptr, h2, w2, s);
-        hipLaunchKernelGGL((products_window_coarsity_kernel<PX, ROWS>), grid4, blk2, 0, st, ix, iy, out, h4, w4, k, binomial);
+        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelPair>), l2.grid, threads, 0, st, l2.blocks, gray, ix, iy, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((products_window_coarsity_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ix, iy, out, h4, w4, k, binomial);
     }
 }
 

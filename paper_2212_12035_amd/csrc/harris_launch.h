@@ -142,10 +142,10 @@ size_t grouped_workspace_floats(int grouping, int batch, int H, int W);
 
 // Whether the kernels of a grouping take four neighbouring pixels of two rows per thread, or one pixel.
 // Smaller images keep one: a launch is then bound by its latency, and eight times the wavefronts hide
-// more of it (the three groupings on 600x800: 48.7 us, wide 52.4; on 720x1000 60.4 and 55.0).  So do narrower
+// more of it (the three groupings on 600x800: 43.6 us, wide 48.5; on 720x1000 55.2 and 51.5).  So do narrower
 // ones: a row of 64 threads takes 256 columns when wide, and most threads of the 3x3 stages would have
-// none (wide against one pixel, 1 million pixels: 16 columns 153 / 132 us, 40 columns 91 / 78, 64 columns
-// 75 / 67, 96 columns 69 / 75, 128 columns 62 / 69; 8 million: 64 columns 363 / 331, 96 columns 304 / 402).
+// none (wide against one pixel: 16 images of 651x64 63.4 / 53.2 us, of 651x96 68.2 / 70.9, 64 of 128x128 62.5 / 66.2; with
+// workgroups dealt out one by one, 8 million pixels: 64 columns 363 / 331, 96 columns 304 / 402).
 inline bool grouped_wide(int batch, int H, int W) { return (long long)batch * H * W >= 5LL << 17 && W >= 96; }
 
 // Workgroups of `each` pixels (or rows) that cover `size` of them; size + each may lie beyond int.
