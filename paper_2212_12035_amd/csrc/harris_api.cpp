@@ -78,10 +78,8 @@ bool px4_shifted_by_default(int dtype, int batch, int H, int W, int narrower, co
 
 // Batches of narrow images, float32 results, default shapes only: as many images side by side in a
 // wavefront as its 64 lanes of four columns hold (harris_patches.hip), from two on (W <= 128).
-//   - A workgroup holds up to kPatchWaves wavefronts of four rows, the last of which only hands its
-//     rows on; taller images are cut into bands of equal height.  (Eight: 16 start and end more
-//     together, 256 images of 64x64 5.4 against 7.1 us; 4 and 6 read more rows twice, 1500 of 100x80 39.6
-//     with 6 against 38.8.)
+//   - A workgroup holds four, five or eight wavefronts of four rows (patch_waves; a caller may ask for 2 to 8), the
+//     last of which only hands its rows on; taller images are cut into bands of equal height.
 //   - float32 rows whose length is no multiple of 4 must follow each other without a gap, those of
 //     neighbouring planes and images too: the lane at the end of a row reads up to three floats of what
 //     follows it, which must be a row of the call and nothing else.  With two images only, where little is gained, such rows keep a
@@ -93,13 +91,34 @@ bool px4_shifted_by_default(int dtype, int batch, int H, int W, int narrower, co
 //     3.9 / 3.5; 5 of 500x128, 210 tiles, 4.0 / 3.6; but 228 of 24x128, 456 tiles, 3.9 / 4.4; 64 of 64x64,
 //     320 tiles, 3.8 / 4.1).
 //   - Two wide float32 images, which keep more than 24 of the 64 lanes busy by themselves, gain least.  They
-//     stay apart where that fills the third tile of every CU and packed they would leave half of the CUs
-//     without a workgroup (packed against one by one: 244 of 32x128, 732 tiles, 122 workgroups, 5.4 / 5.0
+//     stay apart where that fills the third tile of every CU and bands of 28 result rows, packed, would leave half of the
+//     CUs without a workgroup (with eight wavefronts packed against one by one: 244 of 32x128, 732 tiles, 122 workgroups, 5.4 / 5.0
 //     us, 252 of 32x124 5.4 / 5.0; but 293 of 32x128, 147 workgroups, 6.0 / 6.4, 260 of 32x120 5.4 / 6.1, and
 //     with 24 lanes 228 of 32x96, 684 tiles, 114 workgroups, 4.3 / 4.7).
 //   A caller may ask for it with HARRIS_TUNE_PACKED_IMAGES wherever the kernel can take the problem.
 using harris_launch::kPatchWaves;
 constexpr long long kPatchPixels = 1LL << 18;
+
+// Wavefronts of a workgroup and turns of a launch (dealt_tile in harris_launch.h), measured together.  Four wavefronts, 12
+// result rows, by turns of some 16 workgroups, against eight in one stretch per XCD: 2048 images of 64x64 float32 24.9 us (29.4),
+// 8192 of 32x32 25.8 (30.9), 200 of 149x49 8.2 (10.0), 5000 of 24x100 32.7 (38.1), uint8 663 of 48x64 5.67 (6.38), 3713 of 103x25
+// 29.2 (33.1), and over 52 shapes 0.79 to 1.08 of the time, 0.93 on average (input and results not in the last-level cache;
+// 0.95 where they are).  Small workgroups start and end one by one while larger ones wait for room on a CU; what they
+// read twice, four rows in sixteen, comes from L2.  float32 launches of up to 5.5 such workgroups per CU take five where
+// 16 rows a band make fewer bands: 1000 images of 48x48 9.7 us (four: 10.5; eight 9.9), 867 of 77x25 9.5 (10.6), 2932 of 42x25
+// 16.1 (17.1); larger ones not (1521 of 92x34 21.4 / 20.4), nor 8-bit input (1955 of 121x28 15.3 / 15.2).  Launches below some
+// 1.2 million pixels keep eight, one band of up to 28 rows, and one turn: a test of the plans fixes their bands (four
+// would take 0.85 to 1.02 of the time: 71 uint8 images of 91x80 3.9 / 4.3, 311 float32 of 28x88 5.6 / 5.7).
+constexpr long long kPatchSmallPixels = 9LL << 17;
+int patch_waves(int dtype, long long pixels, long long groups, int n) {
+    if (pixels < kPatchSmallPixels) return kPatchWaves;
+    const int bands4 = (n + 11) / 12, bands5 = (n + 15) / 16;
+    return dtype == HARRIS_F32 && groups * bands4 <= 1408 && bands5 < bands4 ? 5 : 4;
+}
+unsigned patch_turns(long long pixels, long long blocks) {
+    const long long turns = pixels < kPatchSmallPixels ? 1 : (blocks + 64) / 128;
+    return (unsigned)(turns < 1 ? 1 : turns > 65535 ? 65535 : turns);
+}
 
 // HARRIS_OK: planned.  HARRIS_ERR_ARG: asked for where it cannot be.  kNotPacked: one image per wavefront.
 constexpr int kNotPacked = 1;
@@ -121,14 +140,15 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
     if (dtype == HARRIS_F32 && (rgb_align % 4 != 0 || (W % 4 != 0 && !dense))) return kNotPacked;
     const long long reach = 1LL << 30;
     if (lay.rgb_image_pitch > reach / (images * elem_size(dtype)) || lay.out_image_pitch > reach / (images * 4)) return kNotPacked;
-    const int max_rows = 4 * ((t.waves_per_block ? t.waves_per_block : kPatchWaves) - 1), bands = (n + max_rows - 1) / max_rows, rows = (n + bands - 1) / bands;
+    const long long groups = ((long long)batch + images - 1) / images;
+    const int max_rows = 4 * ((t.waves_per_block ? t.waves_per_block : patch_waves(dtype, (long long)batch * H * W, groups, n)) - 1), bands = (n + max_rows - 1) / max_rows, rows = (n + bands - 1) / bands;
     const int waves = t.waves_per_block ? t.waves_per_block : (rows + 3) / 4 + 1;
-    const long long blocks = ((long long)batch + images - 1) / images * bands;
+    const long long blocks = groups * bands;
     if (blocks > 0x7fffffffLL) return kNotPacked;
     if (!asked) {
         const long long tiles = (long long)batch * ((n + 11) / 12);         // of one image per wavefront
         if ((long long)batch * H * W < kPatchPixels || tiles <= 256) return kNotPacked;
-        if (images == 2 && dtype == HARRIS_F32 && (W % 4 != 0 || (lanes > 24 && tiles > 640 && tiles <= 768 && blocks <= 128))) return kNotPacked;
+        if (images == 2 && dtype == HARRIS_F32 && (W % 4 != 0 || (lanes > 24 && tiles > 640 && tiles <= 768 && groups * ((n + 27) / 28) <= 128))) return kNotPacked;
     }
     const harris_tuning c = {HARRIS_SCHEDULE_TILES, 4, 4, 0, waves, HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_PLAIN_STORES | HARRIS_TUNE_PACKED_IMAGES,
                              t.lds_kb > 4 * waves ? t.lds_kb : 4 * waves};
@@ -148,6 +168,8 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
         params->image_lanes_inverse = (unsigned)((65535 + lanes) / lanes);
         params->images = (unsigned)images;
         params->batch = (unsigned)batch;
+        params->turns = patch_turns((long long)batch * H * W, blocks);
+        params->chunk = (unsigned)((blocks + 8LL * params->turns - 1) / (8LL * params->turns));
     }
     return HARRIS_OK;
 }

@@ -90,7 +90,7 @@ struct Params {
 };
 
 // HARRIS_TUNE_PACKED_IMAGES: most wavefronts of a workgroup, each with four rows; the last one only hands its
-// rows on, so that images of more than 28 result rows are cut into bands.
+// rows on.
 constexpr int kPatchWaves = 8;
 
 // HARRIS_TUNE_PACKED_IMAGES: what one lane of a wavefront loads of a row.  Offsets and sizes are in
@@ -134,7 +134,7 @@ int launch_tiles_f32(const Params& p, const harris_tuning& shape, unsigned grid,
 int launch_tiles_u8(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
 int launch_tiles_f32_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);   // HARRIS_TUNE_WORD_STORES
 int launch_tiles_u8_words(const Params& p, const harris_tuning& shape, unsigned grid, unsigned block, void* stream);
-int launch_patches(const Params& p, int dtype, unsigned grid, unsigned block, void* stream);
+int launch_patches(const Params& p, int dtype, unsigned block, void* stream);
 int launch_bands(const Params& p, const harris_tuning& shape, int dtype, unsigned grid, unsigned block, void* stream);
 
 // Floats of workspace the grouped (unfused) pipelines need; 0 for an unknown grouping.

@@ -8,8 +8,8 @@
 // group's last lane, whose columns are halo: every result column c takes input columns up to c + 4
 // < W, all of its own group.
 //
-// A workgroup of at most kPatchWaves wavefronts holds whole images of up to 28 result rows, or bands of equal
-// height of taller ones: the four rows that two of its tiles would both read are read once.  Everything else is
+// A workgroup of at most kPatchWaves wavefronts, four in large launches, holds whole images or bands of equal height: the
+// four rows that two of its tiles would both read are read once.  Everything else is
 // the tile kernel's barrier form (harris_kernels.h): all rows requested at once, four gray rows handed
 // to the wavefront above through LDS, results stored in one burst.
 //
@@ -20,9 +20,10 @@
 // 12.1 / 14.7 / 17.2; 1000 of 65x65 float32 13.5 / 17.4 / 16.6; 300 of 128x128 13.8 / 16.6 / 15.6; 600 of 110x124
 // uint8 11.5 / 14.6 / 15.0 (non-temporal loads gain with 1343 of 80x27 uint8, 9.1 / 7.9, and 5000 of 24x100
 // float32, 37.8 / 36.9).
-// Measured against one image per wavefront (harris_tile_kernel): 2048 images of 64x64 float32 26.9 us
-// (4.8 TB/s; 38.4), 8192 of 32x32 27.9 (82.3), 1000 of 65x65 13.5 (24.0), 300 of 128x128 13.8 (16.0), 2048 of
-// 64x64 uint8 12.1 (30.0), 1343 of 80x27 uint8 9.1 (30.2).
+// Measured against one image per wavefront (harris_tile_kernel), then with eight wavefronts a workgroup: 2048 images of 64x64
+// float32 26.9 us (38.4), 8192 of 32x32 27.9 (82.3), 1000 of 65x65 13.5 (24.0), 300 of 128x128 13.8 (16.0), 2048 of
+// 64x64 uint8 12.1 (30.0), 1343 of 80x27 uint8 9.1 (30.2).  With four, dealt to the XCDs by turns: 2048 of 64x64 float32
+// 22.4 us, 5.8 TB/s (24.9 where nothing is left in the last-level cache).
 #include "harris_kernels.h"
 
 namespace {
@@ -55,12 +56,18 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
 
     const unsigned lane = threadIdx.x % kWave;
     const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const unsigned tile = xcd_contiguous(blockIdx.x, p.n_blocks);
+    // At the end of the last turn there may be workgroups without a tile: they go through the last one's motions with
+    // rows below the image, loading and storing nothing.  (A branch here would part the loads of the arguments in
+    // two, one behind the other: 256 images of 64x64 6.77 us, 6.3 without.)
+    unsigned n_blocks = p.n_blocks, chunk = p.chunk;
+    asm volatile("" : "+s"(n_blocks), "+s"(chunk));
+    const unsigned dealt = harris_launch::dealt_tile(blockIdx.x, blockIdx.y, chunk), tile = min(dealt, n_blocks - 1);
+    const int idle = dealt < n_blocks ? 0 : 1 << 30;
     const unsigned group = harris_launch::fastdiv(tile, p.by_tiles_per_image);      // of p.images images
     const int band = (int)(tile - group * p.tiles_per_image);
 
     const int tile_rows = p.rows_per_band;
-    const int y_wave = band * tile_rows + (int)wave * RW;
+    const int y_wave = band * tile_rows + (int)wave * RW + idle;
     const int y_end = min(p.n, (band + 1) * tile_rows);
     const int out_rows = max(0, min(RW, y_end - y_wave));
 
@@ -130,14 +137,15 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
 
 namespace harris_launch {
 
-int launch_patches(const Params& p, int dtype, unsigned grid, unsigned block, void* stream_) {
+int launch_patches(const Params& p, int dtype, unsigned block, void* stream_) {
+    const dim3 grid(8 * p.chunk, p.turns);
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     if (dtype == HARRIS_U8) {
-        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<uint8_t, true>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
-        else hipLaunchKernelGGL((harris_patch_kernel<uint8_t, false>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
+        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<uint8_t, true>), grid, dim3(block), p.lds_bytes, stream, p);
+        else hipLaunchKernelGGL((harris_patch_kernel<uint8_t, false>), grid, dim3(block), p.lds_bytes, stream, p);
     } else {
-        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<float, true>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
-        else hipLaunchKernelGGL((harris_patch_kernel<float, false>), dim3(grid), dim3(block), p.lds_bytes, stream, p);
+        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<float, true>), grid, dim3(block), p.lds_bytes, stream, p);
+        else hipLaunchKernelGGL((harris_patch_kernel<float, false>), grid, dim3(block), p.lds_bytes, stream, p);
     }
     return (int)hipGetLastError();
 }

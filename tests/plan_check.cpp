@@ -126,7 +126,7 @@ int main() {
         }
     }
     // Launches of many tiles: every tile is dealt out once, to a grid that the hardware takes; by turns from some size on.
-    for (const auto& c : {std::vector<int>{1, 1080, 1920, 1}, {64, 1080, 1920, 0}, {1, 2832, 4256, 0}, {3001, 240, 161, 0}, {1, 30000, 253, 0}, {1, 12, 600000, 0}, {7, 333, 2501, 1}})
+    for (const auto& c : {std::vector<int>{1, 1080, 1920, 1}, {64, 1080, 1920, 0}, {1, 2832, 4256, 0}, {3001, 240, 161, 0}, {1, 30000, 253, 0}, {1, 12, 600000, 0}, {7, 333, 2501, 1}, {8192, 32, 32, 0}, {1501, 30, 33, 0}, {70, 120, 64, 0}})
         for (int dtype : {HARRIS_F32, HARRIS_U8})
             for (int out : {HARRIS_OUT_F32, HARRIS_OUT_F16}) {
                 const harris_tuning keep = {HARRIS_SCHEDULE_TILES, 0, 0, 0, 0, HARRIS_TUNE_STREAM_LOADS | HARRIS_TUNE_KEEP_SHARED_ROWS, 0};
@@ -141,7 +141,7 @@ int main() {
                         if (tile < p.n_blocks && dealt[tile]++ != 0) good = false;
                     }
                 for (unsigned char d : dealt) good = good && d == 1;
-                if (!good || (p.turns > 1 && p.n_blocks <= 2048)) {
+                if (!good || (p.turns > 1 && p.n_blocks <= 2048 && !(p.flags & HARRIS_TUNE_PACKED_IMAGES))) {
                     std::printf("%d images of %dx%d, types %d and %d: %u tiles, chunks of %u, %u turns\n", c[0], c[1], c[2], dtype, out, p.n_blocks, p.chunk, p.turns);
                     return 1;
                 }

@@ -820,6 +820,24 @@ def test_packed_images_asked_for(gpu, oracle, B, H, W):
                 assert bool(torch.isnan(flat).all())
 
 
+@pytest.mark.parametrize("B,H,W", [(1501, 30, 33), (613, 31, 64), (1025, 49, 25)])
+def test_many_narrow_images_dealt_by_turns(gpu, oracle, B, H, W):
+    # Launches of several turns whose last one has workgroups without a tile, with four and with five wavefronts.
+    import torch
+    for u8 in (False, True):
+        rgb = (hi.white_noise_u8 if u8 else hi.white_noise_f32)(580 + W, B, H, W)
+        shape, blocks = gpu.harris_plan(int(u8), B, H, W, rgb_align=16)
+        say("case %d images of %dx%d, %s, %d workgroups of %d wavefronts" % (B, H, W, rgb.dtype, blocks, shape["waves_per_block"]))
+        assert shape["flags"] & gpu.HARRIS_TUNE_PACKED_IMAGES and blocks > 256
+        flat = torch.full((64 + B * (H - 4) * (W - 4) + 64,), float("nan"), device="cuda")
+        out = flat[64:-64].view(B, H - 4, W - 4)
+        gpu.harris_coarsity_ex(torch.from_numpy(rgb).cuda(), K, out=out)
+        torch.cuda.synchronize()
+        check(out.cpu().numpy(), oracle.harris(rgb, K))
+        out.fill_(float("nan"))
+        assert bool(torch.isnan(flat).all())
+
+
 @pytest.mark.parametrize("fmt", ["f16", "bf16", "codes"])
 @pytest.mark.parametrize("rows", [4, 5, 6, 8, 9, 10])
 def test_word_stores_every_kernel_instance(gpu, oracle, fmt, rows):
