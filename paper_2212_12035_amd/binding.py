@@ -4,6 +4,10 @@ The functions have the names and argument order of the C entry points.  Images
 are torch tensors on a ROCm device; their data pointers and the current HIP stream
 are handed to the library unchanged.  There is no fallback: if the shared library
 is missing the first call raises.
+
+Plain calls of the fused entry points (ordinary tensors on the current device, its current stream,
+no launch shape) are marshalled in native code where that module is built (cbinding/harris_call.cpp);
+it declines whatever else comes, and the code below takes it.
 """
 from __future__ import annotations
 
@@ -52,6 +56,7 @@ class HarrisTuning(ctypes.Structure):
 
 
 _lib = None
+_native = None          # the native marshalling, bound to the library's functions by load_library
 
 
 def library_path() -> str:
@@ -98,7 +103,24 @@ def load_library() -> ctypes.CDLL:
     lib.harris_strerror.argtypes = [ci]
     lib.harris_strerror.restype = ctypes.c_char_p
     _lib = lib
+    _bind_native(lib)
     return lib
+
+
+def _bind_native(lib):
+    """Hands the native marshalling the functions it calls.  It is optional: without it, or with a torch that lacks
+    the function for the current stream's handle, every call takes the Python code."""
+    global _native
+    _native = None
+    try:
+        import torch
+        from . import _harris_call
+        current_device, current_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    except (ImportError, AttributeError):
+        return
+    address = lambda function: ctypes.cast(function, ctypes.c_void_p).value
+    _harris_call.bind(address(lib.harris_coarsity_typed), address(lib.harris_coarsity_quantized), current_device, current_stream)
+    _native = _harris_call
 
 
 def harris_strerror(status: int) -> str:
@@ -186,6 +208,10 @@ def _enqueue(function, device, stream, *args):
 
 def harris_coarsity(rgb, k: float = 0.04, out=None, stream=None):
     """float32 rgb[batch][3][H][W] -> float32 out[batch][H-4][W-4]; integer Sobel, 3x3 sum."""
+    if stream is None and _native is not None:
+        done = _native.dense(rgb, out, k, 1.0, HARRIS_WINDOW_BOX, HARRIS_F32)
+        if done is not None:
+            return done
     import torch
     B, H, W, out = _prepare(rgb, out, torch.float32)
     _enqueue(load_library().harris_coarsity, rgb.device, stream, rgb.data_ptr(), B, H, W, k, out.data_ptr())
@@ -194,6 +220,10 @@ def harris_coarsity(rgb, k: float = 0.04, out=None, stream=None):
 
 def harris_coarsity_u8(rgb, k: float = 0.04, out=None, stream=None):
     """uint8 rgb[batch][3][H][W] (taken as u/255) -> float32 out[batch][H-4][W-4]."""
+    if stream is None and _native is not None:
+        done = _native.dense(rgb, out, k, 1.0, HARRIS_WINDOW_BOX, HARRIS_U8)
+        if done is not None:
+            return done
     import torch
     B, H, W, out = _prepare(rgb, out, torch.uint8)
     _enqueue(load_library().harris_coarsity_u8, rgb.device, stream, rgb.data_ptr(), B, H, W, k, out.data_ptr())
@@ -203,6 +233,10 @@ def harris_coarsity_u8(rgb, k: float = 0.04, out=None, stream=None):
 def harris_coarsity_ex(rgb, k: float = 0.04, sobel_scale: float = 1.0, window: int = HARRIS_WINDOW_BOX,
                        out=None, tuning=None, stream=None):
     """General form; the element type is taken from rgb.dtype (float32 or uint8)."""
+    if stream is None and tuning is None and _native is not None:
+        done = _native.dense(rgb, out, k, sobel_scale, window, -1)
+        if done is not None:
+            return done
     import torch
     if not isinstance(rgb, torch.Tensor) or rgb.dtype not in (torch.float32, torch.uint8):
         raise TypeError("rgb must be a float32 or uint8 torch tensor")
@@ -239,6 +273,10 @@ def _strided(rgb, out, out_dtypes, what):
 def harris_coarsity_pitched(rgb, out, k: float = 0.04, sobel_scale: float = 1.0, window: int = HARRIS_WINDOW_BOX,
                             tuning=None, stream=None):
     """General form for strided tensors (views); float32 result."""
+    if stream is None and tuning is None and _native is not None:
+        done = _native.views(rgb, out, k, sobel_scale, window, 0, 1.0, 0.0)
+        if done is not None:
+            return done
     import torch
     B, H, W, lay, dtype = _strided(rgb, out, (torch.float32,), "float32")
     _enqueue(load_library().harris_coarsity_pitched, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k,
@@ -249,6 +287,10 @@ def harris_coarsity_pitched(rgb, out, k: float = 0.04, sobel_scale: float = 1.0,
 def harris_coarsity_typed(rgb, out, k: float = 0.04, sobel_scale: float = 1.0, window: int = HARRIS_WINDOW_BOX,
                           tuning=None, stream=None):
     """harris_coarsity_pitched with the result type taken from `out`: float32, float16 or bfloat16."""
+    if stream is None and tuning is None and _native is not None:
+        done = _native.views(rgb, out, k, sobel_scale, window, 1, 1.0, 0.0)
+        if done is not None:
+            return done
     import torch
     kinds = {torch.float32: HARRIS_OUT_F32, torch.float16: HARRIS_OUT_F16, torch.bfloat16: HARRIS_OUT_BF16}
     B, H, W, lay, dtype = _strided(rgb, out, kinds, "float32, float16 or bfloat16")
@@ -260,6 +302,10 @@ def harris_coarsity_typed(rgb, out, k: float = 0.04, sobel_scale: float = 1.0, w
 def harris_coarsity_quantized(rgb, out, q_scale: float, q_offset: float, k: float = 0.04, sobel_scale: float = 1.0,
                               window: int = HARRIS_WINDOW_BOX, tuning=None, stream=None):
     """8-bit result: out (uint8 [batch][H-4][W-4], may be a view) = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)."""
+    if stream is None and tuning is None and _native is not None:
+        done = _native.views(rgb, out, k, sobel_scale, window, 2, q_scale, q_offset)
+        if done is not None:
+            return done
     import torch
     B, H, W, lay, dtype = _strided(rgb, out, (torch.uint8,), "uint8")
     _enqueue(load_library().harris_coarsity_quantized, rgb.device, stream, rgb.data_ptr(), dtype, B, H, W, ctypes.byref(lay), k,

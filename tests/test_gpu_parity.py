@@ -1162,6 +1162,87 @@ def test_stream_probes_touch_what_they_say(gpu):
     assert bool((guard == -7).all())
 
 
+# ---------------------------------------------------------------- the binding's native marshalling
+
+def test_native_marshalling_does_what_the_python_code_does(gpu, monkeypatch):
+    # Every entry point that has it, plain calls and calls that it declines: the same values, the same result object
+    # or error with and without it; and it does take the plain ones.
+    import torch
+    from paper_2212_12035_amd import binding
+    assert binding._native is not None
+
+    class Sub(torch.Tensor):
+        pass
+
+    class Mode(torch.overrides.TorchFunctionMode):
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    f32 = torch.from_numpy(hi.white_noise_f32(640, 3, 24, 37)).cuda()
+    u8 = torch.from_numpy(hi.white_noise_u8(641, 3, 24, 37)).cuda()
+    empty = lambda dt, *shape: torch.full(shape, 7, dtype=dt, device="cuda")
+    wide32, wide8 = torch.rand(3, 3, 30, 50, device="cuda"), torch.randint(0, 256, (3, 3, 30, 50), device="cuda", dtype=torch.uint8)
+    view32, view8 = wide32[:, :, 3:27, 5:42], wide8[:, :, 3:27, 5:42]
+    grad = f32.clone().requires_grad_()
+    images = [f32, u8, view32, view8, f32[:1], view32[1:2], u8[:0], f32[:, :, :4], f32[:, :, :, :4], f32[:, :, :5, :5].contiguous(), f32[:, :2], f32[0], f32.double(), f32.cpu(),
+              f32.transpose(2, 3), f32.as_subclass(Sub), grad, None, [1.0]]
+    scalars = [(K, 1.0, 0), (0.06, S12, 1), (0, 1.0, 0), (np.float64(K), 1.0, 0), (float("nan"), 1.0, 0), (K, float("inf"), 0), (K, 1.0, 2), (K, 1, 0), ("x", 1.0, 0)]
+
+    def outs(rgb, dt):
+        if not isinstance(rgb, torch.Tensor) or rgb.dim() != 4:
+            return [empty(dt, 3, 20, 33)]
+        B, n, m = rgb.shape[0], max(0, rgb.shape[2] - 4), max(0, rgb.shape[3] - 4)
+        return [empty(dt, B, n, m), empty(dt, B, n + 2, m + 3)[:, 1:n + 1, 2:m + 2], empty(dt, B, n, m + 1), empty(torch.int32, B, n, m),
+                torch.full((B, n, m), 7, dtype=dt), empty(dt, B, m, n).transpose(1, 2), None]
+
+    def calls():
+        for rgb in images:
+            for k, scale, window in scalars:
+                for out in outs(rgb, torch.float32):
+                    if (scale, window) == (1.0, 0):
+                        yield "dense", out, lambda: gpu.harris_coarsity(rgb, k, out=out)
+                        yield "u8", out, lambda: gpu.harris_coarsity_u8(rgb, k, out=out)
+                    yield "ex", out, lambda: gpu.harris_coarsity_ex(rgb, k, scale, window, out=out)
+                    yield "pitched", out, lambda: gpu.harris_coarsity_pitched(rgb, out, k, scale, window)
+                for dt in (torch.float16, torch.bfloat16, torch.float32):
+                    for out in outs(rgb, dt)[:4]:
+                        yield "typed", out, lambda: gpu.harris_coarsity_typed(rgb, out, k, scale, window)
+                for out in outs(rgb, torch.uint8)[:4]:
+                    yield "codes", out, lambda: gpu.harris_coarsity_quantized(rgb, out, 1.5, 90.0, k, scale, window)
+                    yield "codes of whole scale", out, lambda: gpu.harris_coarsity_quantized(rgb, out, 2, 90, k, scale, window)
+
+    def outcome(name, out, call):
+        if isinstance(out, torch.Tensor):
+            out.fill_(7)
+        try:
+            got = call()
+        except Exception as e:                               # the type and text of what is refused
+            return type(e), str(e)
+        torch.cuda.synchronize()
+        assert out is None or got is out
+        return type(got), got.dtype, tuple(got.shape), tuple(got.stride()), got.requires_grad, bytes(got.detach().contiguous().reshape(-1).view(torch.uint8).cpu().numpy())
+
+    native, count = binding._native, 0
+    for name, out, call in calls():
+        monkeypatch.setattr(binding, "_native", native)
+        with_native = outcome(name, out, call)
+        monkeypatch.setattr(binding, "_native", None)
+        assert with_native == outcome(name, out, call), (name, with_native)
+        count += 1
+    say("compared %d calls" % count)
+    # Taken: plain calls.  Declined: a mode that watches torch functions, a wrapped tensor.
+    out = empty(torch.float32, 3, 20, 33)
+    assert native.dense(f32, out, K, 1.0, 0, 0) is out and native.dense(u8, None, K, 1.0, 0, -1) is not None
+    assert native.views(view8, out, K, 1.0, 0, 0, 1.0, 0.0) is out
+    with Mode():
+        assert native.dense(f32, out, K, 1.0, 0, 0) is None
+    def wrapped(x):
+        assert native.dense(x, None, K, 1.0, 0, 0) is None
+        return x.sum()
+    torch.func.vmap(wrapped)(f32[None])
+    torch.func.grad(wrapped)(f32)
+
+
 # ---------------------------------------------------------------- unfused kernel groupings (baselines)
 
 @pytest.mark.parametrize("grouping", [1, 2, 3, 4])
