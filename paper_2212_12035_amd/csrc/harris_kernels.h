@@ -191,6 +191,8 @@ __device__ __forceinline__ void load_row_shifted(RawRow<uint8_t, 4>& r, uint32_t
     }
 }
 
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
 __device__ __forceinline__ void realign_row(RawRow<uint8_t, 4>& r, const uint32_t (&shift)[3]) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
@@ -627,8 +629,13 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // wait for it and then be computed by all at once (1536x2560: 12.2 against 12.4 us); with many
 // small tiles the barrier is faster (720x1280: 6.1 against 6.4 us).
 //
-// SHIFTED (8-bit input, four pixels per lane): rows start on any byte and are loaded as the
-// aligned 32-bit words that hold them (load_row_shifted, realign_row).
+// SHIFTED (8-bit input, four pixels per lane): rows start on any byte.  Launches that the vector ALUs or latency bound, WORDS
+// and SMALL in tiles of four rows per wavefront and one tile per CU, load their pixels where they are (BYTES): the lane shifts and byte-aligns of
+// whole words are 24 of some 430 vector operations per wavefront, and the loads, all of one policy, stand in one
+// straight line.  16 images of 768x1366 to codes 21.7 us (23.3 with words), 9 of 2442x1862 52.1 (57.1), 8 of 1079x1919 to
+// binary16 21.9 (23.8), 1079x1919 to float32 5.67 (5.97), 19 of 300x401 6.50 (6.89).  Large launches to float32 are bound
+// by memory and load aligned words (load_row_shifted, realign_row), non-temporal but for the rows that tiles share:
+// 8191x8191 88 us (92), 4 of 2159x3839 45.7 (48.6).
 //
 // WORDS (16-bit results or 8-bit codes, four pixels per lane): result rows start on any byte of their
 // type and are stored as the aligned words that hold them (pack_row_shifted).  Instances of their
@@ -726,12 +733,24 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // right than otherwise, which supplies the last lane's missing bytes); the descriptor's
     // size stops the lanes right of the row.
     [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_pitch + 8 + reach ? col : 0x80000000u;
+    constexpr bool BYTES = SHIFTED && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
+    // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does; a lane whose columns end
+    // behind the row the row's last four, shifted down by `drop`.  No load leaves the row; rows below the image
+    // load its last one, and nobody uses what comes of them.
+    [[maybe_unused]] const unsigned last_col = (unsigned)p.W - 4u, byte_voff = min(col, last_col);
+    [[maybe_unused]] const unsigned drop = col > last_col ? 8u * ((col - last_col) & 3u) : 0u;
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         const int r = y_wave + t;
         const In* row_in = img_in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch;
         const uint32_t row_bytes = r < p.H ? in_row_bytes : 0u;
-        if constexpr (SHIFTED) {
+        if constexpr (BYTES) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const u32_any* at = reinterpret_cast<const u32_any*>(row_in + c * plane + byte_voff);
+                raw[t].w[c][0] = LAUX == kAuxNonTemporal ? __builtin_nontemporal_load(at) : *at;
+            }
+        } else if constexpr (SHIFTED) {
             if constexpr (LAUX == kAuxKeepShared) {
                 const bool shared = (t < 4 && wave == 0) || (t >= RW - 4 && wave + 1 == n_waves);
                 if (shared) load_row_shifted<kAuxDefault>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
@@ -799,7 +818,12 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
 
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
-        if constexpr (SHIFTED) realign_row(raw[t], shift[t]);
+        if constexpr (BYTES) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) raw[t].w[c][0] >>= drop;
+        } else if constexpr (SHIFTED) {
+            realign_row(raw[t], shift[t]);
+        }
         gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
         if constexpr (HAND_SOBEL) {
             if constexpr (t < 2) publish(t, gc);

@@ -28,8 +28,6 @@
 
 namespace {
 
-typedef uint32_t u32_any __attribute__((aligned(1)));
-
 // One row of the three planes of a lane's image.  rows[c] is the row's first element in the group's
 // first image, `bytes` what lies from there to the row's end in the group's last image; voff the
 // lane's offset (patch_lane).  Loads beyond the end give zeros.  A float32 lane that straddles the end of its
