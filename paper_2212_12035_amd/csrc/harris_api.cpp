@@ -101,19 +101,34 @@ constexpr long long kPatchPixels = 1LL << 18;
 
 // Wavefronts of a workgroup and turns of a launch (dealt_tile in harris_launch.h), measured together.  Four wavefronts, 12
 // result rows, by turns of some 16 workgroups, against eight in one stretch per XCD: 2048 images of 64x64 float32 24.9 us (29.4),
-// 8192 of 32x32 25.8 (30.9), 200 of 149x49 8.2 (10.0), 5000 of 24x100 32.7 (38.1), uint8 663 of 48x64 5.67 (6.38), 3713 of 103x25
-// 29.2 (33.1), and over 52 shapes 0.79 to 1.08 of the time, 0.93 on average (input and results not in the last-level cache;
-// 0.95 where they are).  Small workgroups start and end one by one while larger ones wait for room on a CU; what they
-// read twice, four rows in sixteen, comes from L2.  float32 launches of up to 5.5 such workgroups per CU take five where
-// 16 rows a band make fewer bands: 1000 images of 48x48 9.7 us (four: 10.5; eight 9.9), 867 of 77x25 9.5 (10.6), 2932 of 42x25
-// 16.1 (17.1); larger ones not (1521 of 92x34 21.4 / 20.4), nor 8-bit input (1955 of 121x28 15.3 / 15.2).  Launches below some
-// 1.2 million pixels keep eight, one band of up to 28 rows, and one turn: a test of the plans fixes their bands (four
-// would take 0.85 to 1.02 of the time: 71 uint8 images of 91x80 3.9 / 4.3, 311 float32 of 28x88 5.6 / 5.7).
-constexpr long long kPatchSmallPixels = 9LL << 17;
+// 8192 of 32x32 25.8 (30.9), 5000 of 24x100 32.7 (38.1), uint8 663 of 48x64 5.67 (6.38), 3713 of 103x25 29.2 (33.1).  Small
+// workgroups start and end one by one while larger ones wait for room on a CU; what they read twice, four rows in
+// sixteen, comes from L2.  But a launch that the chip holds at once takes as long as its fullest CU, which a band more or less per
+// image moves by a quarter: of four, five and eight wavefronts those are taken that leave the fewest on that CU, four being
+// worth 0.92 and five 1.04 of as many in workgroups of eight, and four wherever they make no more than two workgroups per CU.
+// 460 float32 images of 150x37, 16 wavefronts by fours, 20 by fives, 16 by eights, 11.9 / 14.5 / 12.6 us; 394 of 104x35, 12 / 10 / 8, 9.9 /
+// 8.5 / 8.0; 219 of 97x64, 8 / 10 / 7, 6.5 / 7.3 / 7.0; uint8 1140 of 67x47, 24 / 20 / 21, 10.9 / 8.6 / 8.8; 2526 of 50x33, 24 / 25 / 21, 12.3 / 13.5
+// / 10.2.  From float32 the chip is kept busiest by fours beyond that (1931 of 61x83 31.5 / 33.3 / 34.3); 8-bit launches gain by the
+// same count at any size.  Over 340 shapes of 1.2 to 13 million pixels, each with its images in the last-level cache and not,
+// 0.94 of the time of eight in one stretch per XCD; 24 of 680 times more than 1.02, at most 1.07 (1906 uint8 images of 133x26 in
+// the cache; 0.96 where not).
+// Launches below some 1.2 million pixels keep eight, one band of up to 28 rows, and one turn: a test of the plans fixes
+// their bands (four would take 0.85 to 1.02 of the time: 71 uint8 images of 91x80 3.9 / 4.3, 311 float32 of 28x88 5.6 / 5.7).  From some
+// 1.44 million on a launch has more than a workgroup per CU, as a test of the turns has it (1787 uint8 images of 32x36, 256
+// workgroups of eight, 512 of five: 5.75 / 5.86 us; others 1.00 to 1.05 of the time).
+constexpr long long kPatchSmallPixels = 9LL << 17, kPatchFewPixels = 11LL << 17;
 int patch_waves(int dtype, long long pixels, long long groups, int n) {
     if (pixels < kPatchSmallPixels) return kPatchWaves;
-    const int bands4 = (n + 11) / 12, bands5 = (n + 15) / 16;
-    return dtype == HARRIS_F32 && groups * bands4 <= 1408 && bands5 < bands4 ? 5 : 4;
+    const auto bands = [&](int most) { return (n + 4 * (most - 1) - 1) / (4 * (most - 1)); };      // of at most `most` wavefronts
+    const auto fullest = [&](int most) {                        // wavefronts on the fullest CU
+        const int rows = (n + bands(most) - 1) / bands(most);
+        return (groups * bands(most) + 255) / 256 * ((rows + 3) / 4 + 1);
+    };
+    if (groups * bands(4) <= 512 || (dtype == HARRIS_F32 && groups * bands(4) * 4 > 256 * 32)) return 4;
+    const long long four = 92 * fullest(4), five = 104 * fullest(5), eight = 100 * fullest(kPatchWaves);
+    const bool eights = pixels < kPatchFewPixels || groups * bands(kPatchWaves) > 256;
+    if (eights && eight <= four && eight <= five) return kPatchWaves;
+    return four < five ? 4 : 5;
 }
 unsigned patch_turns(long long pixels, long long blocks) {
     const long long turns = pixels < kPatchSmallPixels ? 1 : (blocks + 64) / 128;
