@@ -111,7 +111,7 @@ constexpr long long kPatchPixels = 1LL << 18;
 // / 10.2.  From float32 the chip is kept busiest by fours beyond that (1931 of 61x83 31.5 / 33.3 / 34.3); 8-bit launches gain by the
 // same count at any size.  Over 340 shapes of 1.2 to 13 million pixels, each with its images in the last-level cache and not,
 // 0.94 of the time of eight in one stretch per XCD; 24 of 680 times more than 1.02, at most 1.07 (1906 uint8 images of 133x26 in
-// the cache; 0.96 where not).
+// the cache; 1.00 where not).
 // Launches below some 1.2 million pixels keep eight, one band of up to 28 rows, and one turn: a test of the plans fixes
 // their bands (four would take 0.85 to 1.02 of the time: 71 uint8 images of 91x80 3.9 / 4.3, 311 float32 of 28x88 5.6 / 5.7).  From some
 // 1.44 million on a launch has more than a workgroup per CU, as a test of the turns has it (1787 uint8 images of 32x36, 256

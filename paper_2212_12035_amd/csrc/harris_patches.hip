@@ -46,7 +46,10 @@ __device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint
 // Compiled as for workgroups of 1024 threads, twice what the planner launches: within the 64 vector registers that
 // eight wavefronts per SIMD leave it needs no more, and the bound of 512 measures slower (673 images of 33x75
 // uint8 5.23 us, 5.15 with 1024; 291 of 123x77 6.58 / 6.51; float32 the same).
-template <typename In, bool BINOM>
+//
+// TURNS: a launch of several turns.  Smaller ones, which one latency bounds, have a workgroup per tile and less to
+// work out before the first load (259 uint8 images of 49x30 4.39 us, dealt as turns are 4.48; 569 float32 of 68x20 4.68 / 4.76).
+template <typename In, bool BINOM, bool TURNS>
 __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris_patch_kernel(const harris_launch::Params p) {
     constexpr int PX = 4, RW = 4;
     constexpr bool F32 = std::is_same<In, float>::value;
@@ -55,12 +58,19 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
     const unsigned lane = threadIdx.x % kWave;
     const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     // At the end of the last turn there may be workgroups without a tile: they go through the last one's motions with
-    // rows below the image, loading and storing nothing.  (A branch here would part the loads of the arguments in
-    // two, one behind the other: 256 images of 64x64 6.77 us, 6.3 without.)
-    unsigned n_blocks = p.n_blocks, chunk = p.chunk;
-    asm volatile("" : "+s"(n_blocks), "+s"(chunk));
-    const unsigned dealt = harris_launch::dealt_tile(blockIdx.x, blockIdx.y, chunk), tile = min(dealt, n_blocks - 1);
-    const int idle = dealt < n_blocks ? 0 : 1 << 30;
+    // rows below the image, storing nothing (and loading nothing from float32; the last row again from 8-bit input).  (A
+    // branch here would part the loads of the arguments in two, one behind the other: 256 images of 64x64 6.77 us, 6.3 without.)
+    unsigned tile;
+    int idle = 0;
+    if constexpr (TURNS) {
+        unsigned n_blocks = p.n_blocks, chunk = p.chunk;
+        asm volatile("" : "+s"(n_blocks), "+s"(chunk));
+        const unsigned dealt = harris_launch::dealt_tile(blockIdx.x, blockIdx.y, chunk);
+        tile = min(dealt, n_blocks - 1);
+        idle = dealt < n_blocks ? 0 : 1 << 30;
+    } else {
+        tile = xcd_contiguous(blockIdx.x, p.n_blocks);
+    }
     const unsigned group = harris_launch::fastdiv(tile, p.by_tiles_per_image);      // of p.images images
     const int band = (int)(tile - group * p.tiles_per_image);
 
@@ -133,18 +143,25 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
 
 }  // namespace
 
+namespace {
+
+template <typename In>
+void enqueue(const harris_launch::Params& p, dim3 block, hipStream_t stream) {
+    const dim3 one(p.n_blocks), turns(8 * p.chunk, p.turns);
+    if (p.turns == 1 && p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, false>), one, block, p.lds_bytes, stream, p);
+    else if (p.turns == 1) hipLaunchKernelGGL((harris_patch_kernel<In, false, false>), one, block, p.lds_bytes, stream, p);
+    else if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, true>), turns, block, p.lds_bytes, stream, p);
+    else hipLaunchKernelGGL((harris_patch_kernel<In, false, true>), turns, block, p.lds_bytes, stream, p);
+}
+
+}  // namespace
+
 namespace harris_launch {
 
 int launch_patches(const Params& p, int dtype, unsigned block, void* stream_) {
-    const dim3 grid(8 * p.chunk, p.turns);
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    if (dtype == HARRIS_U8) {
-        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<uint8_t, true>), grid, dim3(block), p.lds_bytes, stream, p);
-        else hipLaunchKernelGGL((harris_patch_kernel<uint8_t, false>), grid, dim3(block), p.lds_bytes, stream, p);
-    } else {
-        if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<float, true>), grid, dim3(block), p.lds_bytes, stream, p);
-        else hipLaunchKernelGGL((harris_patch_kernel<float, false>), grid, dim3(block), p.lds_bytes, stream, p);
-    }
+    if (dtype == HARRIS_U8) enqueue<uint8_t>(p, dim3(block), stream);
+    else enqueue<float>(p, dim3(block), stream);
     return (int)hipGetLastError();
 }
 
