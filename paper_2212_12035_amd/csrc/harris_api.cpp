@@ -196,16 +196,31 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
 //     tiles on a CU.  Shorter runs have more bands at their ends, whose shared rows another L2 has: 2832x4256 (18 tiles
 //     a band) one turn 33.0 us, 7 bands 32.1, 4 bands 32.6, 2 bands 33.4; 2 images of 2160x3840 44.5 / 8 bands 42.5 / 2
 //     bands 44.9; 2400x8000 (34 a band) 52.5 / 4 bands 50.1 / 8 bands 53.3.
+//   - One float32 image to float32 beyond 128 MB, 3 tiles on a CU and so 96 on an XCD, is particular where a band has many tiles: runs
+//     of 130 to 150 tiles are fast, of 152 to 178 and of 116 to 126 slow.  Where no number of turns gives the former, up to 101 tiles.
+//     4200x4200 one turn 46.1 us, runs of 119 tiles 47.0, of 148 45.8; 3456x5184 47.0 / 119 48.8 / 149 46.5; 4608x4608 55.8 / 120 56.6 /
+//     144 54.4; 3500x4000 38.5 / 156 39.3 / 94 37.9.  (Two images of 2531x3743 rather take 119, 50.8 us, than 149, 53.6.)
 //   - At least 2 bands and 16 tiles for larger launches, with 2 tiles on a CU, and for 8-bit input: 64 images of 1080x1920
-//     float32 (8 a band) one turn 353 us, 2 bands 334, 6 bands 338, 16 bands 351; 6000x8000 127.2, 2 bands 124.9, 1 band 128; 64 images
-//     of 1080x1920 uint8 176.4, 2 bands 159.5, 16 bands 166; 2832x4256 uint8 19.5, 2 bands 18.9, 10 bands 19.4.
-// Over 45 shapes no launch got slower by more than its spread but 5000x3500 float32 (45.8 and 46.2).
-unsigned chunk_turns(int dtype, int out_dtype, long long footprint, long long n_strips, long long n_tiles) {
+//     float32 (8 a band) one turn 350 us, 2 bands 340; in graphs one turn 353, 2 bands 334, 6 bands 338, 16 bands 351; 6000x8000
+//     127.2, 2 bands 124.9, 1 band 128; 64 images of 1080x1920 uint8 176.4, 2 bands 159.5, 16 bands 166; 2832x4256 uint8 19.5, 2 bands 18.9, 10 bands 19.4.
+//   - Not less than 96 tiles from 8-bit input to float32 up to 128 MB where a band has 16 or more: 4096x4096 (18 a band) one
+//     turn 24.6 us, 2 bands 25.4, 96 tiles 24.6; 2 images of 2048x4096 24.6 / 25.2 / 24.7; over 36 shapes 0.97 of the time of one turn, at
+//     most 1.005 (2 bands: 0.97, at most 1.04).  Narrower images are the same or up to 2 % slower with them.
+// Over 166 shapes no launch got slower than in one turn by more than 1.7 %.
+unsigned chunk_turns(int dtype, int out_dtype, int batch, long long footprint, long long n_strips, long long n_tiles) {
     if (n_tiles <= 2048) return 1;
-    const bool few = dtype == HARRIS_F32 && footprint <= ((out_dtype == HARRIS_OUT_F32 ? 400LL : 256LL) << 20);
+    const auto turns_of = [&](long long chunk) { return (n_tiles + 4 * chunk) / (8 * chunk); };
+    const bool f32 = dtype == HARRIS_F32, to_f32 = out_dtype == HARRIS_OUT_F32, small = footprint <= (128LL << 20);
+    const bool few = f32 && footprint <= ((to_f32 ? 400LL : 256LL) << 20);
     const long long bands = few ? (136 >= 8 * n_strips ? 8 : 136 / n_strips) : (16 + n_strips - 1) / n_strips;
-    const long long chunk = (bands < 2 ? 2 : bands) * n_strips;
-    const long long turns = (n_tiles + 4 * chunk) / (8 * chunk);
+    long long chunk = (bands < 2 ? 2 : bands) * n_strips;
+    if (!f32 && to_f32 && small && n_strips >= 16 && chunk < 96) chunk = 96;
+    long long turns = turns_of(chunk);
+    if (few && to_f32 && !small && batch == 1 && n_strips >= 14) {
+        turns = turns_of(140);
+        const long long each = (n_tiles + 8 * turns - 1) / (8 * turns);
+        if (each < 130 || each > 150) turns = (n_tiles + 8 * 101 - 1) / (8 * 101);
+    }
     return (unsigned)(turns < 1 ? 1 : turns > 65535 ? 65535 : turns);
 }
 
@@ -468,7 +483,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->blocks_per_image = (unsigned)blocks_per_image;
         params->n_blocks = (unsigned)blocks;
         params->waves_per_block = (unsigned)t.waves_per_block;
-        params->turns = chunk_turns(dtype, out_dtype, footprint, n_strips, n_tiles);
+        params->turns = chunk_turns(dtype, out_dtype, batch, footprint, n_strips, n_tiles);
         params->chunk = (unsigned)((n_tiles + 8LL * params->turns - 1) / (8LL * params->turns));
         // Store policy of many-tile launches (the figures stand with kAuxManyStore): written through are
         // float32 results where a row has more strips than ends, from float32 input beyond 400 MB more than six, and
