@@ -876,8 +876,11 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
         // HAND_SOBEL: two rows are read ahead of their use where a launch's tiles are all resident at once and a CU has
         // few wavefronts to hide the reads (AHEAD).  Others hide them, and are slower with the rows in registers
         // (13 images of 277x448 to float32 4.81 us ahead, 5.00 not; 600x800 3.65 / 3.73; but 8 of 1080x1920 to binary16
-        // 21.3 / 19.7, 4000x3000 to codes 15.0 / 14.3, 9 of 2442x1862 to codes on any byte 54.3 / 51.8).
-        constexpr bool AHEAD = HAND_SOBEL && !WORDS && (LAUX == kAuxNonTemporal || SMALL);
+        // 21.3 / 19.7, 4000x3000 to codes 15.0 / 14.3, 9 of 2442x1862 to codes on any byte 54.3 / 51.8).  With the binomial
+        // window that takes 67 vector registers, which leave seven of eight wavefronts: SMALL launches do without
+        // (1080x1920 5.10 us, ahead 5.31; 13 of 277x448 5.00 / 5.19; 1200x1600 5.06 / 5.27); one tile per CU does not mind
+        // (480x640 3.42 us ahead, 3.46 not).
+        constexpr bool AHEAD = HAND_SOBEL && !WORDS && (LAUX == kAuxNonTemporal || (SMALL && !BINOM));
         [[maybe_unused]] float sobel[2][2][PX];
         [[maybe_unused]] float second[PX];
         if constexpr (AHEAD) {

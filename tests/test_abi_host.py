@@ -67,6 +67,17 @@ def test_kernels_use_no_scratch_memory(pkg):
         assert used[b".sgpr_spill_count"] == 0 or (b"harris_tile_kernel" in name and b"ELb1EEEv" in name), (name, used)
 
 
+def test_8_bit_tiles_of_launches_resident_at_once_leave_room_for_eight_wavefronts(pkg):
+    # 8-bit input, four pixels, four rows, shared rows kept: eight wavefronts per SIMD have 64 vector registers each.
+    data = open(pkg.library_path(), "rb").read()
+    counts = {}
+    for m in re.finditer(rb"(_ZN?[A-Za-z0-9_]*harris_tile_kernelIhLi4ELi4ELin1E[A-Za-z0-9_]*?6ParamsE)(?=[\x80-\xff])", data, re.S):
+        at = data.find(b".vgpr_count", m.end(), data.find(b".wavefront_size", m.end()) + 64)
+        if at >= 0:
+            counts[m.group(1)] = data[at + len(b".vgpr_count")]      # one byte: a count below 128
+    assert len(counts) >= 8 and max(counts.values()) <= 64, counts
+
+
 def test_plan_picks_widest_vector_path(pkg):
     shape, blocks = pkg.harris_plan(pkg.HARRIS_F32, 1, 1536, 2560)
     assert shape["px"] == 4 and blocks > 128 and shape["rows"] >= 4
