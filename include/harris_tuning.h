@@ -23,15 +23,15 @@ extern "C" {
  *             one strip from top to bottom (or bottom to top), with `prefetch` input rows
  *             in flight.  HARRIS_SCHEDULE_TILES: a workgroup of `waves_per_block`
  *             wavefronts loads a tile of waves_per_block * rows input rows at once and
- *             hands the gray rows that two wavefronts share through LDS.  0 = chosen
- *             from the size.
+ *             hands the rows that two wavefronts share through LDS.  0 = chosen from the
+ *             size.
  *   px        pixels per lane along x: 1, 2 or 4.  A lane's loads and stores
  *             must be naturally aligned in every row (px divides W, pointers and pitches are
  *             multiples of the access size), else HARRIS_ERR_ARG; except that TILES with px = 4
  *             takes any width and any row alignment the element type allows, as long as result
  *             rows start on 4-byte boundaries, are not 8-bit codes and, if 16-bit, have an even
  *             number of columns (vector accesses on 4-byte boundaries; 8-bit input rows on any
- *             byte are loaded as aligned words and shifted), and with HARRIS_TUNE_WORD_STORES other
+ *             byte are loaded as aligned words and shifted or where they are), and with HARRIS_TUNE_WORD_STORES other
  *             16-bit and 8-bit result rows too.  0 = 4 where that holds, and for large problems
  *             with such other result rows if no field asks for a shape (plans then report
  *             the bit); else the widest of 2, 1 that fits.
@@ -43,13 +43,14 @@ extern "C" {
  *   waves_per_block  BANDS: 1, 2 or 4 (2: two bands of a strip that start on shared rows;
  *             4: the same for two adjacent strips).  TILES: 2 to 16.  0 = default.
  *   flags     HARRIS_TUNE_* bits.
- *   lds_kb    TILES only: kilobytes of LDS to reserve per workgroup, 0 to 64.  A tile needs 4 KB
- *             per wavefront (px = 4; from 8-bit input up to 6 KB, taken where the reservation
- *             reported is smaller); reserving more bounds the workgroups resident on a CU
- *             (160 KB of LDS per CU: 64 -> 2, 48 -> 3, 36 -> 4, 28 -> 5).  Many-tile float32
- *             launches are faster with 10 to 16 wavefronts per CU in flight than with the 28 to
- *             32 that the registers would allow.  0 = chosen from the size (plans report the
- *             reservation in force, at least the tile's own need).
+ *   lds_kb    TILES only: kilobytes of LDS to reserve per workgroup, 0 to 64.  Reserving more than
+ *             a tile needs bounds the workgroups resident on a CU (160 KB of LDS per CU: 64 -> 2,
+ *             48 -> 3, 36 -> 4, 28 -> 5).  Many-tile float32 launches are faster with 10 to 16
+ *             wavefronts per CU in flight than with the 28 to 32 that the registers would allow.
+ *             0 = chosen from the size.  Plans report what is reserved, at least px KB for each
+ *             wavefront.  From 8-bit input with px = 4 a tile of w wavefronts needs 1 + 6 (w - 1)
+ *             KB (4 wavefronts 19, 16 wavefronts 91): a launch takes that where it is more than
+ *             what is reserved, and plans do not report it.
  */
 struct harris_tuning {
     int schedule;

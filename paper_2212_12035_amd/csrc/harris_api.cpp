@@ -408,7 +408,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         if (dtype == HARRIS_U8 && (t.flags & HARRIS_TUNE_FLAG_HANDOFF)) return HARRIS_ERR_ARG;   // ready flags: float32 input only
         if (t.prefetch != 0) return HARRIS_ERR_ARG;
         tile_rows = (long long)t.rows * t.waves_per_block - 4;
-        // The reservation in force: at least the four gray rows each wavefront publishes.
+        // The reservation: at least four rows for each wavefront.  From 8-bit input a tile with 16-byte lanes takes up to
+        // six (tile_lds_bytes), which the launch sees to.
         const int need_kb = (int)(((long long)t.waves_per_block * 4 * 64 * t.px * 4 + 1023) / 1024);
         if (t.lds_kb < need_kb) t.lds_kb = need_kb;
     } else {
@@ -485,6 +486,10 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->waves_per_block = (unsigned)t.waves_per_block;
         params->turns = chunk_turns(dtype, out_dtype, batch, footprint, n_strips, n_tiles);
         params->chunk = (unsigned)((n_tiles + 8LL * params->turns - 1) / (8LL * params->turns));
+        // Wavefronts that a CU holds at once (64 vector registers each), or tiles that its 160 KB of LDS hold.
+        const unsigned lds = harris_launch::tile_lds_bytes(dtype == HARRIS_U8, t.px, (unsigned)t.waves_per_block), reserved = (unsigned)t.lds_kb * 1024u;
+        const long long by_lds = (160 << 10) / (lds > reserved ? lds : reserved), by_waves = 32 / t.waves_per_block;
+        params->resident = t.schedule == HARRIS_SCHEDULE_TILES && n_tiles <= 256 * (by_lds < by_waves ? by_lds : by_waves);
         // Store policy of many-tile launches (the figures stand with kAuxManyStore): written through are
         // float32 results where a row has more strips than ends, from float32 input beyond 400 MB more than six, and
         // their borders lie on 64-byte boundaries, and small launches with two strips or more, up to 16 MB from 8-bit input and 13 from

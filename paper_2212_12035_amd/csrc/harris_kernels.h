@@ -650,10 +650,8 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // before), 9 of 2442x1862 to codes 51.8 (54.1), 10 of 480x640 to float32 6.80 (6.92), 600x800 3.71 (3.82); 8192x8192 to
 // float32 is bound by the memory's view of its tiles (83 us, 84 without any arithmetic) and takes the same time.  At 4 x 4
 // the 19 KB leave eight workgroups on a CU.  float32 input is bound by memory and keeps the gray rows.
-template <typename In, int PX>
-__host__ __device__ constexpr bool hands_sobel() { return std::is_same<In, uint8_t>::value && PX == 4; }
-
-// SMALL (8-bit input, shared rows kept): a launch whose tiles are all resident at once.
+//
+// SMALL (8-bit input, shared rows kept): a launch whose tiles are all resident at once (Params::resident).
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool SMALL = false, bool WORDS = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
@@ -662,7 +660,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     constexpr bool DIFF = std::is_same<In, float>::value && !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF)));
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
     static_assert(!WORDS || PX == 4, "result rows as aligned words: four pixels per lane");
-    constexpr bool HAND_SOBEL = hands_sobel<In, PX>();
+    constexpr bool HAND_SOBEL = harris_launch::hands_sobel(std::is_same<In, uint8_t>::value, PX);
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]; HAND_SOBEL: [1 + (NW - 1) * 6][64][PX]
     __shared__ unsigned ready[16];                              // HANDOFF: wavefront w has published its four rows
 

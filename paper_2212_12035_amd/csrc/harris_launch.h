@@ -78,16 +78,25 @@ struct Params {
     float q_scale, q_offset;   // 8-bit results: code = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)
     int binomial;           // 1: window [1 2 1; 2 4 2; 1 2 1], 0: unweighted 3x3 sum
     unsigned lds_bytes;     // TILES: dynamic LDS per workgroup (the tile's rows, or more to bound the resident workgroups)
-    int in_shifted;         // 1: 8-bit rows that start on any byte, loaded as aligned words and shifted (tile kernel, px 4)
+    int in_shifted;         // 1: 8-bit rows that start on any byte, loaded as aligned words and shifted or where they are (tile kernel, px 4)
     unsigned n_bands;       // bands (BANDS) or tiles down the image (TILES)
     unsigned blocks_x;      // BANDS: workgroups across a row of bands
     unsigned blocks_per_image;  // BANDS: workgroups per image
     // HARRIS_TUNE_PACKED_IMAGES: lanes of an image, 65536 / that rounded up, images of a wavefront, images of the call.
     // tiles_per_image is then the number of bands down the images, rows_per_band their height.
     unsigned image_lanes, image_lanes_inverse, images, batch;
-    // TILES with shared rows kept: tiles that an XCD takes in a row, and how often.
+    // TILES with shared rows kept, and narrow images: tiles that an XCD takes in a row, and how often.
     unsigned chunk, turns;
+    int resident;           // TILES: 1: the chip holds all tiles of the launch at once
 };
+
+// TILES: whether a wavefront hands the one above it Sobel responses (harris_tile_kernel says when), and the bytes of LDS
+// that the wavefronts of a workgroup then need: six rows of all but the first, which has a row to write to, or
+// four gray rows each.
+HARRIS_HOST_DEVICE constexpr bool hands_sobel(bool from_8_bit, int px) { return from_8_bit && px == 4; }
+HARRIS_HOST_DEVICE constexpr unsigned tile_lds_bytes(bool from_8_bit, int px, unsigned waves) {
+    return (hands_sobel(from_8_bit, px) ? 1u + (waves - 1u) * 6u : waves * 4u) * 64u * (unsigned)px * 4u;
+}
 
 // HARRIS_TUNE_PACKED_IMAGES: most wavefronts of a workgroup, each with four rows; the last one only hands its
 // rows on.

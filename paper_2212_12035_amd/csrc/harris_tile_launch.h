@@ -12,7 +12,7 @@ namespace {
 template <typename In, int PX, int RW, int LAUX, bool HANDOFF, bool SHIFTED, bool WORDS>
 hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
     if constexpr (std::is_same<In, uint8_t>::value && PX == 4 && RW == 4 && LAUX == kAuxKeepShared && !WORDS) {
-        if (p.turns == 1) {
+        if (p.resident) {
             if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, p);
             else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, p);
             return hipGetLastError();
@@ -28,10 +28,9 @@ hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 bl
 template <typename In, int PX, int RW, bool WORDS>
 hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, hipStream_t stream) {
     constexpr bool U8 = std::is_same<In, uint8_t>::value;
-    // The four gray rows each wavefront publishes; the planner may reserve more to bound the
-    // number of workgroups resident on a CU.
-    const size_t n_waves = block.x / kWave;
-    const size_t lds_needed = (hands_sobel<In, PX>() ? 1 + (n_waves - 1) * 6 : n_waves * 4) * kWave * PX * sizeof(float);
+    // The rows that the wavefronts publish; the planner may reserve more to bound the number of workgroups resident
+    // on a CU.
+    const size_t lds_needed = harris_launch::tile_lds_bytes(U8, PX, block.x / kWave);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
     // Many tiles with shared rows kept: dealt to the XCDs by turns (dealt_tile).
     if ((p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) && !(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) grid = dim3(8 * p.chunk, p.turns);

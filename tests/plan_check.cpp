@@ -168,6 +168,23 @@ int main() {
             return 1;
         }
     }
+    // Whether the chip holds all tiles of a launch at once: {images, height, width, wavefronts a workgroup or 0, KB reserved, it does}.
+    static const int at_once[][6] = {{1, 1080, 1920, 0, 0, 1}, {1, 2457, 2400, 0, 0, 1}, {1, 2700, 3300, 0, 0, 0}, {1, 12, 600000, 0, 0, 0}, {8, 1079, 1919, 0, 0, 0},
+                                     {1, 1500, 1900, 16, 0, 1}, {1, 8000, 1900, 16, 0, 0}, {1, 1080, 1920, 4, 48, 1}, {1, 1200, 1920, 4, 48, 0}, {1, 700, 960, 8, 0, 1}};
+    for (const auto& c : at_once) {
+        const harris_tuning t = {HARRIS_SCHEDULE_TILES, 4, 4, 0, c[3], 0u, c[4]};
+        if (harris_coarsity_typed((const void*)0x100000, HARRIS_U8, c[0], c[1], c[2], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, HARRIS_OUT_F32, c[3] ? &t : nullptr, nullptr) != HARRIS_OK ||
+            harris_launch::last.resident != c[5]) {
+            std::printf("%d images of %dx%d, %d wavefronts, %d KB: %u tiles resident at once: %d\n", c[0], c[1], c[2], c[3], c[4], harris_launch::last.n_blocks, harris_launch::last.resident);
+            return 1;
+        }
+    }
+    // What a tile needs of LDS: rows of 64 lanes.
+    for (unsigned w = 2; w <= 16; ++w)
+        if (harris_launch::tile_lds_bytes(true, 4, w) != (1 + 6 * (w - 1)) * 1024 || harris_launch::tile_lds_bytes(false, 4, w) != w * 4096 || harris_launch::tile_lds_bytes(true, 2, w) != w * 2048) {
+            std::printf("LDS of %u wavefronts\n", w);
+            return 1;
+        }
     // Groupings: four pixels of two rows per thread only for images that give a row of threads work.
     for (const auto& c : {std::vector<int>{500, 40, 40}, {20000, 8, 8}, {3, 300000, 8}, {16, 7812, 64}, {1, 600, 800}})
         if (harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("wide groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }
