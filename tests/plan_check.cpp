@@ -169,7 +169,7 @@ int main() {
         }
     }
     // Whether the chip holds all tiles of a launch at once: {images, height, width, wavefronts a workgroup or 0, KB reserved, it does}.
-    static const int at_once[][6] = {{1, 1080, 1920, 0, 0, 1}, {1, 2457, 2400, 0, 0, 1}, {1, 2700, 3300, 0, 0, 0}, {1, 12, 600000, 0, 0, 0}, {8, 1079, 1919, 0, 0, 0},
+    static const int at_once[][6] = {{1, 1080, 1920, 0, 0, 1}, {1, 2457, 2400, 0, 0, 1}, {2, 2160, 3840, 0, 0, 0}, {1, 12, 600000, 0, 0, 0}, {8, 1079, 1919, 0, 0, 0},
                                      {1, 1500, 1900, 16, 0, 1}, {1, 8000, 1900, 16, 0, 0}, {1, 1080, 1920, 4, 48, 1}, {1, 1200, 1920, 4, 48, 0}, {1, 700, 960, 8, 0, 1}};
     for (const auto& c : at_once) {
         const harris_tuning t = {HARRIS_SCHEDULE_TILES, 4, 4, 0, c[3], 0u, c[4]};
