@@ -119,7 +119,7 @@ def _bind_native(lib):
     except (ImportError, AttributeError):
         return
     address = lambda function: ctypes.cast(function, ctypes.c_void_p).value
-    _harris_call.bind(address(lib.harris_coarsity_typed), address(lib.harris_coarsity_quantized), current_device, current_stream)
+    _harris_call.bind(address(lib.harris_coarsity_typed), address(lib.harris_coarsity_quantized), current_device, current_stream, _check)
     _native = _harris_call
 
 

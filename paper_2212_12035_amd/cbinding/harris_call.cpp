@@ -5,8 +5,9 @@
 //
 // Every function returns None, with nothing enqueued, for a call that is not plain: an argument of another type, a
 // check that fails, tensor subclasses, wrapped tensors and modes that watch torch functions, a device that is not the
-// current one, a status of the library other than success.  The caller then goes through the Python code, which
-// handles or refuses it.  No errors are raised here.
+// current one.  The caller then goes through the Python code, which handles or refuses it.  Once the library has been
+// called the call is not made again: a status other than success, which may come from a launch that was enqueued all
+// the same, is raised as the Python code raises it.  No other errors are raised here.
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/ATen.h>
 #include <ATen/PythonTorchFunctionTLS.h>
@@ -21,10 +22,11 @@ namespace {
 typedef int (*typed_fn)(const void*, int, int, int, int, const harris_layout*, float, float, int, void*, int, const harris_tuning*, void*);
 typedef int (*quantized_fn)(const void*, int, int, int, int, const harris_layout*, float, float, int, float, float, uint8_t*, const harris_tuning*, void*);
 
-// Set by bind(): the library's functions, and torch's for the current device and its current stream's handle.
+// Set by bind(): the library's functions, torch's for the current device and its current stream's handle, and the
+// Python code's that raises the error of a status.
 typed_fn call_typed = nullptr;
 quantized_fn call_quantized = nullptr;
-PyObject *get_device = nullptr, *get_stream = nullptr;
+PyObject *get_device = nullptr, *get_stream = nullptr, *raise_status = nullptr;
 
 struct Call {
     const at::Tensor *rgb, *out;
@@ -92,18 +94,20 @@ bool strided(Call& c) {
     return true;
 }
 
-// Enqueues the call on the current stream of the tensors' device, which has to be the current one.
-bool enqueue(const Call& c) {
+// Enqueues the call on the current stream of the tensors' device, which has to be the current one.  kDeclined: it has
+// not been made.  kRaised: it has, and failed; the error is set.
+enum Outcome { kDeclined, kDone, kRaised };
+Outcome enqueue(const Call& c) {
     const int index = c.rgb->device().index();
-    if (index_from(PyObject_CallNoArgs(get_device)) != index) return false;
+    if (index_from(PyObject_CallNoArgs(get_device)) != index) return kDeclined;
     PyObject* device = PyLong_FromLong(index);
-    if (device == nullptr) { PyErr_Clear(); return false; }
+    if (device == nullptr) { PyErr_Clear(); return kDeclined; }
     PyObject* stream = PyObject_CallOneArg(get_stream, device);
     Py_DECREF(device);
-    if (stream == nullptr) { PyErr_Clear(); return false; }
+    if (stream == nullptr) { PyErr_Clear(); return kDeclined; }
     void* handle = PyLong_AsVoidPtr(stream);
     Py_DECREF(stream);
-    if (handle == nullptr && PyErr_Occurred()) { PyErr_Clear(); return false; }
+    if (handle == nullptr && PyErr_Occurred()) { PyErr_Clear(); return kDeclined; }
     const void* in = c.rgb->data_ptr();
     void* out = c.out->data_ptr();
     const harris_layout* layout = c.dense ? nullptr : &c.layout;
@@ -114,7 +118,13 @@ bool enqueue(const Call& c) {
     else
         status = call_typed(in, c.dtype, c.batch, c.H, c.W, layout, c.k, c.scale, c.window, out, c.out_dtype, nullptr, handle);
     Py_END_ALLOW_THREADS
-    return status == HARRIS_OK;
+    if (status == HARRIS_OK) return kDone;
+    PyObject* code = PyLong_FromLong(status);
+    if (code == nullptr) return kRaised;
+    Py_XDECREF(PyObject_CallOneArg(raise_status, code));
+    Py_DECREF(code);
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "the library's status was not raised");
+    return kRaised;
 }
 
 bool ready() { return call_typed != nullptr && !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
@@ -138,7 +148,9 @@ PyObject* dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
             c.out = plain_tensor(a[1]);
             if (c.out == nullptr || c.out->scalar_type() != at::kFloat || !result(c) || !c.out->is_contiguous()) Py_RETURN_NONE;
         }
-        if (!enqueue(c)) Py_RETURN_NONE;
+        const Outcome outcome = enqueue(c);
+        if (outcome == kRaised) return nullptr;
+        if (outcome == kDeclined) Py_RETURN_NONE;
         if (a[1] == Py_None) return THPVariable_Wrap(std::move(made));
         Py_INCREF(a[1]);
         return a[1];
@@ -164,7 +176,10 @@ PyObject* views(PyObject*, PyObject* const* a, Py_ssize_t n) {
         else if (kinds == 1 && type == at::kHalf) c.out_dtype = HARRIS_OUT_F16;
         else if (kinds == 1 && type == at::kBFloat16) c.out_dtype = HARRIS_OUT_BF16;
         else Py_RETURN_NONE;
-        if (!strided(c) || !enqueue(c)) Py_RETURN_NONE;
+        if (!strided(c)) Py_RETURN_NONE;
+        const Outcome outcome = enqueue(c);
+        if (outcome == kRaised) return nullptr;
+        if (outcome == kDeclined) Py_RETURN_NONE;
         Py_INCREF(a[1]);
         return a[1];
     } catch (...) {
@@ -173,17 +188,21 @@ PyObject* views(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
 }
 
-// bind(address of harris_coarsity_typed, of harris_coarsity_quantized, current-device function, current-stream function)
+// bind(address of harris_coarsity_typed, of harris_coarsity_quantized, current-device function, current-stream function,
+// function that raises the error of a status)
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
-    if (n != 4) { PyErr_SetString(PyExc_TypeError, "bind takes four arguments"); return nullptr; }
+    if (n != 5) { PyErr_SetString(PyExc_TypeError, "bind takes five arguments"); return nullptr; }
     void *typed = PyLong_AsVoidPtr(a[0]), *quantized = PyLong_AsVoidPtr(a[1]);
     if (PyErr_Occurred()) return nullptr;
     Py_INCREF(a[2]);
     Py_INCREF(a[3]);
+    Py_INCREF(a[4]);
     Py_XDECREF(get_device);
     Py_XDECREF(get_stream);
+    Py_XDECREF(raise_status);
     get_device = a[2];
     get_stream = a[3];
+    raise_status = a[4];
     call_quantized = reinterpret_cast<quantized_fn>(quantized);
     call_typed = reinterpret_cast<typed_fn>(typed);
     Py_RETURN_NONE;

@@ -1243,6 +1243,38 @@ def test_native_marshalling_does_what_the_python_code_does(gpu, monkeypatch):
     torch.func.grad(wrapped)(f32)
 
 
+def test_a_call_that_fails_is_made_once_and_raises(gpu, monkeypatch):
+    # The library's functions are replaced by ones that count and fail: nothing is launched.
+    import ctypes
+    import types
+    import torch
+    from paper_2212_12035_amd import binding
+    real, calls = binding.load_library(), []
+
+    def failing(name):
+        function = getattr(real, name)
+        return ctypes.CFUNCTYPE(ctypes.c_int, *function.argtypes)(lambda *args: calls.append(name) or -4)
+
+    names = [n for n in binding.EXPORTS if n.startswith("harris_coarsity") and "grouped" not in n]
+    fake = types.SimpleNamespace(harris_strerror=real.harris_strerror, **{n: failing(n) for n in names})
+    rgb = torch.zeros(1, 3, 16, 20, dtype=torch.uint8, device="cuda")
+    f32, out, codes = rgb.float(), torch.zeros(1, 12, 16, device="cuda"), torch.zeros(1, 12, 16, dtype=torch.uint8, device="cuda")
+    entries = [lambda: gpu.harris_coarsity(f32, K), lambda: gpu.harris_coarsity_u8(rgb, K, out=out), lambda: gpu.harris_coarsity_ex(f32, K, 1.0, 1),
+               lambda: gpu.harris_coarsity_pitched(rgb, out, K), lambda: gpu.harris_coarsity_typed(f32, out.half(), K),
+               lambda: gpu.harris_coarsity_quantized(rgb, codes, 1.5, 90.0, K)]
+    monkeypatch.setattr(binding, "_lib", fake)
+    try:
+        binding._bind_native(fake)
+        assert binding._native is not None
+        for entry in entries:
+            del calls[:]
+            with pytest.raises(gpu.HarrisError) as e:
+                entry()
+            assert e.value.status == -4 and len(calls) == 1, calls
+    finally:
+        binding._bind_native(real)
+
+
 # ---------------------------------------------------------------- unfused kernel groupings (baselines)
 
 @pytest.mark.parametrize("grouping", [1, 2, 3, 4])
