@@ -129,6 +129,18 @@ Outcome enqueue(const Call& c) {
 
 bool ready() { return call_typed != nullptr && !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
+// A new result for a call.  The interpreter's lock is let go of meanwhile, as torch.empty does: the allocator may have to
+// go to the driver, or to wait for the GPU.
+at::Tensor new_result(const Call& c) {
+    struct Unlocked {
+        PyThreadState* state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }
+    };
+    const auto options = c.rgb->options().dtype(at::kFloat).requires_grad(false);
+    const Unlocked unlocked;
+    return at::empty({c.batch, c.H - 4, c.W - 4}, options);
+}
+
 // dense(rgb, out or None, k, sobel_scale, window, dtype of rgb or -1 for either) -> out or None
 PyObject* dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
     try {
@@ -141,7 +153,7 @@ PyObject* dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
         c.out_dtype = HARRIS_OUT_F32;
         at::Tensor made;
         if (a[1] == Py_None) {
-            made = at::empty({c.batch, c.H - 4, c.W - 4}, c.rgb->options().dtype(at::kFloat).requires_grad(false));
+            made = new_result(c);
             c.out = &made;
             if (!made.has_storage()) Py_RETURN_NONE;
         } else {

@@ -1275,6 +1275,51 @@ def test_a_call_that_fails_is_made_once_and_raises(gpu, monkeypatch):
         binding._bind_native(real)
 
 
+def test_other_threads_run_while_a_result_is_allocated(gpu):
+    # A fresh gigabyte from the driver each time; the function that gives the current device is called right after the
+    # allocation and sees how often another thread has run.  No thread is preempted meanwhile, so that the
+    # other one only runs where the interpreter's lock is let go of.
+    import sys
+    import threading
+    import time
+    import torch
+    from paper_2212_12035_amd import binding
+    real = binding.load_library()
+    rgb = torch.zeros(1, 3, 16004, 16004, dtype=torch.uint8, device="cuda")
+    assert binding._native is not None
+    runs, seen, stop = [0], [], threading.Event()
+
+    def other():
+        while not stop.is_set():
+            runs[0] += 1
+            time.sleep(1e-6)
+
+    def current_device():
+        seen.append(runs[0])
+        return -1                                            # another device: the call is declined, nothing is launched
+
+    functions = [binding.ctypes.cast(f, binding.ctypes.c_void_p).value for f in (real.harris_coarsity_typed, real.harris_coarsity_quantized)]
+    interval, thread = sys.getswitchinterval(), threading.Thread(target=other)
+    torch.cuda.synchronize()
+    thread.start()
+    try:
+        binding._native.bind(*functions, current_device, torch._C._cuda_getCurrentRawStream, binding._check)
+        sys.setswitchinterval(100.0)
+        moved = 0
+        for _ in range(20):
+            torch.cuda.empty_cache()
+            before = runs[0]
+            assert binding._native.dense(rgb, None, K, 1.0, 0, -1) is None
+            moved += seen[-1] != before
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        thread.join()
+        binding._bind_native(real)
+    say("another thread ran during %d of 20 allocations" % moved)
+    assert len(seen) == 20 and moved > 0
+
+
 # ---------------------------------------------------------------- unfused kernel groupings (baselines)
 
 @pytest.mark.parametrize("grouping", [1, 2, 3, 4])
