@@ -108,15 +108,25 @@ def load_library() -> ctypes.CDLL:
 
 
 def _bind_native(lib):
-    """Hands the native marshalling the functions it calls.  It is optional: without it, or with a torch that lacks
-    the function for the current stream's handle, every call takes the Python code."""
+    """Hands the native marshalling the functions it calls.  It is optional: without it, with another torch than it
+    is compiled for, or with one that lacks the function for the current stream's handle, every call takes the
+    Python code.  A module that is missing or of another torch is warned of: calls take some 2 us more."""
     global _native
     _native = None
     try:
         import torch
-        from . import _harris_call
         current_device, current_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
     except (ImportError, AttributeError):
+        return
+    try:
+        from . import _harris_call
+        built_for = _harris_call.torch_version
+    except (ImportError, AttributeError) as e:
+        built_for = str(e)
+    if built_for != torch.__version__:
+        import warnings
+        warnings.warn("calls go through Python: no native marshalling for torch %s (%s); python -m paper_2212_12035_amd.build builds it"
+                      % (torch.__version__, built_for))
         return
     address = lambda function: ctypes.cast(function, ctypes.c_void_p).value
     _harris_call.bind(address(lib.harris_coarsity_typed), address(lib.harris_coarsity_quantized), current_device, current_stream, _check)

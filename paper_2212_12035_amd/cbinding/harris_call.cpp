@@ -228,4 +228,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_harris_call", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__harris_call() { return PyModule_Create(&module); }
+// torch_version: the torch whose headers are compiled in; the binding uses the module with no other.
+PyMODINIT_FUNC PyInit__harris_call() {
+    PyObject* m = PyModule_Create(&module);
+    if (m != nullptr && PyModule_AddStringConstant(m, "torch_version", HARRIS_TORCH_VERSION) != 0) { Py_DECREF(m); return nullptr; }
+    return m;
+}

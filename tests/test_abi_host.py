@@ -36,6 +36,50 @@ def test_every_declared_symbol_is_exported(pkg):
         assert getattr(lib, name) is not None
 
 
+@pytest.mark.parametrize("missing", ["host compiler", "torch", "headers"])
+def test_the_library_builds_without_the_bindings_module(tmp_path, monkeypatch, missing):
+    # hipcc is a script that writes what it is asked for: only what build_library asks for is looked at.
+    from paper_2212_12035_amd import build
+    compiler = tmp_path / "hipcc"
+    compiler.write_text("#!/bin/sh\nwhile [ $# -gt 1 ]; do [ \"$1\" = -o ] && : > \"$2\"; shift; done\n")
+    failing = tmp_path / "c++"
+    failing.write_text("#!/bin/sh\necho no headers\nexit 1\n")
+    for script in (compiler, failing):
+        script.chmod(0o755)
+    monkeypatch.setenv("HIPCC", str(compiler))
+    monkeypatch.setenv("CXX", str(tmp_path / "none") if missing == "host compiler" else str(failing))
+    if missing == "torch":
+        monkeypatch.setitem(sys.modules, "torch", None)
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libharris.so"))
+    monkeypatch.setattr(build, "BUILD_DIR", str(tmp_path / "objects"))
+    monkeypatch.setattr(build, "NATIVE", str(tmp_path / os.path.basename(build.NATIVE)))
+    for stale in (build.NATIVE, str(tmp_path / "_harris_call.so")):      # of another build
+        open(stale, "w").close()
+    with pytest.warns(UserWarning, match="native marshalling is not built"):
+        assert build.build_library() == build.LIB
+    assert os.path.exists(build.LIB)
+    assert [name for name in os.listdir(str(tmp_path)) if name.startswith("_harris_call")] == []
+
+
+def test_the_bindings_module_is_used_with_its_own_torch_alone(pkg, monkeypatch):
+    import types
+    from paper_2212_12035_amd import binding
+    lib, native = binding.load_library(), binding._native
+    assert native is not None                            # the one built for this torch
+    bound = []
+    other = types.SimpleNamespace(torch_version="1.0", bind=lambda *args: bound.append(args))
+    try:
+        for module in (other, types.SimpleNamespace(bind=other.bind)):
+            monkeypatch.setattr(pkg, "_harris_call", module)
+            with pytest.warns(UserWarning, match="no native marshalling for torch"):
+                binding._bind_native(lib)
+            assert binding._native is None and bound == []
+    finally:
+        monkeypatch.undo()
+        binding._bind_native(lib)
+    assert binding._native is native
+
+
 def test_version_and_strerror(pkg):
     assert pkg.harris_version() >= 100
     assert pkg.harris_strerror(0) == "success"
