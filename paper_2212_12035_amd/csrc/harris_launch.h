@@ -160,6 +160,15 @@ inline bool grouped_wide(int batch, int H, int W) { return (long long)batch * H 
 // Workgroups of `each` pixels (or rows) that cover `size` of them; size + each may lie beyond int.
 inline unsigned groups_covering(int size, int each) { return ((unsigned)size + (unsigned)each - 1u) / (unsigned)each; }
 
+// Grid of `blocks` workgroups for an image of a grouping, 8 x chunk by turns (dealt_tile): one turn, in which each XCD
+// takes one run, unless the launch's x dimension would come near the 2^32 threads that a dimension may have (images of
+// few columns and more than 33 million rows).
+struct GroupedGrid { unsigned chunk, turns; };
+inline GroupedGrid grouped_grid(unsigned long long blocks) {
+    const unsigned long long most = 1ull << 23, turns = blocks > most ? (blocks + most - 1) / most : 1;
+    return {(unsigned)((blocks + 8 * turns - 1) / (8 * turns)), (unsigned)turns};
+}
+
 // Enqueue grouping 1, 2 or 3 (see harris_coarsity_grouped).  Returns a harris_status.
 int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k, float sobel_scale, int binomial,
                    int grouping, float* workspace, float* out, void* stream);

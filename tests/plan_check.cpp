@@ -185,6 +185,19 @@ int main() {
             std::printf("LDS of %u wavefronts\n", w);
             return 1;
         }
+    // Grids of the groupings: fewer than 2^32 threads in x, one turn for all but huge launches, every workgroup once.
+    for (unsigned long long blocks : {1ull, 7ull, 8ull, 9ull, 8100ull, (1ull << 23), (1ull << 23) + 1, 17500001ull, (1ull << 29) - 1}) {
+        const harris_launch::GroupedGrid g = harris_launch::grouped_grid(blocks);
+        const unsigned long long grid = 8ull * g.chunk * g.turns;
+        bool good = 8ull * g.chunk * 256 < (1ull << 32) && g.turns >= 1 && g.turns <= 65535 && grid >= blocks && grid - blocks < 8ull * g.turns && (blocks > (1ull << 23) || g.turns == 1);
+        std::vector<unsigned char> dealt(grid < (1ull << 25) ? grid : 0, 0);
+        for (unsigned y = 0; good && !dealt.empty() && y < g.turns; ++y)
+            for (unsigned x = 0; x < 8 * g.chunk; ++x) {
+                const unsigned b = harris_launch::dealt_tile(x, y, g.chunk);
+                if (b >= grid || dealt[b]++ != 0) good = false;
+            }
+        if (!good) { std::printf("%llu workgroups of a grouping: chunks of %u, %u turns\n", blocks, g.chunk, g.turns); return 1; }
+    }
     // Groupings: four pixels of two rows per thread only for images that give a row of threads work.
     for (const auto& c : {std::vector<int>{500, 40, 40}, {20000, 8, 8}, {3, 300000, 8}, {16, 7812, 64}, {1, 600, 800}})
         if (harris_launch::grouped_wide(c[0], c[1], c[2])) { std::printf("wide groupings of %d images of %dx%d\n", c[0], c[1], c[2]); return 1; }

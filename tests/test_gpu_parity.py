@@ -1333,6 +1333,19 @@ def test_kernel_groupings_match_the_oracle(gpu, oracle, grouping):
         check(out.cpu().numpy(), oracle.harris(rgb, k, scale, window))
 
 
+@pytest.mark.parametrize("grouping", [1, 2, 3])
+def test_groupings_of_an_image_with_few_columns_and_very_many_rows(gpu, grouping):
+    # 17.5 million workgroups of 256 threads: more than the 2^32 threads that a grid may have in one dimension.
+    import torch
+    H, W = 70000003, 5
+    say("case grouping %d of 1x3x%dx%d uint8" % (grouping, H, W))
+    rgb = torch.randint(0, 256, (1, 3, H, W), dtype=torch.uint8, device="cuda", generator=torch.Generator("cuda").manual_seed(9))
+    fused = gpu.harris_coarsity_u8(rgb, K)
+    other = gpu.harris_coarsity_grouped(rgb, K, grouping=grouping)
+    bound = 1e-4 * float(fused.abs().max()) + 1e-6
+    assert float((fused - other).abs().max()) <= bound
+
+
 def test_groupings_agree_with_the_fused_kernel_at_full_size(gpu):
     import torch
     rgb = torch.from_numpy(hi.make("noise_f32_1536x2560")).cuda()
