@@ -21,6 +21,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include <mutex>
 
 #include "harris_launch.h"
@@ -43,14 +44,36 @@ constexpr int kTileX = 64, kTileY = 4, kThreads = kTileX * kTileY;      // 64 PX
 // Where a workgroup works.  Grids are 8 x chunk workgroups an image (grouped_grid): the hardware deals them out to the
 // eight XCDs one by one, and each XCD takes one run of neighbours.  The rows that two of its workgroups both read, and
 // most of what the kernel before has just written, are then behind the same L2; with two-dimensional grids dealt out one
-// by one the three groupings of 1600x2400 took 151 us, now 136, 1080x1920 97.7 / 93.4, 480x640 41.6 / 37.7, 4
-// images of 1080x1920 289 / 272.  Workgroups beyond the last have nothing to do.
+// by one the three groupings of 1600x2400 took 151 us, now 138, 1080x1920 98.2 / 90.4, 480x640 41.5 / 37.6, 4
+// images of 1080x1920 289 / 270.  Workgroups beyond the last have nothing to do.
+//
+// FOLD: batches of small images, whose runs would have more workgroups without work than with it: an XCD takes a
+// run of images instead, and a workgroup divides for its own (one by one / a run of each image / a run of images: 500
+// images of 40x40 67.0 / 83.8 / 65.3 us, 20000 of 8x8 189 / 978 / 168, 200 of 96x96 97 / 115 / 98, 2000 of 24x24 uint8 101 / 140 / 96; but
+// 480x640, which waits for the division, 41.5 / 37.6 / 40.5, 4 of 1080x1920 289 / 270 / 278).
+template <bool FOLD>
 struct Blocks {
     unsigned chunk;                         // workgroups of an XCD
     unsigned across;                        // workgroups across an image (3x3 stages)
     harris_launch::FastDiv by_across;
 };
-__device__ __forceinline__ unsigned block_of(const Blocks& b) { return harris_launch::dealt_tile(blockIdx.x, blockIdx.y, b.chunk); }
+template <>
+struct Blocks<true> : Blocks<false> {
+    unsigned total, per_image;              // workgroups that have something to do, and of an image
+    harris_launch::FastDiv by_image;
+};
+// Image and workgroup of it, or false.
+template <bool FOLD>
+__device__ __forceinline__ bool place(const Blocks<FOLD>& blocks, unsigned& image, unsigned& b) {
+    b = harris_launch::dealt_tile(blockIdx.x, blockIdx.y, blocks.chunk);
+    image = blockIdx.z;
+    if constexpr (FOLD) {
+        if (b >= blocks.total) return false;
+        image = harris_launch::fastdiv(b, blocks.by_image);
+        b -= image * blocks.per_image;
+    }
+    return true;
+}
 
 typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
@@ -109,9 +132,11 @@ __device__ __forceinline__ void store_values(float* p, int left, const float (&v
 // row takes its last four values, some of which its neighbour computes and stores as well (the same
 // ones): a path of its own for what is left would cost its wavefront a second memory latency
 // (1431x970, the three groupings: 73.8 against 74.5 us).
-template <int PX>
-__device__ __forceinline__ bool flat(const Blocks& blocks, size_t count, size_t& at, int& left) {
-    at = ((size_t)block_of(blocks) * kThreads + threadIdx.x) * PX;
+template <bool FOLD, int PX>
+__device__ __forceinline__ bool flat(const Blocks<FOLD>& blocks, size_t count, unsigned& image, size_t& at, int& left) {
+    unsigned b;
+    if (!place<FOLD>(blocks, image, b)) return false;
+    at = ((size_t)b * kThreads + threadIdx.x) * PX;
     left = 1;
     if (at >= count) return false;
     if constexpr (PX > 1) {
@@ -122,9 +147,11 @@ __device__ __forceinline__ bool flat(const Blocks& blocks, size_t count, size_t&
 }
 
 // First pixel of this thread in a w x h image, or false.
-template <int PX, int ROWS>
-__device__ __forceinline__ bool pixel(const Blocks& blocks, int w, int h, int& x, int& y) {
-    const unsigned b = block_of(blocks), by = harris_launch::fastdiv(b, blocks.by_across), bx = b - by * blocks.across;
+template <bool FOLD, int PX, int ROWS>
+__device__ __forceinline__ bool pixel(const Blocks<FOLD>& blocks, int w, int h, unsigned& image, int& x, int& y) {
+    unsigned b;
+    if (!place<FOLD>(blocks, image, b)) return false;
+    const unsigned by = harris_launch::fastdiv(b, blocks.by_across), bx = b - by * blocks.across;
     const unsigned ux = (bx * kTileX + threadIdx.x % kTileX) * PX, uy = (by * kTileY + threadIdx.x / kTileX) * ROWS;
     if (ux >= (unsigned)w || uy >= (unsigned)h) return false;
     x = min((int)ux, max(w - PX, 0));
@@ -150,19 +177,20 @@ __device__ __forceinline__ void store_rows(float* out, int w, int h, int y, int 
 }
 
 // Conversion and grayscale.  rgb[b][3][H][W] -> gray[b][H][W]; in_scale is 1 (float32) or 1/255 (uint8).
-template <int PX, typename In>
-__global__ void gray_kernel(const Blocks blocks, const In* rgb, float* gray, size_t plane, float in_scale) {
+template <bool FOLD, int PX, typename In>
+__global__ void gray_kernel(const Blocks<FOLD> blocks, const In* rgb, float* gray, size_t plane, float in_scale) {
+    unsigned nth;
     size_t at;
     int left;
-    if (!flat<PX>(blocks, plane, at, left)) return;
-    const In* p = rgb + (size_t)blockIdx.z * 3 * plane + at;
+    if (!flat<FOLD, PX>(blocks, plane, nth, at, left)) return;
+    const In* p = rgb + (size_t)nth * 3 * plane + at;
     float r[PX], g[PX], b[PX], o[PX];
     load_values(p, left, r);
     load_values(p + plane, left, g);
     load_values(p + 2 * plane, left, b);
 #pragma unroll
     for (int i = 0; i < PX; ++i) o[i] = 0.299f * (r[i] * in_scale) + 0.587f * (g[i] * in_scale) + 0.114f * (b[i] * in_scale);
-    store_values<false>(gray + (size_t)blockIdx.z * plane + at, left, o);
+    store_values<false>(gray + (size_t)nth * plane + at, left, o);
 }
 
 // The two Sobel responses at row r, column i of a thread's pixels.
@@ -176,12 +204,13 @@ __device__ __forceinline__ void sobel_at(const Taps<PX, ROWS>& t, int r, int i, 
 // Sobel stage: one response per launch (Sx or Sy), both, or their three products.  in[b][h+2][w+2] ->
 // out_i[b][h][w].
 enum Stage { kSx, kSy, kSobelPair, kSobelProducts };
-template <int PX, int ROWS, int STAGE>
-__global__ void sobel_kernel(const Blocks blocks, const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
+template <bool FOLD, int PX, int ROWS, int STAGE>
+__global__ void sobel_kernel(const Blocks<FOLD> blocks, const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
+    unsigned nth;
     int x, y;
-    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
+    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
     Taps<PX, ROWS> t;
-    t.load(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, h, y, x);
+    t.load(in + (size_t)nth * (h + 2) * (w + 2), w, h, y, x);
     float a[ROWS][PX], b[ROWS][PX], c[ROWS][PX];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
@@ -193,7 +222,7 @@ __global__ void sobel_kernel(const Blocks blocks, const float* in, float* out0, 
             b[r][i] = STAGE == kSobelProducts ? ix * iy : iy;
             c[r][i] = iy * iy;
         }
-    const size_t image = (size_t)blockIdx.z * h * w;
+    const size_t image = (size_t)nth * h * w;
     store_rows<false>(out0 + image, w, h, y, x, a);
     if constexpr (STAGE >= kSobelPair) store_rows<false>(out1 + image, w, h, y, x, b);
     if constexpr (STAGE == kSobelProducts) store_rows<false>(out2 + image, w, h, y, x, c);
@@ -201,10 +230,11 @@ __global__ void sobel_kernel(const Blocks blocks, const float* in, float* out0, 
 
 // Products, one per launch.
 template <int PX>
-__global__ void mul_kernel(const Blocks blocks, const float* a, const float* b, float* out, size_t count) {
+__global__ void mul_kernel(const Blocks<false> blocks, const float* a, const float* b, float* out, size_t count) {
+    unsigned nth;
     size_t at;
     int left;
-    if (!flat<PX>(blocks, count, at, left)) return;
+    if (!flat<false, PX>(blocks, count, nth, at, left)) return;
     float u[PX], v[PX], o[PX];
     load_values(a + at, left, u);
     load_values(b + at, left, v);
@@ -230,18 +260,19 @@ __device__ __forceinline__ float window_at(const Taps<PX, ROWS>& t, int r, int i
 }
 
 // Window sums, one per launch.  in[b][h+2][w+2] -> out[b][h][w].
-template <int PX, int ROWS>
-__global__ void window_kernel(const Blocks blocks, const float* in, float* out, int h, int w, int binomial) {
+template <bool FOLD, int PX, int ROWS>
+__global__ void window_kernel(const Blocks<FOLD> blocks, const float* in, float* out, int h, int w, int binomial) {
+    unsigned nth;
     int x, y;
-    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
+    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
     Taps<PX, ROWS> t;
-    t.load(in + (size_t)blockIdx.z * (h + 2) * (w + 2), w, h, y, x);
+    t.load(in + (size_t)nth * (h + 2) * (w + 2), w, h, y, x);
     float o[ROWS][PX];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
 #pragma unroll
         for (int i = 0; i < PX; ++i) o[r][i] = window_at(t, r, i, binomial);
-    store_rows<false>(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
+    store_rows<false>(out + (size_t)nth * h * w, w, h, y, x, o);
 }
 
 __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, float k) {
@@ -251,10 +282,11 @@ __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, fl
 
 // Coarsity.
 template <int PX>
-__global__ void coarsity_kernel(const Blocks blocks, const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
+__global__ void coarsity_kernel(const Blocks<false> blocks, const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
+    unsigned nth;
     size_t at;
     int left;
-    if (!flat<PX>(blocks, count, at, left)) return;
+    if (!flat<false, PX>(blocks, count, nth, at, left)) return;
     float a[PX], b[PX], c[PX], o[PX];
     load_values(sxx + at, left, a);
     load_values(sxy + at, left, b);
@@ -265,11 +297,12 @@ __global__ void coarsity_kernel(const Blocks blocks, const float* sxx, const flo
 }
 
 // Window sums and coarsity from the three product images.
-template <int PX, int ROWS>
-__global__ void window_coarsity_kernel(const Blocks blocks, const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
+template <bool FOLD, int PX, int ROWS>
+__global__ void window_coarsity_kernel(const Blocks<FOLD> blocks, const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
+    unsigned nth;
     int x, y;
-    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
-    const size_t image = (size_t)blockIdx.z * (h + 2) * (w + 2);
+    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
+    const size_t image = (size_t)nth * (h + 2) * (w + 2);
     Taps<PX, ROWS> a, b, c;
     a.load(ixx + image, w, h, y, x);
     b.load(ixy + image, w, h, y, x);
@@ -279,15 +312,16 @@ __global__ void window_coarsity_kernel(const Blocks blocks, const float* ixx, co
     for (int r = 0; r < ROWS; ++r)
 #pragma unroll
         for (int i = 0; i < PX; ++i) o[r][i] = coarsity_of(window_at(a, r, i, binomial), window_at(b, r, i, binomial), window_at(c, r, i, binomial), k);
-    store_rows<true>(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
+    store_rows<true>(out + (size_t)nth * h * w, w, h, y, x, o);
 }
 
 // Products, window sums and coarsity from the two Sobel images.
-template <int PX, int ROWS>
-__global__ void products_window_coarsity_kernel(const Blocks blocks, const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
+template <bool FOLD, int PX, int ROWS>
+__global__ void products_window_coarsity_kernel(const Blocks<FOLD> blocks, const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
+    unsigned nth;
     int x, y;
-    if (!pixel<PX, ROWS>(blocks, w, h, x, y)) return;
-    const size_t image = (size_t)blockIdx.z * (h + 2) * (w + 2);
+    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
+    const size_t image = (size_t)nth * (h + 2) * (w + 2);
     Taps<PX, ROWS> gx, gy;
     gx.load(ix + image, w, h, y, x);
     gy.load(iy + image, w, h, y, x);
@@ -308,45 +342,53 @@ __global__ void products_window_coarsity_kernel(const Blocks blocks, const float
                 }
             o[r][i] = coarsity_of(sxx, sxy, syy, k);
         }
-    store_rows<true>(out + (size_t)blockIdx.z * h * w, w, h, y, x, o);
+    store_rows<true>(out + (size_t)nth * h * w, w, h, y, x, o);
 }
 
 // Every launch of grouping 1, 2 or 3.
-template <int PX, int ROWS>
+template <bool FOLD, int PX, int ROWS>
 void enqueue(const void* rgb, int dtype, int batch, int H, int W, float k, float s, int binomial, int grouping, float* ws, float* out, hipStream_t st) {
     const int h2 = H - 2, w2 = W - 2, h4 = H - 4, w4 = W - 4;
     const size_t n0 = (size_t)batch * H * W, n2 = (size_t)batch * h2 * w2, n4 = (size_t)batch * h4 * w4, plane = (size_t)H * W;
     const dim3 threads(kThreads);
-    struct Launch { Blocks blocks; dim3 grid; };
-    auto launch = [](unsigned long long count, unsigned across, int images) {
-        const harris_launch::GroupedGrid grid = harris_launch::grouped_grid(count);
-        return Launch{{grid.chunk, across, harris_launch::make_fastdiv(across)}, dim3(8 * grid.chunk, grid.turns, images)};
+    // A launch of workgroups for every image (fold: an image's `each` divided for by the workgroup) or for all at once.
+    auto launch = [](auto fold, unsigned long long each, unsigned across, int images) {
+        constexpr bool F = decltype(fold)::value;
+        const harris_launch::GroupedGrid grid = harris_launch::grouped_grid(F ? each * images : each);
+        Blocks<F> blocks;
+        blocks.chunk = grid.chunk; blocks.across = across; blocks.by_across = harris_launch::make_fastdiv(across);
+        if constexpr (F) { blocks.total = (unsigned)(each * images); blocks.per_image = (unsigned)each; blocks.by_image = harris_launch::make_fastdiv((unsigned)each); }
+        struct { Blocks<F> blocks; dim3 grid; } l = {blocks, dim3(8 * grid.chunk, grid.turns, F ? 1 : images)};
+        return l;
     };
-    auto area = [&](int w, int h) { const unsigned across = groups_covering(w, kTileX * PX); return launch((unsigned long long)across * groups_covering(h, kTileY * ROWS), across, batch); };
-    auto line = [&](size_t count, int images) { return launch((count + kThreads * PX - 1) / (kThreads * PX), 1, images); };
-    const Launch gray_l = line(plane, batch), l2 = area(w2, h2), l4 = area(w4, h4), f2 = line(n2, 1), f4 = line(n4, 1);
+    constexpr std::integral_constant<bool, FOLD> fold;
+    constexpr std::integral_constant<bool, false> at_once;
+    auto area = [&](int w, int h) { const unsigned across = groups_covering(w, kTileX * PX); return launch(fold, (unsigned long long)across * groups_covering(h, kTileY * ROWS), across, batch); };
+    auto line = [&](size_t count) { return (count + kThreads * PX - 1) / (kThreads * PX); };
+    const auto gray_l = launch(fold, line(plane), 1, batch), l2 = area(w2, h2), l4 = area(w4, h4);
+    const auto f2 = launch(at_once, line(n2), 1, 1), f4 = launch(at_once, line(n4), 1, 1);
     float* gray = ws;
-    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<PX, uint8_t>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
-    else hipLaunchKernelGGL((gray_kernel<PX, float>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const float*>(rgb), gray, plane, 1.0f);
+    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<FOLD, PX, uint8_t>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
+    else hipLaunchKernelGGL((gray_kernel<FOLD, PX, float>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const float*>(rgb), gray, plane, 1.0f);
     if (grouping == 1) {
         float *ix = gray + n0, *iy = ix + n2, *ixx = iy + n2, *ixy = ixx + n2, *iyy = ixy + n2, *sxx = iyy + n2, *sxy = sxx + n4, *syy = sxy + n4;
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSx>), l2.grid, threads, 0, st, l2.blocks, gray, ix, nullptr, nullptr, h2, w2, s);
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSy>), l2.grid, threads, 0, st, l2.blocks, gray, iy, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSx>), l2.grid, threads, 0, st, l2.blocks, gray, ix, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSy>), l2.grid, threads, 0, st, l2.blocks, gray, iy, nullptr, nullptr, h2, w2, s);
         hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, ix, ix, ixx, n2);
         hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, ix, iy, ixy, n2);
         hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, iy, iy, iyy, n2);
-        hipLaunchKernelGGL((window_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, sxx, h4, w4, binomial);
-        hipLaunchKernelGGL((window_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixy, sxy, h4, w4, binomial);
-        hipLaunchKernelGGL((window_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, iyy, syy, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, sxx, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixy, sxy, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, iyy, syy, h4, w4, binomial);
         hipLaunchKernelGGL(coarsity_kernel<PX>, f4.grid, threads, 0, st, f4.blocks, sxx, sxy, syy, out, n4, k);
     } else if (grouping == 2) {
         float *ixx = gray + n0, *ixy = ixx + n2, *iyy = ixy + n2;
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelProducts>), l2.grid, threads, 0, st, l2.blocks, gray, ixx, ixy, iyy, h2, w2, s);
-        hipLaunchKernelGGL((window_coarsity_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, ixy, iyy, out, h4, w4, k, binomial);
+        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSobelProducts>), l2.grid, threads, 0, st, l2.blocks, gray, ixx, ixy, iyy, h2, w2, s);
+        hipLaunchKernelGGL((window_coarsity_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, ixy, iyy, out, h4, w4, k, binomial);
     } else {
         float *ix = gray + n0, *iy = ix + n2;
-        hipLaunchKernelGGL((sobel_kernel<PX, ROWS, kSobelPair>), l2.grid, threads, 0, st, l2.blocks, gray, ix, iy, nullptr, h2, w2, s);
-        hipLaunchKernelGGL((products_window_coarsity_kernel<PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ix, iy, out, h4, w4, k, binomial);
+        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSobelPair>), l2.grid, threads, 0, st, l2.blocks, gray, ix, iy, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((products_window_coarsity_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ix, iy, out, h4, w4, k, binomial);
     }
 }
 
@@ -368,8 +410,9 @@ int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k,
                    int grouping, float* ws, float* out, void* stream_) {
     hipStream_t st = static_cast<hipStream_t>(stream_);
     if (batch > 65535) return HARRIS_ERR_SHAPE;        // images ride on gridDim.z
-    if (grouped_wide(batch, H, W)) enqueue<4, 2>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
-    else enqueue<1, 1>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
+    const bool wide = grouped_wide(batch, H, W), fold = grouped_folded(batch, H, W, wide);
+    const auto run = fold ? (wide ? enqueue<true, 4, 2> : enqueue<true, 1, 1>) : (wide ? enqueue<false, 4, 2> : enqueue<false, 1, 1>);
+    run(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
     return hipGetLastError() == hipSuccess ? HARRIS_OK : HARRIS_ERR_LAUNCH;
 }
 

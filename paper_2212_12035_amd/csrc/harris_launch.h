@@ -160,6 +160,13 @@ inline bool grouped_wide(int batch, int H, int W) { return (long long)batch * H 
 // Workgroups of `each` pixels (or rows) that cover `size` of them; size + each may lie beyond int.
 inline unsigned groups_covering(int size, int each) { return ((unsigned)size + (unsigned)each - 1u) / (unsigned)each; }
 
+// Whether an XCD takes a run of images (FOLD in harris_grouped.hip) instead of one of each image: where an image of several has
+// fewer than 64 workgroups in the 3x3 stages, of which up to seven more than needed are started otherwise (50 uint8
+// images of 240x320, 60 workgroups, 138 / 140 us; 64 of 128x128, 16, 62.2 / 62.3; 30 of 100x200, 100, 55.5 / 55.0; 16 of 651x64, 162, 54.7 / 53.2).
+inline bool grouped_folded(int batch, int H, int W, bool wide) {
+    return batch > 1 && (unsigned long long)groups_covering(W - 4, wide ? 256 : 64) * groups_covering(H - 4, wide ? 8 : 4) < 64;
+}
+
 // Grid of `blocks` workgroups for an image of a grouping, 8 x chunk by turns (dealt_tile): one turn, in which each XCD
 // takes one run, unless the launch's x dimension would come near the 2^32 threads that a dimension may have (images of
 // few columns and more than 33 million rows).

@@ -1333,6 +1333,23 @@ def test_kernel_groupings_match_the_oracle(gpu, oracle, grouping):
         check(out.cpu().numpy(), oracle.harris(rgb, k, scale, window))
 
 
+@pytest.mark.parametrize("B,H,W", [(700, 9, 40), (2, 5, 5), (80, 96, 100), (3, 255, 66), (3, 256, 66), (2, 260, 500)])
+def test_groupings_of_batches_of_small_images(gpu, oracle, B, H, W):
+    # Runs of images on an XCD, with one and with four pixels per thread; up to 63 workgroups an image and from 64 on.
+    import torch
+    for rgb, window in ((hi.white_noise_f32(650 + W, B, H, W), 0), (hi.white_noise_u8(651 + W, B, H, W), 1)):
+        want = oracle.harris(rgb, K, 1.0, window)
+        for grouping in (1, 2, 3):
+            say("case grouping %d of %dx3x%dx%d %s" % (grouping, B, H, W, rgb.dtype))
+            flat = torch.full((64 + want.size + 64,), float("nan"), device="cuda")
+            out = flat[64:-64].view(want.shape)
+            gpu.harris_coarsity_grouped(torch.from_numpy(rgb).cuda(), K, 1.0, window, grouping, out=out)
+            torch.cuda.synchronize()
+            check(out.cpu().numpy(), want)
+            out.fill_(float("nan"))
+            assert bool(torch.isnan(flat).all())
+
+
 @pytest.mark.parametrize("grouping", [1, 2, 3])
 def test_groupings_of_an_image_with_few_columns_and_very_many_rows(gpu, grouping):
     # 17.5 million workgroups of 256 threads: more than the 2^32 threads that a grid may have in one dimension.
