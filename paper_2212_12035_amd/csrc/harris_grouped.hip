@@ -47,27 +47,30 @@ constexpr int kTileX = 64, kTileY = 4, kThreads = kTileX * kTileY;      // 64 PX
 // by one the three groupings of 1600x2400 took 151 us, now 138, 1080x1920 98.2 / 90.4, 480x640 41.5 / 37.6, 4
 // images of 1080x1920 289 / 270.  Workgroups beyond the last have nothing to do.
 //
-// FOLD: batches of small images, whose runs would have more workgroups without work than with it: an XCD takes a
-// run of images instead, and a workgroup divides for its own (one by one / a run of each image / a run of images: 500
-// images of 40x40 67.0 / 83.8 / 65.3 us, 20000 of 8x8 189 / 978 / 168, 200 of 96x96 97 / 115 / 98, 2000 of 24x24 uint8 101 / 140 / 96; but
-// 480x640, which waits for the division, 41.5 / 37.6 / 40.5, 4 of 1080x1920 289 / 270 / 278).
-template <bool FOLD>
+// That is kRunOfEach, for images of many workgroups: runs end in workgroups without work, up to seven an image.  Batches of
+// smaller images take a run of images to an XCD, and a workgroup divides for its own (kRunOfImages), or are left in
+// order (kInOrder); grouped_dealing says when.
+using harris_launch::GroupedDealing;
+using harris_launch::kInOrder;
+using harris_launch::kRunOfEach;
+using harris_launch::kRunOfImages;
+template <GroupedDealing DEALING>
 struct Blocks {
     unsigned chunk;                         // workgroups of an XCD
     unsigned across;                        // workgroups across an image (3x3 stages)
     harris_launch::FastDiv by_across;
 };
 template <>
-struct Blocks<true> : Blocks<false> {
+struct Blocks<kRunOfImages> : Blocks<kRunOfEach> {
     unsigned total, per_image;              // workgroups that have something to do, and of an image
     harris_launch::FastDiv by_image;
 };
 // Image and workgroup of it, or false.
-template <bool FOLD>
-__device__ __forceinline__ bool place(const Blocks<FOLD>& blocks, unsigned& image, unsigned& b) {
-    b = harris_launch::dealt_tile(blockIdx.x, blockIdx.y, blocks.chunk);
+template <GroupedDealing DEALING>
+__device__ __forceinline__ bool place(const Blocks<DEALING>& blocks, unsigned& image, unsigned& b) {
+    b = DEALING == kInOrder ? blockIdx.x : harris_launch::dealt_tile(blockIdx.x, blockIdx.y, blocks.chunk);
     image = blockIdx.z;
-    if constexpr (FOLD) {
+    if constexpr (DEALING == kRunOfImages) {
         if (b >= blocks.total) return false;
         image = harris_launch::fastdiv(b, blocks.by_image);
         b -= image * blocks.per_image;
@@ -132,10 +135,10 @@ __device__ __forceinline__ void store_values(float* p, int left, const float (&v
 // row takes its last four values, some of which its neighbour computes and stores as well (the same
 // ones): a path of its own for what is left would cost its wavefront a second memory latency
 // (1431x970, the three groupings: 73.8 against 74.5 us).
-template <bool FOLD, int PX>
-__device__ __forceinline__ bool flat(const Blocks<FOLD>& blocks, size_t count, unsigned& image, size_t& at, int& left) {
+template <GroupedDealing DEALING, int PX>
+__device__ __forceinline__ bool flat(const Blocks<DEALING>& blocks, size_t count, unsigned& image, size_t& at, int& left) {
     unsigned b;
-    if (!place<FOLD>(blocks, image, b)) return false;
+    if (!place<DEALING>(blocks, image, b)) return false;
     at = ((size_t)b * kThreads + threadIdx.x) * PX;
     left = 1;
     if (at >= count) return false;
@@ -147,10 +150,10 @@ __device__ __forceinline__ bool flat(const Blocks<FOLD>& blocks, size_t count, u
 }
 
 // First pixel of this thread in a w x h image, or false.
-template <bool FOLD, int PX, int ROWS>
-__device__ __forceinline__ bool pixel(const Blocks<FOLD>& blocks, int w, int h, unsigned& image, int& x, int& y) {
+template <GroupedDealing DEALING, int PX, int ROWS>
+__device__ __forceinline__ bool pixel(const Blocks<DEALING>& blocks, int w, int h, unsigned& image, int& x, int& y) {
     unsigned b;
-    if (!place<FOLD>(blocks, image, b)) return false;
+    if (!place<DEALING>(blocks, image, b)) return false;
     const unsigned by = harris_launch::fastdiv(b, blocks.by_across), bx = b - by * blocks.across;
     const unsigned ux = (bx * kTileX + threadIdx.x % kTileX) * PX, uy = (by * kTileY + threadIdx.x / kTileX) * ROWS;
     if (ux >= (unsigned)w || uy >= (unsigned)h) return false;
@@ -177,12 +180,12 @@ __device__ __forceinline__ void store_rows(float* out, int w, int h, int y, int 
 }
 
 // Conversion and grayscale.  rgb[b][3][H][W] -> gray[b][H][W]; in_scale is 1 (float32) or 1/255 (uint8).
-template <bool FOLD, int PX, typename In>
-__global__ void gray_kernel(const Blocks<FOLD> blocks, const In* rgb, float* gray, size_t plane, float in_scale) {
+template <GroupedDealing DEALING, int PX, typename In>
+__global__ void gray_kernel(const Blocks<DEALING> blocks, const In* rgb, float* gray, size_t plane, float in_scale) {
     unsigned nth;
     size_t at;
     int left;
-    if (!flat<FOLD, PX>(blocks, plane, nth, at, left)) return;
+    if (!flat<DEALING, PX>(blocks, plane, nth, at, left)) return;
     const In* p = rgb + (size_t)nth * 3 * plane + at;
     float r[PX], g[PX], b[PX], o[PX];
     load_values(p, left, r);
@@ -204,11 +207,11 @@ __device__ __forceinline__ void sobel_at(const Taps<PX, ROWS>& t, int r, int i, 
 // Sobel stage: one response per launch (Sx or Sy), both, or their three products.  in[b][h+2][w+2] ->
 // out_i[b][h][w].
 enum Stage { kSx, kSy, kSobelPair, kSobelProducts };
-template <bool FOLD, int PX, int ROWS, int STAGE>
-__global__ void sobel_kernel(const Blocks<FOLD> blocks, const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
+template <GroupedDealing DEALING, int PX, int ROWS, int STAGE>
+__global__ void sobel_kernel(const Blocks<DEALING> blocks, const float* in, float* out0, float* out1, float* out2, int h, int w, float s) {
     unsigned nth;
     int x, y;
-    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
+    if (!pixel<DEALING, PX, ROWS>(blocks, w, h, nth, x, y)) return;
     Taps<PX, ROWS> t;
     t.load(in + (size_t)nth * (h + 2) * (w + 2), w, h, y, x);
     float a[ROWS][PX], b[ROWS][PX], c[ROWS][PX];
@@ -230,11 +233,11 @@ __global__ void sobel_kernel(const Blocks<FOLD> blocks, const float* in, float* 
 
 // Products, one per launch.
 template <int PX>
-__global__ void mul_kernel(const Blocks<false> blocks, const float* a, const float* b, float* out, size_t count) {
+__global__ void mul_kernel(const Blocks<kRunOfEach> blocks, const float* a, const float* b, float* out, size_t count) {
     unsigned nth;
     size_t at;
     int left;
-    if (!flat<false, PX>(blocks, count, nth, at, left)) return;
+    if (!flat<kRunOfEach, PX>(blocks, count, nth, at, left)) return;
     float u[PX], v[PX], o[PX];
     load_values(a + at, left, u);
     load_values(b + at, left, v);
@@ -260,11 +263,11 @@ __device__ __forceinline__ float window_at(const Taps<PX, ROWS>& t, int r, int i
 }
 
 // Window sums, one per launch.  in[b][h+2][w+2] -> out[b][h][w].
-template <bool FOLD, int PX, int ROWS>
-__global__ void window_kernel(const Blocks<FOLD> blocks, const float* in, float* out, int h, int w, int binomial) {
+template <GroupedDealing DEALING, int PX, int ROWS>
+__global__ void window_kernel(const Blocks<DEALING> blocks, const float* in, float* out, int h, int w, int binomial) {
     unsigned nth;
     int x, y;
-    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
+    if (!pixel<DEALING, PX, ROWS>(blocks, w, h, nth, x, y)) return;
     Taps<PX, ROWS> t;
     t.load(in + (size_t)nth * (h + 2) * (w + 2), w, h, y, x);
     float o[ROWS][PX];
@@ -282,11 +285,11 @@ __device__ __forceinline__ float coarsity_of(float sxx, float sxy, float syy, fl
 
 // Coarsity.
 template <int PX>
-__global__ void coarsity_kernel(const Blocks<false> blocks, const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
+__global__ void coarsity_kernel(const Blocks<kRunOfEach> blocks, const float* sxx, const float* sxy, const float* syy, float* out, size_t count, float k) {
     unsigned nth;
     size_t at;
     int left;
-    if (!flat<false, PX>(blocks, count, nth, at, left)) return;
+    if (!flat<kRunOfEach, PX>(blocks, count, nth, at, left)) return;
     float a[PX], b[PX], c[PX], o[PX];
     load_values(sxx + at, left, a);
     load_values(sxy + at, left, b);
@@ -297,11 +300,11 @@ __global__ void coarsity_kernel(const Blocks<false> blocks, const float* sxx, co
 }
 
 // Window sums and coarsity from the three product images.
-template <bool FOLD, int PX, int ROWS>
-__global__ void window_coarsity_kernel(const Blocks<FOLD> blocks, const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
+template <GroupedDealing DEALING, int PX, int ROWS>
+__global__ void window_coarsity_kernel(const Blocks<DEALING> blocks, const float* ixx, const float* ixy, const float* iyy, float* out, int h, int w, float k, int binomial) {
     unsigned nth;
     int x, y;
-    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
+    if (!pixel<DEALING, PX, ROWS>(blocks, w, h, nth, x, y)) return;
     const size_t image = (size_t)nth * (h + 2) * (w + 2);
     Taps<PX, ROWS> a, b, c;
     a.load(ixx + image, w, h, y, x);
@@ -316,11 +319,11 @@ __global__ void window_coarsity_kernel(const Blocks<FOLD> blocks, const float* i
 }
 
 // Products, window sums and coarsity from the two Sobel images.
-template <bool FOLD, int PX, int ROWS>
-__global__ void products_window_coarsity_kernel(const Blocks<FOLD> blocks, const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
+template <GroupedDealing DEALING, int PX, int ROWS>
+__global__ void products_window_coarsity_kernel(const Blocks<DEALING> blocks, const float* ix, const float* iy, float* out, int h, int w, float k, int binomial) {
     unsigned nth;
     int x, y;
-    if (!pixel<FOLD, PX, ROWS>(blocks, w, h, nth, x, y)) return;
+    if (!pixel<DEALING, PX, ROWS>(blocks, w, h, nth, x, y)) return;
     const size_t image = (size_t)nth * (h + 2) * (w + 2);
     Taps<PX, ROWS> gx, gy;
     gx.load(ix + image, w, h, y, x);
@@ -346,49 +349,48 @@ __global__ void products_window_coarsity_kernel(const Blocks<FOLD> blocks, const
 }
 
 // Every launch of grouping 1, 2 or 3.
-template <bool FOLD, int PX, int ROWS>
+template <GroupedDealing DEALING, int PX, int ROWS>
 void enqueue(const void* rgb, int dtype, int batch, int H, int W, float k, float s, int binomial, int grouping, float* ws, float* out, hipStream_t st) {
     const int h2 = H - 2, w2 = W - 2, h4 = H - 4, w4 = W - 4;
     const size_t n0 = (size_t)batch * H * W, n2 = (size_t)batch * h2 * w2, n4 = (size_t)batch * h4 * w4, plane = (size_t)H * W;
     const dim3 threads(kThreads);
-    // A launch of workgroups for every image (fold: an image's `each` divided for by the workgroup) or for all at once.
-    auto launch = [](auto fold, unsigned long long each, unsigned across, int images) {
-        constexpr bool F = decltype(fold)::value;
-        const harris_launch::GroupedGrid grid = harris_launch::grouped_grid(F ? each * images : each);
-        Blocks<F> blocks;
+    auto launch = [](auto dealing, unsigned long long each, unsigned across, int images) {
+        constexpr GroupedDealing D = decltype(dealing)::value;
+        const harris_launch::GroupedGrid grid = harris_launch::grouped_grid(D == kRunOfImages ? each * images : each);
+        Blocks<D> blocks;
         blocks.chunk = grid.chunk; blocks.across = across; blocks.by_across = harris_launch::make_fastdiv(across);
-        if constexpr (F) { blocks.total = (unsigned)(each * images); blocks.per_image = (unsigned)each; blocks.by_image = harris_launch::make_fastdiv((unsigned)each); }
-        struct { Blocks<F> blocks; dim3 grid; } l = {blocks, dim3(8 * grid.chunk, grid.turns, F ? 1 : images)};
+        if constexpr (D == kRunOfImages) { blocks.total = (unsigned)(each * images); blocks.per_image = (unsigned)each; blocks.by_image = harris_launch::make_fastdiv((unsigned)each); }
+        struct { Blocks<D> blocks; dim3 grid; } l = {blocks, D == kInOrder ? dim3((unsigned)each, 1, images) : dim3(8 * grid.chunk, grid.turns, D == kRunOfImages ? 1 : images)};
         return l;
     };
-    constexpr std::integral_constant<bool, FOLD> fold;
-    constexpr std::integral_constant<bool, false> at_once;
-    auto area = [&](int w, int h) { const unsigned across = groups_covering(w, kTileX * PX); return launch(fold, (unsigned long long)across * groups_covering(h, kTileY * ROWS), across, batch); };
+    constexpr std::integral_constant<GroupedDealing, DEALING> dealing;
+    constexpr std::integral_constant<GroupedDealing, kRunOfEach> whole;             // products and coarsity: one array for all images
+    auto area = [&](int w, int h) { const unsigned across = groups_covering(w, kTileX * PX); return launch(dealing, (unsigned long long)across * groups_covering(h, kTileY * ROWS), across, batch); };
     auto line = [&](size_t count) { return (count + kThreads * PX - 1) / (kThreads * PX); };
-    const auto gray_l = launch(fold, line(plane), 1, batch), l2 = area(w2, h2), l4 = area(w4, h4);
-    const auto f2 = launch(at_once, line(n2), 1, 1), f4 = launch(at_once, line(n4), 1, 1);
+    const auto gray_l = launch(dealing, line(plane), 1, batch), l2 = area(w2, h2), l4 = area(w4, h4);
+    const auto f2 = launch(whole, line(n2), 1, 1), f4 = launch(whole, line(n4), 1, 1);
     float* gray = ws;
-    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<FOLD, PX, uint8_t>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
-    else hipLaunchKernelGGL((gray_kernel<FOLD, PX, float>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const float*>(rgb), gray, plane, 1.0f);
+    if (dtype == HARRIS_U8) hipLaunchKernelGGL((gray_kernel<DEALING, PX, uint8_t>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const uint8_t*>(rgb), gray, plane, 1.0f / 255.0f);
+    else hipLaunchKernelGGL((gray_kernel<DEALING, PX, float>), gray_l.grid, threads, 0, st, gray_l.blocks, static_cast<const float*>(rgb), gray, plane, 1.0f);
     if (grouping == 1) {
         float *ix = gray + n0, *iy = ix + n2, *ixx = iy + n2, *ixy = ixx + n2, *iyy = ixy + n2, *sxx = iyy + n2, *sxy = sxx + n4, *syy = sxy + n4;
-        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSx>), l2.grid, threads, 0, st, l2.blocks, gray, ix, nullptr, nullptr, h2, w2, s);
-        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSy>), l2.grid, threads, 0, st, l2.blocks, gray, iy, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((sobel_kernel<DEALING, PX, ROWS, kSx>), l2.grid, threads, 0, st, l2.blocks, gray, ix, nullptr, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((sobel_kernel<DEALING, PX, ROWS, kSy>), l2.grid, threads, 0, st, l2.blocks, gray, iy, nullptr, nullptr, h2, w2, s);
         hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, ix, ix, ixx, n2);
         hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, ix, iy, ixy, n2);
         hipLaunchKernelGGL(mul_kernel<PX>, f2.grid, threads, 0, st, f2.blocks, iy, iy, iyy, n2);
-        hipLaunchKernelGGL((window_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, sxx, h4, w4, binomial);
-        hipLaunchKernelGGL((window_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixy, sxy, h4, w4, binomial);
-        hipLaunchKernelGGL((window_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, iyy, syy, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<DEALING, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, sxx, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<DEALING, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixy, sxy, h4, w4, binomial);
+        hipLaunchKernelGGL((window_kernel<DEALING, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, iyy, syy, h4, w4, binomial);
         hipLaunchKernelGGL(coarsity_kernel<PX>, f4.grid, threads, 0, st, f4.blocks, sxx, sxy, syy, out, n4, k);
     } else if (grouping == 2) {
         float *ixx = gray + n0, *ixy = ixx + n2, *iyy = ixy + n2;
-        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSobelProducts>), l2.grid, threads, 0, st, l2.blocks, gray, ixx, ixy, iyy, h2, w2, s);
-        hipLaunchKernelGGL((window_coarsity_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, ixy, iyy, out, h4, w4, k, binomial);
+        hipLaunchKernelGGL((sobel_kernel<DEALING, PX, ROWS, kSobelProducts>), l2.grid, threads, 0, st, l2.blocks, gray, ixx, ixy, iyy, h2, w2, s);
+        hipLaunchKernelGGL((window_coarsity_kernel<DEALING, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ixx, ixy, iyy, out, h4, w4, k, binomial);
     } else {
         float *ix = gray + n0, *iy = ix + n2;
-        hipLaunchKernelGGL((sobel_kernel<FOLD, PX, ROWS, kSobelPair>), l2.grid, threads, 0, st, l2.blocks, gray, ix, iy, nullptr, h2, w2, s);
-        hipLaunchKernelGGL((products_window_coarsity_kernel<FOLD, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ix, iy, out, h4, w4, k, binomial);
+        hipLaunchKernelGGL((sobel_kernel<DEALING, PX, ROWS, kSobelPair>), l2.grid, threads, 0, st, l2.blocks, gray, ix, iy, nullptr, h2, w2, s);
+        hipLaunchKernelGGL((products_window_coarsity_kernel<DEALING, PX, ROWS>), l4.grid, threads, 0, st, l4.blocks, ix, iy, out, h4, w4, k, binomial);
     }
 }
 
@@ -410,9 +412,17 @@ int launch_grouped(const void* rgb, int dtype, int batch, int H, int W, float k,
                    int grouping, float* ws, float* out, void* stream_) {
     hipStream_t st = static_cast<hipStream_t>(stream_);
     if (batch > 65535) return HARRIS_ERR_SHAPE;        // images ride on gridDim.z
-    const bool wide = grouped_wide(batch, H, W), fold = grouped_folded(batch, H, W, wide);
-    const auto run = fold ? (wide ? enqueue<true, 4, 2> : enqueue<true, 1, 1>) : (wide ? enqueue<false, 4, 2> : enqueue<false, 1, 1>);
-    run(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
+    const bool wide = grouped_wide(batch, H, W);
+    const auto run = [&](auto dealing) {
+        constexpr GroupedDealing D = decltype(dealing)::value;
+        if (wide) enqueue<D, 4, 2>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
+        else enqueue<D, 1, 1>(rgb, dtype, batch, H, W, k, sobel_scale, binomial, grouping, ws, out, st);
+    };
+    switch (grouped_dealing(batch, H, W, wide)) {
+        case kRunOfEach: run(std::integral_constant<GroupedDealing, kRunOfEach>()); break;
+        case kRunOfImages: run(std::integral_constant<GroupedDealing, kRunOfImages>()); break;
+        case kInOrder: run(std::integral_constant<GroupedDealing, kInOrder>()); break;
+    }
     return hipGetLastError() == hipSuccess ? HARRIS_OK : HARRIS_ERR_LAUNCH;
 }
 

@@ -198,10 +198,10 @@ int main() {
             }
         if (!good) { std::printf("%llu workgroups of a grouping: chunks of %u, %u turns\n", blocks, g.chunk, g.turns); return 1; }
     }
-    // Groupings: batches of small images in runs of images.
-    for (const auto& c : {std::vector<int>{500, 40, 40, 1}, {20000, 8, 8, 1}, {65535, 6, 6, 1}, {200, 96, 96, 1}, {2, 64, 96, 1}, {1, 64, 96, 0}, {4, 1080, 1920, 0}, {16, 651, 64, 0}, {3, 300000, 8, 0}})
-        if (harris_launch::grouped_folded(c[0], c[1], c[2], harris_launch::grouped_wide(c[0], c[1], c[2])) != (c[3] != 0)) {
-            std::printf("runs of images: %d of %dx%d\n", c[0], c[1], c[2]);
+    // Groupings: batches of small images in runs of images, small batches of them in order.
+    for (const auto& c : {std::vector<int>{500, 40, 40, 1}, {20000, 8, 8, 1}, {65535, 6, 6, 1}, {200, 96, 96, 1}, {2, 64, 96, 2}, {1, 64, 96, 0}, {4, 1080, 1920, 0}, {16, 651, 64, 0}, {3, 300000, 8, 0}})
+        if (harris_launch::grouped_dealing(c[0], c[1], c[2], harris_launch::grouped_wide(c[0], c[1], c[2])) != c[3]) {
+            std::printf("dealing of %d images of %dx%d\n", c[0], c[1], c[2]);
             return 1;
         }
     // Groupings: four pixels of two rows per thread only for images that give a row of threads work.
