@@ -105,13 +105,13 @@ constexpr long long kPatchPixels = 1LL << 18;
 // workgroups start and end one by one while larger ones wait for room on a CU; what they read twice, four rows in
 // sixteen, comes from L2.  But a launch that the chip holds at once takes as long as its fullest CU, which a band more or less per
 // image moves by a quarter: of four, five and eight wavefronts those are taken that leave the fewest on that CU, four being
-// worth 0.92 and five 1.04 of as many in workgroups of eight, and four wherever they make no more than two workgroups per CU.
+// worth 0.94 and five 1.04 of as many in workgroups of eight, and four wherever they make no more than two workgroups per CU.
 // 460 float32 images of 150x37, 16 wavefronts by fours, 20 by fives, 16 by eights, 11.9 / 14.5 / 12.6 us; 394 of 104x35, 12 / 10 / 8, 9.9 /
 // 8.5 / 8.0; 219 of 97x64, 8 / 10 / 7, 6.5 / 7.3 / 7.0; uint8 1140 of 67x47, 24 / 20 / 21, 10.9 / 8.6 / 8.8; 2526 of 50x33, 24 / 25 / 21, 12.3 / 13.5
 // / 10.2.  From float32 the chip is kept busiest by fours beyond that (1931 of 61x83 31.5 / 33.3 / 34.3); 8-bit launches gain by the
 // same count at any size.  Over 340 shapes of 1.2 to 13 million pixels, each with its images in the last-level cache and not,
 // 0.94 of the time of eight in one stretch per XCD; 24 of 680 times more than 1.02, at most 1.07 (1906 uint8 images of 133x26 in
-// the cache; 1.00 where not).
+// the cache; 1.00 where not).  Of images of 5 to 24 columns 2795 uint8 images of 116x13 take 1.10, 25029 float32 of 15x7 1.06.
 // Launches below some 1.2 million pixels keep eight, one band of up to 28 rows, and one turn: a test of the plans fixes
 // their bands (four would take 0.85 to 1.02 of the time: 71 uint8 images of 91x80 3.9 / 4.3, 311 float32 of 28x88 5.6 / 5.7).  From some
 // 1.44 million on a launch has more than a workgroup per CU, as a test of the turns has it (1787 uint8 images of 32x36, 256
@@ -125,7 +125,7 @@ int patch_waves(int dtype, long long pixels, long long groups, int n) {
         return (groups * bands(most) + 255) / 256 * ((rows + 3) / 4 + 1);
     };
     if (groups * bands(4) <= 512 || (dtype == HARRIS_F32 && groups * bands(4) * 4 > 256 * 32)) return 4;
-    const long long four = 92 * fullest(4), five = 104 * fullest(5), eight = 100 * fullest(kPatchWaves);
+    const long long four = 94 * fullest(4), five = 104 * fullest(5), eight = 100 * fullest(kPatchWaves);
     const bool eights = pixels < kPatchFewPixels || groups * bands(kPatchWaves) > 256;
     if (eights && eight <= four && eight <= five) return kPatchWaves;
     return four < five ? 4 : 5;

@@ -163,7 +163,7 @@ inline unsigned groups_covering(int size, int each) { return ((unsigned)size + (
 // How the workgroups of a grouping's launches are dealt to the XCDs (harris_grouped.hip): a run of each image to an XCD, a run
 // of images, or one by one in order.  Of images with few workgroups the first starts up to seven more than needed for each (in
 // order / a run of each / a run of images, the three groupings: 500 images of 40x40 67.0 / 83.8 / 64.9 us, 20000 of 8x8 189 / 977 / 168, 200 of
-// 96x96 97 / 113 / 96, 1336 of 307x7, 76 workgroups, 547 / 567 / 529); the division that the second needs is waited for in large images and in small
+// 96x96 97 / 113 / 96, 1336 of 307x7, 76 workgroups, 548 / 568 / 532); the division that the second needs is waited for in large images and in small
 // launches (480x640 41.5 / 37.6 / 40.5; 4 of 1080x1920 289 / 270 / 278; 16 of 651x64, 162 workgroups, 56.7 / 53.2 / 54.7; 30 of 100x200, 100, 59.5 / 55.0 /
 // 55.5; images and workspace not in the last-level cache: 30 of 25x66, 180 in all, 30.4 / 30.7 / 32.5, 1284 of 6x28 uint8, 1284, 36.7 / 83 / 39.6, 299 of
 // 29x70 uint8, 4186, 68.9 / 69.7 / 62.3).

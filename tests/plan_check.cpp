@@ -149,7 +149,7 @@ int main() {
     // Narrow images: as many wavefronts a workgroup as leave the fewest on the fullest CU, or four.
     static const int waves[][5] = {{HARRIS_F32, 460, 150, 37, 4}, {HARRIS_F32, 394, 104, 35, 8}, {HARRIS_F32, 501, 117, 44, 7}, {HARRIS_F32, 2900, 50, 26, 5}, {HARRIS_F32, 2048, 64, 64, 4},
                                    {HARRIS_F32, 8192, 32, 32, 4}, {HARRIS_F32, 1931, 61, 84, 4}, {HARRIS_U8, 1140, 67, 47, 5}, {HARRIS_U8, 2526, 50, 33, 7}, {HARRIS_U8, 2816, 26, 63, 7},
-                                   {HARRIS_U8, 805, 39, 121, 4}, {HARRIS_U8, 309, 112, 52, 4}, {HARRIS_F32, 100, 60, 60, 8}};
+                                   {HARRIS_U8, 22916, 17, 9, 5}, {HARRIS_U8, 805, 39, 121, 4}, {HARRIS_U8, 309, 112, 52, 4}, {HARRIS_F32, 100, 60, 60, 8}};
     for (const auto& c : waves) {
         if (harris_coarsity_typed((const void*)0x100000, c[0], c[1], c[2], c[3], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, HARRIS_OUT_F32, nullptr, nullptr) != HARRIS_OK ||
             !(harris_launch::last.flags & HARRIS_TUNE_PACKED_IMAGES) || harris_launch::last_shape.waves_per_block != c[4]) {
