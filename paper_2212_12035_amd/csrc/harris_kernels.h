@@ -732,11 +732,9 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // size stops the lanes right of the row.
     [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_pitch + 8 + reach ? col : 0x80000000u;
     constexpr bool BYTES = SHIFTED && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
-    // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does; a lane whose columns end
-    // behind the row the row's last four, shifted down by `drop`.  No load leaves the row; rows below the image
-    // load its last one, and nobody uses what comes of them.
-    [[maybe_unused]] const unsigned last_col = (unsigned)p.W - 4u, byte_voff = min(col, last_col);
-    [[maybe_unused]] const unsigned drop = col > last_col ? 8u * ((col - last_col) & 3u) : 0u;
+    // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does (byte_lane).  Rows below
+    // the image load its last one, and nobody uses what comes of them.
+    [[maybe_unused]] const harris_launch::ByteLane bytes = harris_launch::byte_lane(col, (unsigned)p.W);
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         const int r = y_wave + t;
@@ -745,7 +743,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
         if constexpr (BYTES) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const u32_any* at = reinterpret_cast<const u32_any*>(row_in + c * plane + byte_voff);
+                const u32_any* at = reinterpret_cast<const u32_any*>(row_in + c * plane + bytes.voff);
                 raw[t].w[c][0] = LAUX == kAuxNonTemporal ? __builtin_nontemporal_load(at) : *at;
             }
         } else if constexpr (SHIFTED) {
@@ -818,7 +816,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
         constexpr int t = decltype(tt)::value;
         if constexpr (BYTES) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) raw[t].w[c][0] >>= drop;
+            for (int c = 0; c < 3; ++c) raw[t].w[c][0] >>= bytes.drop;
         } else if constexpr (SHIFTED) {
             realign_row(raw[t], shift[t]);
         }

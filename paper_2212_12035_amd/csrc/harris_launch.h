@@ -98,6 +98,15 @@ HARRIS_HOST_DEVICE constexpr unsigned tile_lds_bytes(bool from_8_bit, int px, un
     return (hands_sobel(from_8_bit, px) ? 1u + (waves - 1u) * 6u : waves * 4u) * 64u * (unsigned)px * 4u;
 }
 
+// TILES, 8-bit rows on any byte loaded where they are: the byte of a row of W >= 4 pixels at which the lane of column
+// `col` loads four, and the bits by which it shifts them down: a lane whose columns end behind the row loads the
+// row's last four.  No load leaves the row.
+struct ByteLane { unsigned voff, drop; };
+HARRIS_HOST_DEVICE inline ByteLane byte_lane(unsigned col, unsigned W) {
+    const unsigned last = W - 4u;
+    return {col < last ? col : last, col > last ? 8u * ((col - last) & 3u) : 0u};
+}
+
 // HARRIS_TUNE_PACKED_IMAGES: most wavefronts of a workgroup, each with four rows; the last one only hands its
 // rows on.
 constexpr int kPatchWaves = 8;

@@ -179,6 +179,15 @@ int main() {
             return 1;
         }
     }
+    // 8-bit rows on any byte loaded where they are: every lane, also beyond the row, loads inside it, and has the pixels
+    // of its columns that the row has.
+    for (unsigned W = 5; W <= 600; ++W)
+        for (unsigned col = 0; col < W + 300; col += 4) {
+            const harris_launch::ByteLane l = harris_launch::byte_lane(col, W);
+            bool good = l.voff + 4 <= W && l.drop <= 24 && l.drop % 8 == 0;
+            for (unsigned i = 0; i < 4 && col + i < W; ++i) good = good && l.drop / 8 + i < 4 && l.voff + l.drop / 8 + i == col + i;
+            if (!good) { std::printf("lane of column %u of %u loads at %u, shifted by %u\n", col, W, l.voff, l.drop); return 1; }
+        }
     // What a tile needs of LDS: rows of 64 lanes.
     for (unsigned w = 2; w <= 16; ++w)
         if (harris_launch::tile_lds_bytes(true, 4, w) != (1 + 6 * (w - 1)) * 1024 || harris_launch::tile_lds_bytes(false, 4, w) != w * 4096 || harris_launch::tile_lds_bytes(true, 2, w) != w * 2048) {

@@ -282,6 +282,27 @@ def test_u8_sobel_responses_handed_over(gpu, oracle, rows, waves):
         check(got, oracle.harris(rgb, K, 1.0, window), referee=(oracle, rgb, K, 1.0, window))
 
 
+@pytest.mark.parametrize("window", [0, 1])
+@pytest.mark.parametrize("W", [1300, 1301, 1303])
+def test_u8_launches_that_are_not_resident_at_once(gpu, oracle, W, window):
+    # More than the 2048 tiles of 4 x 4 rows that the chip holds: the instances of large launches, on aligned rows and on rows on
+    # any byte (loaded as aligned words), with several strips, the last tile of 4 result rows.
+    import torch
+    B, H = 9, 500
+    tuning = dict(schedule=2, px=4, rows=4, waves_per_block=4, flags=gpu.HARRIS_TUNE_STREAM_LOADS | gpu.HARRIS_TUNE_KEEP_SHARED_ROWS)
+    tiles = gpu.harris_plan(gpu.HARRIS_U8, B, H, W, rgb_align=4 if W % 4 == 0 else 1, out_align=4, tuning=tuning)[1]
+    assert tiles > 256 * 8, tiles
+    rgb = hi.white_noise_u8(660 + W, B, H, W)
+    say("case %dx3x%dx%d uint8 window %d, %d tiles" % (B, H, W, window, tiles))
+    flat = torch.full((64 + B * (H - 4) * (W - 4) + 64,), float("nan"), device="cuda")
+    out = flat[64:-64].view(B, H - 4, W - 4)
+    gpu.harris_coarsity_ex(torch.from_numpy(rgb).cuda(), K, 1.0, window, out=out, tuning=tuning)
+    torch.cuda.synchronize()
+    check(out.cpu().numpy(), oracle.harris(rgb, K, 1.0, window), referee=(oracle, rgb, K, 1.0, window))
+    out.fill_(float("nan"))
+    assert bool(torch.isnan(flat).all())
+
+
 @pytest.mark.parametrize("px", [1, 2, 4])
 @pytest.mark.parametrize("prefetch", [3])
 def test_u8_every_kernel_instance(gpu, oracle, px, prefetch):
@@ -366,7 +387,8 @@ def test_any_width_and_row_alignment_with_16_byte_lanes(gpu, oracle, W):
     # The tile kernel keeps four pixels per lane when rows are not naturally aligned: float32
     # rows on any 4-byte boundary (vector accesses need no more; the lane that straddles the
     # end of a row loads zeros beyond it and stores nothing there), 8-bit rows on any byte
-    # (loaded as the aligned words that hold them, then shifted).  Input and result are views
+    # (loaded where they are, as in all launches that the chip holds at once; larger ones load the
+    # aligned words that hold them, then shift).  Input and result are views
     # inside larger buffers: guard bands show that nothing else is written, and whatever a
     # straddling access did would stay inside an allocation.
     import torch
@@ -1484,7 +1506,7 @@ def test_concurrent_calls_from_host_threads_on_their_own_streams(gpu, oracle):
 def test_captured_in_a_graph_and_replayed(gpu, oracle):
     # The library allocates nothing and never synchronises, so its launches can be captured.
     # A graph of three launches (barrier hand-over, ready flags with 64 KB of LDS reserved, 8-bit
-    # input through the shifted loads) is replayed several times with fresh inputs and eager work in between; every
+    # input on any byte) is replayed several times with fresh inputs and eager work in between; every
     # replay is checked against the oracle and against the eager launch, bit for bit.
     import torch
     H, W = 150, 1000
