@@ -104,14 +104,17 @@ constexpr long long kPatchPixels = 1LL << 18;
 // 8192 of 32x32 25.8 (30.9), 5000 of 24x100 32.7 (38.1), uint8 663 of 48x64 5.67 (6.38), 3713 of 103x25 29.2 (33.1).  Small
 // workgroups start and end one by one while larger ones wait for room on a CU; what they read twice, four rows in
 // sixteen, comes from L2.  But a launch that the chip holds at once takes as long as its fullest CU, which a band more or less per
-// image moves by a quarter: of four, five and eight wavefronts those are taken that leave the fewest on that CU, four being
-// worth 0.94 and five 1.04 of as many in workgroups of eight, and four wherever they make no more than two workgroups per CU.
-// 460 float32 images of 150x37, 16 wavefronts by fours, 20 by fives, 16 by eights, 11.9 / 14.5 / 12.6 us; 394 of 104x35, 12 / 10 / 8, 9.9 /
-// 8.5 / 8.0; 219 of 97x64, 8 / 10 / 7, 6.5 / 7.3 / 7.0; uint8 1140 of 67x47, 24 / 20 / 21, 10.9 / 8.6 / 8.8; 2526 of 50x33, 24 / 25 / 21, 12.3 / 13.5
-// / 10.2.  From float32 the chip is kept busiest by fours beyond that (1931 of 61x83 31.5 / 33.3 / 34.3); 8-bit launches gain by the
-// same count at any size.  Over 340 shapes of 1.2 to 13 million pixels, each with its images in the last-level cache and not,
-// 0.94 of the time of eight in one stretch per XCD; 24 of 680 times more than 1.02, at most 1.07 (1906 uint8 images of 133x26 in
-// the cache; 1.00 where not).  Of images of 5 to 24 columns 2795 uint8 images of 116x13 take 1.10, 25029 float32 of 15x7 1.06.
+// image moves by a quarter: of four, five and eight wavefronts those are taken that leave the fewest on that CU, where four and
+// five count less than as many in workgroups of eight (from float32 0.88 and 0.98, from 8-bit input 0.84 and 1.04), and four
+// wherever they make no more than two workgroups per CU.  (In us by fours / fives / eights, wavefronts on the fullest CU in
+// brackets, input and results not in the last-level cache: 460 float32 images of 150x37 11.9 / 14.5 / 12.6 [16 / 20 / 16]; 394 of 104x35 9.9 / 8.5 / 8.0 [12 / 10 / 8];
+// 219 of 97x64 6.5 / 7.3 / 7.0 [8 / 10 / 7]; uint8 1648 of 60x55 14.1 / 14.6 / 15.0 [36 / 35 / 32].)
+//   - From float32 fours keep the chip busiest beyond 24 wavefronts a CU (1931 of 61x83 31.5 / 33.3 / 34.3).
+//   - From 8-bit input six workgroups of four a CU count 0.90 (1140 of 67x47 10.9 / 8.6 / 8.8 [24 / 20 / 21]; 2526 of 50x33 12.3 / 13.5 / 10.2 [24 /
+//     25 / 21]), and fours whose bands are of eight rows or less or that take over 1.25 times the wavefronts of eights 0.94 (7323 of 18x96,
+//     two bands for one, 1.07 / 0.98 / 1.00 of the time, 22916 of 17x9 15.7 / 12.6 / 12.6, 6814 of 32x28 1.01 / 1.00 / 0.92).
+// Over 480 shapes of 1.2 to 25 million pixels, each with its images in the last-level cache and not, 0.94 of the time of eight in
+// one stretch per XCD; at most 1.1.  Of images of 5 to 24 columns 2795 uint8 images of 116x13 take 1.10, 25029 float32 of 15x7 1.06.
 // Launches below some 1.2 million pixels keep eight, one band of up to 28 rows, and one turn: a test of the plans fixes
 // their bands (four would take 0.85 to 1.02 of the time: 71 uint8 images of 91x80 3.9 / 4.3, 311 float32 of 28x88 5.6 / 5.7).  From some
 // 1.44 million on a launch has more than a workgroup per CU, as a test of the turns has it (1787 uint8 images of 32x36, 256
@@ -119,16 +122,22 @@ constexpr long long kPatchPixels = 1LL << 18;
 constexpr long long kPatchSmallPixels = 9LL << 17, kPatchFewPixels = 11LL << 17;
 int patch_waves(int dtype, long long pixels, long long groups, int n) {
     if (pixels < kPatchSmallPixels) return kPatchWaves;
-    const auto bands = [&](int most) { return (n + 4 * (most - 1) - 1) / (4 * (most - 1)); };      // of at most `most` wavefronts
-    const auto fullest = [&](int most) {                        // wavefronts on the fullest CU
-        const int rows = (n + bands(most) - 1) / bands(most);
-        return (groups * bands(most) + 255) / 256 * ((rows + 3) / 4 + 1);
+    struct Shape { long long blocks; int rows, waves; long long fullest; };     // rows of a band; wavefronts of a workgroup and on the fullest CU
+    const auto shape = [&](int most) {
+        const int bands = (n + 4 * (most - 1) - 1) / (4 * (most - 1)), rows = (n + bands - 1) / bands, waves = (rows + 3) / 4 + 1;
+        return Shape{groups * bands, rows, waves, (groups * bands + 255) / 256 * waves};
     };
-    if (groups * bands(4) <= 512 || (dtype == HARRIS_F32 && groups * bands(4) * 4 > 256 * 32)) return 4;
-    const long long four = 94 * fullest(4), five = 104 * fullest(5), eight = 100 * fullest(kPatchWaves);
-    const bool eights = pixels < kPatchFewPixels || groups * bands(kPatchWaves) > 256;
-    if (eights && eight <= four && eight <= five) return kPatchWaves;
-    return four < five ? 4 : 5;
+    const Shape four = shape(4), five = shape(5), eight = shape(kPatchWaves);
+    if (four.blocks <= 512 || (dtype == HARRIS_F32 && four.blocks * 4 > 256 * 24)) return 4;
+    long long weight4 = 88, weight5 = 98;
+    if (dtype == HARRIS_U8) {
+        weight4 = four.rows <= 8 || 4 * four.blocks * four.waves > 5 * eight.blocks * eight.waves ? 94 : four.fullest > 20 && four.fullest <= 24 ? 90 : 84;
+        weight5 = 104;
+    }
+    const long long cost4 = weight4 * four.fullest, cost5 = weight5 * five.fullest, cost8 = 100 * eight.fullest;
+    const bool eights = pixels < kPatchFewPixels || eight.blocks > 256;
+    if (eights && cost8 <= cost4 && cost8 <= cost5) return kPatchWaves;
+    return cost4 < cost5 ? 4 : 5;
 }
 unsigned patch_turns(long long pixels, long long blocks) {
     const long long turns = pixels < kPatchSmallPixels ? 1 : (blocks + 64) / 128;
