@@ -206,9 +206,10 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
 //     a band) one turn 33.0 us, 7 bands 32.1, 4 bands 32.6, 2 bands 33.4; 2 images of 2160x3840 44.5 / 8 bands 42.5 / 2
 //     bands 44.9; 2400x8000 (34 a band) 52.5 / 4 bands 50.1 / 8 bands 53.3.
 //   - One float32 image to float32 beyond 128 MB, 3 tiles on a CU and so 96 on an XCD, is particular where a band has many tiles: runs
-//     of 130 to 150 tiles are fast, of 152 to 178 and of 116 to 126 slow.  Where no number of turns gives the former, up to 101 tiles.
+//     of 127 to 150 tiles are fast, of 152 to 178 and of 116 to 126 slow.  Where no number of turns gives the former, up to 101 tiles.
 //     4200x4200 one turn 46.1 us, runs of 119 tiles 47.0, of 148 45.8; 3456x5184 47.0 / 119 48.8 / 149 46.5; 4608x4608 55.8 / 120 56.6 /
-//     144 54.4; 3500x4000 38.5 / 156 39.3 / 94 37.9.  (Two images of 2531x3743 rather take 119, 50.8 us, than 149, 53.6.)
+//     144 54.4; 3500x4000 38.5 / 156 39.3 / 94 37.9;
+//     5778x4238 65.2 / 96 63.5 / 128 62.0.  (Two images of 2531x3743 rather take 119, 50.8 us, than 149, 53.6.)
 //   - At least 2 bands and 16 tiles for larger launches, with 2 tiles on a CU, and for 8-bit input: 64 images of 1080x1920
 //     float32 (8 a band) one turn 350 us, 2 bands 340; in graphs one turn 353, 2 bands 334, 6 bands 338, 16 bands 351; 6000x8000
 //     127.2, 2 bands 124.9, 1 band 128; 64 images of 1080x1920 uint8 176.4, 2 bands 159.5, 16 bands 166; 2832x4256 uint8 19.5, 2 bands 18.9, 10 bands 19.4.
@@ -226,9 +227,10 @@ unsigned chunk_turns(int dtype, int out_dtype, int batch, long long footprint, l
     if (!f32 && to_f32 && small && n_strips >= 16 && chunk < 96) chunk = 96;
     long long turns = turns_of(chunk);
     if (few && to_f32 && !small && batch == 1 && n_strips >= 14) {
+        const auto each = [&](long long t) { return (n_tiles + 8 * t - 1) / (8 * t); };
+        const auto good = [&](long long t) { return each(t) >= 127 && each(t) <= 150; };
         turns = turns_of(140);
-        const long long each = (n_tiles + 8 * turns - 1) / (8 * turns);
-        if (each < 130 || each > 150) turns = (n_tiles + 8 * 101 - 1) / (8 * 101);
+        turns = good(turns) ? turns : good(turns + 1) ? turns + 1 : (n_tiles + 8 * 101 - 1) / (8 * 101);
     }
     return (unsigned)(turns < 1 ? 1 : turns > 65535 ? 65535 : turns);
 }

@@ -159,7 +159,7 @@ int main() {
     }
     // How many tiles an XCD takes in a row, where the wrong number is slower than one turn: {input type, images, height, width, least, most}.
     static const int runs[][6] = {{HARRIS_F32, 1, 4200, 4200, 130, 150}, {HARRIS_F32, 1, 3456, 5184, 130, 150}, {HARRIS_F32, 1, 4608, 4608, 130, 150}, {HARRIS_F32, 1, 2832, 4256, 130, 150},
-                                  {HARRIS_F32, 1, 4096, 4300, 130, 150}, {HARRIS_F32, 1, 3500, 4000, 70, 101}, {HARRIS_F32, 2, 2531, 3743, 110, 125}, {HARRIS_U8, 1, 4096, 4096, 90, 105},
+                                  {HARRIS_F32, 1, 4096, 4300, 130, 150}, {HARRIS_F32, 1, 5778, 4238, 127, 130}, {HARRIS_F32, 1, 3500, 4000, 70, 101}, {HARRIS_F32, 2, 2531, 3743, 110, 125}, {HARRIS_U8, 1, 4096, 4096, 90, 105},
                                   {HARRIS_U8, 2, 2048, 4096, 90, 105}, {HARRIS_U8, 8, 1080, 1920, 16, 17}, {HARRIS_U8, 1, 8192, 8192, 70, 71}};
     for (const auto& c : runs) {
         if (harris_coarsity_typed((const void*)0x100000, c[0], c[1], c[2], c[3], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, HARRIS_OUT_F32, nullptr, nullptr) != HARRIS_OK ||
