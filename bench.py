@@ -35,9 +35,9 @@ SETTLE_MS = 20.0               # untimed launches before the timed region, in GP
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (summaries under profiles/), valid only
 # for the kernel sources they were taken with: (sha256 of the csrc files without comments, {workload: bytes}).
-TRAFFIC_SOURCES_SHA256 = "a13db7237a36f3a353d0c1286ebcc668494de997f4042c6c7c2d76f791da2a15"
-TRAFFIC_BYTES = {"noise_f32_1536x2560": 65194719, "rects_f32_64x1080x1920": 2283691494,
-                 "blobs_f32_2832x4256": 199633036, "noise_u8_8192x8192": 510303731}
+TRAFFIC_SOURCES_SHA256 = "99863ea9ec95ff5a7c4ab86c76d67c4de45b7939372d4c886af40f8633717307"
+TRAFFIC_BYTES = {"noise_f32_1536x2560": 65199200, "rects_f32_64x1080x1920": 2283600892,
+                 "blobs_f32_2832x4256": 199652355, "noise_u8_8192x8192": 510160381}
 
 
 def kernel_sources_sha256():

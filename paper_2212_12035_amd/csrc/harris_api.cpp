@@ -374,15 +374,17 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         // flight per CU, not with the 28 to 32 the registers allow (every wavefront requests all
         // its rows at once; with fewer in flight the requests stay within what L2 and the memory
         // controllers handle well), so the planner reserves LDS to hold the resident tiles down:
-        // 36 KB -> 4 tiles per CU, 48 KB -> 3, 64 KB -> 2.  Measured (shape x reservation swept
-        // together; 4 x 4 rows without reservation in brackets):
+        // 36 KB -> 4 tiles per CU, 48 KB -> 3, 64 KB -> 2.  Measured with the tiles of an XCD in one stretch (shape x
+        // reservation swept together; 4 x 4 rows without reservation in brackets).  Dealt by turns every one of these is
+        // faster, but not all by as much: beyond 128 MB other shapes than those taken here are then up to 4.5 %
+        // faster (4 x 6 at 48 KB: 6000x8000 117 us, the planner's 5 x 6 122, 4320x7680 84.6 / 86.5; 5 x 6: 64x1080x1920 332 / 341,
+        // 16x1080x1920 82.4 / 84.3, 4096x4096 43.5 / 44.2).  The choice has not been swept again.  In one stretch:
         //   float32 results, up to 400 MB: 4 wavefronts x 5 rows, 3 per CU (2832x4256 32.7 [34.8]
         //     us, 2x2160x3840 44.5 [49.1]);
         //   beyond, 8 images or more: 5 x 5, 2 per CU (16x1080x1920 87.1 [103.7] us, 64x1080x1920
         //     351 [378], 128x720x1280 318 [350]); fewer, larger images: 5 x 6, 2 per CU
         //     (4320x7680 92.0 [105.7] us, 4 x 5: 99.2; 6000x8000 122.3, 4 x 5: 124.3; 8192x8192 170 to 172
-        //     [191.6], 4 x 5: 172.7; replayed from a graph on three input sets 180.3 and 173.0, but then too 93.4
-        //     and 98.3 for 4320x7680, 129.6 and 133.4 for 6000x8000);
+        //     [191.6], 4 x 5: 172.7);
         //   16-bit results and 8-bit codes up to 256 MB: 4 x 4, 4 per CU (2832x4256 to binary16 27.8 us, 29.4
         //     with 4 x 6 and 3 per CU; 3000x3000 22.1 / 23.2, 8x1080x1920 39.0 / 40.1, 2832x4256 to codes
         //     27.3 / 29.1); above: 4 x 6, 3 per CU (16x1080x1920 75.7 [89.7] us, 64x1080x1920 331

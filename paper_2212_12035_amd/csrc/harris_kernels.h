@@ -631,7 +631,7 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 //
 // SHIFTED (8-bit input, four pixels per lane): rows start on any byte.  Launches that the vector ALUs or latency bound, WORDS
 // and SMALL in tiles of four rows per wavefront and one tile per CU, load their pixels where they are (BYTES): the lane shifts and byte-aligns of
-// whole words are 24 of some 430 vector operations per wavefront, and the loads, all of one policy, stand in one
+// whole words are 24 of some 480 vector operations per wavefront (codes; counters: 456 without), and the loads, all of one policy, stand in one
 // straight line.  16 images of 768x1366 to codes 21.7 us (23.3 with words), 9 of 2442x1862 52.1 (57.1), 8 of 1079x1919 to
 // binary16 21.9 (23.8), 1079x1919 to float32 5.67 (5.97), 19 of 300x401 6.50 (6.89).  Large launches to float32 are bound
 // by memory and load aligned words (load_row_shifted, realign_row), non-temporal but for the rows that tiles share:
@@ -645,8 +645,8 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 //
 // 8-bit input with four pixels per lane hands over, instead of four gray rows, the first two and the Sobel responses
 // that the wavefront has computed from all four (six rows of LDS): the wavefront above needs exactly these, and does
-// not compute them again (4 instead of 6 rows of responses for 4 result rows; 50 of some 430 vector operations per
-// wavefront at 4 x 4).  8-bit launches that are not held up by memory gain: 16 images of 768x1366 to codes 22.4 us (23.0
+// not compute them again (4 instead of 6 rows of responses for 4 result rows; 8192x8192 at 4 x 4: 390 vector
+// operations per wavefront by the counters, 423 before).  8-bit launches that are not held up by memory gain: 16 images of 768x1366 to codes 22.4 us (23.0
 // before), 9 of 2442x1862 to codes 51.8 (54.1), 10 of 480x640 to float32 6.80 (6.92), 600x800 3.71 (3.82); 8192x8192 to
 // float32 is bound by the memory's view of its tiles (83 us, 84 without any arithmetic) and takes the same time.  At 4 x 4
 // the 19 KB leave eight workgroups on a CU.  float32 input is bound by memory and keeps the gray rows.

@@ -46,8 +46,8 @@ HARRIS_HOST_DEVICE inline unsigned fastdiv(unsigned x, const FastDiv& f) {
 // Tile of workgroup (x, y) of a launch of many tiles, 8 chunk x turns workgroups: the hardware deals workgroups out
 // to the eight XCDs one by one, and XCD i takes the tiles of chunks i, i + 8, i + 16, ..., `chunk` neighbouring tiles each.  All
 // XCDs together then work on one stretch of the images that moves on, instead of on eight stretches far apart;
-// memory serves that faster (64 images of 1080x1920 float32: 354 us in eight stretches, 333 by turns; to
-// binary16, 28 images: 155 and 137; uint8, 64 images: 177 and 160; 4320x7680: 94.6 and 88.6).  Workgroups beyond the last
+// memory serves that faster (replayed from graphs, 64 images of 1080x1920 float32: 354 us in eight stretches, 333 by turns, called one
+// after the other 350 and 340; to binary16, 28 images: 155 and 137; uint8, 64 images: 177 and 160; 4320x7680: 94.6 and 88.6).  Workgroups beyond the last
 // tile, at the end of the last turn, have nothing to do.
 HARRIS_HOST_DEVICE inline unsigned dealt_tile(unsigned x, unsigned y, unsigned chunk) { return (y * 8u + x % 8u) * chunk + x / 8u; }
 
