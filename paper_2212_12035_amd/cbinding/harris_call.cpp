@@ -14,6 +14,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 
 #include <climits>
+#include <utility>
 
 #include "harris.h"
 
@@ -152,20 +153,25 @@ PyObject* dense(PyObject*, PyObject* const* a, Py_ssize_t n) {
         c.dense = true;
         c.out_dtype = HARRIS_OUT_F32;
         at::Tensor made;
+        struct Owned {
+            PyObject* object = nullptr;
+            ~Owned() { Py_XDECREF(object); }
+        } returned;                             // made before the call: nothing that could fail comes after it
         if (a[1] == Py_None) {
             made = new_result(c);
             c.out = &made;
             if (!made.has_storage()) Py_RETURN_NONE;
+            returned.object = THPVariable_Wrap(made);
+            if (returned.object == nullptr) { PyErr_Clear(); Py_RETURN_NONE; }
         } else {
             c.out = plain_tensor(a[1]);
             if (c.out == nullptr || c.out->scalar_type() != at::kFloat || !result(c) || !c.out->is_contiguous()) Py_RETURN_NONE;
+            returned.object = Py_NewRef(a[1]);
         }
         const Outcome outcome = enqueue(c);
         if (outcome == kRaised) return nullptr;
         if (outcome == kDeclined) Py_RETURN_NONE;
-        if (a[1] == Py_None) return THPVariable_Wrap(std::move(made));
-        Py_INCREF(a[1]);
-        return a[1];
+        return std::exchange(returned.object, nullptr);
     } catch (...) {
         PyErr_Clear();
         Py_RETURN_NONE;
