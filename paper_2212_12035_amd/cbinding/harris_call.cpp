@@ -131,7 +131,7 @@ Outcome enqueue(const Call& c) {
 bool ready() { return call_typed != nullptr && !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
 
 // A new result for a call.  The interpreter's lock is let go of meanwhile, as torch.empty does: the allocator may have to
-// go to the driver, or to wait for the GPU.
+// ask the runtime for memory, or to wait for the GPU.
 at::Tensor new_result(const Call& c) {
     struct Unlocked {
         PyThreadState* state = PyEval_SaveThread();

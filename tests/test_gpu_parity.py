@@ -1298,7 +1298,7 @@ def test_a_call_that_fails_is_made_once_and_raises(gpu, monkeypatch):
 
 
 def test_other_threads_run_while_a_result_is_allocated(gpu):
-    # A fresh gigabyte from the driver each time; the function that gives the current device is called right after the
+    # A fresh gigabyte from the runtime each time; the function that gives the current device is called right after the
     # allocation and sees how often another thread has run.  No thread is preempted meanwhile, so that the
     # other one only runs where the interpreter's lock is let go of.
     import sys
