@@ -513,6 +513,8 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->flags = t.flags | (through ? harris_launch::kWriteThrough : 0u);
         params->out_kind = (unsigned)out_dtype;
         params->in_shifted = in_shifted ? 1 : 0;
+        params->out_shift = out_dtype == HARRIS_OUT_F32 ? 2u : out_dtype == HARRIS_OUT_U8 ? 0u : 1u;
+        params->strip_reach = (unsigned)(pitch + 4 + (out_shifted ? 4 : border_reach));
         params->lds_bytes = (unsigned)t.lds_kb * 1024u;
     }
     return HARRIS_OK;
@@ -583,17 +585,26 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
         out_align = common_alignment(out_align, lay.out_image_pitch * out_elem_size(out_dtype));
     }
 
-    harris_launch::Params p;
+    harris_launch::Params p = {};
     harris_tuning shape;
     long long n_blocks = 0;
     int rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, tuning, &shape, &n_blocks, &p);
     if (rc != HARRIS_OK) return rc;
     if (empty) return HARRIS_OK;
+    // Rows of hundreds of megabytes, or that far apart: the one kernel that addresses each by itself, whatever shape was asked for.
+    if (shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) && harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows)) {
+        const harris_tuning narrow = {HARRIS_SCHEDULE_TILES, 1, 4, 0, 4, 0u, 0};
+        rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, &narrow, &shape, &n_blocks, &p);
+        if (rc != HARRIS_OK) return rc;
+        p.far_rows = 1;
+    }
 
     p.rgb = rgb;
     p.out = out;
     p.in_row_pitch = lay.rgb_row_pitch; p.in_plane_pitch = lay.rgb_plane_pitch; p.in_image_pitch = lay.rgb_image_pitch;
     p.out_row_pitch = lay.out_row_pitch; p.out_image_pitch = lay.out_image_pitch;
+    p.out_row_bytes = (unsigned long long)lay.out_row_pitch * out_elem_size(out_dtype);
+    p.out_image_bytes = (unsigned long long)lay.out_image_pitch * out_elem_size(out_dtype);
     // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it (and the
     // 1/255 of 8-bit input) into the three gray weights.
     const float in_scale = dtype == HARRIS_U8 ? sobel_scale / 255.0f : sobel_scale;

@@ -128,6 +128,8 @@ constexpr int kAuxNonTemporal = HARRIS_LOAD_AUX;
 // default policy.  The launches that use it are those of many small tiles; their float32 stores are
 // written through (kAuxManyStore) if strips end on 64-byte boundaries.
 constexpr int kAuxKeepShared = -1;
+// Tile kernel only: the default policy, and rows that do not lie within 2 GB of each other.
+constexpr int kAuxFar = -2;
 constexpr int kAuxStore = HARRIS_STORE_AUX, kAuxManyStore = HARRIS_MANY_STORE_AUX;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -146,30 +148,34 @@ struct RawRow {
     uint32_t w[3][NW];
 };
 
+// One plane's part of it: voff is the lane's byte offset and soff the wavefront's, both from where rs begins.  The
+// hardware loads zeros where voff is not below the descriptor's size less soff.
+template <typename In, int PX, int AUX>
+__device__ __forceinline__ void load_plane_row(RawRow<In, PX>& r, int c, __amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
+    constexpr int BYTES = PX * (int)sizeof(In);
+    if constexpr (BYTES >= 16) {
+#pragma unroll
+        for (int j = 0; j < BYTES / 16; ++j) {
+            u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * j, soff, AUX);
+            r.w[c][4 * j + 0] = v.x; r.w[c][4 * j + 1] = v.y; r.w[c][4 * j + 2] = v.z; r.w[c][4 * j + 3] = v.w;
+        }
+    } else if constexpr (BYTES == 8) {
+        u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, soff, AUX);
+        r.w[c][0] = v.x; r.w[c][1] = v.y;
+    } else if constexpr (BYTES == 4) {
+        r.w[c][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, AUX);
+    } else if constexpr (BYTES == 2) {
+        r.w[c][0] = __builtin_amdgcn_raw_buffer_load_b16(rs, voff, soff, AUX);
+    } else {
+        r.w[c][0] = __builtin_amdgcn_raw_buffer_load_b8(rs, voff, soff, AUX);
+    }
+}
+
 // row points at column 0 of the row in plane 0; voff is the lane's byte offset in the row.
 template <typename In, int PX, int AUX>
 __device__ __forceinline__ void load_row(RawRow<In, PX>& r, const In* row, size_t plane, uint32_t row_bytes, uint32_t voff) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(row + c * plane, row_bytes);
-        constexpr int BYTES = PX * (int)sizeof(In);
-        if constexpr (BYTES >= 16) {
-#pragma unroll
-            for (int j = 0; j < BYTES / 16; ++j) {
-                u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16 * j, 0, AUX);
-                r.w[c][4 * j + 0] = v.x; r.w[c][4 * j + 1] = v.y; r.w[c][4 * j + 2] = v.z; r.w[c][4 * j + 3] = v.w;
-            }
-        } else if constexpr (BYTES == 8) {
-            u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, voff, 0, AUX);
-            r.w[c][0] = v.x; r.w[c][1] = v.y;
-        } else if constexpr (BYTES == 4) {
-            r.w[c][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, voff, 0, AUX);
-        } else if constexpr (BYTES == 2) {
-            r.w[c][0] = __builtin_amdgcn_raw_buffer_load_b16(rs, voff, 0, AUX);
-        } else {
-            r.w[c][0] = __builtin_amdgcn_raw_buffer_load_b8(rs, voff, 0, AUX);
-        }
-    }
+    for (int c = 0; c < 3; ++c) load_plane_row<In, PX, AUX>(r, c, make_rsrc(row + c * plane, row_bytes), voff, 0);
 }
 
 // 8-bit rows that start on any byte, four pixels per lane: every lane loads the aligned 32-bit
@@ -203,7 +209,8 @@ __device__ __forceinline__ void realign_row(RawRow<uint8_t, 4>& r, const uint32_
 }
 
 // PX results of one lane to a result row described by rs (its size is the row's
-// bytes, or 0 to store nothing); voff is the lane's byte offset in the row.
+// bytes, or 0 to store nothing); voff is the lane's byte offset in the row.  (No offset in a scalar register: the compiler lets the
+// data of a 16-byte store that has one be overwritten by the next instruction, and wrong results were stored.)
 template <int PX, int AUX = kAuxStore>
 __device__ __forceinline__ void store_row(const float (&o)[PX], __amdgpu_buffer_rsrc_t rs, uint32_t voff) {
     if constexpr (PX >= 4) {
@@ -652,6 +659,17 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // the 19 KB leave eight workgroups on a CU.  float32 input is bound by memory and keeps the gray rows.
 //
 // SMALL (8-bit input, shared rows kept): a launch whose tiles are all resident at once (Params::resident).
+//
+// Scalar work: a SIMD issues a scalar instruction every four cycles (measured: 4.5 with eight wavefronts), no faster than vector ones, so the
+// address arithmetic of short-lived wavefronts can take as long as their pixels.  Rows are therefore loaded through a descriptor
+// per plane and a row offset (NEAR), in one branch for a wavefront's load policy, and the result rows' descriptors take a dozen
+// instructions each: 8192x8192 uint8 in 4 x 4 tiles some 190 scalar instructions per wavefront by the counters, 327 with a descriptor
+// worked out for each row and plane and a branch for each row.  In us (before): 8192x8192 uint8 81.2 (83.6), 4096x4096 23.3 (24.5), 8 of 1080x1920
+// 23.1 (23.9), 1536x2560 7.04 (7.47), 480x640 3.06 (3.28), 16 images of 768x1366 to codes 19.6 (20.8), 31 of 598x300 to
+// bfloat16 10.6 (10.9), 64x96 float32 2.66 (2.80).  float32 tiles of 8 rows and more gain nothing and keep a descriptor per row.
+//
+// kAuxFar: a wavefront's rows do not lie within 2 GB of each other; 64-bit addresses for each row (one lane width, PX = 1; run() in
+// harris_api.cpp sees to it).
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool SMALL = false, bool WORDS = false>
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
@@ -706,23 +724,20 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // load is checked against the descriptor's size by itself.
     const unsigned lcol = min(col, ((unsigned)p.W - 1u) & ~(unsigned)(PX - 1));
     // Results are float32, 16-bit or 8-bit: esh is log2 of a result element's bytes.
-    const unsigned esh = p.out_kind == HARRIS_OUT_F32 ? 2u : p.out_kind == HARRIS_OUT_U8 ? 0u : 1u;
+    const unsigned esh = p.out_shift;
     // With aligned stores the border between this strip and the next lies, in each result row,
     // on the first 64-byte boundary of that row's address at or after the nominal border: up to
-    // 12 (float32), 28 (16-bit) or 60 (8-bit) columns further right.  border_mask is the number
-    // of columns per 64 bytes, minus one (15, 31 or 63), or 0.
+    // 12 (float32), 28 (16-bit) or 60 (8-bit) columns further right.
     // WORDS: the border moves to the next 4-byte boundary, up to 1 or 3 columns.
-    const unsigned border_mask = WORDS ? (4u >> esh) - 1u : (p.flags & HARRIS_TUNE_ALIGNED_STORES) ? (64u >> esh) - 1u : 0u;
     const unsigned x0 = (unsigned)strip * p.strip_pitch;        // first result column of this strip
     // Lanes beyond the strip's columns, the border's reach and the 4-column halo request nothing
     // (out-of-range offset).
-    const unsigned reach = WORDS ? 4u : border_mask & ~3u;
-    const uint32_t load_voff = lane * PX < p.strip_pitch + 4 + reach ? lcol * (uint32_t)sizeof(In) : 0x80000000u;
+    const uint32_t load_voff = lane * PX < p.strip_reach ? lcol * (uint32_t)sizeof(In) : 0x80000000u;
     const uint32_t in_row_bytes = (uint32_t)p.W * (uint32_t)sizeof(In);
 
     const size_t plane = (size_t)p.in_plane_pitch;
     const In* img_in = static_cast<const In*>(p.rgb) + (size_t)img * (size_t)p.in_image_pitch;
-    const uintptr_t img_out = reinterpret_cast<uintptr_t>(p.out) + (((size_t)img * (size_t)p.out_image_pitch) << esh);
+    const uintptr_t img_out = reinterpret_cast<uintptr_t>(p.out) + (uintptr_t)img * p.out_image_bytes;
 
     // All RW rows of this wavefront at once; rows below the image get an empty descriptor.
     RawRow<In, PX> raw[RW];
@@ -730,67 +745,116 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // Shifted rows: every lane within reach loads the word at its own column (one lane further
     // right than otherwise, which supplies the last lane's missing bytes); the descriptor's
     // size stops the lanes right of the row.
-    [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_pitch + 8 + reach ? col : 0x80000000u;
+    [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_reach + 4 ? col : 0x80000000u;
     constexpr bool BYTES = SHIFTED && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
     // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does (byte_lane).  Rows below
     // the image load its last one, and nobody uses what comes of them.
     [[maybe_unused]] const harris_launch::ByteLane bytes = harris_launch::byte_lane(col, (unsigned)p.W);
-    static_for<0, RW>([&](auto tt) {
-        constexpr int t = decltype(tt)::value;
-        const int r = y_wave + t;
-        const In* row_in = img_in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch;
-        const uint32_t row_bytes = r < p.H ? in_row_bytes : 0u;
-        if constexpr (BYTES) {
+    constexpr bool NEAR = LAUX != kAuxFar && (std::is_same<In, uint8_t>::value ? !SHIFTED || BYTES : RW <= 6);
+    if constexpr (NEAR) {
+        const int last = p.H - 1 - y_wave;                      // the image's last row, counted from this wavefront's first; negative below the image
+        const uint32_t pitch = (uint32_t)p.in_row_pitch * (uint32_t)sizeof(In), last_off = (uint32_t)max(last, 0) * pitch;
+        const In* first = img_in + (size_t)(unsigned)min(y_wave, p.H - 1) * (size_t)p.in_row_pitch;
+        // A plane's rows from the wavefront's first on, as far as it needs them and the image has them; rows below the image
+        // load its last one again, which nobody uses, and wavefronts below it nothing.  From float32, whose lanes may straddle a row's end, every
+        // row has a descriptor that ends with it.
+        constexpr bool EACH = std::is_same<In, float>::value;
+        const uint32_t rows = last < 0 ? 0u : min(last_off, (RW - 1) * pitch) + in_row_bytes;
+        auto load_all = [&](auto head, auto tail) {
+            static_for<0, RW>([&](auto tt) {
+                constexpr int t = decltype(tt)::value;
+                constexpr bool SHARED = (t < 4 && decltype(head)::value) || (t >= RW - 4 && decltype(tail)::value);
+                constexpr int AUX = LAUX != kAuxKeepShared ? LAUX : SHARED ? kAuxDefault : kAuxNonTemporal;
+                const uint32_t off = min(t * pitch, last_off), end = EACH && last >= 0 ? off + in_row_bytes : rows;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const u32_any* at = reinterpret_cast<const u32_any*>(row_in + c * plane + bytes.voff);
-                raw[t].w[c][0] = LAUX == kAuxNonTemporal ? __builtin_nontemporal_load(at) : *at;
-            }
-        } else if constexpr (SHIFTED) {
-            if constexpr (LAUX == kAuxKeepShared) {
-                const bool shared = (t < 4 && wave == 0) || (t >= RW - 4 && wave + 1 == n_waves);
-                if (shared) load_row_shifted<kAuxDefault>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
-                else load_row_shifted<kAuxNonTemporal>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
-            } else {
-                load_row_shifted<LAUX>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
-            }
-        } else if constexpr (LAUX == kAuxKeepShared) {
+                for (int c = 0; c < 3; ++c) {
+                    if constexpr (BYTES) {
+                        const u32_any* at = reinterpret_cast<const u32_any*>(first + c * plane + (bytes.voff + off));
+                        raw[t].w[c][0] = LAUX == kAuxNonTemporal ? __builtin_nontemporal_load(at) : *at;
+                    } else {
+                        load_plane_row<In, PX, AUX>(raw[t], c, make_rsrc(first + c * plane, end), load_voff, off);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);              // row by row: the first is worked on when it is there
+            });
+        };
+        if constexpr (LAUX != kAuxKeepShared || BYTES) load_all(std::false_type{}, std::false_type{});
+        else if (wave == 0 || (RW == 4 && wave + 1 == n_waves)) load_all(std::true_type{}, std::false_type{});
+        else if (RW != 4 && wave + 1 == n_waves) load_all(std::false_type{}, std::true_type{});
+        else load_all(std::false_type{}, std::false_type{});
+    } else {
+        static_for<0, RW>([&](auto tt) {
+            constexpr int t = decltype(tt)::value;
+            const int r = y_wave + t;
+            const In* row_in = img_in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch;
+            const uint32_t row_bytes = r < p.H ? in_row_bytes : 0u;
             const bool shared = (t < 4 && wave == 0) || (t >= RW - 4 && wave + 1 == n_waves);
-            if (shared) load_row<In, PX, kAuxDefault>(raw[t], row_in, plane, row_bytes, load_voff);
-            else load_row<In, PX, kAuxNonTemporal>(raw[t], row_in, plane, row_bytes, load_voff);
-        } else {
-            load_row<In, PX, LAUX>(raw[t], row_in, plane, row_bytes, load_voff);
-        }
-    });
+            if constexpr (SHIFTED) {
+                if constexpr (LAUX == kAuxKeepShared) {
+                    if (shared) load_row_shifted<kAuxDefault>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
+                    else load_row_shifted<kAuxNonTemporal>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
+                } else {
+                    load_row_shifted<LAUX>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
+                }
+            } else if constexpr (LAUX == kAuxKeepShared) {
+                if (shared) load_row<In, PX, kAuxDefault>(raw[t], row_in, plane, row_bytes, load_voff);
+                else load_row<In, PX, kAuxNonTemporal>(raw[t], row_in, plane, row_bytes, load_voff);
+            } else {
+                load_row<In, PX, LAUX == kAuxFar ? kAuxDefault : LAUX>(raw[t], row_in, plane, row_bytes, load_voff);
+            }
+        });
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     // Descriptors of the RW result rows, worked out while the loads are in flight (scalar
     // arithmetic that would otherwise sit between the last result and the first store).
-    // Result row j of this wavefront is row y_wave + j; rows past the tile or the image get
-    // an empty descriptor, whose address is never used.  The descriptor covers this strip's
-    // columns [b0, b1) of the row; a lane's offset is relative to b0 and wraps to a huge
-    // value for lanes left of it, so lanes outside store nothing.
+    // Result row j of this wavefront is row y_wave + j.  A descriptor covers the strip's columns in that row, from its left border, out_skip
+    // bytes behind the strip's first column x0, to its right one; rows past the tile or the image get an empty descriptor,
+    // whose address is never used.  A lane's offset counts from the left border and wraps to a huge value for
+    // lanes left of it, so lanes outside store nothing.
     __amdgpu_buffer_rsrc_t out_rs[RW];
-    uint32_t out_lead[RW];                                      // byte offset of column x0 from column b0 (<= 0, wrapped)
+    [[maybe_unused]] uint32_t out_skip[RW];
     // The empty statement makes everything below depend on values defined after the loads:
     // none of this arithmetic is moved in front of them.
     unsigned sx0 = x0;
     int sy = y_wave;
     asm volatile("" : "+s"(sx0), "+s"(sy) : : "memory");
     const unsigned sx1 = sx0 + p.strip_pitch;
-    constexpr uint32_t whole_words = WORDS ? ~3u : ~0u;         // WORDS: a row's last word is not stored whole
-    const uintptr_t out_first = img_out + (((size_t)sy * (size_t)p.out_row_pitch) << esh);
-    static_for<0, RW>([&](auto jj) {
-        constexpr int j = decltype(jj)::value;
-        const uintptr_t row_addr = out_first + (size_t)j * ((size_t)p.out_row_pitch << esh);
-        const unsigned a = (unsigned)(row_addr >> esh);         // address in result elements
-        const unsigned b0 = sx0 == 0 && !WORDS ? 0u : sx0 + ((0u - (a + sx0)) & border_mask);
-        const unsigned b1 = min((unsigned)p.m, sx1 + ((0u - (a + sx1)) & border_mask));
-        const uint32_t bytes = (j < out_rows && b1 > b0) ? ((b1 - b0) << esh) & whole_words : 0u;
-        out_rs[j] = make_rsrc(reinterpret_cast<const void*>(row_addr + ((size_t)b0 << esh)), bytes);
-        out_lead[j] = (sx0 - b0) << esh;
-        if constexpr (!WORDS) asm volatile("" : "+s"(out_lead[j]));   // finished here, not next to the store
-    });
+    const uintptr_t out_pitch = p.out_row_bytes;
+    const uintptr_t out_first = img_out + (uintptr_t)(unsigned)sy * out_pitch;
+    if constexpr (WORDS) {
+        static_for<0, RW>([&](auto jj) {
+            constexpr int j = decltype(jj)::value;
+            const uintptr_t row_addr = out_first + (size_t)j * out_pitch;
+            const unsigned a = (unsigned)row_addr, c0 = sx0 << esh, c1 = sx1 << esh;
+            const unsigned b0 = c0 + ((0u - (a + c0)) & 3u), b1 = min((unsigned)p.m << esh, c1 + ((0u - (a + c1)) & 3u));
+            const uint32_t bytes = (j < out_rows && b1 > b0) ? (b1 - b0) & ~3u : 0u;        // the row's last word is not stored whole
+            out_rs[j] = make_rsrc(reinterpret_cast<const void*>(row_addr + b0), bytes);
+        });
+    } else {
+        const uintptr_t at = out_first + (uintptr_t)(sx0 << esh);
+        // An image of very many strips may have one that begins behind its last column.
+        const uint32_t rest = (uint32_t)max(p.m - (int)sx0, 0) << esh, width = p.strip_pitch << esh;
+        int32_t size[RW];                                       // from border to border; signed, as the scalar unit has no saturating subtraction
+        const bool moved = p.flags & HARRIS_TUNE_ALIGNED_STORES;
+        if (RW <= 6 && !moved) {                                // (taller tiles: one way for both, whose registers they need)
+#pragma unroll
+            for (int j = 0; j < RW; ++j) { size[j] = (int32_t)min(rest, width); out_skip[j] = 0u; }
+        } else {
+            const uint32_t right = moved ? 63u : 0u, left = sx0 == 0u ? 0u : right;
+            const uint32_t to_left = 0u - (uint32_t)at, to_right = to_left - width, pitch32 = (uint32_t)out_pitch;
+#pragma unroll
+            for (int j = 0; j < RW; ++j) {
+                out_skip[j] = (to_left - (uint32_t)j * pitch32) & left;
+                size[j] = (int32_t)min(rest, width + ((to_right - (uint32_t)j * pitch32) & right)) - (int32_t)out_skip[j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < RW; ++j) {
+            out_rs[j] = make_rsrc(reinterpret_cast<const void*>(at + (size_t)j * out_pitch + out_skip[j]), j < out_rows ? (uint32_t)max(size[j], 0) : 0u);
+            asm volatile("" : "+s"(out_skip[j]));               // finished here, not next to the store
+        }
+    }
     uint32_t lane_bytes = (lane * PX) << esh;
     asm volatile("" : "+v"(lane_bytes));
     __builtin_amdgcn_sched_barrier(0);
@@ -820,6 +884,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
         } else if constexpr (SHIFTED) {
             realign_row(raw[t], shift[t]);
         }
+        if constexpr (RW == 10 && std::is_same<In, float>::value) __builtin_amdgcn_sched_barrier(0);   // or the binomial instance spills six registers
         gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
         if constexpr (HAND_SOBEL) {
             if constexpr (t < 2) publish(t, gc);
@@ -928,8 +993,8 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             const bool ends = sx0 == 0u || sx1 + 4u > (unsigned)p.m;
             static_for<0, RW>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
-                // -out_lead[j], 0 to 3 bytes: worked out again here, it is cheaper than the scalar registers.
-                const uint32_t shift = (0u - (uint32_t)(out_first + (size_t)j * ((size_t)p.out_row_pitch << esh)) - (sx0 << esh)) & 3u;
+                // Bytes in front of the first aligned word, 0 to 3: worked out again here, it is cheaper than the scalar registers.
+                const uint32_t shift = (0u - (uint32_t)(out_first + (size_t)j * out_pitch) - (sx0 << esh)) & 3u;
                 const PackedRow<KIND> r = pack_row_shifted<KIND>(results[j], p.q_scale, p.q_offset, shift);
                 if constexpr (KIND == HARRIS_OUT_U8) __builtin_amdgcn_raw_buffer_store_b32(r.word[0], out_rs[j], lane_bytes, 0, SAUX);
                 else __builtin_amdgcn_raw_buffer_store_b64(u32x2{r.word[0], r.word[1]}, out_rs[j], lane_bytes, 0, SAUX);
@@ -948,7 +1013,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     } else if (__builtin_expect(p.out_kind == HARRIS_OUT_F32, 1)) {
         store_all([&](auto aux, auto jj) {
             constexpr int j = decltype(jj)::value;
-            store_row<PX, decltype(aux)::value>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+            store_row<PX, decltype(aux)::value>(results[j], out_rs[j], lane_bytes - out_skip[j]);
         });
     } else {
         // A value of its own, or the compiler makes one switch of all kinds and moves the float32 stores behind
@@ -958,17 +1023,17 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
         if (kind == HARRIS_OUT_F16) {
             store_all([&](auto aux, auto jj) {
                 constexpr int j = decltype(jj)::value;
-                store_row_16<PX, false, decltype(aux)::value>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+                store_row_16<PX, false, decltype(aux)::value>(results[j], out_rs[j], lane_bytes - out_skip[j]);
             });
         } else if (kind == HARRIS_OUT_BF16) {
             store_all([&](auto aux, auto jj) {
                 constexpr int j = decltype(jj)::value;
-                store_row_16<PX, true, decltype(aux)::value>(results[j], out_rs[j], lane_bytes + out_lead[j]);
+                store_row_16<PX, true, decltype(aux)::value>(results[j], out_rs[j], lane_bytes - out_skip[j]);
             });
         } else {
             static_for<0, RW>([&](auto jj) {
                 constexpr int j = decltype(jj)::value;
-                if (j < RW - 4 || wave + 1 < n_waves) store_row_8<PX, SAUX>(results[j], p.q_scale, p.q_offset, out_rs[j], lane_bytes + out_lead[j]);
+                if (j < RW - 4 || wave + 1 < n_waves) store_row_8<PX, SAUX>(results[j], p.q_scale, p.q_offset, out_rs[j], lane_bytes - out_skip[j]);
             });
         }
     }

@@ -74,6 +74,9 @@ struct Params {
     float wr, wg, wb;       // gray weights, times the Sobel scale (and 1/255 for 8-bit input)
     float k;                // coarsity constant
     unsigned flags;         // HARRIS_TUNE_* bits, kWriteThrough
+    unsigned long long out_row_bytes, out_image_bytes;        // TILES: the result's pitches in bytes
+    unsigned out_shift;     // log2 of a result element's bytes
+    unsigned strip_reach;   // TILES: columns of a strip's rows that its lanes load
     unsigned out_kind;      // a harris_out_dtype (other than float32: tile kernel only)
     float q_scale, q_offset;   // 8-bit results: code = clamp(rint(fma(v, q_scale, q_offset)), 0, 255)
     int binomial;           // 1: window [1 2 1; 2 4 2; 1 2 1], 0: unweighted 3x3 sum
@@ -87,6 +90,7 @@ struct Params {
     unsigned image_lanes, image_lanes_inverse, images, batch;
     // TILES with shared rows kept, and narrow images: tiles that an XCD takes in a row, and how often.
     unsigned chunk, turns;
+    int far_rows;           // TILES: 1: the rows that a wavefront loads do not lie within 2 GB (rows_are_far)
     int resident;           // TILES: 1: the chip holds all tiles of the launch at once
 };
 
@@ -96,6 +100,13 @@ struct Params {
 HARRIS_HOST_DEVICE constexpr bool hands_sobel(bool from_8_bit, int px) { return from_8_bit && px == 4; }
 HARRIS_HOST_DEVICE constexpr unsigned tile_lds_bytes(bool from_8_bit, int px, unsigned waves) {
     return (hands_sobel(from_8_bit, px) ? 1u + (waves - 1u) * 6u : waves * 4u) * 64u * (unsigned)px * 4u;
+}
+
+// TILES: whether the rows of a wavefront lie too far apart for the 32-bit offsets from the first one's start at which the
+// kernel loads them; those from 2 GB on are for lanes that load nothing.
+inline bool rows_are_far(long long row_pitch, int W, int elem, int rows) {
+    const long long most = 1LL << 31;
+    return row_pitch > most / elem / rows || (rows - 1) * row_pitch * elem + (long long)W * elem > most;
 }
 
 // TILES, 8-bit rows on any byte loaded where they are: the byte of a row of W >= 4 pixels at which the lane of column

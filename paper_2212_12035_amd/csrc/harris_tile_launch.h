@@ -23,6 +23,14 @@ hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 bl
     return hipGetLastError();
 }
 
+// Rows too far apart for 32-bit offsets (Params::far_rows).
+template <typename In>
+hipError_t launch_far_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, 1, 4, kAuxFar, true, false>), grid, block, lds, stream, p);
+    else hipLaunchKernelGGL((harris_tile_kernel<In, 1, 4, kAuxFar, false, false>), grid, block, lds, stream, p);
+    return hipGetLastError();
+}
+
 // WORDS: result rows stored as the aligned words that hold them, four pixels per lane.  Rows of 8-bit input
 // are then always loaded that way too (the planner takes them so wherever a row is not naturally aligned).
 template <typename In, int PX, int RW, bool WORDS>
@@ -32,6 +40,10 @@ hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, h
     // on a CU.
     const size_t lds_needed = harris_launch::tile_lds_bytes(U8, PX, block.x / kWave);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
+    if (p.far_rows) {
+        if constexpr (PX == 1 && RW == 4) return launch_far_tiles<In>(p, grid, block, lds, stream);
+        else return hipErrorInvalidValue;
+    }
     // Many tiles with shared rows kept: dealt to the XCDs by turns (dealt_tile).
     if ((p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) && !(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) grid = dim3(8 * p.chunk, p.turns);
     const bool cached = p.flags & HARRIS_TUNE_CACHED_LOADS, keep = p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS, handoff = p.flags & HARRIS_TUNE_FLAG_HANDOFF;

@@ -586,6 +586,29 @@ def _ulp16(x, fmt):
     return 2.0 ** (e - frac_bits)
 
 
+@pytest.mark.parametrize("dtype, pitch", [("u8", 700000004), ("u8", 715827860), ("u8", 715827901), ("f32", 125000000), ("f32", 180000000), ("f32", 330000000)])
+def test_rows_that_lie_far_apart(gpu, oracle, dtype, pitch):
+    # The rows of one wavefront (four, five or six) just within 2 GB, and further apart.
+    import torch
+    H, W = 7, 70
+    rgb = hi.white_noise_u8(31, 1, H, W) if dtype == "u8" else hi.rectangles_f32(32, 1, H, W)
+    size = torch.from_numpy(rgb).element_size()
+    say("case far rows %s pitch %d bytes" % (dtype, pitch * size))
+    frame = torch.empty((20 * pitch + W,), dtype=torch.uint8 if dtype == "u8" else torch.float32, device="cuda")
+    view = frame.as_strided((1, 3, H, W), (21 * pitch, 7 * pitch, pitch, 1))
+    view.copy_(torch.from_numpy(rgb))
+    for out_dtype in (torch.float32, torch.float16):
+        out = torch.full((1, H - 4, W - 4), -7.0, dtype=out_dtype, device="cuda")
+        gpu.harris_coarsity_typed(view, out, K)
+        want = torch.empty_like(out)
+        gpu.harris_coarsity_typed(torch.from_numpy(rgb).cuda(), want, K)
+        if out_dtype == torch.float32:
+            check(out.cpu().numpy(), oracle.harris(rgb, K))
+        assert float((out.float() - want.float()).abs().max()) <= 1e-2 * float(want.float().abs().max())
+    del frame, view
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
 def test_16_bit_results(gpu, oracle, fmt):
     # Two checks.  (1) The 16-bit result is the float32 result of the same kernel rounded to
