@@ -1,6 +1,7 @@
 // C interface of libharris: argument checks, launch-shape planning, dispatch.
 // Everything here runs on the host and touches no device memory.
 
+#include <float.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -605,12 +606,14 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
     p.out_row_pitch = lay.out_row_pitch; p.out_image_pitch = lay.out_image_pitch;
     p.out_row_bytes = (unsigned long long)lay.out_row_pitch * out_elem_size(out_dtype);
     p.out_image_bytes = (unsigned long long)lay.out_image_pitch * out_elem_size(out_dtype);
-    // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it (and the
-    // 1/255 of 8-bit input) into the three gray weights.
-    const float in_scale = dtype == HARRIS_U8 ? sobel_scale / 255.0f : sobel_scale;
-    p.wr = 0.299f * in_scale;
-    p.wg = 0.587f * in_scale;
-    p.wb = 0.114f * in_scale;
+    // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it into the three gray weights; from 8-bit input, whose
+    // weights are whole numbers, its fourth power and theirs into the factor of the result.  (Scales from 3e9 on have
+    // factors beyond float32; flat regions are to stay zero then.)
+    p.wr = 0.299f * sobel_scale;
+    p.wg = 0.587f * sobel_scale;
+    p.wb = 0.114f * sobel_scale;
+    const double unit = sobel_scale * (262144.0 / 255000.0), gain = unit * unit * unit * unit;
+    p.gain = gain < FLT_MAX ? (float)gain : FLT_MAX;
     p.k = k;
     p.binomial = window == HARRIS_WINDOW_BINOMIAL ? 1 : 0;
     p.q_scale = q_scale;

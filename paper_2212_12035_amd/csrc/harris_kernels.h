@@ -287,28 +287,69 @@ __device__ __forceinline__ void store_row_8(const float (&o)[PX], float scale, f
     }
 }
 
-// Conversion and grayscale: element i of plane c as float (8-bit values are converted; their
-// 1/255 is folded into the gray weights), then gray = wr*R + wg*G + wb*B.
+// Grayscale.  float32 input: gray = wr*R + wg*G + wb*B.  8-bit input: 299 R + 587 G + 114 B, a whole number below 2^18, in units of
+// 2^-18: exact, and so are the sums and differences of gray values that the Sobel responses are made of (whole numbers below 2^21).  The
+// result is multiplied by what that leaves out, the Sobel scale and 1/255000 each to the fourth power (Params::gain), when it is complete.
+constexpr float kGrayUnit = 1.0f / 262144.0f;
 template <typename In, int PX>
 __device__ __forceinline__ void gray_row(const RawRow<In, PX>& r, float wr, float wg, float wb, float (&g)[PX]) {
 #pragma unroll
     for (int i = 0; i < PX; ++i) {
-        float ch[3];
+        if constexpr (std::is_same<In, float>::value) {
+            g[i] = fmaf(wb, __uint_as_float(r.w[2][i]), fmaf(wg, __uint_as_float(r.w[1][i]), wr * __uint_as_float(r.w[0][i])));
+        } else {
+            float ch[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if constexpr (std::is_same<In, float>::value) ch[c] = __uint_as_float(r.w[c][i]);
-            else ch[c] = (float)((r.w[c][i / 4] >> (8 * (i % 4))) & 0xffu);
+            for (int c = 0; c < 3; ++c) ch[c] = (float)((r.w[c][i / 4] >> (8 * (i % 4))) & 0xffu);
+            g[i] = fmaf(114.0f * kGrayUnit, ch[2], fmaf(587.0f * kGrayUnit, ch[1], (299.0f * kGrayUnit) * ch[0]));
         }
-        g[i] = fmaf(wb, ch[2], fmaf(wg, ch[1], wr * ch[0]));
     }
+}
+
+// The same numbers for 8-bit input with four pixels per lane, on the matrix cores.  v_mfma_f32_4x4x4 multiplies sixteen pairs of 4x4
+// matrices, one for every four lanes: each lane brings four values, its column of the right matrix, and gets four, its column of
+// the product.  With a diagonal matrix on the left, lane l of four holding row l, every lane's four pixels of a plane are multiplied by
+// the plane's weight and added to its sums, exactly: bytes and weights are exact in binary16, sums in float32.  A byte becomes
+// binary16 by standing alone in 16 bits, a subnormal number of as many 2^-24; 64 times the weight makes that units of
+// 2^-18.  Six byte permutes and three matrix instructions take the place of twelve conversions and twelve multiply-adds: launches that
+// vector instructions bound gain, 3712x2348 to codes 11.0 us (11.4 without), 31 images of 598x300 to bfloat16 10.3 (10.6), 1580x2832 9.2 (9.5).
+// (Loads that convert, buffer_load_format_d16_xyzw, save the permutes too but run at half the rate: 8192x8192 90 us against 81.)
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+struct GrayMatrix {
+    u32x2 row[3];           // this lane's row of the three matrices
+    uint32_t select[2];     // the permutes that put a lane's pixels 0 and 1, 2 and 3 into halves of a word
+};
+// drop: bits by which the lane's pixels stand further up in the loaded word than they should.
+__device__ __forceinline__ GrayMatrix gray_matrix(unsigned lane, unsigned drop) {
+    const uint32_t half = 0xffffu << (16u * (lane & 1u)), lo = lane & 2u ? 0u : half, hi = lane & 2u ? half : 0u;
+    constexpr uint32_t kWeights[3] = {0x74ac74acu, 0x78967896u, 0x6f206f20u};       // 64 x 299, 64 x 587 and 64 x 114 in binary16, twice
+    GrayMatrix a;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) a.row[c] = u32x2{lo & kWeights[c], hi & kWeights[c]};
+    a.select[0] = 0x0c010c00u + (drop >> 3) * 0x00010001u;
+    a.select[1] = 0x0c030c02u + (drop >> 3) * 0x00010001u;      // may name a byte of the word again: of columns that nobody uses
+    return a;
+}
+__device__ __forceinline__ void gray_row(const RawRow<uint8_t, 4>& r, const GrayMatrix& a, float (&g)[4]) {
+    f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const uint32_t w = r.w[c][0];
+        const u32x2 pixels = {__builtin_amdgcn_perm(w, w, a.select[0]), __builtin_amdgcn_perm(w, w, a.select[1])};
+        sum = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4, a.row[c]), __builtin_bit_cast(f16x4, pixels), sum, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = sum[i];
 }
 
 // ---------------------------------------------------------------- the pipeline state of one lane
 
 template <int PX>
 struct LineBuffers {
-    float g[2][PX];       // the last two gray rows
-    float d[2][PX];       // DIFF: and their differences along the row, [-1 0 1]
+    float g[2][PX];       // the last two gray rows (kQuads: the last one)
+    float d[2][PX];       // kDifferences: and their differences along the row, [-1 0 1]
+    float q[2][PX];       // kQuads: the last row of sums over 2x2 gray values
     float x[2][PX];       // box window: Ix, Iy of the last even row
     float p[2][3][PX];    // Ix*Ix, Ix*Iy, Iy*Iy: of the last odd row (box, in p[1]), of the last two rows (binomial)
     float t[3][PX];       // box window: sums of the products of two neighbouring rows, an odd one and the even one below it
@@ -321,22 +362,41 @@ struct LineBuffers {
 // STAGE 0: gray only (first two rows of a band); 1: also Sobel and products (next
 // two rows); 2: also window sums and coarsity: one result row in o, for the caller to store.
 //
-// Both Sobel kernels are separated, and either order of the two passes costs the same.  DIFF takes the
-// difference along the row first, of gray values that are close to each other: it is small and mostly
-// exact, and what is added up afterwards rounds at that size (1536x2560 float32: error of the result
-// against 64 bits 2.4e-7 of its norm, 3.0e-7 with the sums first).  It keeps two rows of differences
-// more, which 8-bit input, bound by the vector ALUs at full occupancy, pays for (8 images of
-// 1080x1920 to 8-bit codes: 19.2 against 18.4 us): that takes the sums first.  float32 input pays 3 to 7
-// registers a lane and, in launches of 8 to 15 MB in tiles of 4 x 4, up to 4 % (6 images of 260x332 4.16 us, 3.95
-// with the sums first; 4 of 480x642 5.39 / 5.31; larger ones nothing).
+// Both Sobel kernels are separated, and the order of the passes is free at six operations a pixel:
+//   kDifferences  takes the difference along the row first, of gray values that are close to each other: it is small and mostly
+//                 exact, and what is added up afterwards rounds at that size (1536x2560 float32: error of the result
+//                 against 64 bits 2.4e-7 of its norm, 3.0e-7 with the sums first).  float32 input, which pays 3 to 7
+//                 registers a lane for two rows of differences and, in launches of 8 to 15 MB in tiles of 4 x 4, up to 4 % (6 images of 260x332 4.16 us,
+//                 3.95 with the sums first; 4 of 480x642 5.39 / 5.31; larger ones nothing).
+//   kSums         sums down the column first; for float32 instances without these registers.
+//   kQuads        sums over 2x2 gray values first; their differences along the two diagonals are, added and subtracted,
+//                 the responses: three lane shifts a row instead of five.  8-bit input, where every one of these numbers is exact: the
+//                 result's error against 64 bits is 1.1e-7 of its norm, 4.0e-7 with gray values that are rounded.  (The window sums could be taken of the
+//                 diagonal differences themselves, which are the gradient turned by 45 degrees; that saves two more operations a
+//                 pixel, but an edge along the rows or columns then cancels in the determinant: up to 6.1e-7.)
 //
 // A row's Sobel responses can go out to the wavefront above (kSobelOut, in `sobel`) or come from the one below
-// (kSobelIn; gc is not looked at then).
-enum SobelRow { kSobelOwn, kSobelOut, kSobelIn };
-template <int STAGE, int T, int PX, bool BINOM, bool DIFF, int SOBEL>
-__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX], float (&sobel)[2][PX]) {
+// (kSobelIn; gc is not looked at then).  kQuadsIn: gc is the row's 2x2 sums.
+enum SobelRow { kSobelOwn, kSobelOut, kSobelIn, kQuadsIn };
+enum SobelOrder { kSums, kDifferences, kQuads };
+struct Coarsity { float k, gain; };     // gain: kQuads
+
+template <int STAGE, int T, int PX, bool BINOM, int ORDER, int SOBEL>
+__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], const Coarsity& cs, float (&o)[PX], float (&sobel)[2][PX]) {
     constexpr int PS = T % 2;
-    constexpr bool GIVEN = SOBEL == kSobelIn;
+    constexpr bool GIVEN = SOBEL == kSobelIn, DIFF = ORDER == kDifferences, QUADS = ORDER == kQuads;
+    if constexpr (QUADS && SOBEL == kQuadsIn) {
+#pragma unroll
+        for (int i = 0; i < PX; ++i) lb.q[PS][i] = gc[i];
+    } else if constexpr (QUADS && T >= 1 && !GIVEN) {
+        float pair[PX];
+#pragma unroll
+        for (int i = 0; i < PX; ++i) pair[i] = lb.g[1 - PS][i] + gc[i];
+        static_for<0, PX>([&](auto ii) {
+            constexpr int i = decltype(ii)::value;
+            lb.q[PS][i] = column<i + 1, PX>(pair) + pair[i];
+        });
+    }
     [[maybe_unused]] float dx[PX];                // DIFF: [-1 0 1] along the row
     if constexpr (DIFF && !GIVEN) {
         static_for<0, PX>([&](auto ii) {
@@ -349,17 +409,24 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
         [[maybe_unused]] float sy[PX];            // without DIFF: [1 2 1] down the column
         [[maybe_unused]] float dy[PX];            // [-1 0 1] down the column
 #pragma unroll
-        for (int i = 0; i < PX && !GIVEN; ++i) {
+        for (int i = 0; i < PX && !GIVEN && !QUADS; ++i) {
             dy[i] = gc[i] - lb.g[PS][i];
             if constexpr (!DIFF) sy[i] = fmaf(2.0f, lb.g[1 - PS][i], lb.g[PS][i] + gc[i]);
         }
         static_for<0, PX>([&](auto ii) {
             constexpr int i = decltype(ii)::value;
             float ix, iy;
+            [[maybe_unused]] float falling, rising;
+            if constexpr (QUADS && !GIVEN) {
+                falling = column<i + 1, PX>(lb.q[PS]) - lb.q[1 - PS][i];
+                rising = lb.q[PS][i] - column<i + 1, PX>(lb.q[1 - PS]);
+            }
             if constexpr (GIVEN) ix = sobel[0][i];
+            else if constexpr (QUADS) ix = falling - rising;
             else if constexpr (DIFF) ix = fmaf(2.0f, lb.d[1 - PS][i], lb.d[PS][i] + dx[i]);
             else ix = column<i + 2, PX>(sy) - sy[i];
             if constexpr (GIVEN) iy = sobel[1][i];
+            else if constexpr (QUADS) iy = falling + rising;
             else iy = fmaf(2.0f, column<i + 1, PX>(dy), column<i + 2, PX>(dy) + dy[i]);   // [1 2 1] along the row
             if constexpr (SOBEL == kSobelOut) { sobel[0][i] = ix; sobel[1][i] = iy; }
             // Products and window sums down the column (the window is separated too, c = 1 for
@@ -396,7 +463,7 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
         });
     }
 #pragma unroll
-    for (int i = 0; i < PX && !GIVEN; ++i) {
+    for (int i = 0; i < PX && !GIVEN && SOBEL != kQuadsIn; ++i) {
         lb.g[PS][i] = gc[i];
         if constexpr (DIFF) lb.d[PS][i] = dx[i];
     }
@@ -431,15 +498,16 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
         for (int i = 0; i < PX; ++i) {
             float det = fmaf(s[0][i], s[2][i], -(s[1][i] * s[1][i]));
             float tr = s[0][i] + s[2][i];
-            o[i] = fmaf(-(k * tr), tr, det);
+            o[i] = fmaf(-(cs.k * tr), tr, det);
+            if constexpr (QUADS) o[i] *= cs.gain;
         }
     }
 }
 
-template <int STAGE, int T, int PX, bool BINOM, bool DIFF>
-__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], float k, float (&o)[PX]) {
+template <int STAGE, int T, int PX, bool BINOM, int ORDER>
+__device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], const Coarsity& cs, float (&o)[PX]) {
     [[maybe_unused]] float none[2][PX];
-    row_step<STAGE, T, PX, BINOM, DIFF, kSobelOwn>(lb, gc, k, o, none);
+    row_step<STAGE, T, PX, BINOM, ORDER, kSobelOwn>(lb, gc, cs, o, none);
 }
 
 // ---------------------------------------------------------------- the kernel
@@ -454,7 +522,7 @@ __device__ __forceinline__ unsigned xcd_contiguous(unsigned b, unsigned nb) {
 
 template <typename In, int PX, int D, int LAUX, bool BINOM>
 __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::Params p) {
-    constexpr bool DIFF = std::is_same<In, float>::value;
+    constexpr int ORDER = std::is_same<In, float>::value ? kDifferences : kQuads;
     constexpr int U = lcm_c(2, D);            // row steps per loop trip: queue slots and parities stay static
 
     const unsigned lane = threadIdx.x % kWave;
@@ -514,6 +582,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
     });
 
     LineBuffers<PX> lb;
+    const Coarsity cs = {p.k, p.gain};
     float gc[PX], o[PX];
 
     // Rows 0..3 of the band fill the pipeline.
@@ -523,7 +592,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
         __builtin_amdgcn_sched_barrier(0);
         load_row<In, PX, LAUX>(queue[t % D], in_row_ptr(t + D), plane, in_row_size(t + D), load_voff);
         __builtin_amdgcn_sched_barrier(0);
-        row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, o);
+        row_step<(t < 2 ? 0 : 1), t, PX, BINOM, ORDER>(lb, gc, cs, o);
     });
 
     for (int t0 = 4; t0 < steps; t0 += U) {
@@ -540,7 +609,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
             // past the band's end get an empty descriptor and store nothing.
             const int orow = max(0, min(p.n - 1, up ? y0 + rows + 3 - t : y0 + t - 4));
             const __amdgpu_buffer_rsrc_t out_rs = make_rsrc(img_out + (size_t)orow * (size_t)p.out_row_pitch, t < steps ? out_row_bytes : 0u);
-            row_step<2, 4 + u, PX, BINOM, DIFF>(lb, gc, p.k, o);
+            row_step<2, 4 + u, PX, BINOM, ORDER>(lb, gc, cs, o);
             store_row<PX>(o, out_rs, store_voff);
         });
     }
@@ -621,7 +690,7 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // wavefront requests its RW rows (3*RW loads) at once, so no wavefront goes through a
 // chain of dependent memory round trips.  Wavefront w turns its rows into gray,
 // publishes its first four gray rows in LDS and, after one barrier, takes the four
-// gray rows below its own from wavefront w+1 there (8-bit input: two gray rows and two
+// gray rows below its own from wavefront w+1 there (8-bit input: a gray row, a row of 2x2 sums and two
 // of Sobel responses, below): nothing is read twice inside a tile.  Each wavefront then runs the same register pipeline as the band kernel over
 // its RW+4 gray rows and stores RW result rows (the last wavefront has no neighbour
 // below and stores RW-4).  A tile yields NW*RW-4 result rows; the tile below re-reads
@@ -650,7 +719,7 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // to 28 vector registers in scratch memory; 2160x3840 23.0 us, 22.2 without; 2159x3839 to binary16
 // itself 21.9 and 20.8).
 //
-// 8-bit input with four pixels per lane hands over, instead of four gray rows, the first two and the Sobel responses
+// 8-bit input with four pixels per lane hands over, instead of four gray rows, the first one, the 2x2 sums of the first two and the Sobel responses
 // that the wavefront has computed from all four (six rows of LDS): the wavefront above needs exactly these, and does
 // not compute them again (4 instead of 6 rows of responses for 4 result rows; 8192x8192 at 4 x 4: 390 vector
 // operations per wavefront by the counters, 423 before).  8-bit launches that are not held up by memory gain: 16 images of 768x1366 to codes 22.4 us (23.0
@@ -675,9 +744,10 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
     // two rows of differences would push into scratch memory (none that float32 results take by default)
     // take the sums first.
-    constexpr bool DIFF = std::is_same<In, float>::value && !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF)));
+    constexpr int ORDER = std::is_same<In, uint8_t>::value ? kQuads : !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF))) ? kDifferences : kSums;
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
     static_assert(!WORDS || PX == 4, "result rows as aligned words: four pixels per lane");
+    constexpr bool MATRIX = std::is_same<In, uint8_t>::value && PX == 4;
     constexpr bool HAND_SOBEL = harris_launch::hands_sobel(std::is_same<In, uint8_t>::value, PX);
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]; HAND_SOBEL: [1 + (NW - 1) * 6][64][PX]
     __shared__ unsigned ready[16];                              // HANDOFF: wavefront w has published its four rows
@@ -860,6 +930,9 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     __builtin_amdgcn_sched_barrier(0);
 
     LineBuffers<PX> lb;
+    const Coarsity cs = {p.k, p.gain};
+    [[maybe_unused]] GrayMatrix gray;
+    if constexpr (MATRIX) gray = gray_matrix(lane, BYTES ? bytes.drop : 0u);
     float gc[PX], none[PX];
     // The RW result rows stay in registers until the wavefront has used up all its loads and
     // are stored together at the end: bursts of reads and bursts of writes use the memory
@@ -878,16 +951,12 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
 
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
-        if constexpr (BYTES) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) raw[t].w[c][0] >>= bytes.drop;
-        } else if constexpr (SHIFTED) {
-            realign_row(raw[t], shift[t]);
-        }
+        if constexpr (SHIFTED && !BYTES) realign_row(raw[t], shift[t]);
         if constexpr (RW == 10 && std::is_same<In, float>::value) __builtin_amdgcn_sched_barrier(0);   // or the binomial instance spills six registers
-        gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
+        if constexpr (MATRIX) gray_row(raw[t], gray, gc);
+        else gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
         if constexpr (HAND_SOBEL) {
-            if constexpr (t < 2) publish(t, gc);
+            if constexpr (t == 0) publish(0, gc);
         } else if constexpr (t < 4) {
 #pragma unroll
             for (int i = 0; i < PX; ++i) my_halo[(size_t)t * kWave * PX + i] = gc[i];
@@ -903,13 +972,14 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
         }
         if constexpr (HAND_SOBEL && (t == 2 || t == 3)) {
             float sobel[2][PX];
-            row_step<1, t, PX, BINOM, DIFF, kSobelOut>(lb, gc, p.k, none, sobel);
+            row_step<1, t, PX, BINOM, ORDER, kSobelOut>(lb, gc, cs, none, sobel);
             publish(2 * t - 2, sobel[0]);
             publish(2 * t - 1, sobel[1]);
         } else if constexpr (t < 4) {
-            row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, none);
+            row_step<(t < 2 ? 0 : 1), t, PX, BINOM, ORDER>(lb, gc, cs, none);
+            if constexpr (HAND_SOBEL && t == 1) publish(1, lb.q[1]);
         } else {
-            row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
+            row_step<2, t, PX, BINOM, ORDER>(lb, gc, cs, results[t - 4]);
             pin_values<PX>(results[t - 4]);
         }
         // Each row is worked through as soon as it has arrived: without this the compiler
@@ -959,12 +1029,14 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
                 if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (HAND_SOBEL && row >= 2) {
-                row_step<2, t, PX, BINOM, DIFF, kSobelIn>(lb, gc, p.k, results[t - 4], sobel[row - 2]);
-            } else if constexpr (AHEAD && row == 1) {
-                row_step<2, t, PX, BINOM, DIFF>(lb, second, p.k, results[t - 4]);
+                row_step<2, t, PX, BINOM, ORDER, kSobelIn>(lb, gc, cs, results[t - 4], sobel[row - 2]);
+            } else if constexpr (HAND_SOBEL && row == 1) {
+                [[maybe_unused]] float nobody[2][PX];
+                if constexpr (!AHEAD) fetch(row, second);
+                row_step<2, t, PX, BINOM, ORDER, kQuadsIn>(lb, second, cs, results[t - 4], nobody);
             } else {
                 if constexpr (!AHEAD) fetch(row, gc);
-                row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
+                row_step<2, t, PX, BINOM, ORDER>(lb, gc, cs, results[t - 4]);
             }
             pin_values<PX>(results[t - 4]);
         });

@@ -71,7 +71,8 @@ struct Params {
     FastDiv by_tiles_per_image, by_n_strips;   // TILES: division by these two
     unsigned n_blocks;      // workgroups of the launch (the grid size)
     unsigned waves_per_block;  // wavefronts per workgroup (the block size / 64)
-    float wr, wg, wb;       // gray weights, times the Sobel scale (and 1/255 for 8-bit input)
+    float wr, wg, wb;       // float32 input: gray weights, times the Sobel scale
+    float gain;             // 8-bit input: (Sobel scale 2^18 / 255000)^4, the result is that multiple of what the kernel works out
     float k;                // coarsity constant
     unsigned flags;         // HARRIS_TUNE_* bits, kWriteThrough
     unsigned long long out_row_bytes, out_image_bytes;        // TILES: the result's pitches in bytes

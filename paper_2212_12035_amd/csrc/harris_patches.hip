@@ -34,13 +34,13 @@ namespace {
 // row reads the start of the row that follows it in memory, of whichever plane or image: the planner lets it
 // where the images are dense, so that all of this belongs to the call.  Nobody uses it.
 // 8-bit rows start on any byte: a lane loads its four bytes where they are, the last lane of a row the
-// row's last four, shifted down by `drop` bits.
-__device__ __forceinline__ void load_patch_row(RawRow<float, 4>& r, const float* row, size_t plane, uint32_t bytes, uint32_t voff, uint32_t) {
+// row's last four, which gray_row takes from where they stand.
+__device__ __forceinline__ void load_patch_row(RawRow<float, 4>& r, const float* row, size_t plane, uint32_t bytes, uint32_t voff) {
     load_row<float, 4, kAuxDefault>(r, row, plane, bytes, voff);
 }
-__device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint8_t* row, size_t plane, uint32_t, uint32_t voff, uint32_t drop) {
+__device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint8_t* row, size_t plane, uint32_t, uint32_t voff) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) r.w[c][0] = *reinterpret_cast<const u32_any*>(row + c * plane + voff) >> drop;
+    for (int c = 0; c < 3; ++c) r.w[c][0] = *reinterpret_cast<const u32_any*>(row + c * plane + voff);
 }
 
 // Compiled as for workgroups of 1024 threads, twice what the planner launches: within the 64 vector registers that
@@ -95,20 +95,24 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         const int r = y_wave + t;
-        load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? l.in_bytes : 0u, l.in_voff, l.drop);
+        load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? l.in_bytes : 0u, l.in_voff);
     });
     __builtin_amdgcn_sched_barrier(0);
 
-    constexpr bool DIFF = F32;
+    constexpr int ORDER = F32 ? kDifferences : kQuads;
     LineBuffers<PX> lb;
+    const Coarsity cs = {p.k, p.gain};
+    [[maybe_unused]] GrayMatrix gray;
+    if constexpr (!F32) gray = gray_matrix(lane, l.drop);
     float gc[PX], none[PX], results[RW][PX];
     float* my_halo = halo_lds + ((size_t)wave * 4 * kWave + lane) * PX;
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
-        gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
+        if constexpr (F32) gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
+        else gray_row(raw[t], gray, gc);
 #pragma unroll
         for (int i = 0; i < PX; ++i) my_halo[(size_t)t * kWave * PX + i] = gc[i];
-        row_step<(t < 2 ? 0 : 1), t, PX, BINOM, DIFF>(lb, gc, p.k, none);
+        row_step<(t < 2 ? 0 : 1), t, PX, BINOM, ORDER>(lb, gc, cs, none);
         __builtin_amdgcn_sched_barrier(0);
     });
     __syncthreads();
@@ -118,7 +122,7 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
         constexpr int t = decltype(tt)::value;
 #pragma unroll
         for (int i = 0; i < PX; ++i) gc[i] = below[(size_t)(t - RW) * kWave * PX + i];
-        row_step<2, t, PX, BINOM, DIFF>(lb, gc, p.k, results[t - 4]);
+        row_step<2, t, PX, BINOM, ORDER>(lb, gc, cs, results[t - 4]);
         pin_values<PX>(results[t - 4]);
     });
     __builtin_amdgcn_sched_barrier(0);

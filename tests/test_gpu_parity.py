@@ -268,6 +268,28 @@ def test_lds_reservation_changes_nothing_but_the_residency(gpu, oracle):
         assert e.value.status == -3
 
 
+@pytest.mark.parametrize("tune", [None, dict(schedule=1, px=1), dict(schedule=1, px=4), dict(schedule=2, px=1), dict(schedule=2, px=2),
+                                  dict(schedule=2, rows=4, waves_per_block=2), dict(schedule=2, rows=8, waves_per_block=3), dict(flags=512)])
+@pytest.mark.parametrize("window", [0, 1])
+def test_u8_responses_are_exact(gpu, oracle, tune, window):
+    # The Sobel responses of 8-bit images are whole numbers that float32 holds; what is left to round are nine products and eight sums
+    # per window (9 halves of eps each, relative to sums that the trace bounds), two products of those and one of their sum with
+    # itself (k = 0.04), and the factor that follows: below 7 eps of trace^2.  Rounded gray values alone would not show here;
+    # a unit that computes them with less than 18 bits does.
+    import torch
+    H, W = 41, 72
+    rgb = hi.white_noise_u8(19, 3, H, W)
+    rgb[1] = np.where(rgb[1] < 128, 0, 255)                          # the largest steps
+    rgb[2] = rgb[2] // 128                                           # the smallest
+    got = run_gpu(gpu, rgb, k=K, window=window, tuning=tune)
+    for b in range(3):
+        assert rounding_distance(oracle, got[b:b + 1], rgb[b:b + 1], K, 1.0, window) <= 7.0
+    # A Sobel scale that is a power of two changes the exponents alone.
+    for e in (-20, -3, 7, 24):
+        assert np.array_equal(run_gpu(gpu, rgb, k=K, window=window, sobel_scale=2.0 ** e, tuning=tune), got * np.float32(2.0 ** (4 * e)))
+    assert not run_gpu(gpu, np.full_like(rgb, 200), k=K, window=window, sobel_scale=3e38, tuning=tune).any()
+
+
 @pytest.mark.parametrize("rows", [4, 5, 8, 10])
 @pytest.mark.parametrize("waves", [2, 3, 12, 16])        # 6 KB of LDS each: from 12 on more than 64 KB
 def test_u8_sobel_responses_handed_over(gpu, oracle, rows, waves):
