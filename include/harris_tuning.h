@@ -90,9 +90,9 @@ struct harris_tuning {
 #define HARRIS_TUNE_PLAIN_STORES 32u /* strips end at the same column in every row.  With neither bit
                                         the library decides                                         */
 #define HARRIS_TUNE_WORD_STORES 256u /* TILES with px = 4, 16-bit results or 8-bit codes: rows of any width on any
-                                        boundary of their type are stored as the aligned 32-bit words
-                                        that hold them, the ends of each row element by element.  Rows that px = 4
-                                        can store directly are, and plans then leave the bit out; not
+                                        boundary of their type, each lane's four results with one
+                                        store on any byte, the end of a row in pieces.  Rows that px = 4
+                                        can store aligned are, and plans then leave the bit out; not
                                         with HARRIS_TUNE_ALIGNED_STORES                              */
 #define HARRIS_TUNE_PACKED_IMAGES 512u /* TILES with px = 4 and rows = 4, float32 results, at least two images of at
                                         most 128 columns: as many images side by side in a wavefront as

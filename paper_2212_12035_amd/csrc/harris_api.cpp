@@ -45,8 +45,7 @@ bool px4_fits_word_aligned(int dtype, int out_dtype, int W, int rgb_align, int o
 }
 
 // Four pixels per lane for rows of 16-bit results and 8-bit codes on any boundary of their element type:
-// the tile kernel stores the aligned words that hold them and the ends of each row element by
-// element (HARRIS_TUNE_WORD_STORES).
+// the tile kernel stores a lane's four where they belong and the ends of rows in pieces (HARRIS_TUNE_WORD_STORES).
 bool px4_fits_shifted(int dtype, int out_dtype, int rgb_align) {
     return out_dtype != HARRIS_OUT_F32 && !(dtype == HARRIS_F32 && rgb_align % 4 != 0);
 }
@@ -285,7 +284,6 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
                  (px_fits(t.px, dtype, out_dtype, W, rgb_align, out_align) || (t.px == 4 && word_aligned_px4)))) {
         return HARRIS_ERR_ARG;
     }
-    const bool out_shifted = t.flags & HARRIS_TUNE_WORD_STORES;
     if (t.rows < 0 || t.prefetch < 0 || t.waves_per_block < 0 || t.lds_kb < 0 || t.lds_kb > 64) return HARRIS_ERR_ARG;
     // A prefetch depth exists only in the band schedule.
     if (t.schedule == 0) t.schedule = t.prefetch == 0 ? HARRIS_SCHEDULE_TILES : HARRIS_SCHEDULE_BANDS;
@@ -313,8 +311,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     const long long border_reach = (t.flags & HARRIS_TUNE_ALIGNED_STORES) ? 64 / out_elem_size(out_dtype) - 4 : 0;
     // 8-bit rows loaded as aligned words and shifted: the last lane only supplies bytes to its left neighbour.
     const bool in_shifted = dtype == HARRIS_U8 && tile4 && !can_align;
-    // Shifted result rows: the strip's last word may take columns of the lane beyond the strip.
-    const long long max_pitch = (long long)harris_launch::valid_lanes(t.px) * t.px - border_reach - (in_shifted ? 4 : 0) - (out_shifted ? 4 : 0);
+    const long long max_pitch = (long long)harris_launch::valid_lanes(t.px) * t.px - border_reach - (in_shifted ? 4 : 0);
     const long long n_strips = m > 0 ? (m + max_pitch - 1) / max_pitch : 0;
     const long long pitch = n_strips > 0 ? ((m + n_strips - 1) / n_strips + t.px - 1) / t.px * t.px : max_pitch;
 
@@ -515,7 +512,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->out_kind = (unsigned)out_dtype;
         params->in_shifted = in_shifted ? 1 : 0;
         params->out_shift = out_dtype == HARRIS_OUT_F32 ? 2u : out_dtype == HARRIS_OUT_U8 ? 0u : 1u;
-        params->strip_reach = (unsigned)(pitch + 4 + (out_shifted ? 4 : border_reach));
+        params->strip_reach = (unsigned)(pitch + 4 + border_reach);
         params->lds_bytes = (unsigned)t.lds_kb * 1024u;
     }
     return HARRIS_OK;

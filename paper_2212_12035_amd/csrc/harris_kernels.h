@@ -626,61 +626,51 @@ __device__ __forceinline__ void pin_values(float (&v)[PX]) {
 }
 
 // Rows of 16-bit results or 8-bit codes that may start on any byte their element type allows, four
-// pixels per lane (kOutShifted).  Stores are checked against the end of a row by whole 32-bit words, so
-// lanes store the aligned words of the row: with `shift` bytes in front of the strip's first aligned
-// word, a lane's word is the upper bytes of its own packed results and the lower ones of the lane
-// to its right (one lane shift and one byte-align).  The border between two strips lies on such a
-// boundary, so that only a row's first and last word are shared with what lies around the row: their
-// elements, up to three codes or one 16-bit result at either end, are stored one by one by a few lanes
-// of the strip that holds the end (store_row_ends).
-// Against the narrower lanes such rows had before: 2831x4255 float32 to binary16 33.1 us (one pixel per
-// lane: 39.3), 8 images of 1079x1919 uint8 to binary16 25.2 us (49.1), 16 images of 768x1366 uint8 to
-// codes 23.9 us (two pixels per lane: 26.2).
+// pixels per lane (WORDS): a lane stores its four results where they belong, with one store at any byte, which the hardware
+// does; the lane that straddles the end of a row stores the one to three results it has there in one or two pieces.  Nothing is shifted
+// between lanes, no descriptor is worked out, and the border between two strips stays where it is.  Against storing the aligned
+// words of a row, shifted together from two lanes, and its ends element by element: 16 images of 768x1366 uint8 to codes 19.5 us
+// (20.7), 4 of 1289x1121 binomial 10.9 (11.8), 776 of 64x161 13.2 (14.3), 8 of 1079x1919 uint8 to binary16 19.5 (20.2), 3 of
+// 1679x1413 float32 to codes 19.9 (20.6); large float32 launches to 16 bits the same within 0.5 %.
 template <int KIND>
 struct PackedRow {
     static constexpr int NW = KIND == HARRIS_OUT_U8 ? 1 : 2;        // 32-bit words of four results
-    uint32_t own[NW], word[NW];                                     // packed as computed; the aligned words
+    uint32_t w[NW];
 };
-
 template <int KIND>
-__device__ __forceinline__ PackedRow<KIND> pack_row_shifted(const float (&o)[4], float q_scale, float q_offset, uint32_t shift) {
+__device__ __forceinline__ PackedRow<KIND> pack_row(const float (&o)[4], float q_scale, float q_offset) {
     PackedRow<KIND> r;
     if constexpr (KIND == HARRIS_OUT_U8) {
-        r.own[0] = 0u;
+        r.w[0] = 0u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) r.own[0] = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(o[i], q_scale, q_offset), (uint32_t)i, r.own[0]);
+        for (int i = 0; i < 4; ++i) r.w[0] = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(o[i], q_scale, q_offset), (uint32_t)i, r.w[0]);
     } else {
-        r.own[0] = to_16bit_pair<KIND == HARRIS_OUT_BF16>(o[0], o[1]);
-        r.own[1] = to_16bit_pair<KIND == HARRIS_OUT_BF16>(o[2], o[3]);
-    }
-    const uint32_t right = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)r.own[0], 0x130, 0xf, 0xf, true);
-    if constexpr (KIND == HARRIS_OUT_U8) {
-        r.word[0] = __builtin_amdgcn_alignbyte(right, r.own[0], shift);
-    } else {
-        r.word[0] = __builtin_amdgcn_alignbyte(r.own[1], r.own[0], shift);
-        r.word[1] = __builtin_amdgcn_alignbyte(right, r.own[1], shift);
+        r.w[0] = to_16bit_pair<KIND == HARRIS_OUT_BF16>(o[0], o[1]);
+        r.w[1] = to_16bit_pair<KIND == HARRIS_OUT_BF16>(o[2], o[3]);
     }
     return r;
 }
-
-// Bytes [0, lead) and [tail_at, tail_at + tail) of a row of row_bytes bytes, lead and tail below 4: the
-// first come from lane 0's own word, the second from the aligned word number tail_word of the strip.
-template <int KIND, int AUX>
-__device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr_t row, uint32_t row_bytes, uint32_t lead, uint32_t tail,
-                                               uint32_t tail_at, uint32_t tail_word, unsigned lane) {
-    constexpr uint32_t SIZE = KIND == HARRIS_OUT_U8 ? 1u : 2u;
-    const uint32_t first = __builtin_amdgcn_readfirstlane(r.own[0]);
-    uint32_t last = __builtin_amdgcn_readlane(r.word[0], tail_word / PackedRow<KIND>::NW);
-    if constexpr (PackedRow<KIND>::NW == 2) last = (tail_word & 1u) ? __builtin_amdgcn_readlane(r.word[1], tail_word / 2u) : last;
-    // Lanes 0 to 2: the first elements; lanes 4 to 6: the last ones.
-    const bool at_end = lane >= 4u;
-    const uint32_t byte = (lane & 3u) * SIZE;
-    const bool store = at_end ? lane < 8u && byte < tail : byte < lead;
-    const uint32_t at = store ? (at_end ? tail_at : 0u) + byte : 0x80000000u;
-    const uint32_t value = (at_end ? last : first) >> (8u * (byte & 3u));
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const void*>(row), row_bytes);
-    if constexpr (SIZE == 1u) __builtin_amdgcn_raw_buffer_store_b8((unsigned char)value, rs, at, 0, AUX);
-    else __builtin_amdgcn_raw_buffer_store_b16((unsigned short)value, rs, at, 0, AUX);
+typedef u32x2 u32x2_any __attribute__((aligned(1)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+template <typename T> using in_device_memory = __attribute__((address_space(1))) T;      // or the compiler makes flat stores
+// row: the strip's first column in the row; voff the lane's byte offset from there.
+template <int KIND>
+__device__ __forceinline__ void store_packed(const PackedRow<KIND>& r, uintptr_t row, uint32_t voff) {
+    in_device_memory<char>* at = reinterpret_cast<in_device_memory<char>*>(row) + voff;
+    if constexpr (KIND == HARRIS_OUT_U8) __builtin_nontemporal_store(r.w[0], reinterpret_cast<in_device_memory<u32_any>*>(at));
+    else __builtin_nontemporal_store(u32x2{r.w[0], r.w[1]}, reinterpret_cast<in_device_memory<u32x2_any>*>(at));
+}
+// The lane's first `tail` results, 1 to 3.
+template <int KIND>
+__device__ __forceinline__ void store_packed_tail(const PackedRow<KIND>& r, uintptr_t row, uint32_t voff, uint32_t tail) {
+    in_device_memory<char>* at = reinterpret_cast<in_device_memory<char>*>(row) + voff;
+    if constexpr (KIND == HARRIS_OUT_U8) {
+        if (tail & 2u) __builtin_nontemporal_store((uint16_t)r.w[0], reinterpret_cast<in_device_memory<u16_any>*>(at));
+        if (tail & 1u) __builtin_nontemporal_store((uint8_t)(tail & 2u ? r.w[0] >> 16 : r.w[0]), reinterpret_cast<in_device_memory<uint8_t>*>(at + (tail & 2u)));
+    } else {
+        if (tail & 2u) __builtin_nontemporal_store(r.w[0], reinterpret_cast<in_device_memory<u32_any>*>(at));
+        if (tail & 1u) __builtin_nontemporal_store((uint16_t)(tail & 2u ? r.w[1] : r.w[0]), reinterpret_cast<in_device_memory<u16_any>*>(at + (tail & 2u) * 2u));
+    }
 }
 
 // ---------------------------------------------------------------- the tile kernel
@@ -714,7 +704,7 @@ __device__ __forceinline__ void store_row_ends(const PackedRow<KIND>& r, uintptr
 // 8191x8191 88 us (92), 4 of 2159x3839 45.7 (48.6).
 //
 // WORDS (16-bit results or 8-bit codes, four pixels per lane): result rows start on any byte of their
-// type and are stored as the aligned words that hold them (pack_row_shifted).  Instances of their
+// type and are stored where they are (store_packed).  Instances of their
 // own: as a branch of every four-pixel kernel this code cost the others registers (float32, 10 rows: up
 // to 28 vector registers in scratch memory; 2160x3840 23.0 us, 22.2 without; 2159x3839 to binary16
 // itself 21.9 and 20.8).
@@ -746,7 +736,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // take the sums first.
     constexpr int ORDER = std::is_same<In, uint8_t>::value ? kQuads : !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF))) ? kDifferences : kSums;
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
-    static_assert(!WORDS || PX == 4, "result rows as aligned words: four pixels per lane");
+    static_assert(!WORDS || PX == 4, "result rows on any byte: four pixels per lane");
     constexpr bool MATRIX = std::is_same<In, uint8_t>::value && PX == 4;
     constexpr bool HAND_SOBEL = harris_launch::hands_sobel(std::is_same<In, uint8_t>::value, PX);
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]; HAND_SOBEL: [1 + (NW - 1) * 6][64][PX]
@@ -798,7 +788,6 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // With aligned stores the border between this strip and the next lies, in each result row,
     // on the first 64-byte boundary of that row's address at or after the nominal border: up to
     // 12 (float32), 28 (16-bit) or 60 (8-bit) columns further right.
-    // WORDS: the border moves to the next 4-byte boundary, up to 1 or 3 columns.
     const unsigned x0 = (unsigned)strip * p.strip_pitch;        // first result column of this strip
     // Lanes beyond the strip's columns, the border's reach and the 4-column halo request nothing
     // (out-of-range offset).
@@ -889,19 +878,9 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     unsigned sx0 = x0;
     int sy = y_wave;
     asm volatile("" : "+s"(sx0), "+s"(sy) : : "memory");
-    const unsigned sx1 = sx0 + p.strip_pitch;
     const uintptr_t out_pitch = p.out_row_bytes;
     const uintptr_t out_first = img_out + (uintptr_t)(unsigned)sy * out_pitch;
-    if constexpr (WORDS) {
-        static_for<0, RW>([&](auto jj) {
-            constexpr int j = decltype(jj)::value;
-            const uintptr_t row_addr = out_first + (size_t)j * out_pitch;
-            const unsigned a = (unsigned)row_addr, c0 = sx0 << esh, c1 = sx1 << esh;
-            const unsigned b0 = c0 + ((0u - (a + c0)) & 3u), b1 = min((unsigned)p.m << esh, c1 + ((0u - (a + c1)) & 3u));
-            const uint32_t bytes = (j < out_rows && b1 > b0) ? (b1 - b0) & ~3u : 0u;        // the row's last word is not stored whole
-            out_rs[j] = make_rsrc(reinterpret_cast<const void*>(row_addr + b0), bytes);
-        });
-    } else {
+    if constexpr (!WORDS) {
         const uintptr_t at = out_first + (uintptr_t)(sx0 << esh);
         // An image of very many strips may have one that begins behind its last column.
         const uint32_t rest = (uint32_t)max(p.m - (int)sx0, 0) << esh, width = p.strip_pitch << esh;
@@ -1061,23 +1040,28 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     if constexpr (WORDS) {
         auto store_words = [&](auto kind) {
             constexpr int KIND = decltype(kind)::value;
-            // The row's ends lie in this strip or not: decided per row, looked at only where one can.
-            const bool ends = sx0 == 0u || sx1 + 4u > (unsigned)p.m;
-            static_for<0, RW>([&](auto jj) {
-                constexpr int j = decltype(jj)::value;
-                // Bytes in front of the first aligned word, 0 to 3: worked out again here, it is cheaper than the scalar registers.
-                const uint32_t shift = (0u - (uint32_t)(out_first + (size_t)j * out_pitch) - (sx0 << esh)) & 3u;
-                const PackedRow<KIND> r = pack_row_shifted<KIND>(results[j], p.q_scale, p.q_offset, shift);
-                if constexpr (KIND == HARRIS_OUT_U8) __builtin_amdgcn_raw_buffer_store_b32(r.word[0], out_rs[j], lane_bytes, 0, SAUX);
-                else __builtin_amdgcn_raw_buffer_store_b64(u32x2{r.word[0], r.word[1]}, out_rs[j], lane_bytes, 0, SAUX);
-                if (ends && j < out_rows) {
-                    const uint32_t row_bytes = (uint32_t)p.m << esh, b0 = (sx0 << esh) + shift, b1 = min(row_bytes, (sx1 << esh) + shift);
-                    const uint32_t bytes = b1 > b0 ? b1 - b0 : 0u;
-                    const uint32_t lead = sx0 == 0u ? min(shift, row_bytes) : 0u, tail = b1 == row_bytes ? bytes & 3u : 0u;
-                    if (lead + tail != 0u)
-                        store_row_ends<KIND, SAUX>(r, out_first + (size_t)j * ((size_t)p.out_row_pitch << esh), row_bytes, lead, tail, b0 + (bytes & ~3u), bytes / 4u, lane);
-                }
-            });
+            constexpr uint32_t SIZE = KIND == HARRIS_OUT_U8 ? 1u : 2u;
+            const uint32_t columns = (uint32_t)min(max(p.m - (int)sx0, 0), (int)p.strip_pitch), tail = columns & 3u;
+            const uintptr_t at = out_first + (uintptr_t)(sx0 * SIZE);
+            float q_offset = p.q_offset;
+            asm volatile("" : "+v"(q_offset));                  // a multiply-add takes one scalar operand
+            if (lane * 4u + 4u <= columns) {
+                static_for<0, RW>([&](auto jj) {
+                    constexpr int j = decltype(jj)::value;
+                    uintptr_t row = at + (size_t)j * out_pitch;
+                    asm volatile("" : "+s"(row));               // a scalar base for the lanes' offsets
+                    if (j < out_rows) store_packed<KIND>(pack_row<KIND>(results[j], p.q_scale, q_offset), row, lane_bytes);
+                });
+            }
+            if (tail == 0u) return;
+            if (lane == columns / 4u) {
+                static_for<0, RW>([&](auto jj) {
+                    constexpr int j = decltype(jj)::value;
+                    uintptr_t row = at + (size_t)j * out_pitch;
+                    asm volatile("" : "+s"(row));
+                    if (j < out_rows) store_packed_tail<KIND>(pack_row<KIND>(results[j], p.q_scale, q_offset), row, lane_bytes, tail);
+                });
+            }
         };
         if (p.out_kind == HARRIS_OUT_U8) store_words(std::integral_constant<int, HARRIS_OUT_U8>{});
         else if (p.out_kind == HARRIS_OUT_F16) store_words(std::integral_constant<int, HARRIS_OUT_F16>{});

@@ -1,6 +1,6 @@
 // Host-side selection of a tile-kernel instance from a planned launch; included by the
 // translation units that instantiate harris_tile_kernel (two per input type, one of them for result
-// rows stored as aligned words, so that they compile in parallel).
+// rows on any byte, so that they compile in parallel).
 #ifndef HARRIS_TILE_LAUNCH_H
 #define HARRIS_TILE_LAUNCH_H
 
@@ -31,7 +31,7 @@ hipError_t launch_far_tiles(const harris_launch::Params& p, dim3 grid, dim3 bloc
     return hipGetLastError();
 }
 
-// WORDS: result rows stored as the aligned words that hold them, four pixels per lane.  Rows of 8-bit input
+// WORDS: result rows on any byte, four pixels per lane.  Rows of 8-bit input
 // are then always loaded that way too (the planner takes them so wherever a row is not naturally aligned).
 template <typename In, int PX, int RW, bool WORDS>
 hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, hipStream_t stream) {

@@ -1,4 +1,4 @@
-// The tile-schedule kernels for 8-bit input and result rows stored as aligned words (see harris_kernels.h).
+// The tile-schedule kernels for 8-bit input and result rows on any byte (see harris_kernels.h).
 #include "harris_tile_launch.h"
 
 namespace harris_launch {
