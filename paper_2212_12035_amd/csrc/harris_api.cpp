@@ -183,7 +183,6 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
         params->H = H; params->W = W; params->n = n; params->m = m;
         params->rows_per_band = rows;
         params->tiles_per_image = (unsigned)bands;
-        params->by_tiles_per_image = harris_launch::make_fastdiv((unsigned)bands);
         params->n_blocks = (unsigned)blocks;
         params->waves_per_block = (unsigned)waves;
         params->flags = c.flags;
@@ -489,8 +488,7 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
         params->strip_pitch = (unsigned)pitch;
         params->n_bands = (unsigned)n_bands;
         params->tiles_per_image = (unsigned)tiles_per_image;
-        params->by_tiles_per_image = harris_launch::make_fastdiv(tiles_per_image > 0 ? (unsigned)tiles_per_image : 1u);
-        params->by_n_strips = harris_launch::make_fastdiv(n_strips > 0 ? (unsigned)n_strips : 1u);
+        params->far_rows = 0;
         params->blocks_x = (unsigned)blocks_x;
         params->blocks_per_image = (unsigned)blocks_per_image;
         params->n_blocks = (unsigned)blocks;
@@ -583,26 +581,33 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
         out_align = common_alignment(out_align, lay.out_image_pitch * out_elem_size(out_dtype));
     }
 
-    harris_launch::Params p = {};
+    harris_launch::Params p;
     harris_tuning shape;
     long long n_blocks = 0;
     int rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, tuning, &shape, &n_blocks, &p);
     if (rc != HARRIS_OK) return rc;
     if (empty) return HARRIS_OK;
-    // Rows of hundreds of megabytes, or that far apart: the one kernel that addresses each by itself, whatever shape was asked for.
-    if (shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) && harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows)) {
-        const harris_tuning narrow = {HARRIS_SCHEDULE_TILES, 1, 4, 0, 4, 0u, 0};
-        rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, &narrow, &shape, &n_blocks, &p);
+    const auto place = [&] {
+        p.rgb = rgb;
+        p.out = out;
+        p.in_row_pitch = lay.rgb_row_pitch; p.in_plane_pitch = lay.rgb_plane_pitch; p.in_image_pitch = lay.rgb_image_pitch;
+        p.out_row_pitch = lay.out_row_pitch; p.out_image_pitch = lay.out_image_pitch;
+        if (batch == 1) p.in_image_pitch = p.out_image_pitch = 0;       // of no matter, and they may be long
+        p.out_row_bytes = (unsigned long long)lay.out_row_pitch * out_elem_size(out_dtype);
+        p.out_image_bytes = (unsigned long long)p.out_image_pitch * out_elem_size(out_dtype);
+    };
+    place();
+    // Rows of hundreds of megabytes or that far apart, images of more than 2^32 pixels: the kernels that address each row by itself, whatever shape was asked for.
+    if (shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) &&
+        (harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows) || !harris_launch::compact::fits(p))) {
+        const harris_tuning four = {HARRIS_SCHEDULE_TILES, shape.px == 4 && !(shape.flags & HARRIS_TUNE_WORD_STORES) ? 4 : 1, 4, 0, 4, 0u, 0};
+        rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, &four, &shape, &n_blocks, &p);
         if (rc != HARRIS_OK) return rc;
+        place();
         p.far_rows = 1;
+        p.by_tiles_per_image = harris_launch::make_fastdiv(p.tiles_per_image);
+        p.by_n_strips = harris_launch::make_fastdiv(p.n_strips);
     }
-
-    p.rgb = rgb;
-    p.out = out;
-    p.in_row_pitch = lay.rgb_row_pitch; p.in_plane_pitch = lay.rgb_plane_pitch; p.in_image_pitch = lay.rgb_image_pitch;
-    p.out_row_pitch = lay.out_row_pitch; p.out_image_pitch = lay.out_image_pitch;
-    p.out_row_bytes = (unsigned long long)lay.out_row_pitch * out_elem_size(out_dtype);
-    p.out_image_bytes = (unsigned long long)lay.out_image_pitch * out_elem_size(out_dtype);
     // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it into the three gray weights; from 8-bit input, whose
     // weights are whole numbers, its fourth power and theirs into the factor of the result.  (Scales from 3e9 on have
     // factors beyond float32; flat regions are to stay zero then.)

@@ -306,6 +306,17 @@ __device__ __forceinline__ void gray_row(const RawRow<In, PX>& r, float wr, floa
     }
 }
 
+// The same of float32 input in the registers of the red row.  Ten rows in flight leave a wavefront of 128 registers none for another row: the
+// compiler, which does not reuse a loaded row's registers one by one, spills there.
+template <int PX>
+__device__ __forceinline__ void gray_row_in_place(RawRow<float, PX>& r, float wr, float wg, float wb, float (&g)[PX]) {
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+        asm("v_mul_f32_e32 %0, %1, %0" : "+v"(r.w[0][i]) : "s"(wr));
+        g[i] = fmaf(wb, __uint_as_float(r.w[2][i]), fmaf(wg, __uint_as_float(r.w[1][i]), __uint_as_float(r.w[0][i])));
+    }
+}
+
 // The same numbers for 8-bit input with four pixels per lane, on the matrix cores.  v_mfma_f32_4x4x4 multiplies sixteen pairs of 4x4
 // matrices, one for every four lanes: each lane brings four values, its column of the right matrix, and gets four, its column of
 // the product.  With a diagonal matrix on the left, lane l of four holding row l, every lane's four pixels of a plane are multiplied by
@@ -727,10 +738,12 @@ __device__ __forceinline__ void store_packed_tail(const PackedRow<KIND>& r, uint
 // 23.1 (23.9), 1536x2560 7.04 (7.47), 480x640 3.06 (3.28), 16 images of 768x1366 to codes 19.6 (20.8), 31 of 598x300 to
 // bfloat16 10.6 (10.9), 64x96 float32 2.66 (2.80).  float32 tiles of 8 rows and more gain nothing and keep a descriptor per row.
 //
-// kAuxFar: a wavefront's rows do not lie within 2 GB of each other; 64-bit addresses for each row (one lane width, PX = 1; run() in
-// harris_api.cpp sees to it).
-template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool SMALL = false, bool WORDS = false>
-__global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::Params p) {
+// kAuxFar: a wavefront's rows do not lie within 2 GB of each other, or pitches do not fit the compact arguments: 64-bit addresses for each row and all
+// arguments whole (four rows per wavefront; run() in harris_api.cpp sees to it).
+// Args: compact::Params, or Params for kAuxFar.
+template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED, bool SMALL, bool WORDS, typename Args>
+__device__ __forceinline__ void harris_tile(const Args& args) {
+    const harris_launch::compact::Tile p = harris_launch::compact::unpack(args, sizeof(In), RW);
     // Ten rows fill the 128 vector registers that a workgroup of 16 wavefronts leaves each.  Instances that the
     // two rows of differences would push into scratch memory (none that float32 results take by default)
     // take the sums first.
@@ -767,9 +780,9 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     }
     // Every workgroup that gets here has a tile, and every wavefront of it reaches the barrier.
 
-    const unsigned img = harris_launch::fastdiv(tile, p.by_tiles_per_image);
-    const unsigned rem = tile - img * p.tiles_per_image;
-    const int band = (int)harris_launch::fastdiv(rem, p.by_n_strips);
+    const unsigned img = harris_launch::compact::image_of(args, tile);
+    const unsigned rem = tile - img * args.tiles_per_image;
+    const int band = (int)harris_launch::compact::band_of(args, rem);
     const int strip = (int)(rem - (unsigned)band * p.n_strips);
 
     const int tile_rows = p.rows_per_band;                      // result rows per tile: NW*RW - 4
@@ -805,7 +818,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     // right than otherwise, which supplies the last lane's missing bytes); the descriptor's
     // size stops the lanes right of the row.
     [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_reach + 4 ? col : 0x80000000u;
-    constexpr bool BYTES = SHIFTED && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
+    constexpr bool BYTES = SHIFTED && LAUX != kAuxFar && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
     // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does (byte_lane).  Rows below
     // the image load its last one, and nobody uses what comes of them.
     [[maybe_unused]] const harris_launch::ByteLane bytes = harris_launch::byte_lane(col, (unsigned)p.W);
@@ -853,7 +866,7 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
                     if (shared) load_row_shifted<kAuxDefault>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
                     else load_row_shifted<kAuxNonTemporal>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
                 } else {
-                    load_row_shifted<LAUX>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
+                    load_row_shifted<LAUX == kAuxFar ? kAuxDefault : LAUX>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
                 }
             } else if constexpr (LAUX == kAuxKeepShared) {
                 if (shared) load_row<In, PX, kAuxDefault>(raw[t], row_in, plane, row_bytes, load_voff);
@@ -931,8 +944,8 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
         if constexpr (SHIFTED && !BYTES) realign_row(raw[t], shift[t]);
-        if constexpr (RW == 10 && std::is_same<In, float>::value) __builtin_amdgcn_sched_barrier(0);   // or the binomial instance spills six registers
         if constexpr (MATRIX) gray_row(raw[t], gray, gc);
+        else if constexpr (RW == 10) gray_row_in_place<PX>(raw[t], p.wr, p.wg, p.wb, gc);
         else gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
         if constexpr (HAND_SOBEL) {
             if constexpr (t == 0) publish(0, gc);
@@ -1093,6 +1106,15 @@ __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::
             });
         }
     }
+}
+
+template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED = false, bool SMALL = false, bool WORDS = false>
+__global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::compact::Params args) {
+    harris_tile<In, PX, RW, LAUX, BINOM, HANDOFF, SHIFTED, SMALL, WORDS>(args);
+}
+template <typename In, int PX, bool BINOM, bool SHIFTED>
+__global__ __launch_bounds__(1024) void harris_far_tile_kernel(const harris_launch::Params args) {
+    harris_tile<In, PX, 4, kAuxFar, BINOM, false, SHIFTED, false, false>(args);
 }
 
 }  // namespace

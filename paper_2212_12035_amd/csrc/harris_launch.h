@@ -68,7 +68,7 @@ struct Params {
     unsigned n_strips;      // strips per band
     unsigned strip_pitch;   // result columns per strip (a multiple of px, at most valid_lanes(px)*px; 12 less with aligned stores)
     unsigned tiles_per_image;  // n_bands * n_strips (TILES: one workgroup each)
-    FastDiv by_tiles_per_image, by_n_strips;   // TILES: division by these two
+    FastDiv by_tiles_per_image, by_n_strips;   // TILES: division by these two, where far_rows
     unsigned n_blocks;      // workgroups of the launch (the grid size)
     unsigned waves_per_block;  // wavefronts per workgroup (the block size / 64)
     float wr, wg, wb;       // float32 input: gray weights, times the Sobel scale
@@ -91,9 +91,107 @@ struct Params {
     unsigned image_lanes, image_lanes_inverse, images, batch;
     // TILES with shared rows kept, and narrow images: tiles that an XCD takes in a row, and how often.
     unsigned chunk, turns;
-    int far_rows;           // TILES: 1: the rows that a wavefront loads do not lie within 2 GB (rows_are_far)
+    int far_rows;           // TILES: 1: the rows that a wavefront loads do not lie within 2 GB (rows_are_far), or compact::fits does not hold
     int resident;           // TILES: 1: the chip holds all tiles of the launch at once
 };
+
+// TILES: the same in 96 bytes, which is what the kernels take.  The runtime writes a launch's arguments into memory
+// that the GPU reads, from some host cores slowly: an empty kernel with 240 bytes then takes 3.8 us a launch, with 96 bytes 2.8 (2.5 and 2.4 from the others).
+// Pitches of 2^32 elements and more, result rows of 2 GB and rows that are far apart take Params itself (compact::fits).
+namespace compact {
+
+// Division by a divisor of at most 2^31 of numbers below 2^31: floor(x mul / 2^(31 + l)) with l = ceil(log2 d) and mul = ceil(2^(31 + l) / d), which is at
+// most 2^32 - 1 and off by less than d / d, so that x times the error stays below 2^(31 + l).  (Granlund and Montgomery 1994, theorem 4.2.)
+inline unsigned divide_shift(unsigned d) { return d <= 1u ? 0u : 32u - (unsigned)__builtin_clz(d - 1u); }
+inline unsigned divide_mul(unsigned d) { return (unsigned)(((1ull << (31 + divide_shift(d))) + d - 1) / d); }
+HARRIS_HOST_DEVICE inline unsigned divide(unsigned x, unsigned mul, unsigned l) { return (unsigned)(((unsigned long long)x * mul) >> (31u + l)); }
+
+struct Params {
+    const void* rgb;
+    void* out;
+    unsigned in_row_bytes, out_row_bytes;
+    unsigned in_plane, in_image, out_image;     // in elements
+    int H, W;
+    unsigned n_strips, tiles_per_image, n_blocks, chunk;
+    unsigned by_tiles_per_image, by_n_strips;   // divide_mul
+    float weights[3];                           // float32 input: wr, wg, wb; 8-bit input: gain
+    float k, q_scale, q_offset;
+    // strip_pitch 8 bits, strip_reach - strip_pitch = 4 << e: e 3, wavefronts - 1: 4, divide_shift of tiles_per_image and n_strips 5 each,
+    // out_kind 2, out_shift 2, not dealt to the XCDs 1, borders moved 1, written through 1.
+    unsigned bits;
+};
+static_assert(sizeof(Params) == 96, "more than the runtime writes quickly");
+
+inline bool fits(const harris_launch::Params& p) {
+    const long long most = 1LL << 32;
+    return !p.far_rows && p.in_plane_pitch < most && p.in_image_pitch < most && p.out_image_pitch < most && p.out_row_bytes < (1ull << 31);
+}
+
+inline Params pack(const harris_launch::Params& p, int elem) {
+    Params c;
+    c.rgb = p.rgb; c.out = p.out;
+    c.in_row_bytes = (unsigned)(p.in_row_pitch * elem); c.out_row_bytes = (unsigned)p.out_row_bytes;
+    c.in_plane = (unsigned)p.in_plane_pitch; c.in_image = (unsigned)p.in_image_pitch; c.out_image = (unsigned)p.out_image_pitch;
+    c.H = p.H; c.W = p.W;
+    c.n_strips = p.n_strips; c.tiles_per_image = p.tiles_per_image; c.n_blocks = p.n_blocks; c.chunk = p.chunk;
+    c.by_tiles_per_image = divide_mul(p.tiles_per_image); c.by_n_strips = divide_mul(p.n_strips);
+    c.weights[0] = elem == 1 ? p.gain : p.wr; c.weights[1] = p.wg; c.weights[2] = p.wb;
+    c.k = p.k; c.q_scale = p.q_scale; c.q_offset = p.q_offset;
+    unsigned e = 0;
+    while (e < 7 && p.strip_pitch + (4u << e) < p.strip_reach) ++e;
+    c.bits = p.strip_pitch | e << 8 | (p.waves_per_block - 1u) << 11 | divide_shift(p.tiles_per_image) << 15 | divide_shift(p.n_strips) << 20 |
+             p.out_kind << 25 | p.out_shift << 27 | (p.flags & HARRIS_TUNE_NO_XCD_REMAP ? 1u << 29 : 0u) | (p.flags & HARRIS_TUNE_ALIGNED_STORES ? 1u << 30 : 0u) |
+             (p.flags & kWriteThrough ? 1u << 31 : 0u);
+    return c;
+}
+
+// What the kernel works with; `rows` result and input rows of a wavefront.
+struct Tile {
+    const void* rgb;
+    void* out;
+    unsigned long long in_row_pitch, in_plane_pitch, in_image_pitch;    // in elements
+    unsigned long long out_row_bytes, out_image_bytes;
+    int H, W, n, m, rows_per_band;
+    unsigned n_strips, strip_pitch, strip_reach, n_blocks, chunk, waves_per_block, flags, out_kind, out_shift;
+    float wr, wg, wb, gain, k, q_scale, q_offset;
+};
+HARRIS_HOST_DEVICE inline Tile unpack(const Params& c, unsigned elem, int rows) {
+    Tile t;
+    const unsigned waves = (c.bits >> 11 & 15u) + 1u;
+    t.rgb = c.rgb; t.out = c.out;
+    t.in_row_pitch = c.in_row_bytes / elem; t.in_plane_pitch = c.in_plane; t.in_image_pitch = c.in_image;
+    t.out_shift = c.bits >> 27 & 3u;
+    t.out_row_bytes = c.out_row_bytes; t.out_image_bytes = (unsigned long long)c.out_image << t.out_shift;
+    t.H = c.H; t.W = c.W; t.n = c.H - 4; t.m = c.W - 4;
+    t.rows_per_band = rows * (int)waves - 4;
+    t.n_strips = c.n_strips; t.n_blocks = c.n_blocks; t.chunk = c.chunk; t.waves_per_block = waves;
+    t.strip_pitch = c.bits & 255u;
+    t.strip_reach = t.strip_pitch + (4u << (c.bits >> 8 & 7u));
+    t.flags = (c.bits >> 29 & 1u) * HARRIS_TUNE_NO_XCD_REMAP | (c.bits >> 30 & 1u) * HARRIS_TUNE_ALIGNED_STORES | (c.bits >> 31) * kWriteThrough;
+    t.out_kind = c.bits >> 25 & 3u;
+    t.wr = t.gain = c.weights[0]; t.wg = c.weights[1]; t.wb = c.weights[2];
+    t.k = c.k; t.q_scale = c.q_scale; t.q_offset = c.q_offset;
+    return t;
+}
+HARRIS_HOST_DEVICE inline Tile unpack(const harris_launch::Params& p, unsigned, int) {
+    Tile t;
+    t.rgb = p.rgb; t.out = p.out;
+    t.in_row_pitch = (unsigned long long)p.in_row_pitch; t.in_plane_pitch = (unsigned long long)p.in_plane_pitch; t.in_image_pitch = (unsigned long long)p.in_image_pitch;
+    t.out_shift = p.out_shift; t.out_row_bytes = p.out_row_bytes; t.out_image_bytes = p.out_image_bytes;
+    t.H = p.H; t.W = p.W; t.n = p.n; t.m = p.m; t.rows_per_band = p.rows_per_band;
+    t.n_strips = p.n_strips; t.n_blocks = p.n_blocks; t.chunk = p.chunk; t.waves_per_block = p.waves_per_block;
+    t.strip_pitch = p.strip_pitch; t.strip_reach = p.strip_reach; t.flags = p.flags; t.out_kind = p.out_kind;
+    t.wr = p.wr; t.wg = p.wg; t.wb = p.wb; t.gain = p.gain;
+    t.k = p.k; t.q_scale = p.q_scale; t.q_offset = p.q_offset;
+    return t;
+}
+// Image of a tile, and band of a tile of an image.
+HARRIS_HOST_DEVICE inline unsigned image_of(const Params& c, unsigned tile) { return divide(tile, c.by_tiles_per_image, c.bits >> 15 & 31u); }
+HARRIS_HOST_DEVICE inline unsigned band_of(const Params& c, unsigned tile) { return divide(tile, c.by_n_strips, c.bits >> 20 & 31u); }
+HARRIS_HOST_DEVICE inline unsigned image_of(const harris_launch::Params& p, unsigned tile) { return fastdiv(tile, p.by_tiles_per_image); }
+HARRIS_HOST_DEVICE inline unsigned band_of(const harris_launch::Params& p, unsigned tile) { return fastdiv(tile, p.by_n_strips); }
+
+}  // namespace compact
 
 // TILES: whether a wavefront hands the one above it Sobel responses (harris_tile_kernel says when), and the bytes of LDS
 // that the wavefronts of a workgroup then need: six rows of all but the first, which has a row to write to, or
@@ -152,6 +250,52 @@ HARRIS_HOST_DEVICE inline PatchLane patch_lane(const Params& p, unsigned images,
     l.drop = l.col > last_col ? 8u * ((l.col - last_col) & 3u) : 0u;
     return l;
 }
+
+// Narrow images: the arguments of their kernel, 88 bytes (namespace compact says why).  The planner keeps an image's pitch below 2^30 elements, and with it
+// those of rows and planes.
+namespace compact_patch {
+
+struct Params {
+    const void* rgb;
+    void* out;
+    unsigned in_row, in_plane, in_image, out_row, out_image;    // in elements
+    int H, W;
+    unsigned bands, n_blocks, chunk, batch, by_bands;           // by_bands: compact::divide_mul
+    float weights[3], k;                                        // as in compact::Params
+    unsigned image_lanes_inverse;
+    unsigned bits;                                              // rows_per_band 5 bits, divide_shift of bands 5, image_lanes 6, images 7
+};
+static_assert(sizeof(Params) <= 96, "more than the runtime writes quickly");
+
+inline Params pack(const harris_launch::Params& p, int elem) {
+    Params c;
+    c.rgb = p.rgb; c.out = p.out;
+    c.in_row = (unsigned)p.in_row_pitch; c.in_plane = (unsigned)p.in_plane_pitch; c.in_image = (unsigned)p.in_image_pitch;
+    c.out_row = (unsigned)p.out_row_pitch; c.out_image = (unsigned)p.out_image_pitch;
+    c.H = p.H; c.W = p.W;
+    c.bands = p.tiles_per_image; c.n_blocks = p.n_blocks; c.chunk = p.chunk; c.batch = p.batch; c.by_bands = compact::divide_mul(p.tiles_per_image);
+    c.weights[0] = elem == 1 ? p.gain : p.wr; c.weights[1] = p.wg; c.weights[2] = p.wb;
+    c.k = p.k;
+    c.image_lanes_inverse = p.image_lanes_inverse;
+    c.bits = (unsigned)p.rows_per_band | compact::divide_shift(p.tiles_per_image) << 5 | p.image_lanes << 10 | p.images << 16;
+    return c;
+}
+HARRIS_HOST_DEVICE inline harris_launch::Params unpack(const Params& c) {
+    harris_launch::Params p;
+    p.rgb = c.rgb; p.out = c.out;
+    p.in_row_pitch = c.in_row; p.in_plane_pitch = c.in_plane; p.in_image_pitch = c.in_image;
+    p.out_row_pitch = c.out_row; p.out_image_pitch = c.out_image;
+    p.H = c.H; p.W = c.W; p.n = c.H - 4; p.m = c.W - 4;
+    p.rows_per_band = (int)(c.bits & 31u);
+    p.tiles_per_image = c.bands; p.n_blocks = c.n_blocks; p.chunk = c.chunk; p.batch = c.batch;
+    p.wr = p.gain = c.weights[0]; p.wg = c.weights[1]; p.wb = c.weights[2];
+    p.k = c.k;
+    p.image_lanes = c.bits >> 10 & 63u; p.images = c.bits >> 16 & 127u; p.image_lanes_inverse = c.image_lanes_inverse;
+    return p;
+}
+HARRIS_HOST_DEVICE inline unsigned group_of(const Params& c, unsigned tile) { return compact::divide(tile, c.by_bands, c.bits >> 5 & 31u); }
+
+}  // namespace compact_patch
 
 // Enqueue the fused kernel.  `shape` must come from harris_plan (all fields set).
 // Returns a harris_status.

@@ -50,7 +50,8 @@ __device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint
 // TURNS: a launch of several turns.  Smaller ones, which one latency bounds, have a workgroup per tile and less to
 // work out before the first load (259 uint8 images of 49x30 4.39 us, dealt as turns are 4.48; 569 float32 of 68x20 4.68 / 4.76).
 template <typename In, bool BINOM, bool TURNS>
-__global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris_patch_kernel(const harris_launch::Params p) {
+__global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris_patch_kernel(const harris_launch::compact_patch::Params args) {
+    const harris_launch::Params p = harris_launch::compact_patch::unpack(args);
     constexpr int PX = 4, RW = 4;
     constexpr bool F32 = std::is_same<In, float>::value;
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]
@@ -71,7 +72,7 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
     } else {
         tile = xcd_contiguous(blockIdx.x, p.n_blocks);
     }
-    const unsigned group = harris_launch::fastdiv(tile, p.by_tiles_per_image);      // of p.images images
+    const unsigned group = harris_launch::compact_patch::group_of(args, tile);      // of p.images images
     const int band = (int)(tile - group * p.tiles_per_image);
 
     const int tile_rows = p.rows_per_band;
@@ -152,10 +153,11 @@ namespace {
 template <typename In>
 void enqueue(const harris_launch::Params& p, dim3 block, hipStream_t stream) {
     const dim3 one(p.n_blocks), turns(8 * p.chunk, p.turns);
-    if (p.turns == 1 && p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, false>), one, block, p.lds_bytes, stream, p);
-    else if (p.turns == 1) hipLaunchKernelGGL((harris_patch_kernel<In, false, false>), one, block, p.lds_bytes, stream, p);
-    else if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, true>), turns, block, p.lds_bytes, stream, p);
-    else hipLaunchKernelGGL((harris_patch_kernel<In, false, true>), turns, block, p.lds_bytes, stream, p);
+    const harris_launch::compact_patch::Params c = harris_launch::compact_patch::pack(p, sizeof(In));
+    if (p.turns == 1 && p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, false>), one, block, p.lds_bytes, stream, c);
+    else if (p.turns == 1) hipLaunchKernelGGL((harris_patch_kernel<In, false, false>), one, block, p.lds_bytes, stream, c);
+    else if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, true>), turns, block, p.lds_bytes, stream, c);
+    else hipLaunchKernelGGL((harris_patch_kernel<In, false, true>), turns, block, p.lds_bytes, stream, c);
 }
 
 }  // namespace

@@ -11,23 +11,24 @@ namespace {
 // Enqueues the instance that the other arguments and the call's flags name.
 template <typename In, int PX, int RW, int LAUX, bool HANDOFF, bool SHIFTED, bool WORDS>
 hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
+    const harris_launch::compact::Params c = harris_launch::compact::pack(p, sizeof(In));
     if constexpr (std::is_same<In, uint8_t>::value && PX == 4 && RW == 4 && LAUX == kAuxKeepShared && !WORDS) {
         if (p.resident) {
-            if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, p);
-            else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, p);
+            if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, c);
+            else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, true, WORDS>), grid, block, lds, stream, c);
             return hipGetLastError();
         }
     }
-    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, false, WORDS>), grid, block, lds, stream, p);
-    else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, false, WORDS>), grid, block, lds, stream, p);
+    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, true, HANDOFF, SHIFTED, false, WORDS>), grid, block, lds, stream, c);
+    else hipLaunchKernelGGL((harris_tile_kernel<In, PX, RW, LAUX, false, HANDOFF, SHIFTED, false, WORDS>), grid, block, lds, stream, c);
     return hipGetLastError();
 }
 
-// Rows too far apart for 32-bit offsets (Params::far_rows).
-template <typename In>
+// Rows too far apart for 32-bit offsets, or pitches too long for the compact arguments (Params::far_rows).
+template <typename In, int PX, bool SHIFTED>
 hipError_t launch_far_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
-    if (p.binomial) hipLaunchKernelGGL((harris_tile_kernel<In, 1, 4, kAuxFar, true, false>), grid, block, lds, stream, p);
-    else hipLaunchKernelGGL((harris_tile_kernel<In, 1, 4, kAuxFar, false, false>), grid, block, lds, stream, p);
+    if (p.binomial) hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, true, SHIFTED>), grid, block, lds, stream, p);
+    else hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, false, SHIFTED>), grid, block, lds, stream, p);
     return hipGetLastError();
 }
 
@@ -41,8 +42,14 @@ hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, h
     const size_t lds_needed = harris_launch::tile_lds_bytes(U8, PX, block.x / kWave);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
     if (p.far_rows) {
-        if constexpr (PX == 1 && RW == 4) return launch_far_tiles<In>(p, grid, block, lds, stream);
-        else return hipErrorInvalidValue;
+        if constexpr (RW == 4 && !WORDS && PX != 2) {
+            if constexpr (U8 && PX == 4) {
+                if (p.in_shifted) return launch_far_tiles<In, PX, true>(p, grid, block, lds, stream);
+            }
+            return launch_far_tiles<In, PX, false>(p, grid, block, lds, stream);
+        } else {
+            return hipErrorInvalidValue;
+        }
     }
     // Many tiles with shared rows kept: dealt to the XCDs by turns (dealt_tile).
     if ((p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) && !(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) grid = dim3(8 * p.chunk, p.turns);

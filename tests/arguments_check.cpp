@@ -1,0 +1,135 @@
+// Host check of the compact kernel arguments (namespaces compact and compact_patch of harris_launch.h): over random calls of
+// the C interface, what a kernel unpacks is what the planner decided, or the launch takes the kernels with whole
+// arguments; and the division they use is exact.  Built and run by tests/test_abi_host.py; prints "ok ..." or the first fault.
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include <initializer_list>
+
+#include "harris_launch.h"
+
+namespace harris_launch {
+
+static long long tiles = 0, patches = 0, far = 0;
+static bool wrong = false;
+
+#define SAME(a, b) do { if ((a) != (b)) { std::printf("%s is not %s\n", #a, #b); wrong = true; } } while (0)
+template <typename T>
+static void same_bits(const T& a, const T& b, const char* what) {
+    if (std::memcmp(&a, &b, sizeof(T)) != 0) { std::printf("%s differs\n", what); wrong = true; }
+}
+
+static void check_tile(const Params& p, const harris_tuning& shape, int dtype) {
+    const unsigned elem = dtype == HARRIS_U8 ? 1u : 4u;
+    const compact::Params c = compact::pack(p, (int)elem);
+    const compact::Tile t = compact::unpack(c, elem, shape.rows), w = compact::unpack(p, elem, shape.rows);
+    SAME(t.rgb, w.rgb); SAME(t.out, w.out);
+    SAME(t.in_row_pitch, w.in_row_pitch); SAME(t.in_plane_pitch, w.in_plane_pitch); SAME(t.in_image_pitch, w.in_image_pitch);
+    SAME(t.out_row_bytes, w.out_row_bytes); SAME(t.out_image_bytes, w.out_image_bytes);
+    SAME(t.H, w.H); SAME(t.W, w.W); SAME(t.n, w.n); SAME(t.m, w.m); SAME(t.rows_per_band, w.rows_per_band);
+    SAME(t.n_strips, w.n_strips); SAME(t.strip_pitch, w.strip_pitch); SAME(t.strip_reach, w.strip_reach);
+    SAME(t.n_blocks, w.n_blocks); SAME(t.chunk, w.chunk); SAME(t.waves_per_block, w.waves_per_block);
+    SAME(t.flags, w.flags & (HARRIS_TUNE_NO_XCD_REMAP | HARRIS_TUNE_ALIGNED_STORES | kWriteThrough));
+    SAME(t.out_kind, w.out_kind); SAME(t.out_shift, w.out_shift);
+    if (dtype == HARRIS_U8) same_bits(t.gain, w.gain, "gain");
+    else { same_bits(t.wr, w.wr, "wr"); same_bits(t.wg, w.wg, "wg"); same_bits(t.wb, w.wb, "wb"); }
+    same_bits(t.k, w.k, "k"); same_bits(t.q_scale, w.q_scale, "q_scale"); same_bits(t.q_offset, w.q_offset, "q_offset");
+    for (unsigned tile : {0u, 1u, p.n_strips - 1u, p.n_strips, p.tiles_per_image - 1u, p.tiles_per_image, p.n_blocks / 2u, p.n_blocks - 1u}) {
+        SAME(compact::image_of(c, tile), tile / p.tiles_per_image);
+        SAME(compact::band_of(c, tile % p.tiles_per_image), tile % p.tiles_per_image / p.n_strips);
+    }
+}
+
+static void check_patch(const Params& p, int dtype) {
+    const compact_patch::Params c = compact_patch::pack(p, dtype == HARRIS_U8 ? 1 : 4);
+    const Params t = compact_patch::unpack(c);
+    SAME(t.rgb, p.rgb); SAME(t.out, p.out);
+    SAME(t.in_row_pitch, p.in_row_pitch); SAME(t.in_plane_pitch, p.in_plane_pitch); SAME(t.in_image_pitch, p.in_image_pitch);
+    SAME(t.out_row_pitch, p.out_row_pitch); SAME(t.out_image_pitch, p.out_image_pitch);
+    SAME(t.H, p.H); SAME(t.W, p.W); SAME(t.n, p.n); SAME(t.m, p.m); SAME(t.rows_per_band, p.rows_per_band);
+    SAME(t.tiles_per_image, p.tiles_per_image); SAME(t.n_blocks, p.n_blocks); SAME(t.chunk, p.chunk); SAME(t.batch, p.batch);
+    SAME(t.image_lanes, p.image_lanes); SAME(t.image_lanes_inverse, p.image_lanes_inverse); SAME(t.images, p.images);
+    if (dtype == HARRIS_U8) same_bits(t.gain, p.gain, "gain");
+    else { same_bits(t.wr, p.wr, "wr"); same_bits(t.wg, p.wg, "wg"); same_bits(t.wb, p.wb, "wb"); }
+    same_bits(t.k, p.k, "k");
+    for (unsigned tile : {0u, p.tiles_per_image - 1u, p.tiles_per_image, p.n_blocks / 2u, p.n_blocks - 1u}) SAME(compact_patch::group_of(c, tile), tile / p.tiles_per_image);
+}
+
+int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int dtype, void*) {
+    if (n_blocks != (long long)p.n_blocks) return HARRIS_ERR_LAUNCH;
+    if (shape.schedule != HARRIS_SCHEDULE_TILES) return HARRIS_OK;
+    if (shape.flags & HARRIS_TUNE_PACKED_IMAGES) { ++patches; check_patch(p, dtype); return HARRIS_OK; }
+    if (p.far_rows) {
+        ++far;
+        if (shape.rows != 4 || !(shape.px == 4 || shape.px == 1) || (shape.flags & (HARRIS_TUNE_WORD_STORES | HARRIS_TUNE_FLAG_HANDOFF))) { std::printf("no such far kernel\n"); wrong = true; }
+        return HARRIS_OK;
+    }
+    ++tiles;
+    if (!compact::fits(p) || rows_are_far(p.in_row_pitch, p.W, dtype == HARRIS_U8 ? 1 : 4, shape.rows)) { std::printf("does not fit\n"); wrong = true; }
+    check_tile(p, shape, dtype);
+    return HARRIS_OK;
+}
+size_t grouped_workspace_floats(int, int, int, int) { return 0; }
+int launch_grouped(const void*, int, int, int, int, float, float, int, int, float*, float*, void*) { return HARRIS_ERR_LAUNCH; }
+float* scratch_of_current_device() { return nullptr; }
+int launch_copy_probe(const void*, int, int, int, int, float*, void*) { return HARRIS_ERR_LAUNCH; }
+int launch_stream_probe(int, const void*, void*, long long, void*) { return HARRIS_ERR_LAUNCH; }
+
+}  // namespace harris_launch
+
+static uint64_t state = 0x9e3779b97f4a7c15ull;
+static uint32_t next_u32() {
+    state ^= state << 13; state ^= state >> 7; state ^= state << 17;
+    return (uint32_t)(state >> 16);
+}
+static long long below(long long n) { return (long long)(next_u32() % (uint64_t)n); }
+static long long spread(int bits) { return 1 + below(1LL << below(bits + 1)); }      // over the logarithm
+
+static bool divides(uint32_t x, uint32_t d) {
+    namespace c = harris_launch::compact;
+    if (c::divide(x, c::divide_mul(d), c::divide_shift(d)) == x / d) return true;
+    std::printf("mismatch: %u / %u\n", x, d);
+    return false;
+}
+
+int main() {
+    for (uint32_t d = 1; d <= 1024; ++d) {
+        for (uint32_t x = 0; x <= 3072; ++x) if (!divides(x, d)) return 1;
+        for (uint32_t q = 0x7fffffffu / d, i = 0; i < 3; ++i, --q) for (uint32_t o = 0; o < 2; ++o) if (q * d + o >= 1u && q * d + o - 1u <= 0x7fffffffu && !divides(q * d + o - 1u, d)) return 1;
+    }
+    for (int l = 1; l <= 31; ++l)
+        for (int o = -2; o <= 2; ++o) {
+            const uint32_t d = (uint32_t)((1ull << l) + o);
+            if (d == 0u || d > 0x80000000u) continue;
+            for (uint32_t x : {0u, 1u, d - 1u, d, d + 1u, 0x7ffffffeu, 0x7fffffffu}) if (x <= 0x7fffffffu && !divides(x, d)) return 1;
+            for (int i = 0; i < 4000; ++i) if (!divides(next_u32() >> 1, d)) return 1;
+        }
+    for (int i = 0; i < 2000000; ++i) {
+        uint32_t d = next_u32() >> (1 + next_u32() % 31);
+        if (!divides(next_u32() >> 1, d == 0u ? 1u : d)) return 1;
+    }
+
+    void *rgb = reinterpret_cast<void*>(4096), *out = reinterpret_cast<void*>(1 << 20);
+    for (int i = 0; i < 400000 && !harris_launch::wrong; ++i) {
+        const int dtype = (int)below(2), kind = (int)below(4), batch = (int)(below(3) ? spread(12) : 1);
+        const int H = 4 + (int)spread(below(8) ? 13 : 24), W = 4 + (int)spread(below(8) ? 13 : 27);
+        harris_layout lay = {W, (long long)H * W, 3LL * H * W, W - 4, (long long)(H - 4) * (W - 4)};
+        if (below(3) == 0) {
+            lay.rgb_row_pitch += below(2) ? below(64) : spread(31);
+            lay.rgb_plane_pitch = lay.rgb_row_pitch * H + (below(2) ? 0 : spread(34));
+            lay.rgb_image_pitch = 3 * lay.rgb_plane_pitch + (below(2) ? 0 : spread(34));
+            lay.out_row_pitch += below(2) ? below(64) : spread(32);
+            lay.out_image_pitch = lay.out_row_pitch * H + (below(2) ? 0 : spread(34));
+        }
+        harris_tuning t = {(int)below(2) * HARRIS_SCHEDULE_TILES, (int)below(2) * 4, 0, 0, 0, 0u, 0};
+        if (below(3) == 0) { static const int rows[] = {0, 4, 5, 6, 8, 9, 10}; t.rows = rows[below(7)]; t.waves_per_block = 2 + (int)below(15); t.flags = (unsigned)below(1024); }
+        const harris_tuning* tuning = below(2) ? &t : nullptr;
+        const char* at = static_cast<const char*>(rgb) + (dtype == HARRIS_U8 ? below(4) : 4 * below(4));
+        if (kind == HARRIS_OUT_U8) harris_coarsity_quantized(at, dtype, batch, H, W, &lay, 0.04f, 0.5f, (int)below(2), 1.5f, 90.0f, static_cast<uint8_t*>(out), tuning, nullptr);
+        else harris_coarsity_typed(at, dtype, batch, H, W, &lay, 0.04f, 2.0f, (int)below(2), out, kind, tuning, nullptr);
+    }
+    if (harris_launch::wrong) return 1;
+    if (harris_launch::tiles < 50000 || harris_launch::patches < 1000 || harris_launch::far < 1000) { std::printf("too few: %lld %lld %lld\n", harris_launch::tiles, harris_launch::patches, harris_launch::far); return 1; }
+    std::printf("ok %lld tiles, %lld patches, %lld far\n", harris_launch::tiles, harris_launch::patches, harris_launch::far);
+    return 0;
+}

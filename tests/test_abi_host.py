@@ -441,6 +441,18 @@ def test_index_division_by_multiplication_is_exact(tmp_path):
     assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout
 
 
+def test_compact_kernel_arguments(tmp_path):
+    # The tile kernels and those for narrow images take their arguments in 96 bytes: what they unpack is what the planner
+    # decided, over random calls, and calls that do not fit go to the kernels with whole arguments.
+    import subprocess
+    csrc = os.path.join(ROOT, "paper_2212_12035_amd", "csrc")
+    exe = str(tmp_path / "arguments_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
+                    os.path.join(ROOT, "tests", "arguments_check.cpp"), os.path.join(csrc, "harris_api.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout
+
+
 def test_planned_launches(tmp_path):
     # Batches of narrow images in every combination of gaps between rows, planes and images: whatever
     # kernel the planner takes, no lane loads a byte that belongs to no row of the call (harris.h excepts

@@ -608,19 +608,22 @@ def _ulp16(x, fmt):
     return 2.0 ** (e - frac_bits)
 
 
-@pytest.mark.parametrize("dtype, pitch", [("u8", 700000004), ("u8", 715827860), ("u8", 715827901), ("f32", 125000000), ("f32", 180000000), ("f32", 330000000)])
-def test_rows_that_lie_far_apart(gpu, oracle, dtype, pitch):
-    # The rows of one wavefront (four, five or six) just within 2 GB, and further apart.
+@pytest.mark.parametrize("dtype, W, row, plane, image", [
+    ("u8", 70, 700000004, 0, 0), ("u8", 72, 715827860, 0, 0), ("u8", 71, 715827901, 0, 0), ("f32", 70, 125000000, 0, 0), ("f32", 70, 180000000, 0, 0),
+    ("f32", 71, 330000000, 0, 0), ("u8", 300, 304, 1 << 32, 0), ("u8", 299, 301, 0, (1 << 32) + 4), ("f32", 300, 300, (1 << 32) + 8, 0), ("u8", 300, 300, (1 << 32) - 4, 0)])
+def test_rows_planes_and_images_that_lie_far_apart(gpu, oracle, dtype, W, row, plane, image):
+    # The rows of one wavefront (four, five or six) just within 2 GB, and further apart; planes and images of 2^32 elements and just less.
     import torch
-    H, W = 7, 70
-    rgb = hi.white_noise_u8(31, 1, H, W) if dtype == "u8" else hi.rectangles_f32(32, 1, H, W)
-    size = torch.from_numpy(rgb).element_size()
-    say("case far rows %s pitch %d bytes" % (dtype, pitch * size))
-    frame = torch.empty((20 * pitch + W,), dtype=torch.uint8 if dtype == "u8" else torch.float32, device="cuda")
-    view = frame.as_strided((1, 3, H, W), (21 * pitch, 7 * pitch, pitch, 1))
+    H, B = 7, 2 if image else 1
+    plane = plane or 7 * row
+    image = image or 3 * plane
+    rgb = hi.white_noise_u8(31, B, H, W) if dtype == "u8" else hi.rectangles_f32(32, B, H, W)
+    say("case far %s rows %d planes %d images %d" % (dtype, row, plane, image))
+    frame = torch.empty(((B - 1) * image + 2 * plane + 6 * row + W,), dtype=torch.uint8 if dtype == "u8" else torch.float32, device="cuda")
+    view = frame.as_strided((B, 3, H, W), (image, plane, row, 1))
     view.copy_(torch.from_numpy(rgb))
     for out_dtype in (torch.float32, torch.float16):
-        out = torch.full((1, H - 4, W - 4), -7.0, dtype=out_dtype, device="cuda")
+        out = torch.full((B, H - 4, W - 4), -7.0, dtype=out_dtype, device="cuda")
         gpu.harris_coarsity_typed(view, out, K)
         want = torch.empty_like(out)
         gpu.harris_coarsity_typed(torch.from_numpy(rgb).cuda(), want, K)
