@@ -49,7 +49,11 @@ __device__ __forceinline__ void load_patch_row(RawRow<uint8_t, 4>& r, const uint
 //
 // TURNS: a launch of several turns.  Smaller ones, which one latency bounds, have a workgroup per tile and less to
 // work out before the first load (259 uint8 images of 49x30 4.39 us, dealt as turns are 4.48; 569 float32 of 68x20 4.68 / 4.76).
-template <typename In, bool BINOM, bool TURNS>
+//
+// PAIRS: narrow 8-bit images on any byte.  A load of four bytes that starts between words costs an access per half lane, a
+// wavefront's 32 instead of one or a few, and these launches are bound by that: 1296 images of 111x17 took 9.80 us.  Here a
+// lane loads the two aligned words around its four pixels and shifts them together: 6.43 us.
+template <typename In, bool BINOM, bool TURNS, bool PAIRS>
 __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris_patch_kernel(const harris_launch::compact_patch::Params args) {
     const harris_launch::Params p = harris_launch::compact_patch::unpack(args);
     constexpr int PX = 4, RW = 4;
@@ -93,22 +97,43 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
 
     RawRow<In, PX> raw[RW];
     const size_t plane = (size_t)p.in_plane_pitch;
-    static_for<0, RW>([&](auto tt) {
-        constexpr int t = decltype(tt)::value;
-        const int r = y_wave + t;
-        load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? l.in_bytes : 0u, l.in_voff);
-    });
+    [[maybe_unused]] u32x2 pair[RW][3];
+    [[maybe_unused]] uint32_t first_byte;                       // the lane's column in its image's first row, from the aligned word at or before the group
+    const auto row_offset = [&](int t, int c) { return (uint32_t)min(y_wave + t, p.H - 1) * (uint32_t)p.in_row_pitch + (uint32_t)c * (uint32_t)plane; };
+    if constexpr (PAIRS) {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(in);
+        const uint32_t lead = (uint32_t)at & 3u;
+        // The end is the end of the word that holds the group's last byte; a word that begins past it is dropped by itself.
+        // Columns past W and rows past H hold other pixels of the group, and no stored result depends on them.
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const void*>(at - lead), (lead + images * (uint32_t)p.in_image_pitch + 3u) & ~3u);
+        first_byte = lead + (live ? l.image * (uint32_t)p.in_image_pitch + col : 0u);
+        static_for<0, RW>([&](auto tt) {
+            constexpr int t = decltype(tt)::value;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) pair[t][c] = __builtin_amdgcn_raw_buffer_load_b64(rs, (first_byte + row_offset(t, c)) & ~3u, 0, kAuxDefault);
+        });
+    } else {
+        static_for<0, RW>([&](auto tt) {
+            constexpr int t = decltype(tt)::value;
+            const int r = y_wave + t;
+            load_patch_row(raw[t], in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch, plane, r < p.H ? l.in_bytes : 0u, l.in_voff);
+        });
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     constexpr int ORDER = F32 ? kDifferences : kQuads;
     LineBuffers<PX> lb;
     const Coarsity cs = {p.k, p.gain};
     [[maybe_unused]] GrayMatrix gray;
-    if constexpr (!F32) gray = gray_matrix(lane, l.drop);
+    if constexpr (!F32) gray = gray_matrix(lane, PAIRS ? 0u : l.drop);
     float gc[PX], none[PX], results[RW][PX];
     float* my_halo = halo_lds + ((size_t)wave * 4 * kWave + lane) * PX;
     static_for<0, RW>([&](auto tt) {
         constexpr int t = decltype(tt)::value;
+        if constexpr (PAIRS) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) raw[t].w[c][0] = __builtin_amdgcn_alignbyte(pair[t][c].y, pair[t][c].x, (first_byte + row_offset(t, c)) & 3u);
+        }
         if constexpr (F32) gray_row<In, PX>(raw[t], p.wr, p.wg, p.wb, gc);
         else gray_row(raw[t], gray, gc);
 #pragma unroll
@@ -150,14 +175,25 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
 
 namespace {
 
-template <typename In>
+template <typename In, bool PAIRS>
 void enqueue(const harris_launch::Params& p, dim3 block, hipStream_t stream) {
     const dim3 one(p.n_blocks), turns(8 * p.chunk, p.turns);
     const harris_launch::compact_patch::Params c = harris_launch::compact_patch::pack(p, sizeof(In));
-    if (p.turns == 1 && p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, false>), one, block, p.lds_bytes, stream, c);
-    else if (p.turns == 1) hipLaunchKernelGGL((harris_patch_kernel<In, false, false>), one, block, p.lds_bytes, stream, c);
-    else if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, true>), turns, block, p.lds_bytes, stream, c);
-    else hipLaunchKernelGGL((harris_patch_kernel<In, false, true>), turns, block, p.lds_bytes, stream, c);
+    if (p.turns == 1 && p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, false, PAIRS>), one, block, p.lds_bytes, stream, c);
+    else if (p.turns == 1) hipLaunchKernelGGL((harris_patch_kernel<In, false, false, PAIRS>), one, block, p.lds_bytes, stream, c);
+    else if (p.binomial) hipLaunchKernelGGL((harris_patch_kernel<In, true, true, PAIRS>), turns, block, p.lds_bytes, stream, c);
+    else hipLaunchKernelGGL((harris_patch_kernel<In, false, true, PAIRS>), turns, block, p.lds_bytes, stream, c);
+}
+
+// Rows that follow each other without a gap and do not all start on words, up to the widths where pairs win (us, single words /
+// pairs): 528 images of 66x11 6.27 / 5.57, 2292 of 55x14 6.38 / 5.35, 3000 of 50x21 10.66 / 7.00, 3886 of 130x14 32.0 / 28.9.
+// A launch of one turn, up to twice as wide: 214 of 42x46 4.39 / 4.19, 103 of 120x51 4.58 / 4.47, but 273 of 108x73 5.51 / 5.52 and
+// 179 of 25x122 4.17 / 4.26.  Between the two other things bound it: 5833 of 26x27 9.11 / 9.42, 690 of 123x47 8.18 / 8.51 (larger
+// launches, from 10 million pixels on, take 0.91 to 0.97 with their images in the last-level cache, 1.0 to 1.01 without).
+bool in_pairs(const harris_launch::Params& p) {
+    const bool dense = p.in_row_pitch == p.W && p.in_plane_pitch == p.in_row_pitch * p.H && p.in_image_pitch == 3 * p.in_plane_pitch;
+    const bool on_words = p.W % 4 == 0 && reinterpret_cast<uintptr_t>(p.rgb) % 4 == 0;
+    return dense && !on_words && p.W <= (p.turns == 1 ? 60 : 24);
 }
 
 }  // namespace
@@ -166,8 +202,9 @@ namespace harris_launch {
 
 int launch_patches(const Params& p, int dtype, unsigned block, void* stream_) {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    if (dtype == HARRIS_U8) enqueue<uint8_t>(p, dim3(block), stream);
-    else enqueue<float>(p, dim3(block), stream);
+    if (dtype != HARRIS_U8) enqueue<float, false>(p, dim3(block), stream);
+    else if (in_pairs(p)) enqueue<uint8_t, true>(p, dim3(block), stream);
+    else enqueue<uint8_t, false>(p, dim3(block), stream);
     return (int)hipGetLastError();
 }
 

@@ -290,6 +290,28 @@ def test_u8_responses_are_exact(gpu, oracle, tune, window):
     assert not run_gpu(gpu, np.full_like(rgb, 200), k=K, window=window, sobel_scale=3e38, tuning=tune).any()
 
 
+@pytest.mark.parametrize("batch,H,W", [(2, 9, 5), (17, 5, 9), (40, 33, 11), (7, 21, 24), (3001, 50, 21), (6, 61, 57), (33, 8, 60)])
+@pytest.mark.parametrize("window", [0, 1])
+def test_narrow_u8_images_on_any_byte(gpu, oracle, batch, H, W, window):
+    import torch
+    # Dense images, the last byte of which ends their allocation, against rows with a gap behind them, whose lanes load their bytes one
+    # by one: the gray values are exact, so every bit of the results is the same.
+    import torch
+    size = batch * 3 * H * W
+    flat = torch.from_numpy(hi.white_noise_u8(batch + W, batch, H, W).reshape(-1)).cuda()
+    spaced = torch.zeros((batch, 3, H, W + 3), dtype=torch.uint8, device="cuda")
+    spaced[..., :W] = flat.view(batch, 3, H, W)
+    want = torch.empty((batch, H - 4, W - 4), device="cuda")
+    gpu.harris_coarsity_pitched(spaced[..., :W], want, K, window=window)
+    check(want[:2].cpu().numpy(), oracle.harris(flat.view(batch, 3, H, W)[:2].cpu().numpy(), K, 1.0, window))
+    for lead in range(4):
+        say("case u8 %dx3x%dx%d window %d, first byte %d" % (batch, H, W, window, lead))
+        room = torch.full((lead + size,), 255, dtype=torch.uint8, device="cuda")
+        room[lead:] = flat
+        got = gpu.harris_coarsity_ex(room[lead:].view(batch, 3, H, W), K, window=window)
+        assert torch.equal(got, want)
+
+
 @pytest.mark.parametrize("rows", [4, 5, 8, 10])
 @pytest.mark.parametrize("waves", [2, 3, 12, 16])        # 6 KB of LDS each: from 12 on more than 64 KB
 def test_u8_sobel_responses_handed_over(gpu, oracle, rows, waves):
