@@ -35,9 +35,9 @@ SETTLE_MS = 20.0               # untimed launches before the timed region, in GP
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (summaries under profiles/), valid only
 # for the kernel sources they were taken with: (sha256 of the csrc files without comments, {workload: bytes}).
-TRAFFIC_SOURCES_SHA256 = "99863ea9ec95ff5a7c4ab86c76d67c4de45b7939372d4c886af40f8633717307"
-TRAFFIC_BYTES = {"noise_f32_1536x2560": 65199200, "rects_f32_64x1080x1920": 2283600892,
-                 "blobs_f32_2832x4256": 199652355, "noise_u8_8192x8192": 510160381}
+TRAFFIC_SOURCES_SHA256 = "f529cd54518b48cddaf402557427e5644f0fc74feb34d2094f3f92e001bca7b2"
+TRAFFIC_BYTES = {"noise_f32_1536x2560": 65077604, "rects_f32_64x1080x1920": 2281529135,
+                 "blobs_f32_2832x4256": 199561869, "noise_u8_8192x8192": 512372486}
 
 
 def kernel_sources_sha256():

@@ -999,10 +999,9 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
         // HAND_SOBEL: two rows are read ahead of their use where a launch's tiles are all resident at once and a CU has
         // few wavefronts to hide the reads (AHEAD).  Others hide them, and are slower with the rows in registers
         // (13 images of 277x448 to float32 4.81 us ahead, 5.00 not; 600x800 3.65 / 3.73; but 8 of 1080x1920 to binary16
-        // 21.3 / 19.7, 4000x3000 to codes 15.0 / 14.3, 9 of 2442x1862 to codes on any byte 54.3 / 51.8).  With the binomial
-        // window that takes 67 vector registers, which leave seven of eight wavefronts: SMALL launches do without
-        // (1080x1920 5.10 us, ahead 5.31; 13 of 277x448 5.00 / 5.19; 1200x1600 5.06 / 5.27); one tile per CU does not mind
-        // (480x640 3.42 us ahead, 3.46 not).
+        // 21.3 / 19.7, 4000x3000 to codes 15.0 / 14.3, 9 of 2442x1862 to codes on any byte 54.3 / 51.8).  SMALL launches
+        // with the binomial window do without, as it gains a little here and loses a little there (1080x1920 5.01 us, ahead
+        // 4.97; 1200x1600 4.96 / 4.90; 4 images of 600x800 5.37 / 5.43); one tile per CU gains (480x640 3.42 us ahead, 3.46 not).
         constexpr bool AHEAD = HAND_SOBEL && !WORDS && (LAUX == kAuxNonTemporal || (SMALL && !BINOM));
         [[maybe_unused]] float sobel[2][2][PX];
         [[maybe_unused]] float second[PX];
