@@ -35,9 +35,9 @@ SETTLE_MS = 20.0               # untimed launches before the timed region, in GP
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (summaries under profiles/), valid only
 # for the kernel sources they were taken with: (sha256 of the csrc files without comments, {workload: bytes}).
-TRAFFIC_SOURCES_SHA256 = "f529cd54518b48cddaf402557427e5644f0fc74feb34d2094f3f92e001bca7b2"
-TRAFFIC_BYTES = {"noise_f32_1536x2560": 65077604, "rects_f32_64x1080x1920": 2281529135,
-                 "blobs_f32_2832x4256": 199561869, "noise_u8_8192x8192": 512372486}
+TRAFFIC_SOURCES_SHA256 = "6f0724d72fb94a9925aed15277c439520308670f7bfae0dcff24ad0e74b39018"
+TRAFFIC_BYTES = {"noise_f32_1536x2560": 65073431, "rects_f32_64x1080x1920": 2281446681,
+                 "blobs_f32_2832x4256": 199504607, "noise_u8_8192x8192": 511741675}
 
 
 def kernel_sources_sha256():

@@ -183,7 +183,7 @@ __device__ __forceinline__ void load_row(RawRow<In, PX>& r, const In* row, size_
 // misaligned and none leaves the aligned words that hold the row's bytes.  With the row
 // starting `shift` bytes into its first word, a lane's four pixels are the upper bytes of its
 // word and the lower bytes of the word of the lane to its right (realign_row).
-// voff is the lane's first column (a multiple of 4); shift[c] is kept for realign_row.
+// voff is the lane's first column (a multiple of 4); shift[c] is kept for realign_row, which takes it modulo 4.
 template <int AUX>
 __device__ __forceinline__ void load_row_shifted(RawRow<uint8_t, 4>& r, uint32_t (&shift)[3], const uint8_t* row, size_t plane,
                                                  uint32_t row_bytes, uint32_t voff) {
@@ -204,7 +204,7 @@ __device__ __forceinline__ void realign_row(RawRow<uint8_t, 4>& r, const uint32_
     for (int c = 0; c < 3; ++c) {
         const uint32_t own = r.w[c][0];
         const uint32_t right = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0x130, 0xf, 0xf, true);
-        r.w[c][0] = __builtin_amdgcn_alignbyte(right, own, shift[c]);
+        r.w[c][0] = __builtin_amdgcn_alignbyte(right, own, shift[c] & 3u);
     }
 }
 
@@ -822,7 +822,7 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does (byte_lane).  Rows below
     // the image load its last one, and nobody uses what comes of them.
     [[maybe_unused]] const harris_launch::ByteLane bytes = harris_launch::byte_lane(col, (unsigned)p.W);
-    constexpr bool NEAR = LAUX != kAuxFar && (std::is_same<In, uint8_t>::value ? !SHIFTED || BYTES : RW <= 6);
+    constexpr bool NEAR = LAUX != kAuxFar && (std::is_same<In, uint8_t>::value ? !SHIFTED || BYTES || !BINOM : RW <= 6);
     if constexpr (NEAR) {
         const int last = p.H - 1 - y_wave;                      // the image's last row, counted from this wavefront's first; negative below the image
         const uint32_t pitch = (uint32_t)p.in_row_pitch * (uint32_t)sizeof(In), last_off = (uint32_t)max(last, 0) * pitch;
@@ -832,6 +832,18 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
         // row has a descriptor that ends with it.
         constexpr bool EACH = std::is_same<In, float>::value;
         const uint32_t rows = last < 0 ? 0u : min(last_off, (RW - 1) * pitch) + in_row_bytes;
+        // SHIFTED words: a plane's rows from the aligned word that its first one begins in; as each row's descriptor ends with the
+        // word of the row's last byte, no access leaves the words that hold the row's bytes.  Box window, us (a descriptor per row and plane): 8191x8191
+        // 85.1 (87.0), 8 of 1079x1919 23.8 (24.6), 2831x4255 18.3 (18.9), 64 of 333x499 15.5 (16.4); with the binomial window it gains 2 %
+        // or loses as much (8 of 1079x1919 25.3 (25.8), 12 of 1001x1303 25.1 (24.7)) and is left out.
+        [[maybe_unused]] const uint32_t word_voff = last < 0 ? 0x80000000u : shifted_voff;
+        if constexpr (SHIFTED && !BYTES) {
+            static_for<0, RW>([&](auto tt) {
+                constexpr int t = decltype(tt)::value;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) shift[t][c] = ((uint32_t)reinterpret_cast<uintptr_t>(first + c * plane) & 3u) + min(t * pitch, last_off);
+            });
+        }
         auto load_all = [&](auto head, auto tail) {
             static_for<0, RW>([&](auto tt) {
                 constexpr int t = decltype(tt)::value;
@@ -843,6 +855,10 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
                     if constexpr (BYTES) {
                         const u32_any* at = reinterpret_cast<const u32_any*>(first + c * plane + (bytes.voff + off));
                         raw[t].w[c][0] = LAUX == kAuxNonTemporal ? __builtin_nontemporal_load(at) : *at;
+                    } else if constexpr (SHIFTED) {
+                        const uintptr_t word = reinterpret_cast<uintptr_t>(first + c * plane) & ~(uintptr_t)3;
+                        const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const void*>(word), (shift[t][c] + in_row_bytes + 3u) & ~3u);
+                        raw[t].w[c][0] = __builtin_amdgcn_raw_buffer_load_b32(rs, word_voff, shift[t][c] & ~3u, AUX);
                     } else {
                         load_plane_row<In, PX, AUX>(raw[t], c, make_rsrc(first + c * plane, end), load_voff, off);
                     }
