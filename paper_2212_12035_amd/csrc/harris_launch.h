@@ -208,6 +208,19 @@ inline bool rows_are_far(long long row_pitch, int W, int elem, int rows) {
     return row_pitch > most / elem / rows || (rows - 1) * row_pitch * elem + (long long)W * elem > most;
 }
 
+// TILES: where a wavefront of `rows` rows finds them in a plane, in bytes from the start of its first one, row y_wave: row t at
+// near_row(r, t); the rows below the image's last are that one again.  The rows of one wavefront lie within 2 GB (rows_are_far), those of a plane need
+// not: 32 bits do for the former alone.
+struct NearRows { unsigned pitch, last; };
+HARRIS_HOST_DEVICE inline NearRows near_rows(int H, int y_wave, unsigned pitch, int rows) {
+    const int below = H - 1 - y_wave, most = rows - 1;
+    return {pitch, (unsigned)(below < 0 ? 0 : below < most ? below : most) * pitch};
+}
+HARRIS_HOST_DEVICE inline unsigned near_row(const NearRows& r, int t) {
+    const unsigned at = (unsigned)t * r.pitch;
+    return at < r.last ? at : r.last;
+}
+
 // TILES, 8-bit rows on any byte loaded where they are: the byte of a row of W >= 4 pixels at which the lane of column
 // `col` loads four, and the bits by which it shifts them down: a lane whose columns end behind the row loads the
 // row's last four.  No load leaves the row.

@@ -40,6 +40,29 @@ static void check_tile(const Params& p, const harris_tuning& shape, int dtype) {
     }
 }
 
+// The rows that a wavefront loads at 32-bit offsets are the image's, wherever it lies in a plane of any size: wavefronts at either end of the image, and where
+// what is left of the plane comes to just less and just more than a multiple of 4 GB.
+static void check_rows(const Params& p, const harris_tuning& shape, int dtype) {
+    const unsigned elem = dtype == HARRIS_U8 ? 1u : 4u;
+    const long long pitch = p.in_row_pitch * elem;
+    const auto rows_of = [&](long long y) {
+        if (y < 0 || y > p.H + shape.rows * 16LL) return;
+        const NearRows r = near_rows(p.H, (int)y, (unsigned)pitch, shape.rows);
+        const long long left = p.H - 1 - y;
+        for (int t = 0; t < shape.rows; ++t) {
+            const long long at = (left < 0 ? 0 : left < t ? left : t) * pitch;
+            if (near_row(r, t) != (unsigned long long)at || at + (long long)p.W * elem > 1LL << 31) {
+                std::printf("%d rows of %lld bytes: row %d of the wavefront at %lld loaded at %u, not %lld\n", p.H, pitch, t, y, near_row(r, t), at);
+                wrong = true;
+                return;
+            }
+        }
+    };
+    for (long long y : {0LL, (long long)shape.rows, p.H / 2LL, p.H - 11LL, p.H - 5LL, p.H - 2LL, p.H - 1LL, (long long)p.H, p.H + 5LL}) rows_of(y);
+    for (long long end = 1LL << 32; end / pitch < p.H && end <= 16LL << 32; end += 1LL << 32)
+        for (int o = -2; o <= 12; ++o) rows_of(p.H - 1 - end / pitch - o);
+}
+
 static void check_patch(const Params& p, int dtype) {
     const compact_patch::Params c = compact_patch::pack(p, dtype == HARRIS_U8 ? 1 : 4);
     const Params t = compact_patch::unpack(c);
@@ -67,6 +90,7 @@ int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int 
     ++tiles;
     if (!compact::fits(p) || rows_are_far(p.in_row_pitch, p.W, dtype == HARRIS_U8 ? 1 : 4, shape.rows)) { std::printf("does not fit\n"); wrong = true; }
     check_tile(p, shape, dtype);
+    check_rows(p, shape, dtype);
     return HARRIS_OK;
 }
 size_t grouped_workspace_floats(int, int, int, int) { return 0; }

@@ -656,6 +656,32 @@ def test_rows_planes_and_images_that_lie_far_apart(gpu, oracle, dtype, W, row, p
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("H, W, row, tune", [
+    (10, 70, 125000000, None), (300, 70, 1 << 24, None), (600, 1000, 2000000, None),
+    (600, 1000, 2000000, dict(schedule=2, rows=4, waves_per_block=4)), (600, 1000, 2000000, dict(schedule=2, rows=5, waves_per_block=4, flags=8)),
+    (600, 1000, 2000000, dict(schedule=2, rows=6, waves_per_block=5, flags=8 | 64)), (70, 40, 125000000, dict(schedule=2, px=1))])
+def test_rows_near_each_other_in_planes_of_more_than_4_GB(gpu, oracle, H, W, row, tune):
+    # A wavefront's rows are loaded at 32-bit offsets from its first one; what the plane holds below them is more than that.
+    import torch
+    rgb = hi.rectangles_f32(33, 1, H, W)
+    say("case near f32 %dx%d rows %d %s" % (H, W, row, tune))
+    frame = torch.empty(((3 * H - 1) * row + W,), device="cuda")
+    view = frame.as_strided((1, 3, H, W), (3 * H * row, H * row, row, 1))
+    view.copy_(torch.from_numpy(rgb))
+    for out_dtype in (torch.float32, torch.float16):
+        if out_dtype != torch.float32 and tune and tune.get("px") == 1:
+            continue
+        out = torch.full((1, H - 4, W - 4), -7.0, dtype=out_dtype, device="cuda")
+        gpu.harris_coarsity_typed(view, out, K, tuning=tune)
+        want = torch.empty_like(out)
+        gpu.harris_coarsity_typed(torch.from_numpy(rgb).cuda(), want, K, tuning=tune)
+        if out_dtype == torch.float32:
+            check(out.cpu().numpy(), oracle.harris(rgb, K))
+        assert torch.equal(out, want)
+    del frame, view
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("fmt", ["f16", "bf16"])
 def test_16_bit_results(gpu, oracle, fmt):
     # Two checks.  (1) The 16-bit result is the float32 result of the same kernel rounded to
