@@ -1,7 +1,6 @@
 // C interface of libharris: argument checks, launch-shape planning, dispatch.
 // Everything here runs on the host and touches no device memory.
 
-#include <float.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -597,9 +596,16 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
         p.out_image_bytes = (unsigned long long)p.out_image_pitch * out_elem_size(out_dtype);
     };
     place();
+    // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it into the three gray weights; from 8-bit input, whose
+    // weights are whole numbers, its fourth power and theirs into the factor of the result.
+    const double unit = sobel_scale * (262144.0 / 255000.0);
+    float gain, more_gain;
+    harris_launch::split_gain(unit * unit * unit * unit, gain, more_gain);
     // Rows of hundreds of megabytes or that far apart, images of more than 2^32 pixels: the kernels that address each row by itself, whatever shape was asked for.
-    if (shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) &&
-        (harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows) || !harris_launch::compact::fits(p))) {
+    // So are scales whose factor takes two: the others, which multiply by one, have no instruction to spare for them.
+    const bool far = shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) &&
+                     (harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows) || !harris_launch::compact::fits(p));
+    if (far || (dtype == HARRIS_U8 && more_gain != 1.0f)) {
         const harris_tuning four = {HARRIS_SCHEDULE_TILES, shape.px == 4 && !(shape.flags & HARRIS_TUNE_WORD_STORES) ? 4 : 1, 4, 0, 4, 0u, 0};
         rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, &four, &shape, &n_blocks, &p);
         if (rc != HARRIS_OK) return rc;
@@ -608,14 +614,11 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
         p.by_tiles_per_image = harris_launch::make_fastdiv(p.tiles_per_image);
         p.by_n_strips = harris_launch::make_fastdiv(p.n_strips);
     }
-    // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it into the three gray weights; from 8-bit input, whose
-    // weights are whole numbers, its fourth power and theirs into the factor of the result.  (Scales from 3e9 on have
-    // factors beyond float32; flat regions are to stay zero then.)
     p.wr = 0.299f * sobel_scale;
     p.wg = 0.587f * sobel_scale;
     p.wb = 0.114f * sobel_scale;
-    const double unit = sobel_scale * (262144.0 / 255000.0), gain = unit * unit * unit * unit;
-    p.gain = gain < FLT_MAX ? (float)gain : FLT_MAX;
+    p.gain = gain;
+    p.more_gain = more_gain;
     p.k = k;
     p.binomial = window == HARRIS_WINDOW_BINOMIAL ? 1 : 0;
     p.q_scale = q_scale;

@@ -390,7 +390,7 @@ struct LineBuffers {
 // (kSobelIn; gc is not looked at then).  kQuadsIn: gc is the row's 2x2 sums.
 enum SobelRow { kSobelOwn, kSobelOut, kSobelIn, kQuadsIn };
 enum SobelOrder { kSums, kDifferences, kQuads };
-struct Coarsity { float k, gain; };     // gain: kQuads
+struct Coarsity { float k, gain, more_gain; };      // kQuads: gain and more_gain; the latter is the constant 1 but in the far kernels
 
 template <int STAGE, int T, int PX, bool BINOM, int ORDER, int SOBEL>
 __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], const Coarsity& cs, float (&o)[PX], float (&sobel)[2][PX]) {
@@ -510,7 +510,7 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
             float det = fmaf(s[0][i], s[2][i], -(s[1][i] * s[1][i]));
             float tr = s[0][i] + s[2][i];
             o[i] = fmaf(-(cs.k * tr), tr, det);
-            if constexpr (QUADS) o[i] *= cs.gain;
+            if constexpr (QUADS) o[i] = o[i] * cs.gain * cs.more_gain;
         }
     }
 }
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
     });
 
     LineBuffers<PX> lb;
-    const Coarsity cs = {p.k, p.gain};
+    const Coarsity cs = {p.k, p.gain, 1.0f};
     float gc[PX], o[PX];
 
     // Rows 0..3 of the band fill the pipeline.
@@ -738,8 +738,8 @@ __device__ __forceinline__ void store_packed_tail(const PackedRow<KIND>& r, uint
 // 23.1 (23.9), 1536x2560 7.04 (7.47), 480x640 3.06 (3.28), 16 images of 768x1366 to codes 19.6 (20.8), 31 of 598x300 to
 // bfloat16 10.6 (10.9), 64x96 float32 2.66 (2.80).  float32 tiles of 8 rows and more gain nothing and keep a descriptor per row.
 //
-// kAuxFar: a wavefront's rows do not lie within 2 GB of each other, or pitches do not fit the compact arguments: 64-bit addresses for each row and all
-// arguments whole (four rows per wavefront; run() in harris_api.cpp sees to it).
+// kAuxFar: a wavefront's rows do not lie within 2 GB of each other, pitches do not fit the compact arguments, or the factor of 8-bit results takes two
+// numbers: 64-bit addresses for each row and all arguments whole (four rows per wavefront; run() in harris_api.cpp sees to it).
 // Args: compact::Params, or Params for kAuxFar.
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED, bool SMALL, bool WORDS, typename Args>
 __device__ __forceinline__ void harris_tile(const Args& args) {
@@ -938,7 +938,7 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     __builtin_amdgcn_sched_barrier(0);
 
     LineBuffers<PX> lb;
-    const Coarsity cs = {p.k, p.gain};
+    const Coarsity cs = {p.k, p.gain, p.more_gain};
     [[maybe_unused]] GrayMatrix gray;
     if constexpr (MATRIX) gray = gray_matrix(lane, BYTES ? bytes.drop : 0u);
     float gc[PX], none[PX];

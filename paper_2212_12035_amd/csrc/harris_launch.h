@@ -72,7 +72,7 @@ struct Params {
     unsigned n_blocks;      // workgroups of the launch (the grid size)
     unsigned waves_per_block;  // wavefronts per workgroup (the block size / 64)
     float wr, wg, wb;       // float32 input: gray weights, times the Sobel scale
-    float gain;             // 8-bit input: (Sobel scale 2^18 / 255000)^4, the result is that multiple of what the kernel works out
+    float gain, more_gain;  // 8-bit input: (Sobel scale 2^18 / 255000)^4 as two factors (split_gain), the result is that multiple of what the kernel works out
     float k;                // coarsity constant
     unsigned flags;         // HARRIS_TUNE_* bits, kWriteThrough
     unsigned long long out_row_bytes, out_image_bytes;        // TILES: the result's pitches in bytes
@@ -91,13 +91,26 @@ struct Params {
     unsigned image_lanes, image_lanes_inverse, images, batch;
     // TILES with shared rows kept, and narrow images: tiles that an XCD takes in a row, and how often.
     unsigned chunk, turns;
-    int far_rows;           // TILES: 1: the rows that a wavefront loads do not lie within 2 GB (rows_are_far), or compact::fits does not hold
+    int far_rows;           // TILES: 1: the rows that a wavefront loads do not lie within 2 GB (rows_are_far), compact::fits does not hold, or more_gain is not 1
     int resident;           // TILES: 1: the chip holds all tiles of the launch at once
 };
 
+// The factor of 8-bit results as two of float32, the second 1 wherever the first holds it.  Sobel scales from 4.2e9 on have factors beyond
+// float32, and scales below 3.2e-10 such as it holds in fewer than 24 bits or not at all; results of the former may still be finite, and of
+// the latter normal numbers.  The first factor then is 2^96 or 2^-96, which rounds nothing that the second brings back into range.  (From 2.7e67 on it is
+// clamped: every result but zero is infinite then, and zero stays zero.)
+inline void split_gain(double gain, float& first, float& second) {
+    constexpr double kLeast = 1.17549435082228750797e-38, kMost = 3.40282346638528859812e+38, kStep = 79228162514264337593543950336.0;
+    second = 1.0f;
+    if ((gain >= kLeast && gain <= kMost) || gain == 0.0) { first = (float)gain; return; }
+    first = gain > 1.0 ? (float)kStep : (float)(1.0 / kStep);
+    const double rest = gain > 1.0 ? gain / kStep : gain * kStep;
+    second = (float)(rest < kMost ? rest : kMost);
+}
+
 // TILES: the same in 96 bytes, which is what the kernels take.  The runtime writes a launch's arguments into memory
 // that the GPU reads, from some host cores slowly: an empty kernel with 240 bytes then takes 3.8 us a launch, with 96 bytes 2.8 (2.5 and 2.4 from the others).
-// Pitches of 2^32 elements and more, result rows of 2 GB and rows that are far apart take Params itself (compact::fits).
+// Pitches of 2^32 elements and more, result rows of 2 GB, rows that are far apart and scales whose factor takes two numbers take Params itself (compact::fits).
 namespace compact {
 
 // Division by a divisor of at most 2^31 of numbers below 2^31: floor(x mul / 2^(31 + l)) with l = ceil(log2 d) and mul = ceil(2^(31 + l) / d), which is at
@@ -153,7 +166,7 @@ struct Tile {
     unsigned long long out_row_bytes, out_image_bytes;
     int H, W, n, m, rows_per_band;
     unsigned n_strips, strip_pitch, strip_reach, n_blocks, chunk, waves_per_block, flags, out_kind, out_shift;
-    float wr, wg, wb, gain, k, q_scale, q_offset;
+    float wr, wg, wb, gain, more_gain, k, q_scale, q_offset;
 };
 HARRIS_HOST_DEVICE inline Tile unpack(const Params& c, unsigned elem, int rows) {
     Tile t;
@@ -170,6 +183,7 @@ HARRIS_HOST_DEVICE inline Tile unpack(const Params& c, unsigned elem, int rows) 
     t.flags = (c.bits >> 29 & 1u) * HARRIS_TUNE_NO_XCD_REMAP | (c.bits >> 30 & 1u) * HARRIS_TUNE_ALIGNED_STORES | (c.bits >> 31) * kWriteThrough;
     t.out_kind = c.bits >> 25 & 3u;
     t.wr = t.gain = c.weights[0]; t.wg = c.weights[1]; t.wb = c.weights[2];
+    t.more_gain = 1.0f;
     t.k = c.k; t.q_scale = c.q_scale; t.q_offset = c.q_offset;
     return t;
 }
@@ -181,7 +195,7 @@ HARRIS_HOST_DEVICE inline Tile unpack(const harris_launch::Params& p, unsigned, 
     t.H = p.H; t.W = p.W; t.n = p.n; t.m = p.m; t.rows_per_band = p.rows_per_band;
     t.n_strips = p.n_strips; t.n_blocks = p.n_blocks; t.chunk = p.chunk; t.waves_per_block = p.waves_per_block;
     t.strip_pitch = p.strip_pitch; t.strip_reach = p.strip_reach; t.flags = p.flags; t.out_kind = p.out_kind;
-    t.wr = p.wr; t.wg = p.wg; t.wb = p.wb; t.gain = p.gain;
+    t.wr = p.wr; t.wg = p.wg; t.wb = p.wb; t.gain = p.gain; t.more_gain = p.more_gain;
     t.k = p.k; t.q_scale = p.q_scale; t.q_offset = p.q_offset;
     return t;
 }

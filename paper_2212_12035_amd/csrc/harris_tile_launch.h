@@ -24,7 +24,7 @@ hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 bl
     return hipGetLastError();
 }
 
-// Rows too far apart for 32-bit offsets, or pitches too long for the compact arguments (Params::far_rows).
+// Rows too far apart for 32-bit offsets, pitches too long for the compact arguments, or a factor of two numbers (Params::far_rows).
 template <typename In, int PX, bool SHIFTED>
 hipError_t launch_far_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
     if (p.binomial) hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, true, SHIFTED>), grid, block, lds, stream, p);

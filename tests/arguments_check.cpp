@@ -1,6 +1,8 @@
 // Host check of the compact kernel arguments (namespaces compact and compact_patch of harris_launch.h): over random calls of
 // the C interface, what a kernel unpacks is what the planner decided, or the launch takes the kernels with whole
 // arguments; and the division they use is exact.  Built and run by tests/test_abi_host.py; prints "ok ..." or the first fault.
+#include <cfloat>
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -31,7 +33,7 @@ static void check_tile(const Params& p, const harris_tuning& shape, int dtype) {
     SAME(t.n_blocks, w.n_blocks); SAME(t.chunk, w.chunk); SAME(t.waves_per_block, w.waves_per_block);
     SAME(t.flags, w.flags & (HARRIS_TUNE_NO_XCD_REMAP | HARRIS_TUNE_ALIGNED_STORES | kWriteThrough));
     SAME(t.out_kind, w.out_kind); SAME(t.out_shift, w.out_shift);
-    if (dtype == HARRIS_U8) same_bits(t.gain, w.gain, "gain");
+    if (dtype == HARRIS_U8) { same_bits(t.gain, w.gain, "gain"); same_bits(t.more_gain, w.more_gain, "more_gain"); }
     else { same_bits(t.wr, w.wr, "wr"); same_bits(t.wg, w.wg, "wg"); same_bits(t.wb, w.wb, "wb"); }
     same_bits(t.k, w.k, "k"); same_bits(t.q_scale, w.q_scale, "q_scale"); same_bits(t.q_offset, w.q_offset, "q_offset");
     for (unsigned tile : {0u, 1u, p.n_strips - 1u, p.n_strips, p.tiles_per_image - 1u, p.tiles_per_image, p.n_blocks / 2u, p.n_blocks - 1u}) {
@@ -133,6 +135,17 @@ int main() {
         if (!divides(next_u32() >> 1, d == 0u ? 1u : d)) return 1;
     }
 
+    // The factor of 8-bit results: one float32 where that holds it, else two of which neither is subnormal while the result may be a normal number.
+    for (int e = -700; e <= 700; ++e)
+        for (double x : {1.0, 1.25, 1.9999999}) {
+            const double gain = std::ldexp(x, e);
+            float a, b;
+            harris_launch::split_gain(gain, a, b);
+            const bool held = gain >= FLT_MIN && gain <= FLT_MAX;
+            if ((held && (a != (float)gain || b != 1.0f)) || !(a >= FLT_MIN && a <= FLT_MAX) || !(b <= FLT_MAX) || (e >= -200 && b < FLT_MIN) ||
+                (e >= -200 && e <= 200 && std::fabs((double)a * (double)b - gain) > std::ldexp(gain, -24))) { std::printf("factor %g: %g and %g\n", gain, a, b); return 1; }
+        }
+
     void *rgb = reinterpret_cast<void*>(4096), *out = reinterpret_cast<void*>(1 << 20);
     for (int i = 0; i < 400000 && !harris_launch::wrong; ++i) {
         const int dtype = (int)below(2), kind = (int)below(4), batch = (int)(below(3) ? spread(12) : 1);
@@ -152,6 +165,16 @@ int main() {
         if (kind == HARRIS_OUT_U8) harris_coarsity_quantized(at, dtype, batch, H, W, &lay, 0.04f, 0.5f, (int)below(2), 1.5f, 90.0f, static_cast<uint8_t*>(out), tuning, nullptr);
         else harris_coarsity_typed(at, dtype, batch, H, W, &lay, 0.04f, 2.0f, (int)below(2), out, kind, tuning, nullptr);
     }
+    // Scales whose factor takes two numbers: the kernels that multiply by both, whatever shape was asked for.
+    for (float scale : {5e9f, 3e38f, 3e-10f, 1e-45f})
+        for (int shape = 0; shape < 8 && !harris_launch::wrong; ++shape) {
+            const harris_tuning t = {shape == 1 ? HARRIS_SCHEDULE_BANDS : shape ? HARRIS_SCHEDULE_TILES : 0, shape == 4 ? 2 : 0, shape == 2 ? 5 : 0, 0, 0, shape == 3 ? (unsigned)HARRIS_TUNE_PACKED_IMAGES : 0u, 0};
+            const int kind = shape < 5 ? HARRIS_OUT_F32 : HARRIS_OUT_F16, before = (int)harris_launch::far;
+            if (harris_coarsity_typed(rgb, HARRIS_U8, 40, 41, shape == 6 ? 71 : 72, nullptr, 0.04f, scale, 0, out, kind, shape < 6 ? &t : nullptr, nullptr) != HARRIS_OK || harris_launch::far != before + 1) {
+                std::printf("scale %g, shape %d: not the kernel with two factors\n", scale, shape);
+                return 1;
+            }
+        }
     if (harris_launch::wrong) return 1;
     if (harris_launch::tiles < 50000 || harris_launch::patches < 1000 || harris_launch::far < 1000) { std::printf("too few: %lld %lld %lld\n", harris_launch::tiles, harris_launch::patches, harris_launch::far); return 1; }
     std::printf("ok %lld tiles, %lld patches, %lld far\n", harris_launch::tiles, harris_launch::patches, harris_launch::far);

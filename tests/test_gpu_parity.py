@@ -290,6 +290,49 @@ def test_u8_responses_are_exact(gpu, oracle, tune, window):
     assert not run_gpu(gpu, np.full_like(rgb, 200), k=K, window=window, sobel_scale=3e38, tuning=tune).any()
 
 
+@pytest.mark.parametrize("tune", [None, dict(schedule=1, px=1), dict(schedule=1, px=4), dict(schedule=2, px=2),
+                                  dict(schedule=2, rows=4, waves_per_block=2), dict(schedule=2, rows=8, waves_per_block=3), dict(flags=512)])
+@pytest.mark.parametrize("window", [0, 1])
+def test_u8_results_at_large_and_small_scales(gpu, oracle, tune, window):
+    # A Sobel scale multiplies the result by its fourth power, also where float32 does not hold that.  Each of the two results compared is the same
+    # number times a factor rounded to float32 and rounded (two halves of eps each), one of them twice: 5 halves of eps, or a subnormal's spacing.
+    # (That number itself is rounded as the shape has it; at such scales all shapes are of four rows per wavefront.)
+    import torch
+    H, W = 41, 68 if tune and tune.get("px", 1) > 1 else 71
+    rgb = hi.white_noise_u8(19, 3, H, W)
+    rgb[1] = 100 + rgb[1] // 128                                     # small responses, of which some stay finite
+    rgb[2] = rgb[2] // 255
+    top = float(np.finfo(np.float32).max)
+    four = dict(schedule=2, px=1 if tune and tune.get("px", 4) < 4 else 4, rows=4, waves_per_block=4)
+    one = run_gpu(gpu, rgb, k=K, window=window, tuning=four).astype(np.float64)
+    for scale in (5e9, 1e10, 1e12, 1e20, 3e-10, 5e-11, 2e-11, 6e-12, 1e-30):
+        scale = float(np.float32(scale))
+        say("case u8 scale %g window %d %s" % (scale, window, tune))
+        got, want = run_gpu(gpu, rgb, k=K, window=window, sobel_scale=scale, tuning=tune), one * scale ** 4
+        near = np.isclose(np.abs(want), top, rtol=1e-5, atol=0.0)
+        over = (np.abs(want) > top) & ~near
+        rest = ~over & ~near
+        assert np.array_equal(got[over], np.copysign(np.inf, want[over]).astype(np.float32))
+        assert rest.any() and np.all(np.abs(got[rest] - want[rest]) <= 2.5 * np.finfo(np.float32).eps * np.abs(want[rest]) + 2.0 ** -149)
+
+
+@pytest.mark.parametrize("W, flags", [(68, 0), (71, 0), (71, 256)])
+@pytest.mark.parametrize("scale, q", [(1e10, 1e-31), (2e-10, 1e38)])
+def test_u8_codes_at_large_and_small_scales(gpu, W, flags, scale, q):
+    # The codes are those of the float32 results of the same shape, also where rows of codes lie on any byte.
+    import torch
+    rgb = hi.white_noise_u8(19, 1, 41, W)                            # results of some 1e-37 at the small scale
+    if scale > 1:
+        rgb = 100 + rgb // 128                                       # and of some 1e32 at the large one
+    tune = dict(schedule=2, px=4, rows=4, waves_per_block=4)
+    whole = run_gpu(gpu, rgb, k=K, sobel_scale=scale, tuning=tune)
+    codes = torch.zeros(whole.shape, dtype=torch.uint8, device="cuda")
+    gpu.harris_coarsity_quantized(torch.from_numpy(rgb).cuda(), codes, q, 90.0, K, scale, tuning=dict(tune, flags=flags) if flags or W % 4 == 0 else None)
+    want = np.clip(np.rint(whole.astype(np.float64) * float(np.float32(q)) + 90.0), 0, 255)
+    got = codes.cpu().numpy().astype(np.float64)
+    assert 1 < len(np.unique(want)) and np.abs(got - want).max() <= 1 and (got != want).mean() < 0.01
+
+
 @pytest.mark.parametrize("batch,H,W", [(2, 9, 5), (17, 5, 9), (40, 33, 11), (7, 21, 24), (3001, 50, 21), (6, 61, 57), (33, 8, 60)])
 @pytest.mark.parametrize("window", [0, 1])
 def test_narrow_u8_images_on_any_byte(gpu, oracle, batch, H, W, window):
