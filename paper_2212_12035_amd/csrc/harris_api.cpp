@@ -599,8 +599,10 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
     // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it into the three gray weights; from 8-bit input, whose
     // weights are whole numbers, its fourth power and theirs into the factor of the result.
     const double unit = sobel_scale * (262144.0 / 255000.0);
+    double factor = unit * unit * unit * unit;
+    if (dtype == HARRIS_U8) harris_launch::bound_k(k, factor);
     float gain, more_gain;
-    harris_launch::split_gain(unit * unit * unit * unit, gain, more_gain);
+    harris_launch::split_gain(factor, gain, more_gain);
     // Rows of hundreds of megabytes or that far apart, images of more than 2^32 pixels: the kernels that address each row by itself, whatever shape was asked for.
     // So are scales whose factor takes two: the others, which multiply by one, have no instruction to spare for them.
     const bool far = shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) &&

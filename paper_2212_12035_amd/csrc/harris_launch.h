@@ -2,6 +2,7 @@
 #ifndef HARRIS_LAUNCH_H
 #define HARRIS_LAUNCH_H
 
+#include <math.h>
 #include <stddef.h>
 
 #include "harris_tuning.h"
@@ -106,6 +107,17 @@ inline void split_gain(double gain, float& first, float& second) {
     first = gain > 1.0 ? (float)kStep : (float)(1.0 / kStep);
     const double rest = gain > 1.0 ? gain / kStep : gain * kStep;
     second = (float)(rest < kMost ? rest : kMost);
+}
+
+// 8-bit input: k times the square of a trace of scale one, up to 2^18, has to be a finite float32 before the factor is applied to it.  A k from 2^64 on
+// hands its power of two to the factor; det, at most a quarter of the trace's square, is then far below the last bit of
+// the result with either k.
+inline void bound_k(float& k, double& gain) {
+    int e;
+    const double m = frexp((double)k, &e);
+    if (e <= 64) return;
+    k = (float)ldexp(m, 64);
+    gain = ldexp(gain, e - 64);
 }
 
 // TILES: the same in 96 bytes, which is what the kernels take.  The runtime writes a launch's arguments into memory

@@ -146,6 +146,18 @@ int main() {
                 (e >= -200 && e <= 200 && std::fabs((double)a * (double)b - gain) > std::ldexp(gain, -24))) { std::printf("factor %g: %g and %g\n", gain, a, b); return 1; }
         }
 
+    // Large constants k: the same product with the factor, and small enough for the square of any trace.
+    for (float k : {0.0f, 0.04f, -1e19f, 1.8e19f, 1.9e19f, -1e30f, FLT_MAX, -FLT_MAX, FLT_MIN}) {
+        float bounded = k;
+        double gain = 1e-20;
+        harris_launch::bound_k(bounded, gain);
+        if (std::fabs(bounded) > std::ldexp(1.0, 64) || (std::fabs(k) < 1.8e19f && (bounded != k || gain != 1e-20)) ||
+            std::fabs((double)bounded * gain - (double)k * 1e-20) > 1e-15 * std::fabs((double)k * 1e-20) || (std::fabs(k) > 2e19f && std::fabs(bounded) < std::ldexp(1.0, 63))) {
+            std::printf("k %g: %g, factor %g\n", k, bounded, gain);
+            return 1;
+        }
+    }
+
     void *rgb = reinterpret_cast<void*>(4096), *out = reinterpret_cast<void*>(1 << 20);
     for (int i = 0; i < 400000 && !harris_launch::wrong; ++i) {
         const int dtype = (int)below(2), kind = (int)below(4), batch = (int)(below(3) ? spread(12) : 1);

@@ -316,6 +316,23 @@ def test_u8_results_at_large_and_small_scales(gpu, oracle, tune, window):
         assert rest.any() and np.all(np.abs(got[rest] - want[rest]) <= 2.5 * np.finfo(np.float32).eps * np.abs(want[rest]) + 2.0 ** -149)
 
 
+@pytest.mark.parametrize("k, scale", [(3e37, 1e-5), (-1e38, 1e-9), (1e30, 1e-3), (3e38, 1e-20), (1e25, 1e5), (1e-38, 1e3)])
+@pytest.mark.parametrize("tune", [None, dict(schedule=1, px=1), dict(flags=512)])
+def test_u8_results_at_large_constants(gpu, oracle, k, scale, tune):
+    # k trace^2 is a finite number where the scale makes it one.  The trace is a sum of exact squares, of which nine and their eight sums round and the last one: 9 halves
+    # of eps, counted twice; k times it, the square and the factor: below 12 eps of the result, det (none at these k but the last) aside.
+    rgb = hi.white_noise_u8(19, 3, 41, 71)
+    k, scale = float(np.float32(k)), float(np.float32(scale))
+    got = run_gpu(gpu, rgb, k=k, sobel_scale=scale, tuning=tune)
+    want = oracle.harris(rgb, k, scale, 0, precision="f64")
+    over = np.abs(want) > np.finfo(np.float32).max
+    assert np.array_equal(got[over], np.copysign(np.inf, want[over]).astype(np.float32))
+    if k > 1e-30 or k < 0:
+        assert np.all(np.abs(got[~over] - want[~over]) <= 12 * np.finfo(np.float32).eps * np.abs(want[~over]) + 2.0 ** -149)
+    else:
+        assert rounding_distance(oracle, got, rgb, k, scale) <= 7.0
+
+
 @pytest.mark.parametrize("W, flags", [(68, 0), (71, 0), (71, 256)])
 @pytest.mark.parametrize("scale, q", [(1e10, 1e-31), (2e-10, 1e38)])
 def test_u8_codes_at_large_and_small_scales(gpu, W, flags, scale, q):
