@@ -128,8 +128,8 @@ constexpr int kAuxNonTemporal = HARRIS_LOAD_AUX;
 // default policy.  The launches that use it are those of many small tiles; their float32 stores are
 // written through (kAuxManyStore) if strips end on 64-byte boundaries.
 constexpr int kAuxKeepShared = -1;
-// Tile kernel only: the default policy, and rows that do not lie within 2 GB of each other.
-constexpr int kAuxFar = -2;
+// Tile kernel only: rows that do not lie within 2 GB of each other, with the default policy and as kAuxKeepShared.
+constexpr int kAuxFar = -2, kAuxFarKeepShared = -3;
 constexpr int kAuxStore = HARRIS_STORE_AUX, kAuxManyStore = HARRIS_MANY_STORE_AUX;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -390,7 +390,7 @@ struct LineBuffers {
 // (kSobelIn; gc is not looked at then).  kQuadsIn: gc is the row's 2x2 sums.
 enum SobelRow { kSobelOwn, kSobelOut, kSobelIn, kQuadsIn };
 enum SobelOrder { kSums, kDifferences, kQuads };
-struct Coarsity { float k, gain, more_gain; };      // kQuads: gain and more_gain; the latter is the constant 1 but in the far kernels
+struct Coarsity { float k, gain; };     // gain: kQuads
 
 template <int STAGE, int T, int PX, bool BINOM, int ORDER, int SOBEL>
 __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[PX], const Coarsity& cs, float (&o)[PX], float (&sobel)[2][PX]) {
@@ -510,7 +510,7 @@ __device__ __forceinline__ void row_step(LineBuffers<PX>& lb, const float (&gc)[
             float det = fmaf(s[0][i], s[2][i], -(s[1][i] * s[1][i]));
             float tr = s[0][i] + s[2][i];
             o[i] = fmaf(-(cs.k * tr), tr, det);
-            if constexpr (QUADS) o[i] = o[i] * cs.gain * cs.more_gain;
+            if constexpr (QUADS) o[i] *= cs.gain;
         }
     }
 }
@@ -593,7 +593,7 @@ __global__ __launch_bounds__(256) void harris_fused_kernel(const harris_launch::
     });
 
     LineBuffers<PX> lb;
-    const Coarsity cs = {p.k, p.gain, 1.0f};
+    const Coarsity cs = {p.k, p.gain};
     float gc[PX], o[PX];
 
     // Rows 0..3 of the band fill the pipeline.
@@ -738,9 +738,9 @@ __device__ __forceinline__ void store_packed_tail(const PackedRow<KIND>& r, uint
 // 23.1 (23.9), 1536x2560 7.04 (7.47), 480x640 3.06 (3.28), 16 images of 768x1366 to codes 19.6 (20.8), 31 of 598x300 to
 // bfloat16 10.6 (10.9), 64x96 float32 2.66 (2.80).  float32 tiles of 8 rows and more gain nothing and keep a descriptor per row.
 //
-// kAuxFar: a wavefront's rows do not lie within 2 GB of each other, pitches do not fit the compact arguments, or the factor of 8-bit results takes two
+// kAuxFar, kAuxFarKeepShared: a wavefront's rows do not lie within 2 GB of each other, pitches do not fit the compact arguments, or the factor of 8-bit results takes two
 // numbers: 64-bit addresses for each row and all arguments whole (four rows per wavefront; run() in harris_api.cpp sees to it).
-// Args: compact::Params, or Params for kAuxFar.
+// Args: compact::Params, or Params for these two.
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED, bool SMALL, bool WORDS, typename Args>
 __device__ __forceinline__ void harris_tile(const Args& args) {
     const harris_launch::compact::Tile p = harris_launch::compact::unpack(args, sizeof(In), RW);
@@ -750,6 +750,8 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     constexpr int ORDER = std::is_same<In, uint8_t>::value ? kQuads : !(RW == 10 && (LAUX == kAuxKeepShared || WORDS || (BINOM && !HANDOFF))) ? kDifferences : kSums;
     static_assert(!SHIFTED || (std::is_same<In, uint8_t>::value && PX == 4), "shifted rows: 8-bit input, four pixels per lane");
     static_assert(!WORDS || PX == 4, "result rows on any byte: four pixels per lane");
+    constexpr bool FAR = LAUX == kAuxFar || LAUX == kAuxFarKeepShared;
+    constexpr bool KEEP = LAUX == kAuxKeepShared || LAUX == kAuxFarKeepShared;  // the rows that two tiles share with the default policy, tiles dealt by turns
     constexpr bool MATRIX = std::is_same<In, uint8_t>::value && PX == 4;
     constexpr bool HAND_SOBEL = harris_launch::hands_sobel(std::is_same<In, uint8_t>::value, PX);
     extern __shared__ __align__(16) float halo_lds[];           // [NW][4][64][PX]; HAND_SOBEL: [1 + (NW - 1) * 6][64][PX]
@@ -769,7 +771,7 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     // The grid size is read with all other arguments, not in a branch of its own: one wait
     // for the arguments instead of two before the first load can be issued.
     unsigned n_blocks = p.n_blocks;
-    if constexpr (LAUX == kAuxKeepShared) {
+    if constexpr (KEEP) {
         unsigned chunk = p.chunk;
         asm volatile("" : "+s"(n_blocks), "+s"(chunk));
         if (!(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) tile = harris_launch::dealt_tile(tile, blockIdx.y, chunk);
@@ -818,11 +820,11 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     // right than otherwise, which supplies the last lane's missing bytes); the descriptor's
     // size stops the lanes right of the row.
     [[maybe_unused]] const uint32_t shifted_voff = lane * PX < p.strip_reach + 4 ? col : 0x80000000u;
-    constexpr bool BYTES = SHIFTED && LAUX != kAuxFar && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
+    constexpr bool BYTES = SHIFTED && !FAR && (LAUX == kAuxNonTemporal || (RW == 4 && (WORDS || SMALL || LAUX == kAuxDefault)));
     // BYTES: every lane takes its four pixels with one load at any byte, which the hardware does (byte_lane).  Rows below
     // the image load its last one, and nobody uses what comes of them.
     [[maybe_unused]] const harris_launch::ByteLane bytes = harris_launch::byte_lane(col, (unsigned)p.W);
-    constexpr bool NEAR = LAUX != kAuxFar && (std::is_same<In, uint8_t>::value ? !SHIFTED || BYTES || !BINOM : RW <= 6);
+    constexpr bool NEAR = !FAR && (std::is_same<In, uint8_t>::value ? !SHIFTED || BYTES || !BINOM : RW <= 6);
     if constexpr (NEAR) {
         const int last = p.H - 1 - y_wave;                      // the image's last row, counted from this wavefront's first; negative below the image
         const harris_launch::NearRows near = harris_launch::near_rows(p.H, y_wave, (uint32_t)p.in_row_pitch * (uint32_t)sizeof(In), RW);
@@ -871,26 +873,30 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
         else if (RW != 4 && wave + 1 == n_waves) load_all(std::false_type{}, std::true_type{});
         else load_all(std::false_type{}, std::false_type{});
     } else {
-        static_for<0, RW>([&](auto tt) {
-            constexpr int t = decltype(tt)::value;
+        auto load_far = [&](auto tt, auto aux) {
+            constexpr int t = decltype(tt)::value, AUX = decltype(aux)::value;
             const int r = y_wave + t;
             const In* row_in = img_in + (size_t)min(r, p.H - 1) * (size_t)p.in_row_pitch;
             const uint32_t row_bytes = r < p.H ? in_row_bytes : 0u;
-            const bool shared = (t < 4 && wave == 0) || (t >= RW - 4 && wave + 1 == n_waves);
-            if constexpr (SHIFTED) {
-                if constexpr (LAUX == kAuxKeepShared) {
-                    if (shared) load_row_shifted<kAuxDefault>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
-                    else load_row_shifted<kAuxNonTemporal>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
-                } else {
-                    load_row_shifted<LAUX == kAuxFar ? kAuxDefault : LAUX>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
-                }
-            } else if constexpr (LAUX == kAuxKeepShared) {
-                if (shared) load_row<In, PX, kAuxDefault>(raw[t], row_in, plane, row_bytes, load_voff);
-                else load_row<In, PX, kAuxNonTemporal>(raw[t], row_in, plane, row_bytes, load_voff);
-            } else {
-                load_row<In, PX, LAUX == kAuxFar ? kAuxDefault : LAUX>(raw[t], row_in, plane, row_bytes, load_voff);
-            }
-        });
+            if constexpr (SHIFTED) load_row_shifted<AUX>(raw[t], shift[t], row_in, plane, row_bytes, shifted_voff);
+            else load_row<In, PX, AUX>(raw[t], row_in, plane, row_bytes, load_voff);
+        };
+        const std::integral_constant<int, kAuxDefault> shared_aux;
+        const std::integral_constant<int, kAuxNonTemporal> own_aux;
+        static_assert(!FAR || RW == 4, "far rows: four per wavefront");
+        if constexpr (LAUX == kAuxFar) {
+            static_for<0, RW>([&](auto tt) { load_far(tt, shared_aux); });
+        } else if constexpr (LAUX == kAuxFarKeepShared) {       // of four rows all are shared, or none
+            if (wave == 0 || wave + 1 == n_waves) static_for<0, RW>([&](auto tt) { load_far(tt, shared_aux); });
+            else static_for<0, RW>([&](auto tt) { load_far(tt, own_aux); });
+        } else {
+            static_for<0, RW>([&](auto tt) {
+                constexpr int t = decltype(tt)::value;
+                if constexpr (LAUX != kAuxKeepShared) load_far(tt, std::integral_constant<int, LAUX>{});
+                else if ((t < 4 && wave == 0) || (t >= RW - 4 && wave + 1 == n_waves)) load_far(tt, shared_aux);
+                else load_far(tt, own_aux);
+            });
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -938,7 +944,7 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     __builtin_amdgcn_sched_barrier(0);
 
     LineBuffers<PX> lb;
-    const Coarsity cs = {p.k, p.gain, p.more_gain};
+    const Coarsity cs = {p.k, p.gain};
     [[maybe_unused]] GrayMatrix gray;
     if constexpr (MATRIX) gray = gray_matrix(lane, BYTES ? bytes.drop : 0u);
     float gc[PX], none[PX];
@@ -1049,13 +1055,23 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
         });
     }
 
+    // The second factor of 8-bit results: behind a branch of the wavefront, which images that are here for their size pass by (66000x66000 to codes
+    // 4.00 ms, 4.08 multiplied by one).
+    if constexpr (FAR && ORDER == kQuads) {
+        if (__float_as_uint(p.more_gain) != __float_as_uint(1.0f)) {
+#pragma unroll
+            for (int j = 0; j < RW; ++j)
+#pragma unroll
+                for (int i = 0; i < PX; ++i) results[j][i] *= p.more_gain;
+        }
+    }
     // The last wavefront skips the four rows it has no data for.
     if constexpr (HANDOFF) __syncthreads();                     // stores only after all of the workgroup's loads
     __builtin_amdgcn_sched_barrier(0);
     constexpr int SAUX = kAuxStore;
     // The rows of this wavefront in one burst, written through or not (many-tile kernels only).
     [[maybe_unused]] auto store_all = [&](auto&& store_one) {
-        if (LAUX == kAuxKeepShared && (p.flags & harris_launch::kWriteThrough)) {
+        if (KEEP && (p.flags & harris_launch::kWriteThrough)) {
             static_for<0, RW>([&](auto jj) {
                 if (decltype(jj)::value < RW - 4 || wave + 1 < n_waves) store_one(std::integral_constant<int, kAuxManyStore>{}, jj);
             });
@@ -1127,9 +1143,9 @@ template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool 
 __global__ __launch_bounds__(1024) void harris_tile_kernel(const harris_launch::compact::Params args) {
     harris_tile<In, PX, RW, LAUX, BINOM, HANDOFF, SHIFTED, SMALL, WORDS>(args);
 }
-template <typename In, int PX, bool BINOM, bool SHIFTED>
+template <typename In, int PX, int LAUX, bool BINOM, bool SHIFTED, bool WORDS>
 __global__ __launch_bounds__(1024) void harris_far_tile_kernel(const harris_launch::Params args) {
-    harris_tile<In, PX, 4, kAuxFar, BINOM, false, SHIFTED, false, false>(args);
+    harris_tile<In, PX, 4, LAUX, BINOM, false, SHIFTED, false, WORDS>(args);
 }
 
 }  // namespace

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
 
     constexpr int ORDER = F32 ? kDifferences : kQuads;
     LineBuffers<PX> lb;
-    const Coarsity cs = {p.k, p.gain, 1.0f};
+    const Coarsity cs = {p.k, p.gain};
     [[maybe_unused]] GrayMatrix gray;
     if constexpr (!F32) gray = gray_matrix(lane, PAIRS ? 0u : l.drop);
     float gc[PX], none[PX], results[RW][PX];

@@ -25,10 +25,14 @@ hipError_t launch_tile_kernel(const harris_launch::Params& p, dim3 grid, dim3 bl
 }
 
 // Rows too far apart for 32-bit offsets, pitches too long for the compact arguments, or a factor of two numbers (Params::far_rows).
-template <typename In, int PX, bool SHIFTED>
+// Four pixels per lane keep the shared rows and are dealt by turns, like near ones; to 8-bit codes, which the vector and scalar units bound, 8-bit
+// images are faster with one policy and one run per XCD (ms, by turns / one run: 66000x66000 to codes 4.40 / 4.25, to
+// float32 5.58 / 5.77; 2 of 40000x36000 float32 7.85 / 8.53), as long as the grid stays below 2^32 threads.
+template <typename In, int PX, int LAUX, bool SHIFTED, bool WORDS>
 hipError_t launch_far_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, size_t lds, hipStream_t stream) {
-    if (p.binomial) hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, true, SHIFTED>), grid, block, lds, stream, p);
-    else hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, false, SHIFTED>), grid, block, lds, stream, p);
+    if (LAUX == kAuxFarKeepShared) grid = dim3(8 * p.chunk, p.turns);
+    if (p.binomial) hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, LAUX, true, SHIFTED, WORDS>), grid, block, lds, stream, p);
+    else hipLaunchKernelGGL((harris_far_tile_kernel<In, PX, LAUX, false, SHIFTED, WORDS>), grid, block, lds, stream, p);
     return hipGetLastError();
 }
 
@@ -42,14 +46,15 @@ hipError_t launch_tiles(const harris_launch::Params& p, dim3 grid, dim3 block, h
     const size_t lds_needed = harris_launch::tile_lds_bytes(U8, PX, block.x / kWave);
     const size_t lds = p.lds_bytes > lds_needed ? p.lds_bytes : lds_needed;
     if (p.far_rows) {
-        if constexpr (RW == 4 && !WORDS && PX != 2) {
-            if constexpr (U8 && PX == 4) {
-                if (p.in_shifted) return launch_far_tiles<In, PX, true>(p, grid, block, lds, stream);
+        if constexpr (RW == 4 && PX == 1) return launch_far_tiles<In, PX, kAuxFar, false, false>(p, grid, block, lds, stream);
+        if constexpr (RW == 4 && PX == 4 && U8) {
+            if (p.in_shifted) return launch_far_tiles<In, PX, kAuxFarKeepShared, true, WORDS>(p, grid, block, lds, stream);
+            if constexpr (!WORDS) {
+                if (p.out_kind == HARRIS_OUT_U8 && p.n_blocks < (1u << 23)) return launch_far_tiles<In, PX, kAuxFar, false, false>(p, grid, block, lds, stream);
             }
-            return launch_far_tiles<In, PX, false>(p, grid, block, lds, stream);
-        } else {
-            return hipErrorInvalidValue;
         }
+        if constexpr (RW == 4 && PX == 4 && !(U8 && WORDS)) return launch_far_tiles<In, PX, kAuxFarKeepShared, false, WORDS>(p, grid, block, lds, stream);
+        return hipErrorInvalidValue;
     }
     // Many tiles with shared rows kept: dealt to the XCDs by turns (dealt_tile).
     if ((p.flags & HARRIS_TUNE_KEEP_SHARED_ROWS) && !(p.flags & HARRIS_TUNE_NO_XCD_REMAP)) grid = dim3(8 * p.chunk, p.turns);

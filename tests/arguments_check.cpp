@@ -1,6 +1,7 @@
 // Host check of the compact kernel arguments (namespaces compact and compact_patch of harris_launch.h): over random calls of
 // the C interface, what a kernel unpacks is what the planner decided, or the launch takes the kernels with whole
 // arguments; and the division they use is exact.  Built and run by tests/test_abi_host.py; prints "ok ..." or the first fault.
+#include <array>
 #include <cfloat>
 #include <cmath>
 #include <cstdint>
@@ -13,6 +14,7 @@
 namespace harris_launch {
 
 static long long tiles = 0, patches = 0, far = 0;
+static int far_px = 0;
 static bool wrong = false;
 
 #define SAME(a, b) do { if ((a) != (b)) { std::printf("%s is not %s\n", #a, #b); wrong = true; } } while (0)
@@ -85,8 +87,8 @@ int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int 
     if (shape.schedule != HARRIS_SCHEDULE_TILES) return HARRIS_OK;
     if (shape.flags & HARRIS_TUNE_PACKED_IMAGES) { ++patches; check_patch(p, dtype); return HARRIS_OK; }
     if (p.far_rows) {
-        ++far;
-        if (shape.rows != 4 || !(shape.px == 4 || shape.px == 1) || (shape.flags & (HARRIS_TUNE_WORD_STORES | HARRIS_TUNE_FLAG_HANDOFF))) { std::printf("no such far kernel\n"); wrong = true; }
+        ++far; far_px = shape.px;
+        if (shape.rows != 4 || !(shape.px == 4 || shape.px == 1) || (shape.flags & HARRIS_TUNE_FLAG_HANDOFF) || ((shape.flags & HARRIS_TUNE_WORD_STORES) && shape.px != 4)) { std::printf("no such far kernel\n"); wrong = true; }
         return HARRIS_OK;
     }
     ++tiles;
@@ -176,6 +178,17 @@ int main() {
         const char* at = static_cast<const char*>(rgb) + (dtype == HARRIS_U8 ? below(4) : 4 * below(4));
         if (kind == HARRIS_OUT_U8) harris_coarsity_quantized(at, dtype, batch, H, W, &lay, 0.04f, 0.5f, (int)below(2), 1.5f, 90.0f, static_cast<uint8_t*>(out), tuning, nullptr);
         else harris_coarsity_typed(at, dtype, batch, H, W, &lay, 0.04f, 2.0f, (int)below(2), out, kind, tuning, nullptr);
+    }
+    // Images of more than 2^32 pixels: as many pixels per lane as smaller ones have, {input, result, images, height, width, pixels per lane}.
+    for (const auto& c : {std::array<int, 6>{HARRIS_U8, HARRIS_OUT_F16, 1, 66001, 66001, 4}, {HARRIS_F32, HARRIS_OUT_BF16, 1, 66001, 66001, 4}, {HARRIS_U8, HARRIS_OUT_U8, 2, 40001, 36001, 4},
+                          {HARRIS_U8, HARRIS_OUT_F32, 2, 40001, 36001, 4}, {HARRIS_F32, HARRIS_OUT_F32, 2, 40000, 36000, 4}}) {
+        const int before = (int)harris_launch::far;
+        const int rc = c[1] == HARRIS_OUT_U8 ? harris_coarsity_quantized(rgb, c[0], c[2], c[3], c[4], nullptr, 0.04f, 1.0f, 0, 1.0f, 0.0f, static_cast<uint8_t*>(out), nullptr, nullptr)
+                                             : harris_coarsity_typed(rgb, c[0], c[2], c[3], c[4], nullptr, 0.04f, 1.0f, 0, out, c[1], nullptr, nullptr);
+        if (rc != HARRIS_OK || harris_launch::far != before + 1 || harris_launch::far_px != c[5]) {
+            std::printf("%d images of %dx%d, types %d and %d: %d pixels per lane\n", c[2], c[3], c[4], c[0], c[1], harris_launch::far_px);
+            return 1;
+        }
     }
     // Scales whose factor takes two numbers: the kernels that multiply by both, whatever shape was asked for.
     for (float scale : {5e9f, 3e38f, 3e-10f, 1e-45f})

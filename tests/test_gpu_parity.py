@@ -716,6 +716,48 @@ def test_rows_planes_and_images_that_lie_far_apart(gpu, oracle, dtype, W, row, p
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("dtype", ["u8", "f32"])
+@pytest.mark.parametrize("out", ["float16", "bfloat16", "uint8"])
+@pytest.mark.parametrize("window", [0, 1])
+def test_odd_result_rows_of_input_rows_that_lie_far_apart(gpu, dtype, out, window):
+    # Four pixels per lane here too: the same numbers as of a dense image, nothing outside the rows.
+    import torch
+    H, W, row = 19, 271, (1 << (29 if dtype == "u8" else 27)) + 64
+    say("case far %s to %s window %d" % (dtype, out, window))
+    rgb = torch.from_numpy(hi.white_noise_u8(31, 1, H, W) if dtype == "u8" else hi.rectangles_f32(32, 1, H, W)).cuda()
+    frame = torch.empty(((3 * H - 1) * row + W + 1,), dtype=rgb.dtype, device="cuda")
+    view = frame[1:].as_strided((1, 3, H, W), (3 * H * row, H * row, row, 1))
+    view.copy_(rgb)
+    tune = dict(schedule=2, rows=4, waves_per_block=4, flags=256)
+    got, want = (torch.full((1, H - 4, W + 5), 7, dtype=getattr(torch, out), device="cuda") for _ in range(2))
+    for src, dst in ((view, got), (rgb, want)):
+        if out == "uint8":
+            gpu.harris_coarsity_quantized(src, dst[..., 3:W - 1], 9.0, 90.0, K, 1.0, window, tuning=tune)
+        else:
+            gpu.harris_coarsity_typed(src, dst[..., 3:W - 1], K, 1.0, window, tuning=tune)
+    assert torch.equal(got, want) and bool((got[..., :3] == 7).all()) and bool((got[..., W - 1:] == 7).all()) and len(torch.unique(got)) > 8
+    del frame, view
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("H, W", [(1000, 1500), (1001, 1501)])
+@pytest.mark.parametrize("window", [0, 1])
+def test_u8_many_tiles_at_a_large_scale(gpu, H, W, window):
+    # More tiles than one turn of a launch, in the kernels with whole arguments; tolerances as of single tiles.
+    import torch
+    rgb = torch.from_numpy(100 + hi.white_noise_u8(5, 6, H, W) // 128).cuda()
+    scale, q = 1e10, 1e-31
+    one, got = (gpu.harris_coarsity_ex(rgb, K, sobel_scale=s, window=window, tuning=dict(schedule=2, px=4, rows=4, waves_per_block=4)) for s in (1.0, scale))
+    want = one.double() * float(np.float32(scale)) ** 4
+    assert bool(((got - want).abs() <= 2.5 * np.finfo(np.float32).eps * want.abs()).all())
+    assert torch.equal(gpu.harris_coarsity_ex(rgb, K, sobel_scale=scale, window=window), got)
+    codes = torch.zeros(got.shape, dtype=torch.uint8, device="cuda")
+    gpu.harris_coarsity_quantized(rgb, codes, q, 90.0, K, scale, window)
+    want = (got.double() * float(np.float32(q)) + 90.0).round().clamp(0, 255)
+    diff = (codes.double() - want).abs()
+    assert float(diff.max()) <= 1 and float((diff > 0).double().mean()) < 0.01 and len(torch.unique(want)) > 2
+
+
 @pytest.mark.parametrize("H, W, row, tune", [
     (10, 70, 125000000, None), (300, 70, 1 << 24, None), (600, 1000, 2000000, None),
     (600, 1000, 2000000, dict(schedule=2, rows=4, waves_per_block=4)), (600, 1000, 2000000, dict(schedule=2, rows=5, waves_per_block=4, flags=8)),
