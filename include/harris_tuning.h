@@ -108,7 +108,12 @@ struct harris_tuning {
  * `tuning`, which may be NULL), written to *chosen; also the number of workgroups
  * in *n_blocks if n_blocks is not NULL.  rgb_align / out_align are the byte
  * alignments of the base pointers (pass 16 for ordinary allocations).  Images without gaps
- * between rows, planes and images are assumed, which matters for HARRIS_TUNE_PACKED_IMAGES alone.
+ * between rows, planes and images are assumed, which matters for HARRIS_TUNE_PACKED_IMAGES and for the following.
+ * Whatever is asked for, some calls run in tiles of 4 x 4 rows, with 4 pixels per lane or 1, in kernels that address every
+ * row by itself: planes of 2^32 elements or more, several images that lie so far apart, rows of a wavefront more than 2 GB
+ * apart, result rows of 2 GB (plans say so where images without gaps are such); and 8-bit input with a Sobel scale or k
+ * so large or so small that the factor of the results, (sobel_scale * 2^18 / 255000)^4 (times k / 2^64, beyond that), is no normal float32 number,
+ * which plans cannot say.
  * The chosen shape, passed back as `tuning` for the same problem, gives the same launch.  Host only;
  * touches no device.  Returns a harris_status.
  */

@@ -239,8 +239,8 @@ harris_layout dense_layout(int H, int W) {
     return {W, plane, (long long)(3ull * (unsigned long long)plane), m, n * m};
 }
 
-int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_layout& lay, const harris_tuning* tuning,
-         harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
+int plan_shape(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_layout& lay, const harris_tuning* tuning,
+               harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
     if (dtype != HARRIS_F32 && dtype != HARRIS_U8) return HARRIS_ERR_ARG;
     if (!known_out_dtype(out_dtype)) return HARRIS_ERR_ARG;
     if (batch < 0 || H < 4 || W < 4) return HARRIS_ERR_SHAPE;
@@ -515,6 +515,31 @@ int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int o
     return HARRIS_OK;
 }
 
+// The launch of a call: what plan_shape takes, or, whatever shape was asked for, tiles of four rows per wavefront for the kernels that address each row by
+// itself and take all arguments whole.  That is for rows of hundreds of megabytes or that far apart, for images of more than 2^32 pixels, and for what the
+// caller knows to need them (`far`).
+int plan(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align, const harris_layout& lay, const harris_tuning* tuning, bool far,
+         harris_tuning* chosen, long long* n_blocks, harris_launch::Params* params) {
+    harris_tuning shape;
+    int rc = plan_shape(dtype, out_dtype, batch, H, W, rgb_align, out_align, lay, tuning, &shape, n_blocks, params);
+    if (rc != HARRIS_OK) return rc;
+    if (shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) && batch > 0 && H > 4 && W > 4)
+        far = far || harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows) || !harris_launch::compact::fits(lay, batch, out_elem_size(out_dtype));
+    if (far) {
+        // (float32: three tiles on a CU.  2 images of 40000x36000 to float32 7.97 ms, 8.66 with as many as fit, 8.13 with four, 8.54 with two.)
+        const harris_tuning four = {HARRIS_SCHEDULE_TILES, shape.px == 4 ? 4 : 1, 4, 0, 4, shape.flags & HARRIS_TUNE_WORD_STORES, dtype == HARRIS_F32 && shape.px == 4 ? 48 : 0};
+        rc = plan_shape(dtype, out_dtype, batch, H, W, rgb_align, out_align, lay, &four, &shape, n_blocks, params);
+        if (rc != HARRIS_OK) return rc;
+        if (params) {
+            params->far_rows = 1;
+            params->by_tiles_per_image = harris_launch::make_fastdiv(params->tiles_per_image);
+            params->by_n_strips = harris_launch::make_fastdiv(params->n_strips);
+        }
+    }
+    if (chosen) *chosen = shape;
+    return HARRIS_OK;
+}
+
 unsigned pointer_alignment(const void* p) {
     uintptr_t v = (uintptr_t)p;
     unsigned a = 1;
@@ -528,12 +553,12 @@ extern "C" {
 
 int harris_plan(int dtype, int batch, int H, int W, int rgb_align, int out_align,
                 const harris_tuning* tuning, harris_tuning* chosen, long long* n_blocks) {
-    return plan(dtype, HARRIS_OUT_F32, batch, H, W, rgb_align, out_align, dense_layout(H, W), tuning, chosen, n_blocks, nullptr);
+    return plan(dtype, HARRIS_OUT_F32, batch, H, W, rgb_align, out_align, dense_layout(H, W), tuning, false, chosen, n_blocks, nullptr);
 }
 
 int harris_plan_typed(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, int out_align,
                       const harris_tuning* tuning, harris_tuning* chosen, long long* n_blocks) {
-    return plan(dtype, out_dtype, batch, H, W, rgb_align, out_align, dense_layout(H, W), tuning, chosen, n_blocks, nullptr);
+    return plan(dtype, out_dtype, batch, H, W, rgb_align, out_align, dense_layout(H, W), tuning, false, chosen, n_blocks, nullptr);
 }
 
 }  // extern "C"
@@ -583,40 +608,25 @@ int run(const void* rgb, int dtype, int batch, int H, int W, const harris_layout
     harris_launch::Params p;
     harris_tuning shape;
     long long n_blocks = 0;
-    int rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, tuning, &shape, &n_blocks, &p);
-    if (rc != HARRIS_OK) return rc;
-    if (empty) return HARRIS_OK;
-    const auto place = [&] {
-        p.rgb = rgb;
-        p.out = out;
-        p.in_row_pitch = lay.rgb_row_pitch; p.in_plane_pitch = lay.rgb_plane_pitch; p.in_image_pitch = lay.rgb_image_pitch;
-        p.out_row_pitch = lay.out_row_pitch; p.out_image_pitch = lay.out_image_pitch;
-        if (batch == 1) p.in_image_pitch = p.out_image_pitch = 0;       // of no matter, and they may be long
-        p.out_row_bytes = (unsigned long long)lay.out_row_pitch * out_elem_size(out_dtype);
-        p.out_image_bytes = (unsigned long long)p.out_image_pitch * out_elem_size(out_dtype);
-    };
-    place();
     // The Sobel scale multiplies Ix and Iy, which are linear in gray: fold it into the three gray weights; from 8-bit input, whose
-    // weights are whole numbers, its fourth power and theirs into the factor of the result.
+    // weights are whole numbers, its fourth power and theirs into the factor of the result.  The kernels that take it as two numbers are those with whole
+    // arguments; the others have no instruction to spare for them.
     const double unit = sobel_scale * (262144.0 / 255000.0);
     double factor = unit * unit * unit * unit;
     if (dtype == HARRIS_U8) harris_launch::bound_k(k, factor);
     float gain, more_gain;
     harris_launch::split_gain(factor, gain, more_gain);
-    // Rows of hundreds of megabytes or that far apart, images of more than 2^32 pixels: the kernels that address each row by itself, whatever shape was asked for.
-    // So are scales whose factor takes two: the others, which multiply by one, have no instruction to spare for them.
-    const bool far = shape.schedule == HARRIS_SCHEDULE_TILES && !(shape.flags & HARRIS_TUNE_PACKED_IMAGES) &&
-                     (harris_launch::rows_are_far(lay.rgb_row_pitch, W, elem_size(dtype), shape.rows) || !harris_launch::compact::fits(p));
-    if (far || (dtype == HARRIS_U8 && more_gain != 1.0f)) {
-        // (float32: three tiles on a CU.  2 images of 40000x36000 to float32 7.97 ms, 8.66 with as many as fit, 8.13 with four, 8.54 with two.)
-        const harris_tuning four = {HARRIS_SCHEDULE_TILES, shape.px == 4 ? 4 : 1, 4, 0, 4, shape.flags & HARRIS_TUNE_WORD_STORES, dtype == HARRIS_F32 && shape.px == 4 ? 48 : 0};
-        rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, &four, &shape, &n_blocks, &p);
-        if (rc != HARRIS_OK) return rc;
-        place();
-        p.far_rows = 1;
-        p.by_tiles_per_image = harris_launch::make_fastdiv(p.tiles_per_image);
-        p.by_n_strips = harris_launch::make_fastdiv(p.n_strips);
-    }
+    const bool far = dtype == HARRIS_U8 && more_gain != 1.0f && !empty;
+    int rc = plan(dtype, out_dtype, batch, H, W, (int)rgb_align, (int)out_align, lay, tuning, far, &shape, &n_blocks, &p);
+    if (rc != HARRIS_OK) return rc;
+    if (empty) return HARRIS_OK;
+    p.rgb = rgb;
+    p.out = out;
+    p.in_row_pitch = lay.rgb_row_pitch; p.in_plane_pitch = lay.rgb_plane_pitch; p.in_image_pitch = lay.rgb_image_pitch;
+    p.out_row_pitch = lay.out_row_pitch; p.out_image_pitch = lay.out_image_pitch;
+    if (batch == 1) p.in_image_pitch = p.out_image_pitch = 0;           // of no matter, and they may be long
+    p.out_row_bytes = (unsigned long long)lay.out_row_pitch * out_elem_size(out_dtype);
+    p.out_image_bytes = (unsigned long long)p.out_image_pitch * out_elem_size(out_dtype);
     p.wr = 0.299f * sobel_scale;
     p.wg = 0.587f * sobel_scale;
     p.wb = 0.114f * sobel_scale;

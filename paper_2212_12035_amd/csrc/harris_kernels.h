@@ -739,7 +739,7 @@ __device__ __forceinline__ void store_packed_tail(const PackedRow<KIND>& r, uint
 // bfloat16 10.6 (10.9), 64x96 float32 2.66 (2.80).  float32 tiles of 8 rows and more gain nothing and keep a descriptor per row.
 //
 // kAuxFar, kAuxFarKeepShared: a wavefront's rows do not lie within 2 GB of each other, pitches do not fit the compact arguments, or the factor of 8-bit results takes two
-// numbers: 64-bit addresses for each row and all arguments whole (four rows per wavefront; run() in harris_api.cpp sees to it).
+// numbers: 64-bit addresses for each row and all arguments whole (four rows per wavefront; plan() in harris_api.cpp sees to it).
 // Args: compact::Params, or Params for these two.
 template <typename In, int PX, int RW, int LAUX, bool BINOM, bool HANDOFF, bool SHIFTED, bool SMALL, bool WORDS, typename Args>
 __device__ __forceinline__ void harris_tile(const Args& args) {

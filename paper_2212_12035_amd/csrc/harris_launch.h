@@ -147,9 +147,9 @@ struct Params {
 };
 static_assert(sizeof(Params) == 96, "more than the runtime writes quickly");
 
-inline bool fits(const harris_launch::Params& p) {
+inline bool fits(const harris_layout& lay, int batch, int out_elem) {
     const long long most = 1LL << 32;
-    return !p.far_rows && p.in_plane_pitch < most && p.in_image_pitch < most && p.out_image_pitch < most && p.out_row_bytes < (1ull << 31);
+    return lay.rgb_plane_pitch < most && (batch == 1 || (lay.rgb_image_pitch < most && lay.out_image_pitch < most)) && lay.out_row_pitch < (1LL << 31) / out_elem;
 }
 
 inline Params pack(const harris_launch::Params& p, int elem) {

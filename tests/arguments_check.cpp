@@ -15,6 +15,7 @@ namespace harris_launch {
 
 static long long tiles = 0, patches = 0, far = 0;
 static int far_px = 0;
+static long long far_blocks = 0;
 static bool wrong = false;
 
 #define SAME(a, b) do { if ((a) != (b)) { std::printf("%s is not %s\n", #a, #b); wrong = true; } } while (0)
@@ -87,12 +88,13 @@ int launch(const Params& p, const harris_tuning& shape, long long n_blocks, int 
     if (shape.schedule != HARRIS_SCHEDULE_TILES) return HARRIS_OK;
     if (shape.flags & HARRIS_TUNE_PACKED_IMAGES) { ++patches; check_patch(p, dtype); return HARRIS_OK; }
     if (p.far_rows) {
-        ++far; far_px = shape.px;
+        ++far; far_px = shape.px; far_blocks = n_blocks;
         if (shape.rows != 4 || !(shape.px == 4 || shape.px == 1) || (shape.flags & HARRIS_TUNE_FLAG_HANDOFF) || ((shape.flags & HARRIS_TUNE_WORD_STORES) && shape.px != 4)) { std::printf("no such far kernel\n"); wrong = true; }
         return HARRIS_OK;
     }
     ++tiles;
-    if (!compact::fits(p) || rows_are_far(p.in_row_pitch, p.W, dtype == HARRIS_U8 ? 1 : 4, shape.rows)) { std::printf("does not fit\n"); wrong = true; }
+    const harris_layout lay = {p.in_row_pitch, p.in_plane_pitch, p.in_image_pitch, p.out_row_pitch, p.out_image_pitch};
+    if (!compact::fits(lay, 0, 1 << p.out_shift) || rows_are_far(p.in_row_pitch, p.W, dtype == HARRIS_U8 ? 1 : 4, shape.rows)) { std::printf("does not fit\n"); wrong = true; }
     check_tile(p, shape, dtype);
     check_rows(p, shape, dtype);
     return HARRIS_OK;
@@ -185,6 +187,15 @@ int main() {
         const int before = (int)harris_launch::far;
         const int rc = c[1] == HARRIS_OUT_U8 ? harris_coarsity_quantized(rgb, c[0], c[2], c[3], c[4], nullptr, 0.04f, 1.0f, 0, 1.0f, 0.0f, static_cast<uint8_t*>(out), nullptr, nullptr)
                                              : harris_coarsity_typed(rgb, c[0], c[2], c[3], c[4], nullptr, 0.04f, 1.0f, 0, out, c[1], nullptr, nullptr);
+        // The plan says so too, and is accepted.
+        harris_tuning planned, again;
+        long long blocks = 0;
+        const int rp = harris_plan_typed(c[0], c[1], c[2], c[3], c[4], c[0] == HARRIS_U8 ? 1 : 4, c[1] == HARRIS_OUT_U8 ? 1 : c[1] == HARRIS_OUT_F32 ? 4 : 2, nullptr, &planned, &blocks) |
+                       harris_plan_typed(c[0], c[1], c[2], c[3], c[4], c[0] == HARRIS_U8 ? 1 : 4, c[1] == HARRIS_OUT_U8 ? 1 : c[1] == HARRIS_OUT_F32 ? 4 : 2, &planned, &again, nullptr);
+        if (c[4] % 2 != 0 && (rp != HARRIS_OK || planned.rows != 4 || planned.waves_per_block != 4 || blocks != harris_launch::far_blocks || std::memcmp(&planned, &again, sizeof again) != 0)) {
+            std::printf("%d images of %dx%d, types %d and %d: planned %lld tiles of %d rows, launched %lld\n", c[2], c[3], c[4], c[0], c[1], blocks, planned.rows, harris_launch::far_blocks);
+            return 1;
+        }
         if (rc != HARRIS_OK || harris_launch::far != before + 1 || harris_launch::far_px != c[5]) {
             std::printf("%d images of %dx%d, types %d and %d: %d pixels per lane\n", c[2], c[3], c[4], c[0], c[1], harris_launch::far_px);
             return 1;
