@@ -827,13 +827,14 @@ __device__ __forceinline__ void harris_tile(const Args& args) {
     constexpr bool NEAR = !FAR && (std::is_same<In, uint8_t>::value ? !SHIFTED || BYTES || !BINOM : RW <= 6);
     if constexpr (NEAR) {
         const int last = p.H - 1 - y_wave;                      // the image's last row, counted from this wavefront's first; negative below the image
-        const harris_launch::NearRows near = harris_launch::near_rows(p.H, y_wave, (uint32_t)p.in_row_pitch * (uint32_t)sizeof(In), RW);
-        const In* first = img_in + (size_t)(unsigned)min(y_wave, p.H - 1) * (size_t)p.in_row_pitch;
+        const int y_first = min(y_wave, p.H - 1);
+        const harris_launch::NearRows near = harris_launch::near_rows(p.H, y_first, (uint32_t)p.in_row_pitch * (uint32_t)sizeof(In), RW, std::is_same<In, uint8_t>::value);
+        const In* first = img_in + (size_t)(unsigned)y_first * (size_t)p.in_row_pitch;
         // A plane's rows from the wavefront's first on, as far as it needs them and the image has them; rows below the image
         // load its last one again, which nobody uses, and wavefronts below it nothing.  From float32, whose lanes may straddle a row's end, every
         // row has a descriptor that ends with it.
         constexpr bool EACH = std::is_same<In, float>::value;
-        const uint32_t rows = last < 0 ? 0u : near.last + in_row_bytes;
+        const uint32_t rows = last < 0 ? 0u : min(near.last, (RW - 1) * near.pitch) + in_row_bytes;
         // SHIFTED words: a plane's rows from the aligned word that its first one begins in; as each row's descriptor ends with the
         // word of the row's last byte, no access leaves the words that hold the row's bytes.  Box window, us (a descriptor per row and plane): 8191x8191
         // 85.1 (87.0), 8 of 1079x1919 23.8 (24.6), 2831x4255 18.3 (18.9), 64 of 333x499 15.5 (16.4); with the binomial window it gains 2 %

@@ -52,7 +52,7 @@ static void check_rows(const Params& p, const harris_tuning& shape, int dtype) {
     const long long pitch = p.in_row_pitch * elem;
     const auto rows_of = [&](long long y) {
         if (y < 0 || y > p.H + shape.rows * 16LL) return;
-        const NearRows r = near_rows(p.H, (int)y, (unsigned)pitch, shape.rows);
+        const NearRows r = near_rows(p.H, (int)(y < p.H ? y : p.H - 1), (unsigned)pitch, shape.rows, dtype == HARRIS_U8);
         const long long left = p.H - 1 - y;
         for (int t = 0; t < shape.rows; ++t) {
             const long long at = (left < 0 ? 0 : left < t ? left : t) * pitch;
