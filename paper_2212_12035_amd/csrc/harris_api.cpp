@@ -61,13 +61,16 @@ bool px4_fits_shifted(int dtype, int out_dtype, int rgb_align) {
 //     33 of 200x301, two strips for five, 11 tiles, 9.1 / 8.5; but 1079x1919, 8 strips for 32, 11 tiles,
 //     7.6 / 9.1, and 776 of 64x161 as above).  Not from 1.5 million on if the planner's one tile per CU
 //     would leave a third of the CUs without (130 of 64x241, 130 tiles, 9.4 / 8.4; 50 of 64x501, 150, 8.3 / 7.4).
+//   - Strips of four pixels per lane are counted as the planner cuts them from 8-bit input, 248 columns (with 244, before: 178 calls whose rows end in the
+//     last four columns of a strip take 0.90 of the time on average, 6 of them 1.01 to 1.05).  From float32 input they hold 252,
+//     but counted so some launches to codes take four pixels that are slower with them (43 of 100x505 7.4 / 8.2 us), and 248 stand.
 //   Over 1174 shapes of 1.6 to 32 million pixels, 62 to 2831 columns wide, the choice takes on average 0.4 %
 //   longer than the faster of the two; always wide would take 6.8 %, always narrow 12.5 %.
 bool px4_shifted_by_default(int dtype, int batch, int H, int W, int narrower, const harris_tuning& t) {
     if (t.rows != 0 || t.waves_per_block != 0 || t.flags != 0u || t.lds_kb != 0) return false;
     const long long n = H - 4, m = W - 4;
     if (n < 1 || m < 1 || (long long)batch * H * W < 3LL << 19) return false;
-    const long long wide_pitch = harris_launch::valid_lanes(4) * 4 - (dtype == HARRIS_U8 ? 8 : 4), narrow_pitch = harris_launch::valid_lanes(narrower) * narrower;
+    const long long wide_pitch = harris_launch::valid_lanes(4) * 4 - 4, narrow_pitch = harris_launch::valid_lanes(narrower) * narrower;
     const long long wide = (m + wide_pitch - 1) / wide_pitch, narrow = (m + narrow_pitch - 1) / narrow_pitch;
     const int worth = dtype == HARRIS_U8 ? (narrower == 1 ? 180 : 170) : (narrower == 1 ? 215 : 150);     // hundredths of a narrower strip
     if (100 * narrow < worth * wide) return false;

@@ -168,6 +168,18 @@ int main() {
             return 1;
         }
     }
+    // Odd result rows from 8-bit input that one strip of four pixels per lane just holds, or several: {result type, images, height, width, pixels per lane}.
+    static const int odd_rows[][5] = {{HARRIS_OUT_U8, 64, 500, 250, 4}, {HARRIS_OUT_U8, 64, 500, 246, 4}, {HARRIS_OUT_U8, 64, 500, 254, 2}, {HARRIS_OUT_U8, 83, 333, 498, 4}, {HARRIS_OUT_F16, 86, 100, 251, 4},
+                                      {HARRIS_OUT_BF16, 34, 100, 747, 4}, {HARRIS_OUT_F16, 86, 100, 255, 1}};
+    for (const auto& c : odd_rows) {
+        const int rc = c[0] == HARRIS_OUT_U8 ? harris_coarsity_quantized((const void*)0x100000, HARRIS_U8, c[1], c[2], c[3], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, 1.0f, 0.0f, (uint8_t*)0x200000, nullptr, nullptr)
+                                             : harris_coarsity_typed((const void*)0x100000, HARRIS_U8, c[1], c[2], c[3], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, c[0], nullptr, nullptr);
+        const harris_tuning& s = harris_launch::last_shape;
+        if (rc != HARRIS_OK || s.px != c[4] || (s.px == 4 && (long long)harris_launch::last.n_strips * 248 < c[3] - 4)) {
+            std::printf("%d images of %dx%d, result type %d: %d pixels per lane, %u strips\n", c[1], c[2], c[3], c[0], s.px, harris_launch::last.n_strips);
+            return 1;
+        }
+    }
     // Whether the chip holds all tiles of a launch at once: {images, height, width, wavefronts a workgroup or 0, KB reserved, it does}.
     static const int at_once[][6] = {{1, 1080, 1920, 0, 0, 1}, {1, 2457, 2400, 0, 0, 1}, {2, 2160, 3840, 0, 0, 0}, {1, 12, 600000, 0, 0, 0}, {8, 1079, 1919, 0, 0, 0},
                                      {1, 1500, 1900, 16, 0, 1}, {1, 8000, 1900, 16, 0, 0}, {1, 1080, 1920, 4, 48, 1}, {1, 1200, 1920, 4, 48, 0}, {1, 700, 960, 8, 0, 1}};
