@@ -291,6 +291,23 @@ HARRIS_HOST_DEVICE inline PatchLane patch_lane(const Params& p, unsigned images,
     return l;
 }
 
+// The same, dense 8-bit images whose rows start on any byte: a lane loads the two aligned words around its four pixels.  Offsets count from the aligned
+// word that the group begins in, `lead` bytes before its first: the lane's column in its image's first row (the group's first without an image), row y of plane c from
+// there (the image's last for rows below it), and the end of the word that holds the group's last byte, past which nothing is loaded.
+// Rows that follow each other without a gap and do not all start on words, up to the widths where pairs win (us, single words /
+// pairs): 528 images of 66x11 6.27 / 5.57, 2292 of 55x14 6.38 / 5.35, 3000 of 50x21 10.66 / 7.00, 3886 of 130x14 32.0 / 28.9.
+// A launch of one turn, up to twice as wide: 214 of 42x46 4.39 / 4.19, 103 of 120x51 4.58 / 4.47, but 273 of 108x73 5.51 / 5.52 and
+// 179 of 25x122 4.17 / 4.26.  Between the two other things bound it: 5833 of 26x27 9.11 / 9.42, 690 of 123x47 8.18 / 8.51 (larger
+// launches, from 10 million pixels on, take 0.91 to 0.97 with their images in the last-level cache, 1.0 to 1.01 without).
+inline bool patch_in_pairs(const Params& p) {
+    const bool dense = p.in_row_pitch == p.W && p.in_plane_pitch == p.in_row_pitch * p.H && p.in_image_pitch == 3 * p.in_plane_pitch;
+    const bool on_words = p.W % 4 == 0 && (size_t)p.rgb % 4 == 0;
+    return dense && !on_words && p.W <= (p.turns == 1 ? 60 : 24);
+}
+HARRIS_HOST_DEVICE inline unsigned patch_first_byte(const Params& p, const PatchLane& l, unsigned lead) { return lead + (l.live ? l.image * (unsigned)p.in_image_pitch + l.col : 0u); }
+HARRIS_HOST_DEVICE inline unsigned patch_row(const Params& p, int y, int c) { return (unsigned)(y < p.H - 1 ? y : p.H - 1) * (unsigned)p.in_row_pitch + (unsigned)c * (unsigned)p.in_plane_pitch; }
+HARRIS_HOST_DEVICE inline unsigned patch_words_end(const Params& p, unsigned images, unsigned lead) { return (lead + images * (unsigned)p.in_image_pitch + 3u) & ~3u; }
+
 // Narrow images: the arguments of their kernel, 88 bytes (namespace compact says why).  The planner keeps an image's pitch below 2^30 elements, and with it
 // those of rows and planes.
 namespace compact_patch {

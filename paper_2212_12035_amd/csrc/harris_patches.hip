@@ -99,14 +99,14 @@ __global__ __launch_bounds__(2 * kWave * harris_launch::kPatchWaves) void harris
     const size_t plane = (size_t)p.in_plane_pitch;
     [[maybe_unused]] u32x2 pair[RW][3];
     [[maybe_unused]] uint32_t first_byte;                       // the lane's column in its image's first row, from the aligned word at or before the group
-    const auto row_offset = [&](int t, int c) { return (uint32_t)min(y_wave + t, p.H - 1) * (uint32_t)p.in_row_pitch + (uint32_t)c * (uint32_t)plane; };
+    const auto row_offset = [&](int t, int c) { return harris_launch::patch_row(p, y_wave + t, c); };
     if constexpr (PAIRS) {
         const uintptr_t at = reinterpret_cast<uintptr_t>(in);
         const uint32_t lead = (uint32_t)at & 3u;
         // The end is the end of the word that holds the group's last byte; a word that begins past it is dropped by itself.
         // Columns past W and rows past H hold other pixels of the group, and no stored result depends on them.
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const void*>(at - lead), (lead + images * (uint32_t)p.in_image_pitch + 3u) & ~3u);
-        first_byte = lead + (live ? l.image * (uint32_t)p.in_image_pitch + col : 0u);
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(reinterpret_cast<const void*>(at - lead), harris_launch::patch_words_end(p, images, lead));
+        first_byte = harris_launch::patch_first_byte(p, l, lead);
         static_for<0, RW>([&](auto tt) {
             constexpr int t = decltype(tt)::value;
 #pragma unroll
@@ -185,17 +185,6 @@ void enqueue(const harris_launch::Params& p, dim3 block, hipStream_t stream) {
     else hipLaunchKernelGGL((harris_patch_kernel<In, false, true, PAIRS>), turns, block, p.lds_bytes, stream, c);
 }
 
-// Rows that follow each other without a gap and do not all start on words, up to the widths where pairs win (us, single words /
-// pairs): 528 images of 66x11 6.27 / 5.57, 2292 of 55x14 6.38 / 5.35, 3000 of 50x21 10.66 / 7.00, 3886 of 130x14 32.0 / 28.9.
-// A launch of one turn, up to twice as wide: 214 of 42x46 4.39 / 4.19, 103 of 120x51 4.58 / 4.47, but 273 of 108x73 5.51 / 5.52 and
-// 179 of 25x122 4.17 / 4.26.  Between the two other things bound it: 5833 of 26x27 9.11 / 9.42, 690 of 123x47 8.18 / 8.51 (larger
-// launches, from 10 million pixels on, take 0.91 to 0.97 with their images in the last-level cache, 1.0 to 1.01 without).
-bool in_pairs(const harris_launch::Params& p) {
-    const bool dense = p.in_row_pitch == p.W && p.in_plane_pitch == p.in_row_pitch * p.H && p.in_image_pitch == 3 * p.in_plane_pitch;
-    const bool on_words = p.W % 4 == 0 && reinterpret_cast<uintptr_t>(p.rgb) % 4 == 0;
-    return dense && !on_words && p.W <= (p.turns == 1 ? 60 : 24);
-}
-
 }  // namespace
 
 namespace harris_launch {
@@ -203,7 +192,7 @@ namespace harris_launch {
 int launch_patches(const Params& p, int dtype, unsigned block, void* stream_) {
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     if (dtype != HARRIS_U8) enqueue<float, false>(p, dim3(block), stream);
-    else if (in_pairs(p)) enqueue<uint8_t, true>(p, dim3(block), stream);
+    else if (patch_in_pairs(p)) enqueue<uint8_t, true>(p, dim3(block), stream);
     else enqueue<uint8_t, false>(p, dim3(block), stream);
     return (int)hipGetLastError();
 }

@@ -73,8 +73,36 @@ static bool patch_loads_inside_rows(const Params& p, const harris_layout& lay, i
     return true;
 }
 
+// The same of dense 8-bit images loaded as pairs of aligned words: first and last group, every row of a tile's wavefronts and of a workgroup without a
+// tile, every lane.  No word is loaded but those that hold bytes of the group, and the pixels of the image's columns and rows are in the lane's pair.
+static bool patch_pairs_inside_words(const Params& p, int batch) {
+    const unsigned long long base = (size_t)p.rgb, total = (unsigned long long)batch * p.in_image_pitch;
+    const unsigned groups = (p.batch + p.images - 1) / p.images;
+    for (unsigned group = 0; group < groups; group += groups > 2 ? groups - 1 : 1) {
+        const unsigned left = p.batch - group * p.images, images = left < p.images ? left : p.images;
+        const unsigned long long first = base + (unsigned long long)group * p.images * p.in_image_pitch, from = first & ~3ull;
+        const unsigned lead = (unsigned)(first & 3u), end = harris_launch::patch_words_end(p, images, lead);
+        bool good = from + end <= ((base + total + 3) & ~3ull) && end >= lead + images * (unsigned)p.in_image_pitch;
+        for (int y : {0, 1, 2, 3, p.H - 2, p.H - 1, p.H, p.H + 40, 1 << 30})
+            for (int c = 0; c < 3; ++c)
+                for (unsigned lane = 0; lane < 64; ++lane) {
+                    const harris_launch::PatchLane l = harris_launch::patch_lane(p, images, lane, 1);
+                    const unsigned at = harris_launch::patch_first_byte(p, l, lead) + harris_launch::patch_row(p, y, c);
+                    for (unsigned i = 0; l.live && y < p.H && i < 4 && l.col + i < (unsigned)p.W; ++i) {
+                        const unsigned long long pixel = (unsigned long long)l.image * p.in_image_pitch + c * p.in_plane_pitch + y * p.in_row_pitch + l.col + i;
+                        good = good && from + at + i == first + pixel && at + i < end && (at & 3u) + i < 8;
+                    }
+                    for (unsigned word = 0; word < 2; ++word)       // the hardware drops words from the end on
+                        good = good && ((at & ~3u) + 4 * word >= end || (at & ~3u) + 4 * word + 4 <= end);
+                    good = good && (at & ~3u) < 0x80000000u;
+                    if (!good) { std::printf("%d images of %dx%d from byte %llu: group %u, row %d, plane %d, lane %u loads at %u of %u\n", batch, p.H, p.W, base & 3, group, y, c, lane, at, end); return false; }
+                }
+    }
+    return true;
+}
+
 int main() {
-    int packed = 0, gaps_packed = 0;
+    int packed = 0, gaps_packed = 0, pairs = 0;
     for (int W = 5; W <= 128; ++W)
         for (int H : {5, 31, 64})
             for (int dtype : {HARRIS_F32, HARRIS_U8}) {
@@ -107,6 +135,11 @@ int main() {
                     if (!patch_loads_inside_rows(harris_launch::last, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;
                     const Params& p = first;
                     if (!(p.flags & HARRIS_TUNE_PACKED_IMAGES)) continue;
+                    for (size_t lead = 0; lead < 4 && dtype == HARRIS_U8 && gaps == 0; ++lead) {
+                        Params moved = first;
+                        moved.rgb = (const void*)(0x100000 + lead);
+                        if (harris_launch::patch_in_pairs(moved) && (++pairs, !patch_pairs_inside_words(moved, batch))) return 1;
+                    }
                     ++packed;
                     if (gaps) ++gaps_packed;
                     if (!patch_loads_inside_rows(p, lay, batch, dtype == HARRIS_U8 ? 1 : 4)) return 1;
@@ -234,7 +267,7 @@ int main() {
     for (int each : {4, 8, 64, 256})
         for (int size : {1, each, each + 1, 0x7fffffff - 256, 0x7fffffff - 64, 0x7fffffff - 4, 0x7fffffff})
             if (harris_launch::groups_covering(size, each) != (unsigned)(((long long)size + each - 1) / each)) { std::printf("workgroups for %d by %d\n", size, each); return 1; }
-    if (packed == 0 || gaps_packed == 0) { std::printf("the narrow-image kernel was never planned\n"); return 1; }
+    if (packed == 0 || gaps_packed == 0 || pairs < 100) { std::printf("the narrow-image kernel was never planned\n"); return 1; }
     std::printf("ok %d\n", harris_launch::launches);
     return 0;
 }
