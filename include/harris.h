@@ -152,8 +152,8 @@ typedef enum harris_out_dtype {
  *   tuning     as in harris_coarsity_ex, but 16-bit results exist only in the tile schedule
  *              (else HARRIS_ERR_ARG)
  * 16-bit result rows that start on 4-byte boundaries (pointer and pitches) and have an even number of
- * columns are stored as they are.  Other rows are stored as the aligned 32-bit words that hold them,
- * with the ends of each row element by element, or with one pixel per lane, whichever the library
+ * columns are stored as they are.  Other rows are stored four results at a time on any byte their type allows, with the end
+ * of each row in pieces, or with two or one pixel per lane, whichever the library
  * expects to be faster.  Nothing outside the rows is written in any case.
  */
 int harris_coarsity_typed(const void* rgb, int dtype, int batch, int H, int W, const harris_layout* layout,

@@ -121,7 +121,8 @@ inline void bound_k(float& k, double& gain) {
 }
 
 // TILES: the same in 96 bytes, which is what the kernels take.  The runtime writes a launch's arguments into memory
-// that the GPU reads, from some host cores slowly: an empty kernel with 240 bytes then takes 3.8 us a launch, with 96 bytes 2.8 (2.5 and 2.4 from the others).
+// that the GPU reads: an empty kernel takes 2.7 to 2.9 us a launch with 88 to 112 bytes, 3.2 to 3.6 with 120 to 240 (8000 launches one after the other, six runs in three
+// processes; from some host cores all are faster and 240 bytes cost 0.1 us).
 // Pitches of 2^32 elements and more, result rows of 2 GB, rows that are far apart and scales whose factor takes two numbers take Params itself (compact::fits).
 namespace compact {
 

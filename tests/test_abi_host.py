@@ -91,7 +91,7 @@ def test_version_and_strerror(pkg):
 def test_kernels_use_no_scratch_memory(pkg):
     # The library allocates nothing, and a kernel with a private segment makes the runtime back it with device
     # memory.  The code objects inside the library say what every kernel uses.  Scalar registers may go to
-    # vector lanes (no memory) in the kernels that store result rows as aligned words (the last template argument) alone.
+    # vector lanes (no memory) in the kernels that store result rows on any byte (the last template argument) alone.
     data = open(pkg.library_path(), "rb").read()
     kernels = {}
     for m in re.finditer(rb"\.name(?:\xd9(.)|\xda(..)|([\xa0-\xbf]))(_ZN?[A-Za-z0-9_]+?(?:6ParamsE|[a-z]))(?=[\x80-\xff])", data, re.S):

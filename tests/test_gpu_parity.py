@@ -1061,8 +1061,8 @@ def test_many_narrow_images_dealt_by_turns(gpu, oracle, B, H, W):
 @pytest.mark.parametrize("fmt", ["f16", "bf16", "codes"])
 @pytest.mark.parametrize("rows", [4, 5, 6, 8, 9, 10])
 def test_word_stores_every_kernel_instance(gpu, oracle, fmt, rows):
-    # Result rows stored as aligned words, asked for below the size that takes them by default: every number of rows
-    # per wavefront, load policy and hand-over, both windows, rows of fewer columns than a word holds,
+    # Result rows stored where they are on any byte, asked for below the size that takes them by default: every number of rows
+    # per wavefront, load policy and hand-over, both windows, rows of fewer columns than a lane stores,
     # one strip and two.  The values are those of the float32 result of the same tile shape, rounded; with
     # ten rows, whose instances differ in the order of their sums, those of the float32 oracle within a
     # unit of the last place of the 16-bit value (a code) on top of the bar.
