@@ -146,6 +146,18 @@ unsigned patch_turns(long long pixels, long long blocks) {
     return (unsigned)(turns < 1 ? 1 : turns > 65535 ? 65535 : turns);
 }
 
+// Kilobytes of LDS to reserve per workgroup, which bound the workgroups on a CU: three of up to five wavefronts, two of more, for large launches of very
+// narrow 8-bit images.  A row of such an image is a small part of a cache line, which the rows below it need too, and a wavefront works on up
+// to 32 images: with eight workgroups on a CU the lines in use do not fit the XCD's L2 and are fetched again and again, the more the faster
+// a wavefront gets through its rows.  (us, as many as fit / three or two: 20000 images of 72x7 57.9 / 37.3; 4120 of 104x7 18.5 / 13.3; 7107 of 45x14
+// 17.9 / 11.8; 12741 of 138x11 142 / 132.)  Over 306 launches of 2.9 to 40 million pixels, with their images in the last-level cache and not, 0.83 of the time of as
+// many as fit; 4640 of 115x7 take 1.17, some of 12 to 30 rows up to 1.17 (2973 of 48x22 1.23).  From 16 columns on widths on words gain nothing (5507 of 246x24 1.06),
+// smaller launches and workgroups of fewer wavefronts lose (6.7 million pixels of 8x5 1.6), and so do wider images, whose lines fit.
+int patch_lds_kb(int dtype, long long pixels, int W, int waves) {
+    if (dtype != HARRIS_U8 || waves < 4 || pixels < 11LL << 18) return 0;
+    return W <= 12 || (W <= 24 && W % 4 != 0) ? (waves <= 5 ? 52 : 64) : 0;
+}
+
 // HARRIS_OK: planned.  HARRIS_ERR_ARG: asked for where it cannot be.  kNotPacked: one image per wavefront.
 constexpr int kNotPacked = 1;
 int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_align, const harris_layout& lay, const harris_tuning& t,
@@ -176,8 +188,9 @@ int plan_patches(int dtype, int out_dtype, int batch, int H, int W, int rgb_alig
         if ((long long)batch * H * W < kPatchPixels || tiles <= 256) return kNotPacked;
         if (images == 2 && dtype == HARRIS_F32 && (W % 4 != 0 || (lanes > 24 && tiles > 640 && tiles <= 768 && groups * ((n + 27) / 28) <= 128))) return kNotPacked;
     }
+    const int lds_kb = t.lds_kb > 0 ? t.lds_kb : patch_lds_kb(dtype, (long long)batch * H * W, W, waves);
     const harris_tuning c = {HARRIS_SCHEDULE_TILES, 4, 4, 0, waves, HARRIS_TUNE_CACHED_LOADS | HARRIS_TUNE_PLAIN_STORES | HARRIS_TUNE_PACKED_IMAGES,
-                             t.lds_kb > 4 * waves ? t.lds_kb : 4 * waves};
+                             lds_kb > 4 * waves ? lds_kb : 4 * waves};
     if (chosen) *chosen = c;
     if (n_blocks) *n_blocks = blocks;
     if (params) {

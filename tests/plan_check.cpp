@@ -190,6 +190,15 @@ int main() {
             return 1;
         }
     }
+    // Very narrow 8-bit images: few workgroups on a CU: {input type, images, height, width, KB reserved}.
+    static const int reserved[][5] = {{HARRIS_U8, 7107, 45, 14, 52}, {HARRIS_U8, 20000, 72, 7, 52}, {HARRIS_U8, 4120, 104, 7, 52}, {HARRIS_U8, 12741, 138, 11, 64}, {HARRIS_U8, 5507, 246, 24, 16}, {HARRIS_U8, 5507, 246, 25, 16}, {HARRIS_U8, 149162, 8, 14, 8},
+                                      {HARRIS_F32, 7107, 45, 14, 16}, {HARRIS_U8, 2048, 64, 14, 16}};
+    for (const auto& c : reserved)
+        if (harris_coarsity_typed((const void*)0x100000, c[0], c[1], c[2], c[3], nullptr, 0.04f, 1.0f, HARRIS_WINDOW_BOX, (void*)0x200000, HARRIS_OUT_F32, nullptr, nullptr) != HARRIS_OK ||
+            !(harris_launch::last.flags & HARRIS_TUNE_PACKED_IMAGES) || harris_launch::last_shape.lds_kb != c[4] || (int)harris_launch::last.lds_bytes != c[4] * 1024) {
+            std::printf("%d images of %dx%d, type %d: %d wavefronts, %d KB reserved\n", c[1], c[2], c[3], c[0], harris_launch::last_shape.waves_per_block, harris_launch::last_shape.lds_kb);
+            return 1;
+        }
     // How many tiles an XCD takes in a row, where the wrong number is slower than one turn: {input type, images, height, width, least, most}.
     static const int runs[][6] = {{HARRIS_F32, 1, 4200, 4200, 130, 150}, {HARRIS_F32, 1, 3456, 5184, 130, 150}, {HARRIS_F32, 1, 4608, 4608, 130, 150}, {HARRIS_F32, 1, 2832, 4256, 130, 150},
                                   {HARRIS_F32, 1, 4096, 4300, 130, 150}, {HARRIS_F32, 1, 5778, 4238, 127, 130}, {HARRIS_F32, 1, 3500, 4000, 70, 101}, {HARRIS_F32, 2, 2531, 3743, 110, 125}, {HARRIS_U8, 1, 4096, 4096, 90, 105},
