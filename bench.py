@@ -35,9 +35,9 @@ SETTLE_MS = 20.0               # untimed launches before the timed region, in GP
 
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE (summaries under profiles/), valid only
 # for the kernel sources they were taken with: (sha256 of the csrc files without comments, {workload: bytes}).
-TRAFFIC_SOURCES_SHA256 = "05dd1a8cb2205c8504af902759e76abccc322dab7c50281d241cfe2c53672acd"
-TRAFFIC_BYTES = {"noise_f32_1536x2560": 65074284, "rects_f32_64x1080x1920": 2281798670,
-                 "blobs_f32_2832x4256": 199653999, "noise_u8_8192x8192": 513408402}
+TRAFFIC_SOURCES_SHA256 = "18bf603ea25a52e7e525f13805ce32279300bcf433a48904450b9e90a529961f"
+TRAFFIC_BYTES = {"noise_f32_1536x2560": 65082798, "rects_f32_64x1080x1920": 2281905946,
+                 "blobs_f32_2832x4256": 199665736, "noise_u8_8192x8192": 513202915}
 
 
 def kernel_sources_sha256():
